@@ -13,9 +13,9 @@
 // wait is bounded all the same (spin limit; on expiry scale[0] = NaN and nothing is quantized), so every wave
 // leaves the kernel whatever happens.  The arrival count carries a per-call ticket in its upper half, so a stale
 // workspace counts as zero.  Same-address atomics cost about 30 ns each on this part and serialize, which is why
-// larger tensors (more workgroups, and the second read served by the memory-side cache anyway), streams under HIP
-// graph capture (a replay would reuse the ticket) and callers with a small workspace get the three-launch version
-// (clear, absmax with atomic max on the float's bit pattern, quantize); results are identical.
+// larger tensors (more workgroups, and the second read served by the memory-side cache anyway) and streams under HIP
+// graph capture (a replay would reuse the ticket) take two launches (partial maxima, quantize), and callers with a small
+// workspace three (clear, absmax with atomic max on the float's bit pattern, quantize); results are identical.
 #include "common.h"
 
 namespace {
@@ -269,53 +269,118 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t v, int n)
     if (i < n) p[i] = v;
 }
 
-// absmax over the whole [t, c_i] tensor -> *amax_bits (bit pattern of a non-negative float; the
-// integer order of such patterns is the float order, so atomicMax on uint32 is exact).
-template <bool BF16>
-__global__ __launch_bounds__(256) void tensor_absmax_kernel(const uint16_t* __restrict__ x, int64_t ldx, int c_i, int64_t t,
-                                                           const float* __restrict__ inv_s, uint32_t* amax_bits)
-{
-    __shared__ float red[4];
-    const int nvec = c_i >> 3;
-    const int64_t total = t * (int64_t)nvec;
-    float m = 0.0f;
-    for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < total; g += (int64_t)gridDim.x * 256) {
-        const int64_t row = g / nvec;
-        const int idx = (int)(g - row * nvec);
-        float f[8];
-        unpack8<BF16>(((const v4u*)(x + row * ldx))[idx], f);
-        if (inv_s) smooth8(f, inv_s, idx * 8);
-        m = __builtin_fmaxf(m, absmax8(f));
+// The per-tensor kernels number the 16-byte vectors of the whole [t, c_i] tensor and find row and column of each by a
+// division.  Below 2^31 vectors (34 GB of activations) it is a multiply-high and a shift (exact: d >= 2, n < 2^31, m the
+// reciprocal rounded up); the 64-bit division it replaces is some 40 instructions per vector, which is what an 8-element
+// vector's whole quantization costs.  Larger tensors (WIDE) keep the 64-bit form.
+struct RowOf {
+    uint32_t nvec, mul, shift;
+    template <bool WIDE> __device__ __forceinline__ int64_t row(int64_t g) const
+    {
+        if constexpr (WIDE) return g / (int64_t)nvec;
+        else return (int64_t)(__umulhi((uint32_t)g, mul) >> shift);
     }
-    m = block_max_256(m, red);
-    if (threadIdx.x == 0) atomicMax(amax_bits, __builtin_bit_cast(uint32_t, m));
+};
+RowOf row_of(int64_t nvec)
+{
+    uint32_t l = 1;
+    while (((int64_t)1 << l) < nvec) ++l;  // 2^(l-1) < nvec <= 2^l (c_i % 16 == 0: nvec >= 2)
+    return RowOf{(uint32_t)nvec, (uint32_t)((((uint64_t)1 << (31 + l)) / (uint64_t)nvec) + 1), l - 1};
 }
 
-// Elementwise quantization with one step for the whole tensor.  DYNAMIC: the step comes from the
-// absmax pass (and is written to scale[0]); otherwise scale[0] holds the calibrated Delta.
-template <bool BF16, bool DYNAMIC>
-__global__ __launch_bounds__(256) void quant_per_tensor_kernel(const uint16_t* __restrict__ x, int64_t ldx, int c_i, int64_t t,
-                                                              const float* __restrict__ inv_s, float* scale,
-                                                              const uint32_t* amax_bits, int8_t* __restrict__ xq, bool tiled)
+// absmax over the whole [t, c_i] tensor.  Every workgroup takes one contiguous range of vectors, four 16-byte loads per
+// thread in flight, and leaves its maximum in partial[blockIdx.x]: a plain store, nothing to clear beforehand.  (Same-
+// address atomics serialize at about 12 ns: one per workgroup of a 4096-workgroup grid made this pass 49 us on a
+// 1000 x 9216 tensor whose 18 MB take 4; the whole quantization of that tensor went from 57 to 15 us, of 2048 x 12288 from
+// 66 to 25, of 2048 x 49152 from 110 to 83.)  With ATOMIC (scratch of a few bytes only) the maxima meet in partial[0], which
+// the caller has cleared: the integer order of the bit patterns of non-negative floats is the float order.
+constexpr int kAbsmaxThreads = 512, kAbsmaxUnroll = 4;
+template <bool BF16, bool WIDE, bool ATOMIC>
+__global__ __launch_bounds__(kAbsmaxThreads) void tensor_absmax_kernel(const uint16_t* __restrict__ x, int64_t ldx, RowOf ro, int64_t total,
+                                                                      int64_t per_wg, const float* __restrict__ inv_s, uint32_t* partial)
 {
-    float r;
-    if (DYNAMIC) {
-        const float a = __builtin_bit_cast(float, *amax_bits);
-        r = a > 0.0f ? 127.0f / a : 0.0f;
-        if (blockIdx.x == 0 && threadIdx.x == 0) scale[0] = a / 127.0f;
-    } else {
-        const float delta = scale[0];
-        r = delta > 0.0f ? 1.0f / delta : 0.0f;
+    constexpr int NT = kAbsmaxThreads, U = kAbsmaxUnroll;
+    __shared__ float red[NT / 64];
+    const int64_t g0 = (int64_t)blockIdx.x * per_wg, g1 = g0 + per_wg < total ? g0 + per_wg : total;
+    float m = 0.0f;
+    for (int64_t base = g0 + threadIdx.x; base < g1; base += NT * U) {
+        v4u raw[U];
+        int col[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int64_t g = base + i * NT;
+            raw[i] = v4u{0, 0, 0, 0};
+            col[i] = 0;
+            if (g < g1) {
+                const int64_t row = ro.row<WIDE>(g);
+                const int idx = (int)(g - row * ro.nvec);
+                raw[i] = ((const v4u*)(x + row * ldx))[idx];
+                col[i] = idx * 8;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            float f[8];
+            unpack8<BF16>(raw[i], f);
+            if (inv_s) smooth8(f, inv_s, col[i]);
+            m = __builtin_fmaxf(m, absmax8(f));
+        }
     }
-    const int nvec = c_i >> 3;
-    const int64_t total = t * (int64_t)nvec;
-    for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < total; g += (int64_t)gridDim.x * 256) {
-        const int64_t row = g / nvec;
-        const int idx = (int)(g - row * nvec);
-        float f[8];
-        unpack8<BF16>(__builtin_nontemporal_load((const v4u*)(x + row * ldx) + idx), f);
-        if (inv_s) smooth8(f, inv_s, idx * 8);
-        __builtin_nontemporal_store(quant8(f, r), (v2u*)code_dst(xq, row, idx * 8, c_i, tiled));
+    m = block_max<NT>(m, red);
+    if (threadIdx.x == 0) {
+        if constexpr (ATOMIC) atomicMax(partial, __builtin_bit_cast(uint32_t, m));
+        else partial[blockIdx.x] = __builtin_bit_cast(uint32_t, m);
+    }
+}
+
+// Elementwise quantization with one step for the whole tensor, U vectors per thread in flight.  DYNAMIC: the step comes
+// from the n_partial maxima of the absmax pass (and is written to scale[0]); otherwise scale[0] holds the calibrated Delta.
+template <bool BF16, bool DYNAMIC, bool WIDE, int U>
+__global__ __launch_bounds__(256) void quant_per_tensor_kernel(const uint16_t* __restrict__ x, int64_t ldx, int c_i, RowOf ro, int64_t total,
+                                                              const float* __restrict__ inv_s, float* scale,
+                                                              const uint32_t* partial, int n_partial, int8_t* __restrict__ xq, bool tiled)
+{
+    __shared__ float red[4];
+    float r = 0.0f;
+    bool have_r = false;
+    for (int64_t base = (int64_t)blockIdx.x * (256 * U) + threadIdx.x; base - threadIdx.x < total; base += (int64_t)gridDim.x * (256 * U)) {
+        v4u raw[U];
+        int64_t row[U];
+        int idx[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int64_t g = base + i * 256;
+            raw[i] = v4u{0, 0, 0, 0};
+            row[i] = 0;
+            idx[i] = 0;
+            if (g < total) {
+                row[i] = ro.row<WIDE>(g);
+                idx[i] = (int)(g - row[i] * ro.nvec);
+                raw[i] = __builtin_nontemporal_load((const v4u*)(x + row[i] * ldx) + idx[i]);
+            }
+        }
+        if (!have_r) {  // behind the first loads, so that the two latencies overlap
+            have_r = true;
+            if constexpr (DYNAMIC) {
+                float a = 0.0f;
+                for (int i = threadIdx.x; i < n_partial; i += 256) a = __builtin_fmaxf(a, __builtin_bit_cast(float, partial[i]));
+                a = block_max_256(a, red);
+                r = a > 0.0f ? 127.0f / a : 0.0f;
+                if (blockIdx.x == 0 && threadIdx.x == 0) scale[0] = a / 127.0f;
+            } else {
+                const float delta = scale[0];
+                r = delta > 0.0f ? 1.0f / delta : 0.0f;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            if (base + i * 256 < total) {
+                float f[8];
+                unpack8<BF16>(raw[i], f);
+                if (inv_s) smooth8(f, inv_s, idx[i] * 8);
+                __builtin_nontemporal_store(quant8(f, r), (v2u*)code_dst(xq, row[i], idx[i] * 8, c_i, tiled));
+            }
+        }
     }
 }
 
@@ -325,7 +390,7 @@ constexpr int kO2MaxGrid = 512;  // workgroups of the single-launch kernel (= pa
 // spin_limit bounds the wait (0.5 to 2 us per poll); it is not reached unless a workgroup of the grid never gets to
 // run, and if it is, scale[0] becomes NaN and nothing is quantized: every wave still leaves the kernel.
 template <bool BF16, int NV>
-__global__ __launch_bounds__(256) void quant_per_tensor_single_kernel(const uint16_t* __restrict__ x, int64_t ldx, int c_i, int64_t t,
+__global__ __launch_bounds__(256) void quant_per_tensor_single_kernel(const uint16_t* __restrict__ x, int64_t ldx, int c_i, RowOf ro, int total,
                                                                      const float* __restrict__ inv_s, float* scale,
                                                                      unsigned char* ws, uint32_t ticket, uint32_t spin_limit,
                                                                      int8_t* __restrict__ xq, bool tiled)
@@ -334,18 +399,16 @@ __global__ __launch_bounds__(256) void quant_per_tensor_single_kernel(const uint
     __shared__ uint32_t ok_flag;
     unsigned long long* cell = (unsigned long long*)ws;
     uint32_t* partial = (uint32_t*)(ws + 256);
-    const int nvec = c_i >> 3;
-    const int64_t total = t * (int64_t)nvec;
-    const int64_t g0 = (int64_t)blockIdx.x * (256 * NV) + threadIdx.x;
+    const int g0 = blockIdx.x * (256 * NV) + threadIdx.x;
     v4u raw[NV];
     float m = 0.0f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int64_t g = g0 + i * 256;
+        const int g = g0 + i * 256;
         raw[i] = v4u{0, 0, 0, 0};
         if (g < total) {
-            const int64_t row = g / nvec;
-            const int idx = (int)(g - row * nvec);
+            const int64_t row = ro.row<false>(g);
+            const int idx = g - (int)row * (int)ro.nvec;
             raw[i] = __builtin_nontemporal_load((const v4u*)(x + row * ldx) + idx);
             float f[8];
             unpack8<BF16>(raw[i], f);
@@ -381,10 +444,10 @@ __global__ __launch_bounds__(256) void quant_per_tensor_single_kernel(const uint
     if (blockIdx.x == 0 && threadIdx.x == 0) scale[0] = a / 127.0f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int64_t g = g0 + i * 256;
+        const int g = g0 + i * 256;
         if (g < total) {
-            const int64_t row = g / nvec;
-            const int idx = (int)(g - row * nvec);
+            const int64_t row = ro.row<false>(g);
+            const int idx = g - (int)row * (int)ro.nvec;
             float f[8];
             unpack8<BF16>(raw[i], f);
             if (inv_s) smooth8(f, inv_s, idx * 8);
@@ -393,23 +456,56 @@ __global__ __launch_bounds__(256) void quant_per_tensor_single_kernel(const uint
     }
 }
 
-// Per-channel calibration statistic: out_j = max_t |x_tj| (bit patterns, see above).
+// Per-channel calibration statistic: out_j = max_t |x_tj|.  A workgroup owns 64 neighbouring channels (one 128-byte line
+// of a row: 8 lanes) and, 32 rows at a time with four rows per lane in flight, a range of rows; the row groups meet in LDS.
+// While the row range is the whole batch (gridDim.y == 1) the result is stored as it is; longer batches are cut into row
+// ranges whose maxima meet by atomic max on the bit patterns (cleared beforehand).  One atomic per channel and workgroup
+// of two rows each, as this pass did before, took 53 us on a 512 x 5120 batch (5 MB; now 4.4), 91 on 2048 x 12288 (14.8), 146
+// on 40000 x 5120 (99).
+constexpr int kChannelRows = 32;
 template <bool BF16>
-__global__ __launch_bounds__(256) void act_absmax_per_channel_kernel(const uint16_t* __restrict__ x, int c_i, int64_t t,
+__global__ __launch_bounds__(256) void act_absmax_per_channel_kernel(const uint16_t* __restrict__ x, int c_i, int64_t t, int64_t rows_per_wg,
                                                                     uint32_t* out_bits)
 {
+    __shared__ float red[4][64];
     const int nvec = c_i >> 3;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= nvec) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int idx = blockIdx.x * 8 + (threadIdx.x & 7);
+    const int64_t r0 = (int64_t)blockIdx.y * rows_per_wg, r1 = r0 + rows_per_wg < t ? r0 + rows_per_wg : t;
     float m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int64_t row = blockIdx.y; row < t; row += gridDim.y) {
-        float f[8];
-        unpack8<BF16>(((const v4u*)(x + row * (int64_t)c_i))[idx], f);
+    if (idx < nvec) {
+        for (int64_t row = r0 + (threadIdx.x >> 3); row < r1; row += 4 * kChannelRows) {
+            v4u raw[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) m[e] = __builtin_fmaxf(m[e], __builtin_fabsf(f[e]));
+            for (int i = 0; i < 4; ++i) {  // past the end: the first row of this lane again
+                const int64_t rr = row + i * kChannelRows < r1 ? row + i * kChannelRows : row;
+                raw[i] = ((const v4u*)(x + rr * (int64_t)c_i))[idx];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float f[8];
+                unpack8<BF16>(raw[i], f);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) m[e] = __builtin_fmaxf(m[e], __builtin_fabsf(f[e]));
+            }
+        }
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) atomicMax(out_bits + idx * 8 + e, __builtin_bit_cast(uint32_t, m[e]));
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int o = 32; o >= 8; o >>= 1) m[e] = __builtin_fmaxf(m[e], __shfl_xor(m[e], o, 64));
+    if (lane < 8) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) red[wave][lane * 8 + e] = m[e];
+    }
+    __syncthreads();
+    const int c = blockIdx.x * 64 + threadIdx.x;
+    if (threadIdx.x < 64 && c < c_i) {
+        const float v = __builtin_fmaxf(__builtin_fmaxf(red[0][threadIdx.x], red[1][threadIdx.x]),
+                                        __builtin_fmaxf(red[2][threadIdx.x], red[3][threadIdx.x]));
+        if (gridDim.y == 1) out_bits[c] = __builtin_bit_cast(uint32_t, v);
+        else atomicMax(out_bits + c, __builtin_bit_cast(uint32_t, v));
+    }
 }
 
 template <bool BF16>
@@ -445,11 +541,36 @@ void launch_per_token(const uint16_t* x, int64_t ldx, int c_i, int64_t t, const 
 #undef SQ_BLOCK
 }
 
-int grid_for(int64_t work_items)
+// Vectors per thread of the elementwise pass, static mode measured on rotating buffers (rows / tiled codes): two from 2^21
+// vectors on (2048 x 12288: 14.6 / 16.1 us against 15.5 / 15.1 with one and 16.0 / 18.1 with four; 2048 x 49152: 49 / 53
+// against 56 / 55 and 54 / 58), one below (1000 x 9216: 7.0 / 7.3 us against 7.0 / 8.1 and 8.2 / 9.2).
+template <bool BF16, bool DYNAMIC>
+void launch_per_tensor(const uint16_t* x, int64_t ldx, int c_i, int64_t total, const float* inv_s, float* scale, const uint32_t* partial,
+                       int n_partial, int8_t* xq, bool tiled, hipStream_t st)
 {
-    int64_t blocks = (work_items + 255) / 256;
-    const int64_t cap = 256 * 16;
-    return (int)(blocks < 1 ? 1 : (blocks > cap ? cap : blocks));
+    const RowOf ro = row_of(c_i >> 3);
+    auto grid = [&](int u) {
+        const int64_t n = (total + 256 * u - 1) / (256 * u);
+        return dim3((unsigned)(n < 65536 ? n : 65536));  // (the kernel strides over the rest)
+    };
+    if (total >= ((int64_t)1 << 31)) sq_launch((quant_per_tensor_kernel<BF16, DYNAMIC, true, 2>), grid(2), dim3(256), 0, st, x, ldx, c_i, ro, total, inv_s, scale, partial, n_partial, xq, tiled);
+    else if (total >= (1 << 21)) sq_launch((quant_per_tensor_kernel<BF16, DYNAMIC, false, 2>), grid(2), dim3(256), 0, st, x, ldx, c_i, ro, total, inv_s, scale, partial, n_partial, xq, tiled);
+    else sq_launch((quant_per_tensor_kernel<BF16, DYNAMIC, false, 1>), grid(1), dim3(256), 0, st, x, ldx, c_i, ro, total, inv_s, scale, partial, n_partial, xq, tiled);
+}
+
+template <bool BF16, bool ATOMIC>
+int launch_absmax(const uint16_t* x, int64_t ldx, int c_i, int64_t total, const float* inv_s, uint32_t* partial, hipStream_t st)
+{
+    constexpr int64_t chunk = (int64_t)kAbsmaxThreads * kAbsmaxUnroll;
+    int64_t grid = (total + chunk - 1) / chunk;
+    if (grid > kO2MaxGrid) grid = kO2MaxGrid;
+    int64_t per = (total + grid - 1) / grid;
+    per = (per + kAbsmaxThreads - 1) / kAbsmaxThreads * kAbsmaxThreads;
+    grid = (total + per - 1) / per;
+    const RowOf ro = row_of(c_i >> 3);
+    if (total >= ((int64_t)1 << 31)) sq_launch((tensor_absmax_kernel<BF16, true, ATOMIC>), dim3((unsigned)grid), dim3(kAbsmaxThreads), 0, st, x, ldx, ro, total, per, inv_s, partial);
+    else sq_launch((tensor_absmax_kernel<BF16, false, ATOMIC>), dim3((unsigned)grid), dim3(kAbsmaxThreads), 0, st, x, ldx, ro, total, per, inv_s, partial);
+    return (int)grid;
 }
 
 constexpr int kO2NV = 8;  // 16-byte vectors a thread holds: a workgroup covers 256 x 8 x 8 = 16384 elements
@@ -501,34 +622,40 @@ sq_status sq_quantize_act(const void* x, sq_dtype dtype, int64_t t, int64_t c_i,
         else launch_per_token<false>(xp, ldx, (int)c_i, t, inv_s, scale, xq, tiled, st);
         return sq_launch_status();
     }
-    const int grid = grid_for(t * (c_i >> 3));
+    const int64_t vecs = t * (c_i >> 3);
     if (mode == SQ_PER_TENSOR_DYNAMIC) {
-        uint32_t* amax = (uint32_t*)workspace;
-        const int64_t vecs = t * (c_i >> 3);
         const int64_t nwg = (vecs + 256 * kO2NV - 1) / (256 * kO2NV);  // workgroups that hold the whole tensor in registers
         const int limit = bf ? single_launch_grid<true>() : single_launch_grid<false>();
-        // A stream that is being captured into a HIP graph records the three-launch version: a replay would reuse
+        const bool full_ws = ws_bytes >= sq_quantize_workspace_bytes() && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
+        // A stream that is being captured into a HIP graph records the two-launch version: a replay would reuse
         // the ticket.
         hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
         if (hipStreamIsCapturing(st, &cap) != hipSuccess) cap = hipStreamCaptureStatusActive;
-        if (cap == hipStreamCaptureStatusNone && nwg <= limit && ws_bytes >= sq_quantize_workspace_bytes() &&
-            (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
+        if (cap == hipStreamCaptureStatusNone && nwg <= limit && full_ws) {
             const uint32_t ticket = sq_next_ticket(), spin_limit = 1u << 21;
-            if (bf) sq_launch((quant_per_tensor_single_kernel<true, kO2NV>), dim3((unsigned)nwg), dim3(256), 0, st, xp, ldx, (int)c_i, t, inv_s, scale, (unsigned char*)workspace, ticket, spin_limit, xq, tiled);
-            else sq_launch((quant_per_tensor_single_kernel<false, kO2NV>), dim3((unsigned)nwg), dim3(256), 0, st, xp, ldx, (int)c_i, t, inv_s, scale, (unsigned char*)workspace, ticket, spin_limit, xq, tiled);
+            const RowOf ro = row_of(c_i >> 3);
+            if (bf) sq_launch((quant_per_tensor_single_kernel<true, kO2NV>), dim3((unsigned)nwg), dim3(256), 0, st, xp, ldx, (int)c_i, ro, (int)vecs, inv_s, scale, (unsigned char*)workspace, ticket, spin_limit, xq, tiled);
+            else sq_launch((quant_per_tensor_single_kernel<false, kO2NV>), dim3((unsigned)nwg), dim3(256), 0, st, xp, ldx, (int)c_i, ro, (int)vecs, inv_s, scale, (unsigned char*)workspace, ticket, spin_limit, xq, tiled);
             return sq_launch_status();
         }
-        sq_launch(fill_u32_kernel, dim3(1), dim3(64), 0, st, amax, 0u, 1);
-        if (bf) {
-            sq_launch(tensor_absmax_kernel<true>, dim3(grid), dim3(256), 0, st, xp, ldx, (int)c_i, t, inv_s, amax);
-            sq_launch((quant_per_tensor_kernel<true, true>), dim3(grid), dim3(256), 0, st, xp, ldx, (int)c_i, t, inv_s, scale, amax, xq, tiled);
+        // Two launches: partial maxima, then every workgroup of the second kernel reduces them.  A caller with less than
+        // the full workspace gets three (clear one cell, maxima by atomic, quantize); results are identical.
+        int n_partial = 1;
+        uint32_t* amax = (uint32_t*)workspace;
+        if (full_ws) {
+            amax = (uint32_t*)((unsigned char*)workspace + 256);
+            n_partial = bf ? launch_absmax<true, false>(xp, ldx, (int)c_i, vecs, inv_s, amax, st)
+                           : launch_absmax<false, false>(xp, ldx, (int)c_i, vecs, inv_s, amax, st);
         } else {
-            sq_launch(tensor_absmax_kernel<false>, dim3(grid), dim3(256), 0, st, xp, ldx, (int)c_i, t, inv_s, amax);
-            sq_launch((quant_per_tensor_kernel<false, true>), dim3(grid), dim3(256), 0, st, xp, ldx, (int)c_i, t, inv_s, scale, amax, xq, tiled);
+            sq_launch(fill_u32_kernel, dim3(1), dim3(64), 0, st, amax, 0u, 1);
+            if (bf) launch_absmax<true, true>(xp, ldx, (int)c_i, vecs, inv_s, amax, st);
+            else launch_absmax<false, true>(xp, ldx, (int)c_i, vecs, inv_s, amax, st);
         }
+        if (bf) launch_per_tensor<true, true>(xp, ldx, (int)c_i, vecs, inv_s, scale, amax, n_partial, xq, tiled, st);
+        else launch_per_tensor<false, true>(xp, ldx, (int)c_i, vecs, inv_s, scale, amax, n_partial, xq, tiled, st);
     } else {
-        if (bf) sq_launch((quant_per_tensor_kernel<true, false>), dim3(grid), dim3(256), 0, st, xp, ldx, (int)c_i, t, inv_s, scale, (const uint32_t*)nullptr, xq, tiled);
-        else sq_launch((quant_per_tensor_kernel<false, false>), dim3(grid), dim3(256), 0, st, xp, ldx, (int)c_i, t, inv_s, scale, (const uint32_t*)nullptr, xq, tiled);
+        if (bf) launch_per_tensor<true, false>(xp, ldx, (int)c_i, vecs, inv_s, scale, nullptr, 0, xq, tiled, st);
+        else launch_per_tensor<false, false>(xp, ldx, (int)c_i, vecs, inv_s, scale, nullptr, 0, xq, tiled, st);
     }
     return sq_launch_status();
 }
@@ -540,13 +667,17 @@ sq_status sq_act_absmax_per_channel(const void* x, sq_dtype dtype, int64_t t, in
     if (dtype != SQ_F16 && dtype != SQ_BF16) return SQ_ERR_UNSUPPORTED;
     if ((c_i & 15) || !sq_aligned16(x) || !sq_aligned16(out)) return SQ_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
-    sq_launch(fill_u32_kernel, dim3((unsigned)((c_i + 255) / 256)), dim3(256), 0, st, (uint32_t*)out, 0u, (int)c_i);
-    const int nvec = (int)(c_i >> 3);
-    dim3 grid((unsigned)((nvec + 255) / 256), (unsigned)(t < 256 ? t : 256));
-    if (dtype == SQ_BF16)
-        sq_launch(act_absmax_per_channel_kernel<true>, grid, dim3(256), 0, st, (const uint16_t*)x, (int)c_i, t, (uint32_t*)out);
-    else
-        sq_launch(act_absmax_per_channel_kernel<false>, grid, dim3(256), 0, st, (const uint16_t*)x, (int)c_i, t, (uint32_t*)out);
+    // One row range while its 64-channel columns alone give every lane at most 16 rounds of loads, or while they fill the
+    // chip; beyond that, ranges of 2048 rows and more, about four workgroups per compute unit.
+    const int64_t cols = (c_i + 63) / 64;
+    int64_t ranges = (t + 2047) / 2048;
+    if (ranges > (1024 + cols - 1) / cols) ranges = (1024 + cols - 1) / cols;
+    const int64_t per = (t + ranges - 1) / ranges;
+    ranges = (t + per - 1) / per;
+    if (ranges > 1) sq_launch(fill_u32_kernel, dim3((unsigned)((c_i + 255) / 256)), dim3(256), 0, st, (uint32_t*)out, 0u, (int)c_i);
+    const dim3 grid((unsigned)cols, (unsigned)ranges);
+    if (dtype == SQ_BF16) sq_launch(act_absmax_per_channel_kernel<true>, grid, dim3(256), 0, st, (const uint16_t*)x, (int)c_i, t, per, (uint32_t*)out);
+    else sq_launch(act_absmax_per_channel_kernel<false>, grid, dim3(256), 0, st, (const uint16_t*)x, (int)c_i, t, per, (uint32_t*)out);
     return sq_launch_status();
 }
 

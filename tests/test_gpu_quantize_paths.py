@@ -1,0 +1,58 @@
+"""Per-tensor quantization and the calibration statistic at the edges of their launch rules, against the same fixed fp32
+arithmetic in torch (every operation of it is exactly rounded, so codes and steps must be identical)."""
+import pytest
+import torch
+
+from paper_2211_10438_amd import binding as sq
+
+pytestmark = pytest.mark.gpu
+
+
+def _div(a, b):
+    """One IEEE fp32 division on the host (torch turns a division by or of a Python number into a multiplication)."""
+    one = lambda v: torch.as_tensor(v, dtype=torch.float32).cpu().reshape(1)  # noqa: E731
+    return (one(a) / one(b)).cuda()
+
+
+def _codes(x, inv_s, r):
+    v = x.float() if inv_s is None else x.float() * inv_s
+    return (v * r).round().clamp(-127, 127).to(torch.int8)
+
+
+# rows of 2, 3, 511 and 769 vectors (the row of a vector comes from a division), one vector short of and at the switch to
+# two vectors per thread (2^21), a single row, and a tensor of many short rows
+@pytest.mark.parametrize("t,c_i", [(1, 16), (3, 48), (70001, 48), (4104, 4088 // 8 * 8), (2727, 6152), (2728, 6160), (513, 4096), (2049, 8192)])
+@pytest.mark.parametrize("with_s", [False, True])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_per_tensor_edges(t, c_i, with_s, dtype):
+    c_i = c_i // 16 * 16
+    print(f"per-tensor {t}x{c_i} s={with_s} {dtype}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(t + c_i)
+    full = torch.randn((t, c_i + 8), generator=g, device="cuda").to(dtype)
+    x = full[:, :c_i]  # a row stride wider than the row
+    full[:, c_i:] = 1e4  # ... whose other columns must not be seen
+    full[t - 1, c_i - 1] = 9.0  # the maximum is the tensor's last element
+    inv_s = torch.rand(c_i, generator=g, device="cuda") + 0.5 if with_s else None
+    v = x.float() if inv_s is None else x.float() * inv_s
+    a = v.abs().max()
+    small = torch.empty(16, dtype=torch.uint8, device="cuda")
+    for ws in (None, small):
+        q, step = sq.quantize_act(x, sq.PER_TENSOR_DYNAMIC, inv_s=inv_s, workspace=ws)
+        assert torch.equal(step, _div(a, 127.0))
+        assert torch.equal(q, _codes(x, inv_s, _div(127.0, a)))
+    delta = torch.full((1,), 0.0123, device="cuda")
+    q, _ = sq.quantize_act(x, sq.PER_TENSOR_STATIC, inv_s=inv_s, static_scale=delta)
+    assert torch.equal(q, _codes(x, inv_s, _div(1.0, delta)))
+
+
+# one row range and several (2048 rows each at least), channel counts that end inside a 64-channel column
+@pytest.mark.parametrize("t", [1, 31, 129, 2048, 2049, 9000])
+@pytest.mark.parametrize("c_i", [16, 64, 1040])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_channel_maxima(t, c_i, dtype):
+    print(f"channel maxima {t}x{c_i} {dtype}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(t * 3 + c_i)
+    x = torch.randn((t, c_i), generator=g, device="cuda").to(dtype)
+    x[t - 1, c_i - 1] = -50.0
+    x[0, 0] = 51.0
+    assert torch.equal(sq.act_absmax_per_channel(x), x.float().abs().amax(0))
