@@ -1,0 +1,44 @@
+// Argument block of the fused attention kernels (gfx950).
+#pragma once
+#include "gemm_args.h"
+
+struct AttnArgs {
+    const int8_t* Q;  // [b][s_q, d]
+    const int8_t* K;  // [b][s_k, d]
+    const int8_t* V;  // [b][s_k, d]
+    void* O;          // [b][s_q, d] 16-bit
+    int8_t* P;        // optional [b][s_q, s_k]: the probability codes, for inspection; or NULL
+    int s_q, s_k, tiles_m;  // tiles_m: workgroups per batch entry
+    int64_t stride_q, stride_k, stride_v, stride_o;  // batch strides in elements
+    float alpha1, alpha2;
+};
+
+constexpr float kLog2e = 1.44269504088896340736f;
+
+// The 4 probability codes of two pairs of 16-bit probabilities (columns 0,1 in ph01, 2,3 in ph23), one byte each:
+// round(127 p16), exactly rounded.
+template <bool BF16> SQ_DEVICE int prob_codes4(uint32_t ph01, uint32_t ph23)
+{
+    if constexpr (BF16) {
+        // the product is exact in fp32, the add of 1.5 * 2^23 rounds it to nearest-even and leaves the code in the low
+        // mantissa byte
+        const uint32_t ph[2] = {ph01, ph23};
+        uint32_t q[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            q[e] = __builtin_bit_cast(uint32_t, __builtin_fmaf(load16_bits<true>(ph[e >> 1] >> ((e & 1) * 16)), 127.0f, 12582912.0f));
+        return (int)pack4_low_bytes(q[0], q[1], q[2], q[3]);
+    } else {
+        // the same in packed fp16, two codes per instruction: fma(p16, 127, 1024) is one rounding of the exact
+        // 127 p16 + 1024 to a grid of spacing 1 (fp16 in [1024, 2048)), i.e. 1024 + round-half-even(127 p16), the
+        // code in the low byte of each half; one byte permute gathers the four codes
+        const sq_f16x2 k127 = {(_Float16)127.0f, (_Float16)127.0f}, k1024 = {(_Float16)1024.0f, (_Float16)1024.0f};
+        const uint32_t c01 = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(sq_f16x2, ph01), k127, k1024));
+        const uint32_t c23 = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(sq_f16x2, ph23), k127, k1024));
+        return (int)__builtin_amdgcn_perm(c23, c01, 0x06040200u);
+    }
+}
+
+// Few queries over many keys (attn_few.hip).
+bool sq_attn_few_eligible(int64_t batch, int64_t s_q, int64_t s_k);
+void sq_attn_few_launch(AttnArgs a, int64_t batch, int64_t d, bool bf16, bool causal, hipStream_t st);

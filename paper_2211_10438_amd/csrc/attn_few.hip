@@ -1,0 +1,303 @@
+// Fused INT8 attention for few queries (the generation stage), gfx950: the same quantization points as attn_fused.hip --
+// scores rounded to 16 bits, probabilities rounded to 16 bits and then to codes with the fixed step 1/127 -- with the work
+// split along the keys instead of along the query rows.
+//
+// With one query per head the layer is bound by reading K and V once (2 d s_k bytes per head).  The row-block kernel gives
+// a workgroup 128 query rows, computes all of them whatever s_q is, reads K twice and walks along the keys one tile at a
+// time: 144 us at 768 heads x 1 x 2048 x 128 where the bytes take 62 at 6.5 TB/s.  Here a workgroup owns at most 16 query
+// rows of a head and its NW waves deal the 64-key groups among themselves:
+//   phase 1  a wave loads the K rows of its groups straight into registers (v_mfma_i32_16x16x64_i8 takes 16 rows x 64 bytes
+//            as they lie in memory, the next group's loads in flight), keeps the 16-bit scores of ALL its groups in registers
+//            (8 per group and lane, two scores each) and a running maximum and sum of exponentials per lane;
+//   meeting  the maxima and sums of the lanes and waves meet through LDS: the row statistics are final, K is not read again;
+//   phase 2  probabilities, codes and P V per group; V arrives by LDS-DMA in a patch of the wave's own, two groups deep (the
+//            first two are in flight across the meeting), and is read with the LDS transpose read; no workgroup barriers.
+// The int32 sums of the waves meet in LDS at the end.  The scores of a lane are 4 neighbouring keys of one query, and its 16
+// codes of a group (bytes 4 b + v <-> key 16 b + 4 (lane >> 4) + v) are its operand fragment of the P V MFMA; V is fetched in
+// that order.
+#include "attn_args.h"
+
+namespace {
+
+constexpr float kNegInf = -__builtin_inff();
+
+template <bool BF16, int HD, int NW, int G>
+__global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, const int causal)
+{
+    constexpr int NKS = HD / 64;           // MFMA steps of Q K^T
+    constexpr int NB = HD / 16;            // 16-column blocks of O
+    constexpr int TILE = 64 * HD;          // bytes of the V rows of a group
+    constexpr int LV = TILE / 1024;        // LDS-DMA loads per group
+    constexpr int CH = HD / 16, RPB = 1024 / HD;  // 16-byte chunks per row, rows per 1 KB
+    constexpr int OP = HD + 4;             // ints per row of the output staging
+    static_assert(HD == 128 || HD == 64, "head dimension");
+    static_assert(16 * OP * 4 <= 2 * TILE, "output staging fits a wave's V patch");
+    __shared__ __attribute__((aligned(1024))) char smem[NW * 2 * TILE];
+    __shared__ float red[2][NW][16];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r16 = lane & 15, g = lane >> 4;
+
+    // Consecutive workgroup ids go round-robin to the 8 XCDs; each XCD gets a contiguous range of the logical order, so
+    // that the row blocks of one head run on one L2.
+    int64_t pid;
+    {
+        const int64_t wg = blockIdx.x, j = wg >> 3, per = (int64_t)gridDim.x >> 3;
+        const int xcd = (int)(wg & 7), r = (int)(gridDim.x & 7);
+        pid = xcd * per + (xcd < r ? xcd : r) + j;
+    }
+    const int64_t batch = pid / p.tiles_m;
+    const int q0 = (int)(pid - batch * p.tiles_m) * 16;
+    const int last_q = q0 + 15 < p.s_q ? q0 + 15 : p.s_q - 1;
+    // keys 0 .. row + coff are visible to a row; n_keys: those the last row of this workgroup sees
+    const int coff = causal ? p.s_k - p.s_q : p.s_k;
+    const int n_keys = last_q + coff + 1 < p.s_k ? last_q + coff + 1 : p.s_k;
+    const int groups = (n_keys + 63) >> 6;
+    const int ng = groups > wave ? (groups - wave + NW - 1) / NW : 0;  // groups of this wave: wave, wave + NW, ...
+    const int myrow = q0 + r16 < p.s_q ? q0 + r16 : p.s_q - 1;  // rows past s_q repeat the last one; never stored
+    const int lim0 = (myrow + coff < p.s_k - 1 ? myrow + coff : p.s_k - 1) - 4 * g;  // key 4 g + x is visible when x <= lim0
+
+    const int8_t* Kb = p.K + batch * p.stride_k;
+    const int8_t* Vb = p.V + batch * p.stride_v;
+
+    // ---- V patch of this wave: row k at k * HD, its chunks permuted (position = chunk ^ swz(k)) so that the 32 rows a
+    // transpose read touches lie over all banks.
+    auto swz = [](int k) { return HD == 128 ? (k >> 1) & 7 : (k >> 2) & 3; };
+    char* patch = smem + wave * 2 * TILE;
+    auto issue_v = [&](int gi, int stage) {  // gi: group number within this wave (clamped: past the end the last one again)
+        const int k0 = ((gi < ng ? gi : ng - 1) * NW + wave) * 64;
+#pragma unroll
+        for (int i = 0; i < LV; ++i) {
+            const int row = i * RPB + lane / CH, pos = lane % CH;
+            int k = k0 + row;
+            k = k < p.s_k ? k : p.s_k - 1;  // (their codes are zero)
+            __builtin_amdgcn_global_load_lds(GPTR(Vb + (int64_t)k * HD + ((pos ^ swz(row)) * 16)), LPTR(patch + stage * TILE + i * 1024), 16, 0, 0);
+        }
+    };
+    int voff;
+    {
+        // within 16 lanes, lanes 2 j and 2 j + 1 name the halves of a key's 16 columns and lane i receives column i of
+        // the eight keys: j = 0..3 key 4 g + j, j = 4..7 key 16 + 4 g + j - 4; the second read takes the keys 32 further on
+        const int j = r16 >> 1, key = 4 * g + (j & 3) + 16 * (j >> 2);
+        voff = key * HD + swz(key) * 16 + (r16 & 1) * 8;
+    }
+    // Four column blocks' fragments.  (In asm, with their wait: the compiler answers the transpose-read builtin, of which it
+    // does not know what it reads, with a wait for every LDS-DMA in flight, the next group's too.)
+    auto v_frags = [&](const char* vt, int jn, v4i(&f)[4]) {
+        const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)vt;
+        const uint32_t a0 = base + (uint32_t)(voff ^ (jn << 4)), a1 = base + (uint32_t)(voff ^ ((jn + 1) << 4)),
+                       a2 = base + (uint32_t)(voff ^ ((jn + 2) << 4)), a3 = base + (uint32_t)(voff ^ ((jn + 3) << 4));
+        v2i lo0, lo1, lo2, lo3, hi0, hi1, hi2, hi3;
+        asm volatile("ds_read_b64_tr_b8 %0, %8\n\tds_read_b64_tr_b8 %1, %8 offset:%12\n\t"
+                     "ds_read_b64_tr_b8 %2, %9\n\tds_read_b64_tr_b8 %3, %9 offset:%12\n\t"
+                     "ds_read_b64_tr_b8 %4, %10\n\tds_read_b64_tr_b8 %5, %10 offset:%12\n\t"
+                     "ds_read_b64_tr_b8 %6, %11\n\tds_read_b64_tr_b8 %7, %11 offset:%12\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(lo0), "=&v"(hi0), "=&v"(lo1), "=&v"(hi1), "=&v"(lo2), "=&v"(hi2), "=&v"(lo3), "=&v"(hi3)
+                     : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "n"(32 * HD)
+                     : "memory");
+        f[0] = v4i{lo0.x, lo0.y, hi0.x, hi0.y};
+        f[1] = v4i{lo1.x, lo1.y, hi1.x, hi1.y};
+        f[2] = v4i{lo2.x, lo2.y, hi2.x, hi2.y};
+        f[3] = v4i{lo3.x, lo3.y, hi3.x, hi3.y};
+    };
+
+    // ---- phase 1
+    v4i fq[NKS];
+    {
+        const int8_t* qp = p.Q + batch * p.stride_q + (int64_t)myrow * HD + g * 16;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) fq[ks] = *(const v4i*)(qp + ks * 64);
+    }
+    v4i kb[2][4][NKS];
+    auto load_k = [&](v4i(&dst)[4][NKS], int gi) {
+        const int k0 = ((gi < ng ? gi : ng - 1) * NW + wave) * 64;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            int k = k0 + b * 16 + r16;
+            k = k < p.s_k ? k : p.s_k - 1;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) dst[b][ks] = *(const v4i*)(Kb + (int64_t)k * HD + ks * 64 + g * 16);
+        }
+    };
+    uint32_t sc[G][4][2];  // scores of group gi, block b: keys 16 b + 4 g + 0,1 and + 2,3 as 16-bit pairs
+    float m_run = kNegInf, l_run = 0.0f;
+    const float alpha1 = p.alpha1;
+    auto phase1 = [&](auto GI_, auto&& self) -> void {
+        constexpr int gi = decltype(GI_)::value;
+        if constexpr (gi + 1 < G) load_k(kb[(gi + 1) & 1], gi + 1);  // on every path, so that the wait for this group's rows leaves these in flight
+        __builtin_amdgcn_sched_barrier(0);  // (left alone, the loads sink to their first use)
+        const int lim = lim0 - (gi * NW + wave) * 64;
+        float s[16];
+        float mx = kNegInf;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            v4i acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(kb[gi & 1][b][0], fq[0], v4i{0, 0, 0, 0}, 0, 0, 0);
+            if constexpr (NKS == 2) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(kb[gi & 1][b][1], fq[1], acc, 0, 0, 0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t pr = store16x2_bits<BF16>((float)acc[2 * h] * alpha1, (float)acc[2 * h + 1] * alpha1);
+                sc[gi][b][h] = pr;
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const float v = 16 * b + 2 * h + e <= lim ? load16_bits<BF16>(pr >> (16 * e)) : kNegInf;
+                    s[4 * b + 2 * h + e] = v;
+                    mx = __builtin_fmaxf(mx, v);
+                }
+            }
+        }
+        const float m_new = __builtin_fmaxf(m_run, mx);
+        const float scale = m_run == m_new ? 1.0f : __builtin_amdgcn_exp2f((m_run - m_new) * kLog2e);
+        const float nm = m_new == kNegInf ? 0.0f : -m_new * kLog2e;  // (nothing visible yet: every exponential below is 0)
+        float part = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) part += __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], kLog2e, nm));
+        l_run = l_run * scale + part;
+        m_run = m_new;
+        if constexpr (gi + 1 < G) {
+            if (gi + 1 < ng) self(std::integral_constant<int, gi + 1>{}, self);
+        }
+    };
+    if (ng > 0) {
+        load_k(kb[0], 0);
+        phase1(std::integral_constant<int, 0>{}, phase1);
+        issue_v(0, 0);
+        issue_v(1, 1);
+    }
+
+    // ---- the row statistics: over the four lanes of a row, then over the waves
+    float M = m_run, L = l_run;
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+        const float m2 = __shfl_xor(M, o, 64), l2 = __shfl_xor(L, o, 64), mm = __builtin_fmaxf(M, m2);
+        L = L * (M == mm ? 1.0f : __builtin_amdgcn_exp2f((M - mm) * kLog2e)) + l2 * (m2 == mm ? 1.0f : __builtin_amdgcn_exp2f((m2 - mm) * kLog2e));
+        M = mm;
+    }
+    if (lane < 16) {
+        red[0][wave][lane] = M;
+        red[1][wave][lane] = L;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();  // (not __syncthreads: the first V rows stay in flight)
+    asm volatile("" ::: "memory");
+    M = kNegInf;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = __builtin_fmaxf(M, red[0][w][r16]);
+    L = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float m = red[0][w][r16];
+        L += red[1][w][r16] * (m == M ? 1.0f : __builtin_amdgcn_exp2f((m - M) * kLog2e));
+    }
+    const float nm = -M * kLog2e - __builtin_amdgcn_logf(L);  // p = 2^(s log2(e) - (M log2(e) + log2(L)))
+
+    // ---- phase 2
+    v4i acc_o[NB];
+#pragma unroll
+    for (int jn = 0; jn < NB; ++jn) acc_o[jn] = v4i{0, 0, 0, 0};
+    int8_t* Prow = nullptr;
+    if (p.P && q0 + r16 < p.s_q) Prow = p.P + (batch * p.s_q + q0 + r16) * (int64_t)p.s_k + 4 * g;
+    auto phase2 = [&](auto GI_, auto&& self) -> void {
+        constexpr int gi = decltype(GI_)::value;
+        const int k0 = (gi * NW + wave) * 64, lim = lim0 - k0;
+        v4i fp;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            uint32_t ph[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float pr[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    pr[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(load16_bits<BF16>(sc[gi][b][h] >> (16 * e)), kLog2e, nm));
+                    pr[e] = 16 * b + 2 * h + e <= lim ? pr[e] : 0.0f;
+                }
+                ph[h] = store16x2_bits<BF16>(pr[0], pr[1]);
+            }
+            fp[b] = prob_codes4<BF16>(ph[0], ph[1]);
+            if (Prow && k0 + 16 * b < p.s_k) *(int*)(Prow + k0 + 16 * b) = fp[b];
+        }
+        wait_vmcnt_imm<LV>();  // this group's V rows have landed; the next group's may be in flight
+        const char* vt = patch + (gi & 1) * TILE;
+#pragma unroll
+        for (int jn = 0; jn < NB; jn += 4) {
+            v4i f[4];
+            v_frags(vt, jn, f);
+            if (jn + 4 == NB) issue_v(gi + 2, gi & 1);  // the last reads are done: the half can be filled again
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc_o[jn + i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], fp, acc_o[jn + i], 0, 0, 0);
+        }
+        if constexpr (gi + 1 < G) {
+            if (gi + 1 < ng) self(std::integral_constant<int, gi + 1>{}, self);
+        }
+    };
+    if (ng > 0) phase2(std::integral_constant<int, 0>{}, phase2);
+    if (Prow)  // groups no row of this workgroup sees
+        for (int c = (groups + wave) * 64; c < p.s_k; c += NW * 64)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                if (c + 16 * b < p.s_k) *(int*)(Prow + c + 16 * b) = 0;
+
+    // ---- the waves' sums meet: accumulator block jn, register v of lane l is query l & 15, column 16 jn + 4 (l >> 4) + v
+    wait_vmcnt_imm<0>();  // the refills past the end have landed: the patch is free
+    int* stg = (int*)patch;
+#pragma unroll
+    for (int jn = 0; jn < NB; ++jn) *(v4i*)(stg + r16 * OP + 16 * jn + 4 * g) = acc_o[jn];
+    __syncthreads();
+    const float alpha2 = p.alpha2;
+    uint16_t* Ob = (uint16_t*)p.O + batch * p.stride_o + (int64_t)q0 * HD;
+    const int items = (last_q - q0 + 1) * (HD / 4);
+    for (int i = threadIdx.x; i < items; i += NW * 64) {
+        const int r = i / (HD / 4), c = (i - r * (HD / 4)) * 4;
+        v4i s = {0, 0, 0, 0};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) s += *(const v4i*)((const int*)(smem + w * 2 * TILE) + r * OP + c);
+        const uint32_t o01 = dequant_pair<BF16>(s[0], s[1], alpha2, alpha2, 0.0f, 0.0f, false, false, 0u, false);
+        const uint32_t o23 = dequant_pair<BF16>(s[2], s[3], alpha2, alpha2, 0.0f, 0.0f, false, false, 0u, false);
+        *(v2u*)(Ob + r * HD + c) = v2u{o01, o23};
+    }
+}
+
+template <bool BF16, int HD, int NW> void launch_g(const AttnArgs& a, unsigned grid, bool causal, hipStream_t st)
+{
+    const int g = ((a.s_k + 63) / 64 + NW - 1) / NW;
+#define SQ_FEW(G) sq_launch((attn_few_kernel<BF16, HD, NW, G>), dim3(grid), dim3(NW * 64), 0, st, a, causal ? 1 : 0)
+    if (g <= 2) SQ_FEW(2);
+    else if (g <= 4) SQ_FEW(4);
+    else if (g <= 8) SQ_FEW(8);
+    else SQ_FEW(16);
+#undef SQ_FEW
+}
+
+constexpr int kFewKeys = 8 * 16 * 64;  // what the registers of eight waves hold
+
+}  // namespace
+
+// Up to 32 queries (two workgroups per head) this form is always the faster one: the row-block kernel computes 128 rows per
+// head (768 heads x 1 x 2048 x 128: 70 against 157-166 us; 288 x 32 x 1024: 24.5 against 48.5; 12 x 1 x 1024 x 64: 6.8 against
+// 23).  Every further 16 rows read K and V again, out of L2, and once the row-block kernel fills the chip by itself (one
+// workgroup per head, two per compute unit) that decides: 64 queries at 288 heads x 1024 keys 36 against 48 us, at 96 x 2048
+// 28 against 57, but at 768 x 512 60 against 41.
+bool sq_attn_few_eligible(int64_t batch, int64_t s_q, int64_t s_k)
+{
+    // (2^21: a grid of 16-row blocks stays below 2^32 threads)
+    return s_k <= kFewKeys && batch < (1 << 21) && (s_q <= 32 || (s_q <= 64 && batch <= 512));
+}
+
+void sq_attn_few_launch(AttnArgs a, int64_t batch, int64_t d, bool bf16, bool causal, hipStream_t st)
+{
+    a.tiles_m = (a.s_q + 15) / 16;
+    const unsigned grid = (unsigned)(batch * a.tiles_m);
+    // Eight waves per workgroup where there is at most one workgroup per compute unit, or where four waves' registers do
+    // not hold the scores (16 groups of 64 keys each); else four, two workgroups per compute unit, so that one loads
+    // while the other is at its meeting or its epilogue.
+    const bool eight = grid <= 256 || a.s_k > 4 * 16 * 64;
+#define SQ_FEW(BF, HD) do { if (eight) launch_g<BF, HD, 8>(a, grid, causal, st); else launch_g<BF, HD, 4>(a, grid, causal, st); } while (0)
+    if (d == 128) {
+        if (bf16) SQ_FEW(true, 128); else SQ_FEW(false, 128);
+    } else {
+        if (bf16) SQ_FEW(true, 64); else SQ_FEW(false, 64);
+    }
+#undef SQ_FEW
+}

@@ -22,22 +22,10 @@
 // cycles); two workgroups per compute unit let one wave's MFMAs run under the other's exponentials.
 #include <type_traits>
 
-#include "gemm_args.h"
+#include "attn_args.h"
 
 namespace {
 
-struct AttnArgs {
-    const int8_t* Q;  // [b][s_q, d]
-    const int8_t* K;  // [b][s_k, d]
-    const int8_t* V;  // [b][s_k, d]
-    void* O;          // [b][s_q, d] 16-bit
-    int8_t* P;        // optional [b][s_q, s_k]: the probability codes, for inspection; or NULL
-    int s_q, s_k, tiles_m;  // tiles_m: workgroups per batch entry (row blocks of 128 queries; pairs of them in the causal form)
-    int64_t stride_q, stride_k, stride_v, stride_o;  // batch strides in elements
-    float alpha1, alpha2;
-};
-
-constexpr float kLog2e = 1.44269504088896340736f;
 constexpr int kIntMin = -2147483647 - 1;
 
 // MODE, one instantiation each, so that the common case carries no mask tests (with the first two forms in one kernel
@@ -314,23 +302,7 @@ __global__ __launch_bounds__(256, 2) void attn_i8_kernel(const AttnArgs p)
                         }
                         ph[e >> 1] = store16x2_bits<BF16>(pr0, pr1);
                     }
-                    if constexpr (BF16) {
-                        // round(127 p16): the product is exact in fp32, the add of 1.5 * 2^23 rounds it to nearest-even and
-                        // leaves the code in the low mantissa byte
-                        uint32_t q[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            q[e] = __builtin_bit_cast(uint32_t, __builtin_fmaf(load16_bits<true>(ph[e >> 1] >> ((e & 1) * 16)), 127.0f, 12582912.0f));
-                        fp[g] = (int)pack4_low_bytes(q[0], q[1], q[2], q[3]);
-                    } else {
-                        // the same in packed fp16, two codes per instruction: fma(p16, 127, 1024) is one rounding of the exact
-                        // 127 p16 + 1024 to a grid of spacing 1 (fp16 in [1024, 2048)), i.e. 1024 + round-half-even(127 p16), the
-                        // code in the low byte of each half; one byte permute gathers the four codes
-                        const sq_f16x2 k127 = {(_Float16)127.0f, (_Float16)127.0f}, k1024 = {(_Float16)1024.0f, (_Float16)1024.0f};
-                        const uint32_t c01 = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(sq_f16x2, ph[0]), k127, k1024));
-                        const uint32_t c23 = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(sq_f16x2, ph[1]), k127, k1024));
-                        fp[g] = (int)__builtin_amdgcn_perm(c23, c01, 0x06040200u);
-                    }
+                    fp[g] = prob_codes4<BF16>(ph[0], ph[1]);
                 }
                 if (Prow) {
 #pragma unroll
@@ -418,8 +390,12 @@ static sq_status attention(const int8_t* q, const int8_t* k, const int8_t* v, fl
     a.tiles_m = (int)(causal ? (tiles_m + 1) / 2 : tiles_m);  // causal: workgroups own pairs of row blocks
     a.stride_q = stride_q; a.stride_k = stride_k; a.stride_v = stride_v; a.stride_o = stride_o;
     a.alpha1 = alpha1; a.alpha2 = alpha2;
-    const dim3 grid((unsigned)(b * a.tiles_m)), block(256);
     hipStream_t st = (hipStream_t)stream;
+    if (sq_attn_few_eligible(b, s_q, s_k)) {
+        sq_attn_few_launch(a, b, d, out == SQ_BF16, causal, st);
+        return sq_launch_status();
+    }
+    const dim3 grid((unsigned)(b * a.tiles_m)), block(256);
     const bool tail = (s_k & 127) != 0;
 #define SQ_ATTN(BF, HD)                                                                        \
     do {                                                                                       \
