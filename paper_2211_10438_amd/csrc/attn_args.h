@@ -8,7 +8,9 @@ struct AttnArgs {
     const int8_t* V;  // [b][s_k, d]
     void* O;          // [b][s_q, d] 16-bit
     int8_t* P;        // optional [b][s_q, s_k]: the probability codes, for inspection; or NULL
-    int s_q, s_k, tiles_m;  // tiles_m: workgroups per batch entry
+    int s_q, s_k, tiles_m;  // tiles_m: workgroups (row blocks) per batch entry
+    int batch, chunk;       // batch entries, and how many of them an XCD works on at a time
+    int causal, coff;       // query i sees the keys j <= min(i + coff, s_k - 1)
     int64_t stride_q, stride_k, stride_v, stride_o;  // batch strides in elements
     float alpha1, alpha2;
 };
@@ -40,5 +42,5 @@ template <bool BF16> SQ_DEVICE int prob_codes4(uint32_t ph01, uint32_t ph23)
 }
 
 // Few queries over many keys (attn_few.hip).
-bool sq_attn_few_eligible(int64_t batch, int64_t s_q, int64_t s_k);
+bool sq_attn_few_eligible(int64_t batch, int64_t s_q, int64_t s_k, int64_t d, bool causal);
 void sq_attn_few_launch(AttnArgs a, int64_t batch, int64_t d, bool bf16, bool causal, hipStream_t st);

@@ -4,16 +4,19 @@
 //
 // With one query per head the layer is bound by reading K and V once (2 d s_k bytes per head).  The row-block kernel gives
 // a workgroup 128 query rows, computes all of them whatever s_q is, reads K twice and walks along the keys one tile at a
-// time: 144 us at 768 heads x 1 x 2048 x 128 where the bytes take 62 at 6.5 TB/s.  Here a workgroup owns at most 16 query
-// rows of a head and its NW waves deal the 64-key groups among themselves:
+// time: 139 us at 768 heads x 1 x 2048 x 128 where the bytes take 62 at 6.5 TB/s (this kernel 66).  Here a workgroup owns at most 16 query
+// rows of a head and its NW waves deal the 128-key groups among themselves:
 //   phase 1  a wave loads the K rows of its groups straight into registers (v_mfma_i32_16x16x64_i8 takes 16 rows x 64 bytes
-//            as they lie in memory, the next group's loads in flight), keeps the 16-bit scores of ALL its groups in registers
-//            (8 per group and lane, two scores each) and a running maximum and sum of exponentials per lane;
-//   meeting  the maxima and sums of the lanes and waves meet through LDS: the row statistics are final, K is not read again;
-//   phase 2  probabilities, codes and P V per group; V arrives by LDS-DMA in a patch of the wave's own, two groups deep (the
-//            first two are in flight across the meeting), and is read with the LDS transpose read; no workgroup barriers.
+//            as they lie in memory, the next 64 in flight), keeps the 16-bit scores of ALL its groups in registers (16 per
+//            group and lane, two scores each) and leaves each group's row maxima in LDS;
+//   sums     with the running maximum over the groups up to its own known, a wave sums the exponentials of each group; the
+//            row statistics are then folded group after group.  Sums and folds run in the order, and with the running maxima,
+//            of the row-block kernel, so that both kernels give the same codes bit for bit (the sum of a row depends on the
+//            order in its last bits, and a code may hang on those);
+//   phase 2  probabilities, codes and P V per 64 keys; V arrives by LDS-DMA in a patch of the wave's own, two deep (the
+//            first two are in flight across the sums), and is read with the LDS transpose read; no workgroup barriers.
 // The int32 sums of the waves meet in LDS at the end.  The scores of a lane are 4 neighbouring keys of one query, and its 16
-// codes of a group (bytes 4 b + v <-> key 16 b + 4 (lane >> 4) + v) are its operand fragment of the P V MFMA; V is fetched in
+// codes of 64 keys (bytes 4 b + v <-> key 16 b + 4 (lane >> 4) + v) are its operand fragment of the P V MFMA; V is fetched in
 // that order.
 #include "attn_args.h"
 
@@ -26,14 +29,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, 
 {
     constexpr int NKS = HD / 64;           // MFMA steps of Q K^T
     constexpr int NB = HD / 16;            // 16-column blocks of O
-    constexpr int TILE = 64 * HD;          // bytes of the V rows of a group
-    constexpr int LV = TILE / 1024;        // LDS-DMA loads per group
+    constexpr int TILE = 64 * HD;          // bytes of the V rows of 64 keys
+    constexpr int LV = TILE / 1024;        // LDS-DMA loads per 64 keys
     constexpr int CH = HD / 16, RPB = 1024 / HD;  // 16-byte chunks per row, rows per 1 KB
     constexpr int OP = HD + 4;             // ints per row of the output staging
     static_assert(HD == 128 || HD == 64, "head dimension");
     static_assert(16 * OP * 4 <= 2 * TILE, "output staging fits a wave's V patch");
     __shared__ __attribute__((aligned(1024))) char smem[NW * 2 * TILE];
-    __shared__ float red[2][NW][16];
+    __shared__ float gmax[G * NW][16];     // row maxima of a group
+    __shared__ float gsum[G * NW][2][16];  // its sums of exponentials, for the keys with bit 2 clear and set
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -41,20 +45,23 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, 
 
     // Consecutive workgroup ids go round-robin to the 8 XCDs; each XCD gets a contiguous range of the logical order, so
     // that the row blocks of one head run on one L2.
-    int64_t pid;
+    uint32_t pid;
     {
-        const int64_t wg = blockIdx.x, j = wg >> 3, per = (int64_t)gridDim.x >> 3;
-        const int xcd = (int)(wg & 7), r = (int)(gridDim.x & 7);
+        const uint32_t j = blockIdx.x >> 3, per = gridDim.x >> 3, xcd = blockIdx.x & 7, r = gridDim.x & 7;
         pid = xcd * per + (xcd < r ? xcd : r) + j;
     }
-    const int64_t batch = pid / p.tiles_m;
-    const int q0 = (int)(pid - batch * p.tiles_m) * 16;
+    const uint32_t head = pid / (uint32_t)p.tiles_m;
+    const int64_t batch = head;
+    const int q0 = (int)(pid - head * (uint32_t)p.tiles_m) * 16;
     const int last_q = q0 + 15 < p.s_q ? q0 + 15 : p.s_q - 1;
     // keys 0 .. row + coff are visible to a row; n_keys: those the last row of this workgroup sees
     const int coff = causal ? p.s_k - p.s_q : p.s_k;
     const int n_keys = last_q + coff + 1 < p.s_k ? last_q + coff + 1 : p.s_k;
-    const int groups = (n_keys + 63) >> 6;
+    const int groups = (n_keys + 127) >> 7;
     const int ng = groups > wave ? (groups - wave + NW - 1) / NW : 0;  // groups of this wave: wave, wave + NW, ...
+    // Its keys in halves of 64: half hi is keys khalf(hi) .. + 63, hi = 2 (number of the group within the wave) + 0 / 1.  Past
+    // the last one comes the last one again (loads that nobody uses keep the number in flight the same on every path).
+    auto khalf = [&](int hi) { const int c = hi < 2 * ng ? hi : 2 * ng - 1; return ((c >> 1) * NW + wave) * 128 + (c & 1) * 64; };
     const int myrow = q0 + r16 < p.s_q ? q0 + r16 : p.s_q - 1;  // rows past s_q repeat the last one; never stored
     const int lim0 = (myrow + coff < p.s_k - 1 ? myrow + coff : p.s_k - 1) - 4 * g;  // key 4 g + x is visible when x <= lim0
 
@@ -65,8 +72,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, 
     // transpose read touches lie over all banks.
     auto swz = [](int k) { return HD == 128 ? (k >> 1) & 7 : (k >> 2) & 3; };
     char* patch = smem + wave * 2 * TILE;
-    auto issue_v = [&](int gi, int stage) {  // gi: group number within this wave (clamped: past the end the last one again)
-        const int k0 = ((gi < ng ? gi : ng - 1) * NW + wave) * 64;
+    auto issue_v = [&](int hi, int stage) {
+        const int k0 = khalf(hi);
 #pragma unroll
         for (int i = 0; i < LV; ++i) {
             const int row = i * RPB + lane / CH, pos = lane % CH;
@@ -83,7 +90,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, 
         voff = key * HD + swz(key) * 16 + (r16 & 1) * 8;
     }
     // Four column blocks' fragments.  (In asm, with their wait: the compiler answers the transpose-read builtin, of which it
-    // does not know what it reads, with a wait for every LDS-DMA in flight, the next group's too.)
+    // does not know what it reads, with a wait for every LDS-DMA in flight, the next rows' too.)
     auto v_frags = [&](const char* vt, int jn, v4i(&f)[4]) {
         const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)vt;
         const uint32_t a0 = base + (uint32_t)(voff ^ (jn << 4)), a1 = base + (uint32_t)(voff ^ ((jn + 1) << 4)),
@@ -111,8 +118,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, 
         for (int ks = 0; ks < NKS; ++ks) fq[ks] = *(const v4i*)(qp + ks * 64);
     }
     v4i kb[2][4][NKS];
-    auto load_k = [&](v4i(&dst)[4][NKS], int gi) {
-        const int k0 = ((gi < ng ? gi : ng - 1) * NW + wave) * 64;
+    auto load_k = [&](v4i(&dst)[4][NKS], int hi) {
+        const int k0 = khalf(hi);
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             int k = k0 + b * 16 + r16;
@@ -121,42 +128,34 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, 
             for (int ks = 0; ks < NKS; ++ks) dst[b][ks] = *(const v4i*)(Kb + (int64_t)k * HD + ks * 64 + g * 16);
         }
     };
-    uint32_t sc[G][4][2];  // scores of group gi, block b: keys 16 b + 4 g + 0,1 and + 2,3 as 16-bit pairs
-    float m_run = kNegInf, l_run = 0.0f;
+    uint32_t sc[2 * G][4][2];  // scores of half hi, block b: keys 16 b + 4 g + 0,1 and + 2,3 as 16-bit pairs
     const float alpha1 = p.alpha1;
-    auto phase1 = [&](auto GI_, auto&& self) -> void {
-        constexpr int gi = decltype(GI_)::value;
-        if constexpr (gi + 1 < G) load_k(kb[(gi + 1) & 1], gi + 1);  // on every path, so that the wait for this group's rows leaves these in flight
+    float mx = kNegInf;
+    auto phase1 = [&](auto HI_, auto&& self) -> void {
+        constexpr int hi = decltype(HI_)::value;
+        if constexpr (hi + 1 < 2 * G) load_k(kb[(hi + 1) & 1], hi + 1);  // on every path, so that the wait for this half's rows leaves these in flight
         __builtin_amdgcn_sched_barrier(0);  // (left alone, the loads sink to their first use)
-        const int lim = lim0 - (gi * NW + wave) * 64;
-        float s[16];
-        float mx = kNegInf;
+        const int lim = lim0 - khalf(hi);
+        if constexpr ((hi & 1) == 0) mx = kNegInf;
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-            v4i acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(kb[gi & 1][b][0], fq[0], v4i{0, 0, 0, 0}, 0, 0, 0);
-            if constexpr (NKS == 2) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(kb[gi & 1][b][1], fq[1], acc, 0, 0, 0);
+            v4i acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(kb[hi & 1][b][0], fq[0], v4i{0, 0, 0, 0}, 0, 0, 0);
+            if constexpr (NKS == 2) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(kb[hi & 1][b][1], fq[1], acc, 0, 0, 0);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const uint32_t pr = store16x2_bits<BF16>((float)acc[2 * h] * alpha1, (float)acc[2 * h + 1] * alpha1);
-                sc[gi][b][h] = pr;
+                sc[hi][b][h] = pr;
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const float v = 16 * b + 2 * h + e <= lim ? load16_bits<BF16>(pr >> (16 * e)) : kNegInf;
-                    s[4 * b + 2 * h + e] = v;
-                    mx = __builtin_fmaxf(mx, v);
-                }
+                for (int e = 0; e < 2; ++e) mx = __builtin_fmaxf(mx, 16 * b + 2 * h + e <= lim ? load16_bits<BF16>(pr >> (16 * e)) : kNegInf);
             }
         }
-        const float m_new = __builtin_fmaxf(m_run, mx);
-        const float scale = m_run == m_new ? 1.0f : __builtin_amdgcn_exp2f((m_run - m_new) * kLog2e);
-        const float nm = m_new == kNegInf ? 0.0f : -m_new * kLog2e;  // (nothing visible yet: every exponential below is 0)
-        float part = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) part += __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], kLog2e, nm));
-        l_run = l_run * scale + part;
-        m_run = m_new;
-        if constexpr (gi + 1 < G) {
-            if (gi + 1 < ng) self(std::integral_constant<int, gi + 1>{}, self);
+        if constexpr (hi & 1) {
+            mx = __builtin_fmaxf(mx, __shfl_xor(mx, 16, 64));
+            mx = __builtin_fmaxf(mx, __shfl_xor(mx, 32, 64));
+            if (lane < 16) gmax[(hi >> 1) * NW + wave][lane] = mx;
+        }
+        if constexpr (hi + 1 < 2 * G) {
+            if (hi + 1 < 2 * ng) self(std::integral_constant<int, hi + 1>{}, self);
         }
     };
     if (ng > 0) {
@@ -165,31 +164,68 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, 
         issue_v(0, 0);
         issue_v(1, 1);
     }
+    auto meet = [&] {  // (not __syncthreads: the first V rows stay in flight)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    meet();
 
-    // ---- the row statistics: over the four lanes of a row, then over the waves
-    float M = m_run, L = l_run;
+    // ---- sums.  The keys of a row with bit 2 = h lie in lanes g = h and g = h + 2, four of a 16-key block in each.  Two groups
+    // are summed together: a swap of lane halves gives the lower lanes both halves of the first group's exponentials and the
+    // upper lanes both of the second's, and each adds its group's 64 in the order of the keys.
+    {
+        float m_cur = kNegInf;
+        int done = 0;  // groups whose maxima m_cur covers
+        auto running_max = [&](int t) {
+            for (; done <= t; ++done) m_cur = __builtin_fmaxf(m_cur, gmax[done][r16]);
+            return m_cur;
+        };
+        auto sums = [&](auto PI_, auto&& self) -> void {
+            constexpr int ga = 2 * decltype(PI_)::value, gb = ga + 1;
+            const int ta = ga * NW + wave, tb = gb * NW + wave;
+            const float nma = -running_max(ta) * kLog2e;
+            const bool two = gb < ng;
+            const float nmb = two ? -running_max(tb) * kLog2e : 0.0f;
+            const int la = lim0 - ta * 128, lb = two ? lim0 - tb * 128 : -1;  // (no second group: nothing of it is visible)
+            float part = 0.0f;
 #pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {
-        const float m2 = __shfl_xor(M, o, 64), l2 = __shfl_xor(L, o, 64), mm = __builtin_fmaxf(M, m2);
-        L = L * (M == mm ? 1.0f : __builtin_amdgcn_exp2f((M - mm) * kLog2e)) + l2 * (m2 == mm ? 1.0f : __builtin_amdgcn_exp2f((m2 - mm) * kLog2e));
-        M = mm;
-    }
-    if (lane < 16) {
-        red[0][wave][lane] = M;
-        red[1][wave][lane] = L;
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();  // (not __syncthreads: the first V rows stay in flight)
-    asm volatile("" ::: "memory");
-    M = kNegInf;
+            for (int b = 0; b < 8; ++b) {
+                float lo[4], up[4];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) M = __builtin_fmaxf(M, red[0][w][r16]);
-    L = 0.0f;
+                for (int v = 0; v < 4; ++v) {
+                    const uint32_t pa = sc[2 * ga + (b >> 2)][b & 3][v >> 1], pb = sc[2 * gb + (b >> 2)][b & 3][v >> 1];
+                    float ea = __builtin_amdgcn_exp2f(__builtin_fmaf(load16_bits<BF16>(pa >> (16 * (v & 1))), kLog2e, nma));
+                    float eb = __builtin_amdgcn_exp2f(__builtin_fmaf(load16_bits<BF16>(pb >> (16 * (v & 1))), kLog2e, nmb));
+                    ea = 16 * b + v <= la ? ea : 0.0f;
+                    eb = 16 * b + v <= lb ? eb : 0.0f;
+                    const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, ea), __builtin_bit_cast(uint32_t, eb), false, false);
+                    const uint32_t s0 = sw[0], s1 = sw[1];  // copies: a vector element is no object to cast from
+                    lo[v] = __builtin_bit_cast(float, s0);
+                    up[v] = __builtin_bit_cast(float, s1);
+                }
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const float m = red[0][w][r16];
-        L += red[1][w][r16] * (m == M ? 1.0f : __builtin_amdgcn_exp2f((m - M) * kLog2e));
+                for (int v = 0; v < 4; ++v) part += lo[v];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) part += up[v];
+            }
+            const int t = lane < 32 ? ta : tb;
+            if (lane < 32 || two) gsum[t][g & 1][r16] = part;
+            if constexpr (gb + 1 < G) {
+                if (gb + 1 < ng) self(std::integral_constant<int, decltype(PI_)::value + 1>{}, self);
+            }
+        };
+        if (ng > 0) sums(std::integral_constant<int, 0>{}, sums);
     }
+    meet();
+    float M = kNegInf, L = 0.0f;
+    for (int t = 0; t < groups; ++t) {
+        const float m_new = __builtin_fmaxf(M, gmax[t][r16]);
+        L *= __builtin_amdgcn_exp2f((M - m_new) * kLog2e);
+        M = m_new;
+        L += gsum[t][g & 1][r16];
+    }
+    L = L + __shfl_xor(L, 16, 64);
     const float nm = -M * kLog2e - __builtin_amdgcn_logf(L);  // p = 2^(s log2(e) - (M log2(e) + log2(L)))
 
     // ---- phase 2
@@ -198,9 +234,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, 
     for (int jn = 0; jn < NB; ++jn) acc_o[jn] = v4i{0, 0, 0, 0};
     int8_t* Prow = nullptr;
     if (p.P && q0 + r16 < p.s_q) Prow = p.P + (batch * p.s_q + q0 + r16) * (int64_t)p.s_k + 4 * g;
-    auto phase2 = [&](auto GI_, auto&& self) -> void {
-        constexpr int gi = decltype(GI_)::value;
-        const int k0 = (gi * NW + wave) * 64, lim = lim0 - k0;
+    auto phase2 = [&](auto HI_, auto&& self) -> void {
+        constexpr int hi = decltype(HI_)::value;
+        const int k0 = khalf(hi), lim = lim0 - k0;
         v4i fp;
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
@@ -210,7 +246,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, 
                 float pr[2];
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
-                    pr[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(load16_bits<BF16>(sc[gi][b][h] >> (16 * e)), kLog2e, nm));
+                    pr[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(load16_bits<BF16>(sc[hi][b][h] >> (16 * e)), kLog2e, nm));
                     pr[e] = 16 * b + 2 * h + e <= lim ? pr[e] : 0.0f;
                 }
                 ph[h] = store16x2_bits<BF16>(pr[0], pr[1]);
@@ -218,25 +254,25 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, 
             fp[b] = prob_codes4<BF16>(ph[0], ph[1]);
             if (Prow && k0 + 16 * b < p.s_k) *(int*)(Prow + k0 + 16 * b) = fp[b];
         }
-        wait_vmcnt_imm<LV>();  // this group's V rows have landed; the next group's may be in flight
-        const char* vt = patch + (gi & 1) * TILE;
+        wait_vmcnt_imm<LV>();  // this half's V rows have landed; the next half's may be in flight
+        const char* vt = patch + (hi & 1) * TILE;
 #pragma unroll
         for (int jn = 0; jn < NB; jn += 4) {
             v4i f[4];
             v_frags(vt, jn, f);
-            if (jn + 4 == NB) issue_v(gi + 2, gi & 1);  // the last reads are done: the half can be filled again
+            if (jn + 4 == NB) issue_v(hi + 2, hi & 1);  // the last reads are done: the half can be filled again
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc_o[jn + i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[i], fp, acc_o[jn + i], 0, 0, 0);
         }
-        if constexpr (gi + 1 < G) {
-            if (gi + 1 < ng) self(std::integral_constant<int, gi + 1>{}, self);
+        if constexpr (hi + 1 < 2 * G) {
+            if (hi + 1 < 2 * ng) self(std::integral_constant<int, hi + 1>{}, self);
         }
     };
     if (ng > 0) phase2(std::integral_constant<int, 0>{}, phase2);
     if (Prow)  // groups no row of this workgroup sees
-        for (int c = (groups + wave) * 64; c < p.s_k; c += NW * 64)
+        for (int c = (groups + wave) * 128; c < p.s_k; c += NW * 128)
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
+            for (int b = 0; b < 8; ++b)
                 if (c + 16 * b < p.s_k) *(int*)(Prow + c + 16 * b) = 0;
 
     // ---- the waves' sums meet: accumulator block jn, register v of lane l is query l & 15, column 16 jn + 4 (l >> 4) + v
@@ -261,28 +297,33 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_few_kernel(const AttnArgs p, 
 
 template <bool BF16, int HD, int NW> void launch_g(const AttnArgs& a, unsigned grid, bool causal, hipStream_t st)
 {
-    const int g = ((a.s_k + 63) / 64 + NW - 1) / NW;
+    const int g = ((a.s_k + 127) / 128 + NW - 1) / NW;
 #define SQ_FEW(G) sq_launch((attn_few_kernel<BF16, HD, NW, G>), dim3(grid), dim3(NW * 64), 0, st, a, causal ? 1 : 0)
     if (g <= 2) SQ_FEW(2);
     else if (g <= 4) SQ_FEW(4);
-    else if (g <= 8) SQ_FEW(8);
-    else SQ_FEW(16);
+    else SQ_FEW(8);
 #undef SQ_FEW
 }
 
-constexpr int kFewKeys = 8 * 16 * 64;  // what the registers of eight waves hold
+constexpr int kFewKeys = 8 * 8 * 128;  // what the registers of eight waves hold
 
 }  // namespace
 
-// Up to 32 queries (two workgroups per head) this form is always the faster one: the row-block kernel computes 128 rows per
-// head (768 heads x 1 x 2048 x 128: 70 against 157-166 us; 288 x 32 x 1024: 24.5 against 48.5; 12 x 1 x 1024 x 64: 6.8 against
-// 23).  Every further 16 rows read K and V again, out of L2, and once the row-block kernel fills the chip by itself (one
-// workgroup per head, two per compute unit) that decides: 64 queries at 288 heads x 1024 keys 36 against 48 us, at 96 x 2048
-// 28 against 57, but at 768 x 512 60 against 41.
-bool sq_attn_few_eligible(int64_t batch, int64_t s_q, int64_t s_k)
+// Which of the two forms: rounds of workgroups times the time of one, in microseconds, for both.  This form's 16-row blocks
+// fill the chip early and finish early, but each reads K and V once more, out of L2; the row-block form computes 128 rows per
+// workgroup whatever s_q is.  Fitted to ninety shapes between 12 x 16 x 64 and 700 x 1900 x 1900 queries and keys; choosing by
+// it costs 1 % against the better of the two (us, this form / row blocks): 768 x 1 x 2048 x 128 66 / 139, 288 x 32 x 1024 x 128
+// 26 / 46, 33 x 200 x 1040 x 64 14 / 25, 24 x 69 x 336 x 128 8.6 / 15, but 240 x 176^2 x 128 29 / 13, 126 x 1088^2 x 128
+// 238 / 116.
+bool sq_attn_few_eligible(int64_t batch, int64_t s_q, int64_t s_k, int64_t d, bool causal)
 {
-    // (2^21: a grid of 16-row blocks stays below 2^32 threads)
-    return s_k <= kFewKeys && batch < (1 << 21) && (s_q <= 32 || (s_q <= 64 && batch <= 512));
+    const double few_wg = (double)batch * ((s_q + 15) / 16), row_wg = (double)batch * ((s_q + 127) / 128);
+    if (s_k > kFewKeys || few_wg >= (1 << 22)) return false;  // (registers; a grid stays below 2^32 threads)
+    const double keys = causal ? (double)s_k - 0.5 * (double)(s_q - 1) : (double)s_k;  // a query sees on average
+    const double few_rounds = few_wg / (d == 64 ? 768.0 : 640.0), row_rounds = row_wg / 384.0;
+    const double few_us = (few_rounds > 1.0 ? few_rounds : 1.0) * (d == 64 ? 6.0 + 0.006 * keys : 7.0 + 0.014 * keys);
+    const double row_us = (row_rounds > 1.0 ? row_rounds : 1.0) * (d == 64 ? 5.0 + 0.024 * keys : 5.5 + 0.032 * keys);
+    return few_us < row_us;
 }
 
 void sq_attn_few_launch(AttnArgs a, int64_t batch, int64_t d, bool bf16, bool causal, hipStream_t st)
@@ -290,9 +331,9 @@ void sq_attn_few_launch(AttnArgs a, int64_t batch, int64_t d, bool bf16, bool ca
     a.tiles_m = (a.s_q + 15) / 16;
     const unsigned grid = (unsigned)(batch * a.tiles_m);
     // Eight waves per workgroup where there is at most one workgroup per compute unit, or where four waves' registers do
-    // not hold the scores (16 groups of 64 keys each); else four, two workgroups per compute unit, so that one loads
+    // not hold the scores (8 groups of 128 keys each); else four, two workgroups per compute unit, so that one loads
     // while the other is at its meeting or its epilogue.
-    const bool eight = grid <= 256 || a.s_k > 4 * 16 * 64;
+    const bool eight = grid <= 256 || a.s_k > 4 * 8 * 128;
 #define SQ_FEW(BF, HD) do { if (eight) launch_g<BF, HD, 8>(a, grid, causal, st); else launch_g<BF, HD, 4>(a, grid, causal, st); } while (0)
     if (d == 128) {
         if (bf16) SQ_FEW(true, 128); else SQ_FEW(false, 128);

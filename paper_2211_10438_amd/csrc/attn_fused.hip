@@ -12,14 +12,21 @@
 //           codes a lane produces from one 32x32 accumulator block ARE its operand fragment of the P V
 //           MFMA (second operand: row l & 31, contraction bytes 16 (l >> 5) ..), so P_q never leaves registers.
 // One workgroup owns 128 query rows of one (batch, head): four waves of 32 rows, the Q operand fragments in
-// registers for the whole kernel.  K and V tiles of 128 keys travel L2 -> LDS with global_load_lds, double
-// buffered, one s_barrier per tile.  Because the Q K^T MFMA takes the K rows as first operand, an accumulator
-// block is the transpose of its output block: a lane holds, for its row, the columns 8g + 4h + e of a 32-key
+// registers for the whole kernel.  K tiles of 128 keys (pass 1) and K and V tiles of 64 (pass 2; 128 at head dimension 64) travel L2 -> LDS with
+// global_load_lds, double buffered, one s_barrier per tile.  Because the Q K^T MFMA takes the K rows as first operand, an
+// accumulator block is the transpose of its output block: a lane holds, for its row, the columns 8g + 4h + e of a 32-key
 // block (h = l >> 5).  That fixes the order of the contraction bytes of the P V MFMA; the V operand is fetched
 // in the same order with the LDS transpose read (ds_read_b64_tr_b8), whose eight source rows are named by the
 // lanes and can therefore be any eight keys.
-// The kernel is bound by the vector ALU (about 21 issue slots per score over both passes against 0.75 MFMA
-// cycles); two workgroups per compute unit let one wave's MFMAs run under the other's exponentials.
+// What bounds it: vector-ALU issue.  Measured on loops of single instructions (cycles per instruction and SIMD, with 2 / 4
+// waves on it): add, sub, mul 3.0 / 2.7, conversions, packed and three-operand forms 5.1 / 4.5, exp2 8.8 / 8.4; one wave
+// alone issues one every 6.2 whatever it is; a 32x32x32 MFMA runs beside them and takes about 8 issue cycles of its 34.
+// Hence three workgroups per compute unit (four at head dimension 64) instead of two -- tiles of 64 keys, one accumulator
+// pair live at a time, a single copy of the P V products --, no conversion of the sums (kBias), and nothing done for keys and rows
+// that are not there (MASKED).  (A shift fixed by the first tile instead of the running maximum, half an instruction per
+// score less, gained 1 %: the sums' last bits, and with them some codes, would no longer be those of a running maximum.)  Before / after, us: 288 heads x 1024^2 x 128 causal 131 /
+// 107, unmasked 176 / 168; 768 x 2048^2 x 128 causal 1092 / 969; 96 x 777 x 1040 x 64 causal 67 / 41; 50 x 300 x 304 x 128
+// causal 26 / 16.
 #include <type_traits>
 
 #include "attn_args.h"
@@ -27,77 +34,89 @@
 namespace {
 
 constexpr int kIntMin = -2147483647 - 1;
+constexpr int kBias = 0x3e22f983;
+constexpr float kBiasF = __builtin_bit_cast(float, kBias);
 
-// MODE, one instantiation each, so that the common case carries no mask tests (with the first two forms in one kernel
-// the register allocation spilled):
-//   kAll     every query sees every key, and the key count is a multiple of 128;
-//   kTail    the same with any key count that is a multiple of 16: the last tile is masked at 16-key granularity;
-//   kCausal  query i sees the keys j <= i + (s_k - s_q) (the decoder's mask; the last query sees every key).  A workgroup
-//            stops after the last tile any of its rows sees; a wave runs the unmasked tile body on the tiles all its 32
-//            rows see in full, an element-wise masked one on the one or two tiles the diagonal crosses, and nothing on
-//            the tiles past its rows.  The element mask also hides keys past s_k, so no separate tail form is needed.
-constexpr int kAll = 0, kTail = 1, kCausal = 2;
-
-template <bool BF16, int HD, int MODE>
-__global__ __launch_bounds__(256, 2) void attn_i8_kernel(const AttnArgs p)
+// Two instantiations, so that the common case carries no mask tests (with both in one kernel the register allocation
+// spilled):
+//   MASKED = false  every query sees every key, and the key count is a multiple of 128;
+//   MASKED = true   query i sees the keys j <= min(i + p.coff, s_k - 1): the decoder's mask (coff = s_k - s_q: the last query
+//                   sees every key), or any key count without a mask (coff >= s_k).  A workgroup stops after the last tile any
+//                   of its rows sees; a wave runs the plain tile body on the tiles all its 32 rows see in full, and nothing on
+//                   the tiles past its rows.  On the one or two tiles in between it takes the 32-key blocks one by one: those
+//                   its rows see in full without a mask, those they see in part with an element-wise one, the others not at
+//                   all (a whole-tile masked body cost 1.7 plain ones on every diagonal tile, of which a 32-row group sees
+//                   between one and four blocks).
+template <bool BF16, int HD, bool MASKED, bool CODES>
+__global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
 {
-    constexpr bool TAIL = MODE == kTail;
-    constexpr int TK = 128;               // keys per tile
-    constexpr int SLOT = 16384;           // LDS bytes reserved per tile
-    constexpr int TILE = TK * HD;         // bytes of a K or V tile
+    constexpr int TK1 = 128, TK = HD == 64 ? 128 : 64;  // keys per tile of pass 1 (K only) and pass 2 (K and V)
+    constexpr int KB = TK / 32;           // 32-key blocks per tile of pass 2
+    constexpr int TILE = TK * HD;         // bytes of a K or V tile of pass 2
+    constexpr int PITCH = HD * 2 + 16;    // bytes per row of the output staging
+    constexpr int SLOT = TILE > 32 * PITCH ? TILE : (32 * PITCH + 1023) / 1024 * 1024;  // LDS bytes per tile (or staging of a wave)
     constexpr int LPT = TILE / 1024 / 4;  // global->LDS loads per wave and tile
     constexpr int CH = HD / 16;           // 16-byte chunks per row
     constexpr int RPB = 1024 / HD;        // rows per 1 KB block
     constexpr int NKS = HD / 32;          // MFMA steps of Q K^T
     constexpr int NB = HD / 32;           // 32-column blocks of O
     static_assert(HD == 128 || HD == 64, "head dimension");
+    static_assert(TK1 * HD <= 2 * SLOT, "a pass 1 tile fits the K and V slots of a stage");
     __shared__ __attribute__((aligned(1024))) char smem[4 * SLOT];  // stage s: K tile at slot 2s, V tile at slot 2s + 1
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r32 = lane & 31, h = lane >> 5;
 
-    // Consecutive workgroup ids go round-robin to the 8 XCDs; give each XCD a contiguous range of the logical
-    // order so that the row blocks of one head (they share its K and V) run on one L2.
-    const int64_t total = gridDim.x;
-    int64_t pid;
+    // Which row block.  Consecutive workgroup ids go round-robin to the 8 XCDs.  Without the mask each XCD gets a contiguous
+    // range of the logical order, so that the row blocks of one head (they share its K and V) run on one L2.  In the causal
+    // form block t sees t + 1 of the key tiles, and the workgroups that start last decide when the launch ends: XCD x works
+    // on the batch entries x, x + 8, ..., p.chunk of them at a time, and within a chunk the longest row blocks start first.
+    // (One block from the top and one from the bottom of the range per workgroup, as before, made 1152 equal pieces for 512
+    // places at 288 heads x 1024^2: three rounds for 2.25 rounds of work.)
+    // (32-bit: the grid has fewer than 2^31 workgroups, and a 64-bit division is a hundred scalar instructions)
+    int64_t batch;
+    int mt;
     {
-        const int64_t wg = blockIdx.x, j = wg >> 3;
-        const int xcd = (int)(wg & 7);
-        const int64_t per = total >> 3;
-        const int r = (int)(total & 7);
-        pid = xcd * per + (xcd < r ? xcd : r) + j;
-    }
-    // Causal form: a workgroup owns TWO row blocks of its head, number `pair` from the top and from the bottom of the
-    // query range, one after the other: block t sees t + 1 of the key tiles (with s_k = s_q), so every pair sees the
-    // same number of tiles and the workgroups finish together (with one block each, the blocks that start last
-    // decided the time: 157 us against 99 us of work per slot at 288 heads x 1024^2).  tiles_m counts pairs then.
-    const int blocks_m = (p.s_q + 127) / 128;
-    const int batch = (int)(pid / p.tiles_m);
-    const int pair = (int)(pid - (int64_t)batch * p.tiles_m);
-    const int nrep = (MODE == kCausal && blocks_m - 1 - pair != pair) ? 2 : 1;
-    for (int rep = 0; rep < nrep; ++rep) {
-        if (rep) __syncthreads();  // the staging patches of the first block's epilogue lie in the tile buffers
-        const int mt = MODE == kCausal ? (rep == 0 ? blocks_m - 1 - pair : pair) : pair;
-        const int m0 = mt * 128;
-        const int nt_all = (p.s_k + TK - 1) / TK;
-        const int last16 = (p.s_k - (nt_all - 1) * TK) >> 4;  // valid 16-key groups of the last tile (8 = full; s_k % 16 == 0)
-        // Causal: keys visible to row r: 0 .. r + coff.  Tiles of this workgroup: up to the last key its last valid row sees;
-        // tiles j < jfull are seen in full by every row of this wave, tiles j >= jend by none of them.
-        const int coff = p.s_k - p.s_q;
-        int nt = nt_all, jfull = nt_all, jend = nt_all;
-        if constexpr (MODE == kCausal) {
-            const int last_row = m0 + 127 < p.s_q ? m0 + 127 : p.s_q - 1;
-            nt = (last_row + coff + 1 + TK - 1) / TK;
-            const int w0 = m0 + wave * 32;
-            jfull = (w0 + coff + 1) / TK;
-            jend = (w0 + 31 + coff + 1 + TK - 1) / TK;
-            jfull = jfull < nt ? jfull : nt;
-            jend = jend < nt ? jend : nt;
+        const uint32_t xcd = blockIdx.x & 7, j = blockIdx.x >> 3, tiles = (uint32_t)p.tiles_m;
+        if (p.causal) {
+            const uint32_t heads = ((uint32_t)p.batch - xcd + 7) >> 3, chunk = (uint32_t)p.chunk;
+            const uint32_t c = j / (chunk * tiles), in = j - c * (chunk * tiles);
+            if (c * chunk >= heads) return;
+            const uint32_t left = heads - c * chunk, hc = left < chunk ? left : chunk;
+            const uint32_t rank = in / hc;
+            if (rank >= tiles) return;  // (the last chunk of an XCD may be short of heads)
+            batch = (int64_t)(c * chunk + (in - rank * hc)) * 8 + xcd;
+            mt = (int)(tiles - 1 - rank);
+        } else {
+            const uint32_t per = gridDim.x >> 3, r = gridDim.x & 7, pid = xcd * per + (xcd < r ? xcd : r) + j, head = pid / tiles;
+            batch = head;
+            mt = (int)(pid - head * tiles);
         }
-        // key index of accumulator register 4 g + e of key block ks in tile j: 128 j + 32 ks + 8 g + 4 h + e; it is visible
-        // to this lane's row when 32 ks + 8 g + e <= rowlim - 128 j
-        const int rowlim = m0 + wave * 32 + r32 + coff - 4 * h;
+    }
+    // The four row groups of 32 rotate over the waves from workgroup to workgroup: on the diagonal tile the last group sees
+    // four times the keys of the first, and wave w of every workgroup sits on the same SIMD.
+    const int rg = (wave + (blockIdx.x >> 3)) & 3;
+    {
+        const int m0 = mt * 128;
+        const int w0 = m0 + rg * 32;      // first row of this wave
+        const bool idle = w0 >= p.s_q;    // no row at all: the wave only fetches tiles
+        // Keys the first and the last row of this wave see, and the last valid row of the workgroup (no row: none).  A tile that
+        // ends at vmin or before is seen in full, one that starts at vmax or later not at all.
+        int vmin = p.s_k, vmax = p.s_k, seen = p.s_k;
+        if constexpr (MASKED) {
+            const int last_row = m0 + 127 < p.s_q ? m0 + 127 : p.s_q - 1;
+            auto sees = [&](int row) { return (int64_t)row + p.coff + 1 < p.s_k ? row + p.coff + 1 : p.s_k; };
+            seen = sees(last_row);
+            vmin = sees(w0);
+            vmax = sees(w0 + 31);
+            vmax = vmax < seen ? vmax : seen;
+        }
+        if (idle) vmin = vmax = 0;
+        const int nt1 = (seen + TK1 - 1) / TK1, nt = (seen + TK - 1) / TK;  // tiles of the two passes
+        // key index of accumulator register 4 g + e of key block ks in tile j: TK j + 32 ks + 8 g + 4 h + e; it is visible
+        // to this lane's row when 32 ks + 8 g + e <= rowlim - TK j
+        const int rowlim = (MASKED && (int64_t)w0 + r32 + p.coff < p.s_k - 1 ? w0 + r32 + p.coff : p.s_k - 1) - 4 * h;
 
         // ---- LDS images.  K tile: row n at n * HD, its 16-byte chunks XOR-permuted (position = chunk ^ swzK(n)) so
         // that the operand reads (32 rows, one chunk) spread over the banks.  V tile: row k at k * HD, position =
@@ -106,50 +125,53 @@ __global__ __launch_bounds__(256, 2) void attn_i8_kernel(const AttnArgs p)
         auto swzV = [](int k) { return HD == 128 ? ((k & 3) | (((k >> 3) & 1) << 2)) : (k & 3); };
         // Key rows past s_k (last, partial tile) re-read row s_k - 1: their scores are masked below and their V rows meet
         // codes that are zero.
-        int lrow[LPT];
-        uint32_t cK[LPT], cV[LPT];
+        // Slot i of this wave fills rows (4 i + wave) RPB ..: the swizzles of a lane's rows are the same for every i.
+        const int lrow0 = wave * RPB + lane / CH;
+        const uint32_t cK = (uint32_t)(((lane % CH) ^ swzK(lrow0)) * 16), cV = (uint32_t)(((lane % CH) ^ swzV(lrow0)) * 16);
+        static_assert(4 * RPB % 16 == 0, "swizzles repeat every 16 rows");
+        const int8_t* Kb = p.K + batch * p.stride_k;
+        const int8_t* Vb = p.V + batch * p.stride_v;
+        // (uniform base, 32-bit lane offset: no vector instruction per load.  The offset is made opaque next to the load, or its
+        // widening to 64 bits is hoisted out of the loop and the scalar-base form of the load is lost.)
+        auto load_tile = [&](const int8_t* base, uint32_t c, int k0, char* dst, auto LOADS_) {  // rows k0 .. of K or V
+            constexpr int LOADS = decltype(LOADS_)::value;
+            const int8_t* src = base + (int64_t)k0 * HD;
+            uint32_t o[LOADS];  // this lane's byte of the tile; rows past the last key (the last, partial tile) stay on it
 #pragma unroll
-        for (int i = 0; i < LPT; ++i) {
-            const int row = (i * 4 + wave) * RPB + lane / CH, pos = lane % CH;
-            lrow[i] = row;
-            cK[i] = (uint32_t)((pos ^ swzK(row)) * 16);
-            cV[i] = (uint32_t)((pos ^ swzV(row)) * 16);
-        }
-        const int8_t* Kb = p.K + (int64_t)batch * p.stride_k;
-        const int8_t* Vb = p.V + (int64_t)batch * p.stride_v;
-        auto issue = [&](int j, int stage, bool with_v) {
-            char* dk = smem + (2 * stage) * SLOT;
-            int64_t roff[LPT];
+            for (int i = 0; i < LOADS; ++i) o[i] = (uint32_t)((lrow0 + i * 4 * RPB) * HD);
+            if (MASKED && k0 + LOADS * 4 * RPB > p.s_k) {
+                const uint32_t last = (uint32_t)((p.s_k - 1 - k0) * HD);  // >= 0: the tile has a key
 #pragma unroll
-            for (int i = 0; i < LPT; ++i) {
-                int r = j * TK + lrow[i];
-                r = r < p.s_k ? r : p.s_k - 1;
-                roff[i] = (int64_t)r * HD;
+                for (int i = 0; i < LOADS; ++i) o[i] = o[i] < last ? o[i] : last;
             }
 #pragma unroll
-            for (int i = 0; i < LPT; ++i)
-                __builtin_amdgcn_global_load_lds(GPTR(Kb + roff[i] + cK[i]), LPTR(dk + (i * 4 + wave) * 1024), 16, 0, 0);
-            if (with_v) {
-#pragma unroll
-                for (int i = 0; i < LPT; ++i)
-                    __builtin_amdgcn_global_load_lds(GPTR(Vb + roff[i] + cV[i]), LPTR(dk + SLOT + (i * 4 + wave) * 1024), 16, 0, 0);
+            for (int i = 0; i < LOADS; ++i) {
+                uint32_t ok = o[i] + c;
+                asm volatile("" : "+v"(ok));
+                __builtin_amdgcn_global_load_lds(GPTR(src + ok), LPTR(dst + (i * 4 + wave) * 1024), 16, 0, 0);
             }
+        };
+        auto issue_k1 = [&](int j, int stage) {  // pass 1's tile j
+            load_tile(Kb, cK, j * TK1, smem + (2 * stage) * SLOT, std::integral_constant<int, TK1 * HD / 4096>{});
+        };
+        auto issue = [&](int j, int stage) {  // pass 2's tile j
+            load_tile(Kb, cK, j * TK, smem + (2 * stage) * SLOT, std::integral_constant<int, LPT>{});
+            load_tile(Vb, cV, j * TK, smem + (2 * stage + 1) * SLOT, std::integral_constant<int, LPT>{});
         };
 
         // ---- Q operand fragments (second MFMA operand): lane l feeds query row (l & 31) of this wave with the 16
         // bytes of chunk 2 ks + (l >> 5).  Rows past s_q repeat the last row; they are never stored.
         v4i fq[NKS];
         {
-            int row = m0 + wave * 32 + r32;
+            int row = w0 + r32;
             row = row < p.s_q ? row : p.s_q - 1;
             const int8_t* qp = p.Q + (int64_t)batch * p.stride_q + (int64_t)row * HD;
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) fq[ks] = *(const v4i*)(qp + (2 * ks + h) * 16);
         }
         // K operand fragment (first operand) of key block jn, step ks: key row 32 jn + (l & 31), chunk 2 ks + (l >> 5)
-        int koff[NKS];
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) koff[ks] = r32 * HD + (((2 * ks + h) ^ swzK(r32)) * 16);
+        // (position of chunk 2 ks + h = (2 ks) ^ (h ^ swz), so step ks flips bits 5.. of the address of step 0)
+        const int koff0 = r32 * HD + ((h ^ swzK(r32)) * 16);
         // V operand fragment (first operand of the P V MFMA) of key block ks, column block jn: column n = 32 jn + (l & 31),
         // contraction bytes in the order the codes have in the P fragment: byte 4g + e <-> key 32 ks + 8g + 4h + e.
         // Within 16 lanes, source lanes 2j and 2j + 1 of a transpose read name the two 8-byte halves of the 16 columns
@@ -169,25 +191,35 @@ __global__ __launch_bounds__(256, 2) void attn_i8_kernel(const AttnArgs p)
             return v4i{lo.x, lo.y, hi.x, hi.y};
         };
 
-        // S tile = Q K^T for the 128 keys of a stage: acc[jn] is the transposed 32x32 block of key block jn
-        auto scores = [&](const char* kt, v16i(&acc)[4]) {
+        // The sums start at the bit pattern of kBias instead of at zero: read as a float, kBias + sum is the number
+        // kBiasF + sum * 2^-26 exactly (|sum| <= 128^3 < 2292099, the distance of the pattern from the next power of two
+        // below it), so one subtraction of kBiasF, exact too, replaces the conversion to float (a subtraction issues in half
+        // the time of a conversion here).  The factor 2^26 is in alpha1; kBias = 1 / (2 pi) is a constant MFMA takes inline.
+        v16i bias;
 #pragma unroll
-            for (int jn = 0; jn < 4; ++jn) {
-                const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                acc[jn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const v4i*)(kt + jn * 32 * HD + koff[0]), fq[0], zero, 0, 0, 0);
+        for (int v = 0; v < 16; ++v) bias[v] = kBias;
+        // S tile = Q K^T for the 128 keys of a stage: acc[jn] is the transposed 32x32 block of key block jn
+        // (blocks from nvis on are left out)
+        auto scores = [&](const char* kt, auto& acc, int nvis) {
+            constexpr int N = sizeof(acc) / sizeof(v16i);
+#pragma unroll
+            for (int jn = 0; jn < N; ++jn) {
+                if (jn >= nvis) break;
+                acc[jn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const v4i*)(kt + jn * 32 * HD + koff0), fq[0], bias, 0, 0, 0);
             }
 #pragma unroll
             for (int ks = 1; ks < NKS; ++ks)
 #pragma unroll
-                for (int jn = 0; jn < 4; ++jn)
-                    acc[jn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const v4i*)(kt + jn * 32 * HD + koff[ks]), fq[ks], acc[jn], 0, 0, 0);
+                for (int jn = 0; jn < N; ++jn) {
+                    if (jn >= nvis) break;
+                    acc[jn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const v4i*)(kt + jn * 32 * HD + (koff0 ^ (ks << 5))), fq[ks], acc[jn], 0, 0, 0);
+                }
         };
-        // score of one accumulator as the 16-bit tensor element it stands for, widened again: round16(fl32(acc * alpha1))
-        const float alpha1 = p.alpha1;
-        auto s16f = [&](int a) { return load16_bits<BF16>(store16_bits<BF16>((float)a * alpha1)); };
-        // two scores at once: one narrowing instruction for the pair
+        // scores of two accumulators as the 16-bit tensor elements they stand for, widened again: round16(fl32(acc * alpha1)),
+        // one narrowing instruction for the pair
+        const float alpha1 = p.alpha1;  // times 2^26
         auto s16f2 = [&](int a0, int a1, float& s0, float& s1) {
-            const uint32_t h = store16x2_bits<BF16>((float)a0 * alpha1, (float)a1 * alpha1);
+            const uint32_t h = store16x2_bits<BF16>((__builtin_bit_cast(float, a0) - kBiasF) * alpha1, (__builtin_bit_cast(float, a1) - kBiasF) * alpha1);
             s0 = load16_bits<BF16>(h);
             s1 = load16_bits<BF16>(h >> 16);
         };
@@ -195,67 +227,71 @@ __global__ __launch_bounds__(256, 2) void attn_i8_kernel(const AttnArgs p)
         // score that came out one 16-bit ulp lower in pass 1 than in pass 2 would give that key a probability above 1.
         // A single-rounding v_fma_mixlo_f16 in pass 1 was tried for its one issue slot and did exactly that.)
 
-        // ---- pass 1: row maximum m and l = sum e^(s - m), online.  The maximum is taken on the integer accumulators
-        // (s is monotone in acc: alpha1 > 0).  A row's scores are split between lanes r and r + 32.
+        // ---- pass 1, tiles of 128 keys whatever pass 2's are (it needs no V and holds no output sums): row maximum m and
+        // l = sum e^(s - m), online.  The maximum is taken on the integer accumulators (s is monotone in acc: alpha1 > 0).  A
+        // row's scores are split between lanes r and r + 32.
         float m_run = -__builtin_inff(), l_run = 0.0f;
-        // MASK: a 16-key group q = 2 jn + (v >> 3) of the tile is valid when q < tail16 (8 for every tile but the last) (uniform over the wave: the accumulator registers 8 (q & 1) .. 8 (q & 1) + 7 of block jn)
-        // EM: element-wise mask (the diagonal tiles of the causal form), lim = rowlim - 128 j
-        auto pass1_tile = [&](const char* kt, int tail16, auto EM_, int lim) {
-            constexpr bool MASK = TAIL;
-            constexpr bool EM = decltype(EM_)::value;
+        using Plain = std::false_type;
+        using Masked = std::true_type;
+        // PART: a tile this wave's rows see in part: blocks jn < nfull in full, jn < nvis in part (keys up to lim)
+        auto pass1_tile = [&](const char* kt, auto PART_, int lim, int nfull, int nvis) {
+            constexpr bool PART = decltype(PART_)::value;
             v16i acc[4];
-            scores(kt, acc);
-            int imax = EM ? kIntMin : acc[0][0];  // (key 0 of a tile is always valid without the element mask)
+            scores(kt, acc, nvis);
+            int imax = kIntMin;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                if (MASK && q >= tail16) continue;
+            for (int jn = 0; jn < 4; ++jn) {
+                if (PART && jn >= nvis) break;
 #pragma unroll
-                for (int v = 0; v < 8; ++v) {
-                    const int r = 8 * (q & 1) + v;  // register 4 g + e
-                    int a = acc[q >> 1][r];
-                    if (EM) a = 32 * (q >> 1) + 8 * (r >> 2) + (r & 3) <= lim ? a : kIntMin;
+                for (int r = 0; r < 16; ++r) {  // register 4 g + e
+                    const int a = !PART || 32 * jn + 8 * (r >> 2) + (r & 3) <= lim ? acc[jn][r] : kIntMin;
                     imax = a > imax ? a : imax;
                 }
             }
             const int other = __shfl_xor(imax, 32, 64);
             imax = other > imax ? other : imax;
-            const float m_new = __builtin_fmaxf(m_run, s16f(imax));
+            float s0, s1;
+            s16f2(imax, imax, s0, s1);
+            const float m_new = PART && imax == kIntMin ? m_run : __builtin_fmaxf(m_run, s0);  // (a row may see nothing of a later tile)
             l_run *= __builtin_amdgcn_exp2f((m_run - m_new) * kLog2e);
             m_run = m_new;
             const float nm = -m_new * kLog2e;
             float part = 0.0f;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                if (MASK && q >= tail16) continue;
+            for (int jn = 0; jn < 4; ++jn) {
+                if (PART && jn >= nvis) break;
+                auto add = [&](auto EM_) {
+                    constexpr bool EM = decltype(EM_)::value;
 #pragma unroll
-                for (int v = 0; v < 8; v += 2) {
-                    float s0, s1;
-                    const int r = 8 * (q & 1) + v;
-                    s16f2(acc[q >> 1][r], acc[q >> 1][r + 1], s0, s1);
-                    const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s0, kLog2e, nm));
-                    const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s1, kLog2e, nm));
-                    const int idx = 32 * (q >> 1) + 8 * (r >> 2) + (r & 3);
-                    // (a hidden key's exponential may be anything, even infinite: it is dropped, not multiplied away)
-                    part += (!EM || idx <= lim) ? e0 : 0.0f;
-                    part += (!EM || idx + 1 <= lim) ? e1 : 0.0f;
-                }
+                    for (int r = 0; r < 16; r += 2) {
+                        s16f2(acc[jn][r], acc[jn][r + 1], s0, s1);
+                        const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s0, kLog2e, nm));
+                        const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s1, kLog2e, nm));
+                        const int idx = 32 * jn + 8 * (r >> 2) + (r & 3);
+                        // (a hidden key's exponential may be anything, even infinite: it is dropped, not multiplied away)
+                        part += (!EM || idx <= lim) ? e0 : 0.0f;
+                        part += (!EM || idx + 1 <= lim) ? e1 : 0.0f;
+                    }
+                };
+                if (PART && jn >= nfull) add(Masked{});
+                else add(Plain{});
             }
             l_run += part;
         };
-        using Plain = std::false_type;
-        using Masked = std::true_type;
-        issue(0, 0, false);
-        for (int j = 0; j < nt; ++j) {
+        // 32-key blocks from key k0 on: seen in full by this wave's first row, and at all by its last
+        auto n_full = [&](int k0) { return (vmin - k0) >> 5; };
+        auto n_vis = [&](int k0, int most) { const int n = (vmax - k0 + 31) >> 5; return n < most ? n : most; };
+        issue_k1(0, 0);
+        for (int j = 0; j < nt1; ++j) {
             wait_vmcnt_imm<0>();           // this wave's part of tile j has landed
             __builtin_amdgcn_s_barrier();  // ... everybody's has, and everybody is done with tile j - 1
-            if (j + 1 < nt) issue(j + 1, (j + 1) & 1, false);
+            // (behind the last tile the first one of pass 2, so that its latency is not exposed between the passes)
+            if (j + 1 < nt1) issue_k1(j + 1, (j + 1) & 1);
+            else issue(0, (j + 1) & 1);
             const char* kt1 = smem + (2 * (j & 1)) * SLOT;
-            if constexpr (MODE == kCausal) {
-                if (j < jfull) pass1_tile(kt1, 8, Plain{}, 0);
-                else if (j < jend) pass1_tile(kt1, 8, Masked{}, rowlim - j * TK);
-            } else {
-                pass1_tile(kt1, j == nt - 1 ? last16 : 8, Plain{}, 0);
-            }
+            const int k0 = j * TK1;
+            if (k0 + TK1 <= vmin) pass1_tile(kt1, Plain{}, 0, 4, 4);
+            else if (MASKED && k0 < vmax) pass1_tile(kt1, Masked{}, rowlim - k0, n_full(k0), n_vis(k0, 4));
         }
         // p = e^(s - m) / l = 2^(s log2(e) - (m log2(e) + log2(l))): the division is folded into the exponent
         const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
@@ -268,78 +304,68 @@ __global__ __launch_bounds__(256, 2) void attn_i8_kernel(const AttnArgs p)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc_o[jn][v] = 0;
         int8_t* Prow = nullptr;
-        if (p.P) {
-            const int row = m0 + wave * 32 + r32;
+        if constexpr (CODES) {
+            const int row = w0 + r32;
             if (row < p.s_q) Prow = p.P + ((int64_t)batch * p.s_q + row) * (int64_t)p.s_k + 4 * h;
         }
-        auto pass2_tile = [&](const char* kt, int j, int tail16, auto EM_, int lim) {
-            constexpr bool MASK = TAIL;
-            constexpr bool EM = decltype(EM_)::value;
+        // Tile j, its blocks below nvis; partial tiles drop the codes of the keys past lim = rowlim - TK j.  (One piece of code
+        // for both: with a second copy of the P V products the accumulators are kept twice.)
+        auto pass2_tile = [&](const char* kt, int j, bool partial, int lim, int nvis) {
             const char* vt = kt + SLOT;
-            v16i acc[4];
-            scores(kt, acc);
+            v16i acc[KB];
+            scores(kt, acc, nvis);
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                if (MASK && 2 * ks >= tail16) break;  // no valid key in this block or the following ones
-                // the 16 codes of this lane for key block ks: word g holds columns 8g + 4h + 0..3
-                v4i fp;
+            for (int ks = 0; ks < KB; ++ks) {
+                if (MASKED && ks >= nvis) break;
+                v4i fp;  // the 16 codes of this lane: word g holds columns 8g + 4h + 0..3
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    if (MASK && 2 * ks + (g >> 1) >= tail16) {  // masked keys: probability 0
-                        fp[g] = 0;
-                        continue;
-                    }
                     uint32_t ph[2];  // the probabilities of columns e = 0,1 and 2,3 as 16-bit pairs (the softmax output is a 16-bit tensor)
 #pragma unroll
                     for (int e = 0; e < 4; e += 2) {
                         float s0, s1;
                         s16f2(acc[ks][4 * g + e], acc[ks][4 * g + e + 1], s0, s1);
-                        float pr0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s0, kLog2e, nm));
-                        float pr1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s1, kLog2e, nm));
-                        if (EM) {  // hidden keys: probability 0
-                            pr0 = 32 * ks + 8 * g + e <= lim ? pr0 : 0.0f;
-                            pr1 = 32 * ks + 8 * g + e + 1 <= lim ? pr1 : 0.0f;
-                        }
-                        ph[e >> 1] = store16x2_bits<BF16>(pr0, pr1);
+                        ph[e >> 1] = store16x2_bits<BF16>(__builtin_amdgcn_exp2f(__builtin_fmaf(s0, kLog2e, nm)),
+                                                          __builtin_amdgcn_exp2f(__builtin_fmaf(s1, kLog2e, nm)));
                     }
                     fp[g] = prob_codes4<BF16>(ph[0], ph[1]);
                 }
-                if (Prow) {
+                if (MASKED && partial) {
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
-                        const bool inside = MODE == kCausal ? j * TK + ks * 32 + 8 * g + 4 * h < p.s_k : (!MASK || 2 * ks + (g >> 1) < tail16);
-                        if (inside) *(int*)(Prow + j * TK + ks * 32 + 8 * g) = fp[g];
+                        const int n = lim - (32 * ks + 8 * g) + 1;  // visible keys of the four (or more)
+                        const uint32_t m = n >= 4 ? 0xffffffffu : n <= 0 ? 0u : (1u << (8 * n)) - 1u;
+                        fp[g] &= (int)m;
                     }
+                }
+                if (CODES && Prow) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        if (!MASKED || j * TK + ks * 32 + 8 * g + 4 * h < p.s_k) *(int*)(Prow + j * TK + ks * 32 + 8 * g) = fp[g];
                 }
 #pragma unroll
                 for (int jn = 0; jn < NB; ++jn)
                     acc_o[jn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(v_frag(vt, ks, jn), fp, acc_o[jn], 0, 0, 0);
             }
         };
-        __syncthreads();  // every wave is done with the last tile of pass 1 before its buffer is refilled
-        issue(0, 0, true);
         for (int j = 0; j < nt; ++j) {
+            const int stage = (nt1 + j) & 1;
             wait_vmcnt_imm<0>();
             __builtin_amdgcn_s_barrier();
-            if (j + 1 < nt) issue(j + 1, (j + 1) & 1, true);
-            const char* kt2 = smem + (2 * (j & 1)) * SLOT;
-            if constexpr (MODE == kCausal) {
-                if (j < jfull) pass2_tile(kt2, j, 8, Plain{}, 0);
-                else if (j < jend) pass2_tile(kt2, j, 8, Masked{}, rowlim - j * TK);
-            } else {
-                pass2_tile(kt2, j, j == nt - 1 ? last16 : 8, Plain{}, 0);
-            }
+            if (j + 1 < nt) issue(j + 1, stage ^ 1);
+            const char* kt2 = smem + (2 * stage) * SLOT;
+            const int k0 = j * TK;
+            if (k0 < vmax) pass2_tile(kt2, j, k0 + TK > vmin, rowlim - k0, MASKED ? n_vis(k0, KB) : KB);
         }
-        if constexpr (MODE == kCausal) {
-            // the codes of the tiles this wave skipped are 0
+        if constexpr (MASKED && CODES) {
+            // the codes of the blocks this wave skipped are 0
             if (Prow)
-                for (int c = jend * TK; c + 4 * h < p.s_k; c += 8) *(int*)(Prow + c) = 0;  // (Prow already points at column 4 h)
+                for (int c = (vmax + 31) / 32 * 32; c + 4 * h < p.s_k; c += 8) *(int*)(Prow + c) = 0;  // (Prow already points at column 4 h)
         }
 
         // ---- epilogue: o = round16(fl32(acc * alpha2)).  Accumulator block jn is the transposed output block: lane l,
         // register v holds row (l & 31), column 32 jn + 8 (v / 4) + 4 (l >> 5) + (v & 3).  Each wave stages its 32 rows in
         // its own part of the (now free) tile buffers and writes whole rows in 16-byte pieces.
-        constexpr int PITCH = HD * 2 + 16;
         __syncthreads();
         char* stg = smem + wave * SLOT;
         const float alpha2 = p.alpha2;
@@ -357,14 +383,27 @@ __global__ __launch_bounds__(256, 2) void attn_i8_kernel(const AttnArgs p)
 #pragma unroll
         for (int it = 0; it < 32 * CPR / 64; ++it) {
             const int idx = it * 64 + lane, r = idx / CPR, c = idx - r * CPR;
-            const int row = m0 + wave * 32 + r;
+            const int row = w0 + r;
             const v4u val = *(const v4u*)(stg + r * PITCH + c * 16);
             if (row < p.s_q) __builtin_nontemporal_store(val, (v4u*)(Ob + (int64_t)row * HD + c * 8));
         }
-    }  // row blocks of this workgroup
+    }
 }
 
 }  // namespace
+
+// Causal form: batch entries (heads) an XCD works on at a time.  Longest-first pays the more the fewer row blocks there are,
+// and the chunks should be equal: all heads at once up to 16 MB of K and V per XCD (288 x 1024^2 x 128: 107 us against 112 in
+// chunks of 8; 96 x 2048^2 121 against 135).  Beyond that their K and V should stay in the 4 MB L2 (768 x 2048^2: 969 us in
+// chunks of 4 MB, 1071 all at once).
+static int attn_chunk(int64_t b, int64_t s_k, int64_t d)
+{
+    const int64_t heads = (b + 7) / 8, bytes = 2 * s_k * d;
+    if (heads * bytes <= (16 << 20)) return (int)heads;
+    int64_t n = (heads * bytes + (4 << 20) - 1) / (4 << 20);
+    if (n > heads) n = heads;
+    return (int)((heads + n - 1) / n);
+}
 
 static sq_status attention(const int8_t* q, const int8_t* k, const int8_t* v, float alpha1, float alpha2, void* o,
                            sq_dtype out, int64_t b, int64_t s_q, int64_t s_k, int64_t d, int64_t stride_q,
@@ -387,21 +426,29 @@ static sq_status attention(const int8_t* q, const int8_t* k, const int8_t* v, fl
     AttnArgs a{};
     a.Q = q; a.K = k; a.V = v; a.O = o; a.P = p_codes;
     a.s_q = (int)s_q; a.s_k = (int)s_k;
-    a.tiles_m = (int)(causal ? (tiles_m + 1) / 2 : tiles_m);  // causal: workgroups own pairs of row blocks
+    a.tiles_m = (int)tiles_m;
     a.stride_q = stride_q; a.stride_k = stride_k; a.stride_v = stride_v; a.stride_o = stride_o;
     a.alpha1 = alpha1; a.alpha2 = alpha2;
     hipStream_t st = (hipStream_t)stream;
-    if (sq_attn_few_eligible(b, s_q, s_k)) {
+    if (sq_attn_few_eligible(b, s_q, s_k, d, causal)) {
         sq_attn_few_launch(a, b, d, out == SQ_BF16, causal, st);
         return sq_launch_status();
     }
-    const dim3 grid((unsigned)(b * a.tiles_m)), block(256);
-    const bool tail = (s_k & 127) != 0;
-#define SQ_ATTN(BF, HD)                                                                        \
-    do {                                                                                       \
-        if (causal) sq_launch((attn_i8_kernel<BF, HD, kCausal>), grid, block, 0, st, a);       \
-        else if (tail) sq_launch((attn_i8_kernel<BF, HD, kTail>), grid, block, 0, st, a);      \
-        else sq_launch((attn_i8_kernel<BF, HD, kAll>), grid, block, 0, st, a);                 \
+    a.batch = (int)b;
+    a.causal = causal ? 1 : 0;
+    a.coff = causal ? (int)(s_k - s_q) : (int)s_k;
+    a.chunk = attn_chunk(b, s_k, d);
+    // The kernel's scores carry a factor 2^-26 (see kBias).  A factor beyond 2^101 makes every difference of two scores
+    // infinite for the softmax, like 2^101 itself.
+    a.alpha1 = (alpha1 < 0x1p+101f ? alpha1 : 0x1p+101f) * 0x1p+26f;
+    const dim3 grid((unsigned)((causal ? (b + 7) / 8 * 8 : b) * tiles_m)), block(256);
+    const bool masked = causal || (s_k & 127) != 0;
+#define SQ_ATTN(BF, HD)                                                                  \
+    do {                                                                                 \
+        if (p_codes && masked) sq_launch((attn_i8_kernel<BF, HD, true, true>), grid, block, 0, st, a); \
+        else if (p_codes) sq_launch((attn_i8_kernel<BF, HD, false, true>), grid, block, 0, st, a);     \
+        else if (masked) sq_launch((attn_i8_kernel<BF, HD, true, false>), grid, block, 0, st, a);      \
+        else sq_launch((attn_i8_kernel<BF, HD, false, false>), grid, block, 0, st, a);                 \
     } while (0)
     if (d == 128) {
         if (out == SQ_BF16) SQ_ATTN(true, 128); else SQ_ATTN(false, 128);

@@ -1,5 +1,6 @@
-"""The few-query form of the fused attention (its launch rule: at most 64 queries, at most 8192 keys) against the oracle's
-chain, at the edges of its 16-row blocks, 64-key groups and register sizes (4 or 8 waves, 2 / 4 / 8 / 16 groups each).
+"""The few-query form of the fused attention (16-row blocks; taken by a time model for few queries, or few heads) against
+the oracle's chain, at the edges of its row blocks, 64-key groups and register sizes (4 or 8 waves, 2 / 4 / 8 / 16 groups
+each); and shapes around the model's border with the row-block form, with scores that leave the range of a fixed shift.
 Gates as for the row-block form: codes within one, at most one in a thousand; the output identical to the oracle's P V of
 the kernel's own codes."""
 import numpy as np
@@ -16,7 +17,10 @@ pytestmark = pytest.mark.gpu
 CASES = [(1, 1, 16, 128), (2, 1, 64, 64), (3, 15, 80, 128), (2, 16, 512, 64), (2, 17, 528, 128), (1, 64, 1024, 128), (1, 64, 1040, 64),
          (1, 65, 1040, 64), (2, 2, 2064, 128), (1, 3, 4112, 64), (1, 1, 8192, 128), (1, 1, 8208, 64),
          (260, 1, 80, 128), (257, 1, 272, 64), (300, 2, 528, 128), (70, 50, 512, 64), (260, 1, 2064, 64), (258, 1, 4096, 128),
-         (258, 1, 4112, 64)]
+         (258, 1, 4112, 64),
+         # row blocks of 128: many heads per query row, a last block of few rows, a last tile of one 16-key group, key counts
+         # on and off the 64- and 128-key tiles
+         (60, 129, 144, 128), (60, 137, 272, 64), (50, 190, 192, 128), (33, 300, 320, 128), (40, 200, 208, 64)]
 
 
 def _codes(shape, seed):
@@ -66,3 +70,35 @@ def test_few_queries_extreme_rows(kind, odt):
     q[:] = np.abs(q)
     k[:, j] = 127
     _check(q, k, v, (4.5 / 127.0) ** 2 / d ** 0.5, True, odt)
+
+
+@pytest.mark.parametrize("b,s_q,s_k,d", [(60, 160, 320, 128), (60, 144, 384, 64)])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("odt", [F16, BF16])
+def test_row_blocks_scores_far_above_the_first_tile(b, s_q, s_k, d, causal, odt):
+    """The maximum moves by hundreds from tile to tile: every earlier sum is rescaled to nothing."""
+    print(f"[case] rising scores b={b} s_q={s_q} s_k={s_k} d={d} causal={causal} dtype={odt}", flush=True)
+    q, k, v = (_codes((b, n, d), 740 + i) for i, n in enumerate((s_q, s_k, s_k)))
+    q = np.maximum(np.abs(q), 20)
+    for j in range(64, s_k, 32):
+        k[:, j] = min(127, 30 + j // 4)
+    _check(q, k, v, 0.05, causal, odt)
+
+
+@pytest.mark.parametrize("s_q,s_k,d", [(100, 400, 128), (130, 1040, 128), (256, 256, 64), (48, 528, 64)])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("odt", [torch.float16, torch.bfloat16])
+def test_both_forms_give_the_same_codes(s_q, s_k, d, causal, odt):
+    """Two heads alone take the few-query form, the same heads among 700 the row-block form; sums and folds run in the same
+    order in both, so codes and outputs are the same bit for bit."""
+    print(f"[case] both forms s_q={s_q} s_k={s_k} d={d} causal={causal} {odt}", flush=True)
+    q, k, v = (dev(_codes((2, n, d), 760 + i)) for i, n in enumerate((s_q, s_k, s_k)))
+    few, rows = 2, 700
+    out = []
+    for b in (few, rows):
+        pq = torch.full((b, s_q, s_k), -128, dtype=torch.int8, device="cuda")
+        o = sq.w8a8_attention(*(x.repeat(b // 2, 1, 1) for x in (q, k, v)), (4.5 / 127.0) ** 2 / d ** 0.5, 1e-3, odt, p_codes=pq,
+                              causal=causal)
+        out.append((pq[:2].clone(), pq[-2:].clone(), o[:2].view(torch.int16).clone()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][0], out[1][1])
+    assert torch.equal(out[0][2], out[1][2])
