@@ -1,6 +1,6 @@
 // Offline weight preparation, gfx950: the statistics of Eq. 4, the smoothed weight of Eq. 3 and its
 // per-tensor quantization by Eq. 1, written transposed ([C_o, C_i], contraction index contiguous)
-// for the GEMM.  One-off work per layer: kept simple, coalesced on both sides of the transpose.
+// for the GEMM.  HBM bound: W is read once per statistic and once for its codes.
 #include "common.h"
 
 namespace {
@@ -14,40 +14,48 @@ template <bool BF16> SQ_DEVICE void unpack8w(const v4u raw, float (&f)[8])
     }
 }
 
-SQ_DEVICE float block_max_256w(float v, float* red)
-{
-    v = wave_max(v);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    const float r = __builtin_fmaxf(__builtin_fmaxf(red[0], red[1]), __builtin_fmaxf(red[2], red[3]));
-    __syncthreads();
-    return r;
-}
-
-// out_j = max_n |W_jn| * (s ? s_j : 1); one workgroup per input channel j (row of W).
-// If tensor_bits is given, also folds the row maxima into the tensor-wide maximum.
-template <bool BF16>
+// Maxima over rows of W: one row (input channel j) per wave, four 16-byte loads per lane in flight.  ROWS: row_out[j] =
+// max_n |W_jn|.  Otherwise the maximum over the tensor, each row scaled by s_j: a wave keeps it over all its rows and
+// adds it to tensor_bits with one atomic (the integer order of the bit patterns of non-negative floats is the float order);
+// one atomic per row on that single cell, some 12 ns each, was the longest part of a narrow weight's preparation.
+template <bool BF16, bool ROWS>
 __global__ __launch_bounds__(256) void weight_row_absmax_kernel(const uint16_t* __restrict__ w, int c_i, int c_o,
                                                                const float* __restrict__ s, float* row_out,
                                                                uint32_t* tensor_bits)
 {
-    __shared__ float red[4];
+    const int lane = threadIdx.x & 63;
     const int nvec = c_o >> 3;
-    for (int j = blockIdx.x; j < c_i; j += gridDim.x) {
-        const v4u* wr = (const v4u*)(w + (int64_t)j * c_o);
+    float all = 0.0f;
+    for (int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); j < c_i; j += (int64_t)gridDim.x * 4) {
+        const v4u* wr = (const v4u*)(w + j * c_o);
         const float sj = s ? s[j] : 1.0f;
         float m = 0.0f;
-        for (int idx = threadIdx.x; idx < nvec; idx += 256) {
-            float f[8];
-            unpack8w<BF16>(wr[idx], f);
+        for (int i0 = lane; i0 < nvec; i0 += 256) {
+            v4u raw[4];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, __builtin_fabsf(s ? f[e] * sj : f[e]));
+            for (int i = 0; i < 4; ++i) raw[i] = wr[i0 + i * 64 < nvec ? i0 + i * 64 : i0];  // past the end: the first one again
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float f[8];
+                unpack8w<BF16>(raw[i], f);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, __builtin_fabsf(s ? f[e] * sj : f[e]));
+            }
         }
-        m = block_max_256w(m, red);
-        if (threadIdx.x == 0) {
-            if (row_out) row_out[j] = m;
-            if (tensor_bits) atomicMax(tensor_bits, __builtin_bit_cast(uint32_t, m));
+        if constexpr (ROWS) {
+            m = wave_max(m);
+            if (lane == 0) row_out[j] = m;
+        } else {
+            all = __builtin_fmaxf(all, m);
         }
+    }
+    if constexpr (!ROWS) {
+        __shared__ float red[4];
+        all = wave_max(all);
+        if (lane == 0) red[threadIdx.x >> 6] = all;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            atomicMax(tensor_bits, __builtin_bit_cast(uint32_t, __builtin_fmaxf(__builtin_fmaxf(red[0], red[1]), __builtin_fmaxf(red[2], red[3]))));
     }
 }
 
@@ -56,72 +64,128 @@ __global__ void zero_u32_kernel(uint32_t* p, int64_t n)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
 
-// Per-output-channel maxima: col_bits[n] = max_j |W_jn * s_j| as the bit pattern of a non-negative float
-// (its integer order is the float order, so atomicMax is exact).  A thread owns 8 neighbouring columns and
-// walks a slab of 64 rows; slabs are spread over blockIdx.y.
+// Per-output-channel maxima: col_bits[n] = max_j |W_jn * s_j| as the bit pattern of a non-negative float.  A workgroup owns
+// 512 columns (a wave's row of 1 KB) over a slab of rows, one row in four per wave with four loads in flight; the waves meet
+// in LDS, the slabs by atomic max.
 template <bool BF16>
 __global__ __launch_bounds__(256) void weight_col_absmax_kernel(const uint16_t* __restrict__ w, int c_i, int c_o,
-                                                               const float* __restrict__ s, uint32_t* col_bits)
+                                                               const float* __restrict__ s, int rows_per_wg, uint32_t* col_bits)
 {
-    const int n = (blockIdx.x * 256 + threadIdx.x) * 8;
-    if (n >= c_o) return;  // c_o % 8 == 0
-    const int j0 = blockIdx.y * 64, j1 = j0 + 64 < c_i ? j0 + 64 : c_i;
+    __shared__ float red[3][512];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = (blockIdx.x * 64 + lane) * 8;
+    const int j0 = blockIdx.y * rows_per_wg, j1 = c_i - j0 < rows_per_wg ? c_i : j0 + rows_per_wg;
     float m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int j = j0; j < j1; ++j) {
-        float f[8];
-        unpack8w<BF16>(*(const v4u*)(w + (int64_t)j * c_o + n), f);
-        const float sj = s ? s[j] : 1.0f;
+    if (n < c_o) {  // c_o % 8 == 0
+        for (int j = j0 + wave; j < j1; j += 16) {
+            v4u raw[4];
+            float sj[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) m[e] = __builtin_fmaxf(m[e], __builtin_fabsf(s ? f[e] * sj : f[e]));
+            for (int i = 0; i < 4; ++i) {
+                const int jj = j + i * 4 < j1 ? j + i * 4 : j;  // past the end: the first row again
+                raw[i] = *(const v4u*)(w + (int64_t)jj * c_o + n);
+                sj[i] = s ? s[jj] : 1.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float f[8];
+                unpack8w<BF16>(raw[i], f);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) m[e] = __builtin_fmaxf(m[e], __builtin_fabsf(s ? f[e] * sj[i] : f[e]));
+            }
+        }
     }
+    if (wave > 0) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) atomicMax(col_bits + n + e, __builtin_bit_cast(uint32_t, m[e]));
+        for (int e = 0; e < 8; ++e) red[wave - 1][e * 64 + lane] = m[e];
+    }
+    __syncthreads();
+    if (wave == 0 && n < c_o) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float v = __builtin_fmaxf(__builtin_fmaxf(m[e], red[0][e * 64 + lane]), __builtin_fmaxf(red[1][e * 64 + lane], red[2][e * 64 + lane]));
+            atomicMax(col_bits + n + e, __builtin_bit_cast(uint32_t, v));
+        }
+    }
 }
 
-// 64 (input channels) x 64 (output channels) tile: read along C_o, quantize, transpose through LDS,
-// write along C_i.
+// Quantize and transpose.  A wave owns 64 input x 128 output channels: lane (ng, jc) loads rows 16 jc .. 16 jc + 15 of its 8
+// columns with sixteen 16-byte loads (256 contiguous bytes of a row per 16 lanes), quantizes them and packs four
+// rows' codes into a word with byte permutes, so that it ends up with one 16-byte chunk (16 input channels of one output
+// channel) per column.  The chunks pass through an LDS image of the wave's own, laid out like the tiled blocks (no workgroup
+// barrier), and leave as whole 1 KB blocks (or 64-byte row segments).  The step of a column is formed once per 16 codes.
+// (A byte-wise transpose of 64 x 64 tiles, a division per code with per-channel steps, took 83 us at 5120 x 20480.)
 template <bool BF16>
 __global__ __launch_bounds__(256) void weight_quant_transpose_kernel(const uint16_t* __restrict__ w, int c_i, int c_o,
                                                                     const float* __restrict__ s,
                                                                     const uint32_t* amax_bits, float* w_scale,
                                                                     int8_t* __restrict__ wq, bool tiled, bool per_channel)
 {
-    __shared__ __attribute__((aligned(16))) int8_t tileT[64][80];  // [n][j], padded pitch
-    const float a = __builtin_bit_cast(float, *amax_bits);  // per-tensor maximum (per_channel: unused)
-    const float r = a > 0.0f ? 127.0f / a : 0.0f;
-    const int j0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+    __shared__ __attribute__((aligned(1024))) char image[4][8192];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ng = lane & 15, jc = lane >> 4;
+    const int n0 = blockIdx.x * 128, j0 = (blockIdx.y * 4 + wave) * 64;
+    if (j0 >= c_i) return;
+    const int n = n0 + ng * 8, j = j0 + jc * 16;
+    const bool valid = n < c_o && j < c_i;  // c_o % 8 == 0, c_i % 16 == 0: a lane's piece is inside or outside as a whole
+    float r[8];
     if (per_channel) {  // amax_bits[n]: maximum of column n
-        if (blockIdx.y == 0 && threadIdx.x < 64 && n0 + threadIdx.x < c_o)
-            w_scale[n0 + threadIdx.x] = __builtin_bit_cast(float, amax_bits[n0 + threadIdx.x]) / 127.0f;
-    } else if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
-        w_scale[0] = a / 127.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float a = n < c_o ? __builtin_bit_cast(float, amax_bits[n + e]) : 0.0f;
+            r[e] = a > 0.0f ? 127.0f / a : 0.0f;
+            if (j0 == 0 && jc == 0 && n < c_o) w_scale[n + e] = a / 127.0f;
+        }
+    } else {
+        const float a = __builtin_bit_cast(float, *amax_bits);
+        const float r0 = a > 0.0f ? 127.0f / a : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) r[e] = r0;
+        if (n0 == 0 && j0 == 0 && lane == 0) w_scale[0] = a / 127.0f;
     }
+    v4u raw[16];
+    float sj[16];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int v = threadIdx.x + h * 256;  // 512 vectors: 64 rows x 8 vectors of 8 channels
-        const int jl = v >> 3, nl = (v & 7) * 8;
-        const int j = j0 + jl, n = n0 + nl;
-        if (j < c_i && n < c_o) {  // c_o % 8 == 0: a vector is inside or outside as a whole
-            float f[8];
-            unpack8w<BF16>(*(const v4u*)(w + (int64_t)j * c_o + n), f);
-            const float sj = s ? s[j] : 1.0f;
+    for (int i = 0; i < 16; ++i) {
+        raw[i] = valid ? __builtin_nontemporal_load((const v4u*)(w + (int64_t)(j + i) * c_o + n)) : v4u{0, 0, 0, 0};
+        sj[i] = s && valid ? s[j + i] : 1.0f;
+    }
+    v4u out[8];  // the 16 codes of column e
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float re = r;
-                if (per_channel) {
-                    const float an = __builtin_bit_cast(float, amax_bits[n + e]);
-                    re = an > 0.0f ? 127.0f / an : 0.0f;
-                }
-                tileT[nl + e][jl] = (int8_t)round_code((s ? f[e] * sj : f[e]) * re);
+    for (int q = 0; q < 4; ++q) {
+        float f[4][8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            unpack8w<BF16>(raw[4 * q + i], f[i]);
+            if (s) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) f[i][e] = f[i][e] * sj[4 * q + i];
             }
         }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            out[e][q] = pack4_low_bytes(code_bits(f[0][e] * r[e]), code_bits(f[1][e] * r[e]), code_bits(f[2][e] * r[e]), code_bits(f[3][e] * r[e]));
     }
-    __syncthreads();
-    {
-        const int nl = threadIdx.x >> 2, jc = (threadIdx.x & 3) * 16;
-        const int n = n0 + nl, j = j0 + jc;
-        if (n < c_o && j < c_i)  // c_i % 16 == 0
-            *(v4u*)code_dst(wq, n, j, c_i, tiled) = *(const v4u*)&tileT[nl][jc];  // 16 codes = one chunk
+    // image: block ng / 2 of 16 output channels, row 8 (ng & 1) + e, chunk jc at position jc ^ sw(row)
+    auto sw = [](int row) { return ((row >> 1) & 3) ^ ((row >> 3) & 1); };
+    char* img = image[wave];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int row = (ng & 1) * 8 + e;
+        *(v4u*)(img + (ng >> 1) * 1024 + row * 64 + ((jc ^ sw(row)) << 4)) = out[e];
+    }
+    __builtin_amdgcn_wave_barrier();  // LDS serves one wave's accesses in order; keep the compiler from reordering
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const v4u val = *(const v4u*)(img + b * 1024 + lane * 16);
+        const int nb = n0 + b * 16;
+        if (nb >= c_o) break;
+        if (tiled) {  // (rows of the last block beyond c_o: padding)
+            __builtin_nontemporal_store(val, (v4u*)(wq + ((int64_t)(nb >> 4) * (c_i >> 6) + (j0 >> 6)) * 1024 + lane * 16));
+        } else {
+            const int row = lane >> 2, jj = j0 + (((lane & 3) ^ sw(row)) << 4);
+            if (nb + row < c_o && jj < c_i) *(v4u*)(wq + (int64_t)(nb + row) * c_i + jj) = val;
+        }
     }
 }
 
@@ -136,11 +200,11 @@ sq_status sq_weight_absmax_per_in_channel(const void* w, sq_dtype dtype, int64_t
     if (c_i <= 0 || c_o <= 0 || c_i >= ((int64_t)1 << 31) || c_o >= ((int64_t)1 << 31)) return SQ_ERR_SHAPE;
     if (dtype != SQ_F16 && dtype != SQ_BF16) return SQ_ERR_UNSUPPORTED;
     if ((c_o & 7) || !sq_aligned16(w)) return SQ_ERR_ALIGN;
-    const unsigned grid = (unsigned)(c_i < 65535 ? c_i : 65535);
+    const unsigned grid = (unsigned)((c_i + 3) / 4);
     if (dtype == SQ_BF16)
-        sq_launch(weight_row_absmax_kernel<true>, dim3(grid), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)w, (int)c_i, (int)c_o, (const float*)nullptr, out, (uint32_t*)nullptr);
+        sq_launch((weight_row_absmax_kernel<true, true>), dim3(grid), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)w, (int)c_i, (int)c_o, (const float*)nullptr, out, (uint32_t*)nullptr);
     else
-        sq_launch(weight_row_absmax_kernel<false>, dim3(grid), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)w, (int)c_i, (int)c_o, (const float*)nullptr, out, (uint32_t*)nullptr);
+        sq_launch((weight_row_absmax_kernel<false, true>), dim3(grid), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)w, (int)c_i, (int)c_o, (const float*)nullptr, out, (uint32_t*)nullptr);
     return sq_launch_status();
 }
 
@@ -162,16 +226,21 @@ sq_status sq_prepare_weight(const void* w, sq_dtype dtype, const float* s, int64
     uint32_t* amax = (uint32_t*)workspace;
     const int64_t ncell = pc ? c_o : 1;
     sq_launch(zero_u32_kernel, dim3((unsigned)((ncell + 255) / 256 < 1024 ? (ncell + 255) / 256 : 1024)), dim3(256), 0, st, amax, ncell);
-    const unsigned grid1 = (unsigned)(c_i < 4096 ? c_i : 4096);
-    dim3 gridc((unsigned)((c_o / 8 + 255) / 256), (unsigned)((c_i + 63) / 64));
-    dim3 grid2((unsigned)((c_o + 63) / 64), (unsigned)((c_i + 63) / 64));
+    const unsigned grid1 = (unsigned)(c_i < 2048 ? (c_i + 3) / 4 : 512);
+    // about four workgroups per compute unit, slabs of at least 64 rows (each slab costs an atomic per column)
+    const int64_t colb = (c_o / 8 + 63) / 64;
+    int64_t slabs = (1024 + colb - 1) / colb;
+    if (slabs > (c_i + 63) / 64) slabs = (c_i + 63) / 64;
+    const int rows = (int)((c_i + slabs - 1) / slabs);
+    const dim3 gridc((unsigned)colb, (unsigned)((c_i + rows - 1) / rows));
+    const dim3 grid2((unsigned)((c_o + 127) / 128), (unsigned)((c_i + 255) / 256));
     if (dtype == SQ_BF16) {
-        if (pc) sq_launch(weight_col_absmax_kernel<true>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax);
-        else sq_launch(weight_row_absmax_kernel<true>, dim3(grid1), dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, (float*)nullptr, amax);
+        if (pc) sq_launch(weight_col_absmax_kernel<true>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, rows, amax);
+        else sq_launch((weight_row_absmax_kernel<true, false>), dim3(grid1), dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, (float*)nullptr, amax);
         sq_launch(weight_quant_transpose_kernel<true>, grid2, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax, w_scale, wq, tiled, pc);
     } else {
-        if (pc) sq_launch(weight_col_absmax_kernel<false>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax);
-        else sq_launch(weight_row_absmax_kernel<false>, dim3(grid1), dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, (float*)nullptr, amax);
+        if (pc) sq_launch(weight_col_absmax_kernel<false>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, rows, amax);
+        else sq_launch((weight_row_absmax_kernel<false, false>), dim3(grid1), dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, (float*)nullptr, amax);
         sq_launch(weight_quant_transpose_kernel<false>, grid2, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax, w_scale, wq, tiled, pc);
     }
     return sq_launch_status();

@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from paper_2211_10438_amd import binding as sq
+from tests._util import tiled_index
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +57,30 @@ def test_channel_maxima(t, c_i, dtype):
     x[t - 1, c_i - 1] = -50.0
     x[0, 0] = 51.0
     assert torch.equal(sq.act_absmax_per_channel(x), x.float().abs().amax(0))
+
+
+# weight tiles of 64 x 128 per wave and 256 x 128 per workgroup, column slabs of 64 rows and more, 512-column workgroups: one
+# piece short of, at and past each edge
+@pytest.mark.parametrize("c_i,c_o", [(16, 8), (64, 120), (80, 136), (240, 512), (256, 520), (272, 128), (4160, 264), (320, 4104)])
+@pytest.mark.parametrize("per_channel", [False, True])
+@pytest.mark.parametrize("with_s", [False, True])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_weight_preparation_edges(c_i, c_o, per_channel, with_s, dtype):
+    print(f"weights {c_i}x{c_o} per_channel={per_channel} s={with_s} {dtype}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(c_i + c_o)
+    w = (torch.randn((c_i, c_o), generator=g, device="cuda") * 0.02).to(dtype)
+    w[c_i - 1, c_o - 1] = -0.5  # the tensor's and its column's maximum is the last element
+    w[:, c_o // 2] = 0.0        # a column of zeros: step 0, codes 0
+    s = torch.rand(c_i, generator=g, device="cuda") + 0.5 if with_s else None
+    v = w.float() if s is None else w.float() * s[:, None]
+    a = (v.abs().amax(0) if per_channel else v.abs().max().reshape(1)).cpu()
+    r = torch.where(a > 0, torch.full_like(a, 127.0) / a, torch.zeros_like(a)).cuda()
+    codes = (v * r).round().clamp(-127, 127).to(torch.int8).t().contiguous()
+    for layout in [sq.ROW_MAJOR] + ([sq.TILED] if c_i % 64 == 0 else []):
+        wq, step = sq.prepare_weight(w, s, layout=layout, per_channel=per_channel)
+        assert torch.equal(step.cpu(), a / torch.full_like(a, 127.0))
+        if layout == sq.TILED:
+            flat = wq._base.reshape(-1) if wq._base is not None else wq.reshape(-1)
+            wq = flat[torch.from_numpy(tiled_index(c_o, c_i)).cuda()]
+        assert torch.equal(wq, codes)
+    assert torch.equal(sq.weight_absmax_per_in_channel(w), w.float().abs().amax(1))
