@@ -102,19 +102,41 @@ SQ_DEVICE int8_t* code_dst(int8_t* base, int64_t r, int c, int k, bool tiled)
     return base + (tiled ? tiled_offset(r, c, k) : r * (int64_t)k + c);
 }
 
-// Wave-wide max over 64 lanes (all lanes receive the result).
-SQ_DEVICE float wave_max(float v)
+// Wave-wide reductions (all lanes receive the result): a butterfly over lane ^ 32, 16, 8, 4, 2, 1 in this order.  The partner's
+// value comes from lane swaps and DPP moves, which are vector instructions; a shuffle goes through the LDS unit, and the six
+// dependent ones of a reduction were most of the time between a row's arrival and its codes.
+template <int o> SQ_DEVICE float lane_xor(float v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = __builtin_fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    const int i = __builtin_bit_cast(int, v);
+    int r;
+    if constexpr (o == 8) {
+        r = __builtin_amdgcn_mov_dpp(i, 0x128, 0xf, 0xf, true);  // rotate a row of 16 by 8
+    } else if constexpr (o == 4) {
+        r = __builtin_amdgcn_update_dpp(0, i, 0x104, 0xf, 0x5, true);  // lanes 0-3, 8-11 of a row: from 4 lanes up
+        r = __builtin_amdgcn_update_dpp(r, i, 0x114, 0xf, 0xa, true);  // the others: from 4 lanes down
+    } else {
+        static_assert(o == 2 || o == 1, "lane distance");
+        r = __builtin_amdgcn_mov_dpp(i, o == 2 ? 0x4e : 0xb1, 0xf, 0xf, true);  // within four lanes
+    }
+    return __builtin_bit_cast(float, r);
 }
-SQ_DEVICE float wave_sum(float v)
+template <class F> SQ_DEVICE float wave_reduce(float v, F&& op)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    const uint32_t a = __builtin_bit_cast(uint32_t, v);
+    const auto s32 = __builtin_amdgcn_permlane32_swap(a, a, false, false);  // {lower half in both halves, upper half in both}
+    const uint32_t lo = s32[0], up = s32[1];
+    v = op(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, up));
+    const uint32_t b = __builtin_bit_cast(uint32_t, v);
+    const auto s16 = __builtin_amdgcn_permlane16_swap(b, b, false, false);  // {even rows of 16 twice, odd rows twice}
+    const uint32_t ev = s16[0], od = s16[1];
+    v = op(__builtin_bit_cast(float, ev), __builtin_bit_cast(float, od));
+    v = op(v, lane_xor<8>(v));
+    v = op(v, lane_xor<4>(v));
+    v = op(v, lane_xor<2>(v));
+    return op(v, lane_xor<1>(v));
 }
+SQ_DEVICE float wave_max(float v) { return wave_reduce(v, [](float a, float b) { return __builtin_fmaxf(a, b); }); }
+SQ_DEVICE float wave_sum(float v) { return wave_reduce(v, [](float a, float b) { return a + b; }); }
 
 // ---- ticketed 64-bit cells {ticket : value} in caller-owned scratch that nobody clears.  A cell whose upper half is
 // not this call's ticket is stale: the first workgroup that sees it so replaces it by {ticket : 0} (one compare-and-

@@ -166,69 +166,104 @@ __global__ __launch_bounds__(256) void softmax_quant_wave_kernel(const uint16_t*
     }
 }
 
-template <bool BF16, int NV, int NT>
-__global__ __launch_bounds__(NT) void ln_quant_kernel(const uint16_t* __restrict__ x, int c_i, const float* __restrict__ gamma_f,
-                                                      const float* __restrict__ beta_f, float eps, float* __restrict__ scale,
-                                                      int8_t* __restrict__ xq, bool tiled)
+// One row per workgroup of up to 512 threads, NV 16-byte vectors per thread, as many threads as that takes.  A wave forms the
+// mean and the sum of squared deviations of its own part of the row (two-pass, in registers), and the parts are combined
+// by the parallel-variance formula, mean = sum S_w / n, M2 = sum (M2_w + n_w (mean_w - mean)^2): two workgroup-wide exchanges
+// per row, statistics and maximum, instead of three, and one barrier each.
+template <bool BF16, int NV>
+__global__ __launch_bounds__(512) void ln_quant_kernel(const uint16_t* __restrict__ x, int c_i, const float* __restrict__ gamma_f,
+                                                       const float* __restrict__ beta_f, float eps, float* __restrict__ scale,
+                                                       int8_t* __restrict__ xq, bool tiled)
 {
-    __shared__ float red[NT / 64];
+    __shared__ float4 part_of[8];  // sum, mean, sum of squared deviations and number of elements of a wave
+    __shared__ float wmax[8];
     const int64_t row = blockIdx.x;
     const v4u* xr = (const v4u*)(x + row * (int64_t)c_i);
-    const int nvec = c_i >> 3;
+    const int nvec = c_i >> 3, nt = blockDim.x, waves = nt >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // Vectors past the end of the row re-read its last one (every load unconditional: a load under a condition is waited for
+    // before the next one is issued, which made a row of NV vectors per thread NV memory latencies long, for x as for
+    // gamma and beta); they take no part in the sums, and in the maximum and the codes they are that vector once more.
+    int idx[NV];
+    v4u raw[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        idx[i] = threadIdx.x + i * nt;
+        idx[i] = idx[i] < nvec ? idx[i] : nvec - 1;
+        raw[i] = __builtin_nontemporal_load(xr + idx[i]);
+    }
     float f[NV][8];
     float sum = 0.0f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int idx = threadIdx.x + i * NT;
-        if (idx < nvec) {
-            unpack8r<BF16>(__builtin_nontemporal_load(xr + idx), f[i]);
+        unpack8r<BF16>(raw[i], f[i]);
+        float part = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sum += f[i][e];
-        }
+        for (int e = 0; e < 8; ++e) part += f[i][e];
+        sum += (int)threadIdx.x + i * nt < nvec ? part : 0.0f;
     }
-    const float mean = block_sum_r<NT>(sum, red) / (float)c_i;
+    // elements of this wave: its 64 lanes hold vectors wave * 64 + i * nt + 0 .. 63
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int left = nvec - (wave * 64 + i * nt);
+        n += left <= 0 ? 0 : left < 64 ? left : 64;
+    }
+    const float wn = (float)(8 * n);  // at least 8: the launch has no wave without a vector
+    sum = wave_sum(sum);
+    const float wmean = sum / wn;
     float sq = 0.0f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int idx = threadIdx.x + i * NT;
-        if (idx < nvec) {
+        float part = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float d = f[i][e] - mean;
-                sq += d * d;
-            }
+        for (int e = 0; e < 8; ++e) {
+            const float d = f[i][e] - wmean;
+            part = __builtin_fmaf(d, d, part);
         }
+        sq += (int)threadIdx.x + i * nt < nvec ? part : 0.0f;
     }
-    const float var = block_sum_r<NT>(sq, red) / (float)c_i;
-    const float rstd = 1.0f / sqrtf(var + eps);
+    sq = wave_sum(sq);
+    if ((threadIdx.x & 63) == 0) {
+        part_of[wave] = float4{sum, wmean, sq, wn};
+    }
+    __syncthreads();
+    // every group of eight lanes holds the waves' parts, one per lane, and reduces them
+    auto sum8 = [](float v) { v += lane_xor<4>(v); v += lane_xor<2>(v); return v + lane_xor<1>(v); };
+    const int w8 = threadIdx.x & 7;
+    const float4 q = w8 < waves ? part_of[w8] : float4{0.0f, 0.0f, 0.0f, 0.0f};
+    const float mean = sum8(q.x) / (float)c_i;
+    const float d = q.y - mean;
+    const float m2 = sum8(q.z + q.w * (d * d));
+    const float rstd = 1.0f / sqrtf(m2 / (float)c_i + eps);
     float m = 0.0f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int idx = threadIdx.x + i * NT;
-        if (idx < nvec) {
-            const float4 g0 = *(const float4*)(gamma_f + idx * 8), g1 = *(const float4*)(gamma_f + idx * 8 + 4);
-            const float4 b0 = *(const float4*)(beta_f + idx * 8), b1 = *(const float4*)(beta_f + idx * 8 + 4);
-            const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-            const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+        const float4 g0 = *(const float4*)(gamma_f + idx[i] * 8), g1 = *(const float4*)(gamma_f + idx[i] * 8 + 4);
+        const float4 b0 = *(const float4*)(beta_f + idx[i] * 8), b1 = *(const float4*)(beta_f + idx[i] * 8 + 4);
+        const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+        const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                f[i][e] = (f[i][e] - mean) * rstd * g[e] + b[e];
-                m = __builtin_fmaxf(m, __builtin_fabsf(f[i][e]));
-            }
+        for (int e = 0; e < 8; ++e) {
+            f[i][e] = __builtin_fmaf((f[i][e] - mean) * rstd, g[e], b[e]);
+            m = __builtin_fmaxf(m, __builtin_fabsf(f[i][e]));
         }
     }
-    const float a = block_max_r<NT>(m, red);
+    m = wave_max(m);
+    if ((threadIdx.x & 63) == 0) wmax[wave] = m;
+    __syncthreads();
+    float a = w8 < waves ? wmax[w8] : 0.0f;
+    a = __builtin_fmaxf(a, lane_xor<4>(a));
+    a = __builtin_fmaxf(a, lane_xor<2>(a));
+    a = __builtin_fmaxf(a, lane_xor<1>(a));
     const float r = a > 0.0f ? 127.0f / a : 0.0f;
     if (threadIdx.x == 0) scale[row] = a / 127.0f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int idx = threadIdx.x + i * NT;
-        if (idx < nvec) {
-            uint32_t q[8];
+        uint32_t codes[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) q[e] = code_bits(f[i][e] * r);
-            __builtin_nontemporal_store(pack8(q), (v2u*)code_dst(xq, row, idx * 8, c_i, tiled));
-        }
+        for (int e = 0; e < 8; ++e) codes[e] = code_bits(f[i][e] * r);
+        if ((int)threadIdx.x + i * nt < nvec) __builtin_nontemporal_store(pack8(codes), (v2u*)code_dst(xq, row, idx[i] * 8, c_i, tiled));
     }
 }
 
@@ -344,16 +379,20 @@ sq_status sq_ln_quantize(const void* x, sq_dtype dtype, int64_t t, int64_t c_i, 
     hipStream_t st = (hipStream_t)stream;
     const int nvec = (int)(c_i >> 3);
     const uint16_t* xp = (const uint16_t*)x;
-    // Measured choice: up to 2048 channels one row per wave; up to 8192 one row per 256-thread workgroup; wider rows
-    // one row per 512-thread workgroup (more loads in flight per row, fewer registers per thread).
-#define SQ_LN(BF, NV, NT) sq_launch((ln_quant_kernel<BF, NV, NT>), dim3((unsigned)t), dim3(NT), 0, st, xp, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
+    // Measured choice: up to 2048 channels one row per wave; wider rows a workgroup of as many threads as the row has vectors
+    // for at NV per thread.  Few rows: short threads, the row's latency counts (1 x 5120 with 2 / 4 vectors 3.2 / 3.9 us,
+    // 1024 x 9216 with 3 / 4 / 5 8.7 / 9.5 / 9.6).  Many rows: the reductions are shared by more elements of a wave
+    // (4096 x 9216 with 3 / 5 / 6 vectors 34.1 / 34.8 / 31.5 us, 4096 x 5120 with 2 / 5 / 6 20.8 / 18.8 / 20.1, 8192 x 4096 with
+    // 3 / 4 / 5 31.7 / 28.3 / 28.6).  With three exchanges, loads under a condition and 3 x 512 threads: 37.8 us at 4096 x 9216,
+    // 11.9 at 1024 x 9216, 4.1 at 1 x 5120.
+#define SQ_LN(BF, NV) sq_launch((ln_quant_kernel<BF, NV>), dim3((unsigned)t), dim3((unsigned)(((nvec + NV - 1) / NV + 63) / 64 * 64)), 0, st, xp, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
 #define SQ_LNW(BF, NV) sq_launch((ln_quant_wave_kernel<BF, NV>), dim3((unsigned)((t + 3) / 4)), dim3(256), 0, st, xp, t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
+    const int nv = t >= 2048 ? (nvec <= 512 ? 4 : nvec <= 768 ? 5 : 6) : (nvec <= 640 ? 2 : nvec <= 1536 ? 3 : 4);
+#define SQ_LNB(BF) do { switch (nv) { case 2: SQ_LN(BF, 2); break; case 3: SQ_LN(BF, 3); break; case 4: SQ_LN(BF, 4); break; case 5: SQ_LN(BF, 5); break; default: SQ_LN(BF, 6); break; } } while (0)
     if (dtype == SQ_BF16) {
-        if (nvec <= 128) SQ_LNW(true, 2); else if (nvec <= 256) SQ_LNW(true, 4); else if (nvec <= 512) SQ_LN(true, 2, 256);
-        else if (nvec <= 1024) SQ_LN(true, 4, 256); else if (nvec <= 1536) SQ_LN(true, 3, 512); else SQ_LN(true, 4, 512);
+        if (nvec <= 128) SQ_LNW(true, 2); else if (nvec <= 256) SQ_LNW(true, 4); else SQ_LNB(true);
     } else {
-        if (nvec <= 128) SQ_LNW(false, 2); else if (nvec <= 256) SQ_LNW(false, 4); else if (nvec <= 512) SQ_LN(false, 2, 256);
-        else if (nvec <= 1024) SQ_LN(false, 4, 256); else if (nvec <= 1536) SQ_LN(false, 3, 512); else SQ_LN(false, 4, 512);
+        if (nvec <= 128) SQ_LNW(false, 2); else if (nvec <= 256) SQ_LNW(false, 4); else SQ_LNB(false);
     }
 #undef SQ_LN
 #undef SQ_LNW
