@@ -81,3 +81,7 @@ void sq_stream_gemm_launch(const GemmArgs& a, bool to_i32, bool bf16, bool tiled
 // Strip kernel for attention scores (bmm_strip.hip): B = [N, K] with K <= 128, alpha-only epilogue.
 bool sq_strip_bmm_eligible(int64_t M, int64_t N, int64_t K, int64_t batch);
 void sq_strip_bmm_launch(const GemmArgs& a, int batch, bool bf16, hipStream_t st);
+
+// Few tokens, few output channels (gemm_i8_narrow.hip): one kernel, no workspace.
+bool sq_narrow_gemm_eligible(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled);
+void sq_narrow_gemm_launch(const GemmArgs& a, bool to_i32, bool bf16, bool tiled, hipStream_t st);
