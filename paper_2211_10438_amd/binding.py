@@ -8,6 +8,7 @@ exception is raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -79,32 +80,44 @@ def _check(st: int, what: str):
         raise SqmiError(f"{what}: {lib().sq_status_string(st).decode()} (status {st})")
 
 
+_DTYPE = {torch.float16: F16, torch.bfloat16: BF16}
+
+
 def _dt(t: torch.Tensor) -> int:
-    if t.dtype == torch.float16:
-        return F16
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError(f"16-bit floating tensor expected, got {t.dtype}")
+    code = _DTYPE.get(t.dtype)
+    if code is None:
+        raise TypeError(f"16-bit floating tensor expected, got {t.dtype}")
+    return code
 
 
 def _dev(t: torch.Tensor, dtype=None, name="tensor"):
+    if t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is dtype):
+        return t.data_ptr()
     if not t.is_cuda:
         raise SqmiError(f"{name} must be a GPU tensor")
     if not t.is_contiguous():
         raise SqmiError(f"{name} must be contiguous")
-    if dtype is not None and t.dtype != dtype:
-        raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
-    return t.data_ptr()
+    raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
 
 
 def _opt(t, dtype, name):
     return None if t is None else _dev(t, dtype, name)
 
 
+# The raw handle of the current device's current stream, without the Stream object around it (a third of the host time
+# of a small call); older or newer torch builds without the two functions take the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or _raw_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    torch.cuda.init()
+    return _raw_stream(_raw_device())
 
 
+@functools.lru_cache(maxsize=4096)
 def workspace_bytes(op: int, t: int, c_i: int, c_o: int) -> int:
     return int(lib().sq_workspace_bytes(op, t, c_i, c_o))
 
@@ -123,10 +136,11 @@ def empty_codes(rows: int, k: int, layout: int = ROW_MAJOR, device="cuda") -> to
     """int8 [rows, k] operand buffer.  In the TILED layout the storage is padded to a multiple of 16 rows
     and the returned tensor is the [rows, k] view of it (its bytes are in tiled order, not row order)."""
     if layout == TILED:
-        nbytes = int(lib().sq_tiled_bytes(rows, k))
-        if nbytes == 0:
+        if rows <= 0 or k <= 0 or k % 64:
             raise SqmiError("tiled layout needs k % 64 == 0")
-        return torch.empty((nbytes // k, k), dtype=torch.int8, device=device)[:rows]
+        padded = (rows + 15) // 16 * 16
+        codes = torch.empty((padded, k), dtype=torch.int8, device=device)
+        return codes if padded == rows else codes[:rows]
     return torch.empty((rows, k), dtype=torch.int8, device=device)
 
 

@@ -43,6 +43,16 @@ sq_status sq_smooth_scales(const float* x_absmax, const float* w_absmax, float a
     if (c_i <= 0) return SQ_ERR_SHAPE;
     if (!(alpha >= 0.0f && alpha <= 1.0f)) return SQ_ERR_UNSUPPORTED;
     const float floor_v = 1e-5f;
+    if (alpha == 0.5f) {  // the usual migration strength: square roots, correctly rounded, for two powers (40 ns a channel)
+        for (int64_t j = 0; j < c_i; ++j) {
+            const double ax = (double)(x_absmax[j] > floor_v ? x_absmax[j] : floor_v);
+            const double aw = (double)(w_absmax[j] > floor_v ? w_absmax[j] : floor_v);
+            const float sj = (float)(sqrt(ax) / sqrt(aw));
+            s[j] = sj;
+            if (inv_s) inv_s[j] = 1.0f / sj;
+        }
+        return SQ_OK;
+    }
     for (int64_t j = 0; j < c_i; ++j) {
         const double ax = (double)(x_absmax[j] > floor_v ? x_absmax[j] : floor_v);
         const double aw = (double)(w_absmax[j] > floor_v ? w_absmax[j] : floor_v);
