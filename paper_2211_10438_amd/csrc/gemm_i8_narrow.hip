@@ -145,7 +145,14 @@ __global__ __launch_bounds__(kNarrowWaves * 64, 2) void gemm_i8_narrow_kernel(co
 // 6.3 / 6.6, 100 x 784 -> 768 7.5 / 13) or a few tokens (1 x 12288 -> 3072 15 / 21) only.
 bool sq_narrow_gemm_eligible(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled)
 {
-    if (batch != 1 || M < 1 || M > 128 || N >= 16 * 256) return false;  // (wider: the streaming kernel)
+    if (batch != 1 || M < 1 || M > 128) return false;
+    if (N >= 16 * 256) {
+        // The streaming kernel's: whole 16-channel units per workgroup, one workgroup per compute unit.  Between one and about
+        // 1.6 units per compute unit it deals two to some and leaves the others idle, and with up to 16 tokens this kernel
+        // is ahead: 20480 -> 5120 31 / 41 us, 5120 -> 5120 12.1 / 13.2-14 (at 9216 -> 9216, 2.25 units, 24 / 22).
+        const int64_t units = (N + 15) / 16;
+        return tiled && M <= 16 && units > 256 && units < 410;
+    }
     if (!tiled && M > 4) return K <= 1024 && N <= 3072;
     const double per_k = !tiled ? 0.80e-3 : M <= 16 ? 0.62e-3 : M <= 32 ? 0.85e-3 : M <= 64 ? 1.27e-3 : 2.0e-3;
     const double this_us = (tiled ? 3.6 : 5.0) + per_k * (double)K;

@@ -12,7 +12,9 @@ pytestmark = pytest.mark.gpu
 # (tokens, C_i, C_o); odd C_o, C_o off 16 and off 4, one K step, an odd number of steps, fewer pairs of steps than waves, a
 # K tail (row-major only)
 CASES = [(1, 16, 1), (2, 64, 8), (15, 128, 24), (16, 768, 3072), (17, 192, 100), (32, 1024, 772), (33, 1088, 16), (64, 960, 2048),
-         (65, 80, 333), (100, 784, 768), (128, 1008, 1030), (128, 3072, 512), (1, 5120, 4095), (4, 12288, 1024), (3, 2064, 3000)]
+         (65, 80, 333), (100, 784, 768), (128, 1008, 1030), (128, 3072, 512), (1, 5120, 4095), (4, 12288, 1024), (3, 2064, 3000),
+         # wider than one 16-channel unit per compute unit, up to 16 tokens: this kernel, then (17 tokens) the streaming one
+         (1, 2048, 5120), (16, 1088, 4112), (9, 512, 6544), (17, 1024, 5120)]
 
 
 def _tile(codes):

@@ -46,6 +46,23 @@ def test_per_tensor_edges(t, c_i, with_s, dtype):
     assert torch.equal(q, _codes(x, inv_s, _div(1.0, delta)))
 
 
+# few rows take one vector per thread (up to 256 rows, 2064 to 8192 channels), more rows longer threads
+@pytest.mark.parametrize("t,c_i", [(1, 2064), (256, 2080), (257, 2080), (2, 8192), (256, 8192), (257, 8192), (3, 8208), (5, 2048)])
+@pytest.mark.parametrize("with_s", [False, True])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_per_token_edges(t, c_i, with_s, dtype):
+    print(f"per-token {t}x{c_i} s={with_s} {dtype}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(t + c_i)
+    x = torch.randn((t, c_i), generator=g, device="cuda").to(dtype)
+    x[t - 1, c_i - 1] = 9.0
+    inv_s = torch.rand(c_i, generator=g, device="cuda") + 0.5 if with_s else None
+    v = x.float() if inv_s is None else x.float() * inv_s
+    a = v.abs().amax(1).cpu()
+    q, step = sq.quantize_act(x, sq.PER_TOKEN_DYNAMIC, inv_s=inv_s)
+    assert torch.equal(step.cpu(), a / torch.full_like(a, 127.0))
+    assert torch.equal(q, _codes(x, inv_s, (torch.full_like(a, 127.0) / a).cuda()[:, None]))
+
+
 # one row range and several (2048 rows each at least), channel counts that end inside a 64-channel column
 @pytest.mark.parametrize("t", [1, 31, 129, 2048, 2049, 9000])
 @pytest.mark.parametrize("c_i", [16, 64, 1040])
