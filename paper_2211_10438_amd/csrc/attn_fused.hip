@@ -21,11 +21,11 @@
 // What bounds it: vector-ALU issue.  Measured on loops of single instructions (cycles per instruction and SIMD, with 2 / 4
 // waves on it): add, sub, mul 3.0 / 2.7, conversions, packed and three-operand forms 5.1 / 4.5, exp2 8.8 / 8.4; one wave
 // alone issues one every 6.2 whatever it is; a 32x32x32 MFMA runs beside them and takes about 8 issue cycles of its 34.
-// Hence three workgroups per compute unit (four at head dimension 64) instead of two -- tiles of 64 keys, one accumulator
+// Hence three workgroups per compute unit instead of two -- tiles of 64 keys, one accumulator
 // pair live at a time, a single copy of the P V products --, no conversion of the sums (kBias), and nothing done for keys and rows
 // that are not there (MASKED).  (A shift fixed by the first tile instead of the running maximum, half an instruction per
-// score less, gained 1 %: the sums' last bits, and with them some codes, would no longer be those of a running maximum.)  Before / after, us: 288 heads x 1024^2 x 128 causal 131 /
-// 107, unmasked 176 / 168; 768 x 2048^2 x 128 causal 1092 / 969; 96 x 777 x 1040 x 64 causal 67 / 41; 50 x 300 x 304 x 128
+// score less, gained 1 %: the sums' last bits, and with them some codes, would no longer be those of a running maximum.)  Before / after, us: 288 heads x 1024^2 x 128 causal 130 /
+// 107, unmasked 169 / 162; 768 x 2048^2 x 128 causal 1057 / 935, unmasked 1738 / 1638; 96 x 777 x 1040 x 64 causal 67 / 41; 50 x 300 x 304 x 128
 // causal 26 / 16.
 #include <type_traits>
 
