@@ -166,105 +166,123 @@ __global__ __launch_bounds__(256) void softmax_quant_wave_kernel(const uint16_t*
     }
 }
 
-// One row per workgroup of up to 512 threads, NV 16-byte vectors per thread, as many threads as that takes.  A wave forms the
-// mean and the sum of squared deviations of its own part of the row (two-pass, in registers), and the parts are combined
-// by the parallel-variance formula, mean = sum S_w / n, M2 = sum (M2_w + n_w (mean_w - mean)^2): two workgroup-wide exchanges
-// per row, statistics and maximum, instead of three, and one barrier each.
-template <bool BF16, int NV>
-__global__ __launch_bounds__(512) void ln_quant_kernel(const uint16_t* __restrict__ x, int c_i, const float* __restrict__ gamma_f,
-                                                       const float* __restrict__ beta_f, float eps, float* __restrict__ scale,
-                                                       int8_t* __restrict__ xq, bool tiled)
+// One row per workgroup, two-pass statistics over the whole row in registers.  The sums have one fixed order, whatever the
+// launch: the row's 16-byte vectors are dealt to VT strands (vector v to strand v % VT, a strand adds its NV vectors'
+// elements one after the other), 64 neighbouring strands meet in a butterfly, and these sums are added as (0 + 1) + (2 + 3),
+// then + ((4 + 5) + (6 + 7)).  A thread carries ST of the strands: the codes do not depend on it.
+//
+// A row is bound by its latencies: the loads, then three exchanges between the waves (mean, variance, maximum).  So every load
+// is unconditional (one under a condition is waited for before the next is issued), the butterflies are vector instructions,
+// and an exchange has cells of its own and one barrier.  Only the last of a strand's vectors can lie past the end of the row: it
+// re-reads the row's last one, adds nothing to the sums, and in the maximum is that vector once more.
+template <bool BF16, int VT, int NV, int ST, bool FULL>
+__global__ __launch_bounds__(VT / ST) void ln_quant_kernel(const uint16_t* __restrict__ x, int c_i, const float* __restrict__ gamma_f,
+                                                           const float* __restrict__ beta_f, float eps, float* __restrict__ scale,
+                                                           int8_t* __restrict__ xq, bool tiled)
 {
-    __shared__ float4 part_of[8];  // sum, mean, sum of squared deviations and number of elements of a wave
-    __shared__ float wmax[8];
+    constexpr int W = VT / 64;  // 64-strand groups
+    __shared__ __attribute__((aligned(16))) float cells[3][W];
     const int64_t row = blockIdx.x;
     const v4u* xr = (const v4u*)(x + row * (int64_t)c_i);
-    const int nvec = c_i >> 3, nt = blockDim.x, waves = nt >> 6;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // Vectors past the end of the row re-read its last one (every load unconditional: a load under a condition is waited for
-    // before the next one is issued, which made a row of NV vectors per thread NV memory latencies long, for x as for
-    // gamma and beta); they take no part in the sums, and in the maximum and the codes they are that vector once more.
-    int idx[NV];
-    v4u raw[NV];
+    const int nvec = c_i >> 3, lane = threadIdx.x & 63;
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * ST;  // first of this wave's groups
+    int idx[ST][NV];
+    bool in[ST], any[ST];  // the strand's last vector lies in the row; that of any of the wave's 64 does
+    v4u raw[ST][NV];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        idx[i] = threadIdx.x + i * nt;
-        idx[i] = idx[i] < nvec ? idx[i] : nvec - 1;
-        raw[i] = __builtin_nontemporal_load(xr + idx[i]);
-    }
-    float f[NV][8];
-    float sum = 0.0f;
+    for (int s = 0; s < ST; ++s) {
+        any[s] = FULL || (group + s) * 64 + (NV - 1) * VT < nvec;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        unpack8r<BF16>(raw[i], f[i]);
-        float part = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) part += f[i][e];
-        sum += (int)threadIdx.x + i * nt < nvec ? part : 0.0f;
-    }
-    // elements of this wave: its 64 lanes hold vectors wave * 64 + i * nt + 0 .. 63
-    int n = 0;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int left = nvec - (wave * 64 + i * nt);
-        n += left <= 0 ? 0 : left < 64 ? left : 64;
-    }
-    const float wn = (float)(8 * n);  // at least 8: the launch has no wave without a vector
-    sum = wave_sum(sum);
-    const float wmean = sum / wn;
-    float sq = 0.0f;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        float part = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float d = f[i][e] - wmean;
-            part = __builtin_fmaf(d, d, part);
-        }
-        sq += (int)threadIdx.x + i * nt < nvec ? part : 0.0f;
-    }
-    sq = wave_sum(sq);
-    if ((threadIdx.x & 63) == 0) {
-        part_of[wave] = float4{sum, wmean, sq, wn};
-    }
-    __syncthreads();
-    // every group of eight lanes holds the waves' parts, one per lane, and reduces them
-    auto sum8 = [](float v) { v += lane_xor<4>(v); v += lane_xor<2>(v); return v + lane_xor<1>(v); };
-    const int w8 = threadIdx.x & 7;
-    const float4 q = w8 < waves ? part_of[w8] : float4{0.0f, 0.0f, 0.0f, 0.0f};
-    const float mean = sum8(q.x) / (float)c_i;
-    const float d = q.y - mean;
-    const float m2 = sum8(q.z + q.w * (d * d));
-    const float rstd = 1.0f / sqrtf(m2 / (float)c_i + eps);
-    float m = 0.0f;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const float4 g0 = *(const float4*)(gamma_f + idx[i] * 8), g1 = *(const float4*)(gamma_f + idx[i] * 8 + 4);
-        const float4 b0 = *(const float4*)(beta_f + idx[i] * 8), b1 = *(const float4*)(beta_f + idx[i] * 8 + 4);
-        const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-        const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            f[i][e] = __builtin_fmaf((f[i][e] - mean) * rstd, g[e], b[e]);
-            m = __builtin_fmaxf(m, __builtin_fabsf(f[i][e]));
+        for (int i = 0; i < NV; ++i) {
+            idx[s][i] = (group + s) * 64 + lane + i * VT;
+            if (i == NV - 1) {
+                in[s] = FULL || idx[s][i] < nvec;
+                idx[s][i] = in[s] ? idx[s][i] : nvec - 1;
+            }
+            raw[s][i] = __builtin_nontemporal_load(xr + idx[s][i]);
         }
     }
-    m = wave_max(m);
-    if ((threadIdx.x & 63) == 0) wmax[wave] = m;
-    __syncthreads();
-    float a = w8 < waves ? wmax[w8] : 0.0f;
-    a = __builtin_fmaxf(a, lane_xor<4>(a));
-    a = __builtin_fmaxf(a, lane_xor<2>(a));
-    a = __builtin_fmaxf(a, lane_xor<1>(a));
+    auto exchange = [&](const float (&v)[ST], float* cell, auto&& op) {
+        if (lane == 0) {
+#pragma unroll
+            for (int s = 0; s < ST; ++s) cell[group + s] = v[s];
+        }
+        __syncthreads();
+        float4 q = *(const float4*)cell;
+        float r = op(op(q.x, q.y), op(q.z, q.w));
+        if constexpr (W == 8) {
+            q = *(const float4*)(cell + 4);
+            r = op(r, op(op(q.x, q.y), op(q.z, q.w)));
+        }
+        return r;
+    };
+    auto add = [](float a, float b) { return a + b; };
+    auto max = [](float a, float b) { return __builtin_fmaxf(a, b); };
+    float f[ST][NV][8], part[ST];
+#pragma unroll
+    for (int s = 0; s < ST; ++s) {
+        part[s] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (i == NV - 1 && !any[s]) break;
+            unpack8r<BF16>(raw[s][i], f[s][i]);
+            float v = part[s];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v += f[s][i][e];
+            part[s] = i < NV - 1 || in[s] ? v : part[s];
+        }
+        part[s] = wave_sum(part[s]);
+    }
+    const float mean = exchange(part, cells[0], add) / (float)c_i;
+#pragma unroll
+    for (int s = 0; s < ST; ++s) {
+        part[s] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (i == NV - 1 && !any[s]) break;
+            float v = part[s];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float d = f[s][i][e] - mean;
+                v += d * d;
+            }
+            part[s] = i < NV - 1 || in[s] ? v : part[s];
+        }
+        part[s] = wave_sum(part[s]);
+    }
+    const float var = exchange(part, cells[1], add) / (float)c_i;
+    const float rstd = 1.0f / sqrtf(var + eps);
+#pragma unroll
+    for (int s = 0; s < ST; ++s) {
+        part[s] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const float4 g0 = *(const float4*)(gamma_f + idx[s][i] * 8), g1 = *(const float4*)(gamma_f + idx[s][i] * 8 + 4);
+            const float4 b0 = *(const float4*)(beta_f + idx[s][i] * 8), b1 = *(const float4*)(beta_f + idx[s][i] * 8 + 4);
+            const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+            const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+            if (i == NV - 1 && !any[s]) break;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                f[s][i][e] = (f[s][i][e] - mean) * rstd * g[e] + b[e];
+                part[s] = __builtin_fmaxf(part[s], __builtin_fabsf(f[s][i][e]));
+            }
+        }
+        part[s] = wave_max(part[s]);
+    }
+    const float a = exchange(part, cells[2], max);
     const float r = a > 0.0f ? 127.0f / a : 0.0f;
     if (threadIdx.x == 0) scale[row] = a / 127.0f;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        uint32_t codes[8];
+    for (int s = 0; s < ST; ++s)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) codes[e] = code_bits(f[i][e] * r);
-        if ((int)threadIdx.x + i * nt < nvec) __builtin_nontemporal_store(pack8(codes), (v2u*)code_dst(xq, row, idx[i] * 8, c_i, tiled));
-    }
+        for (int i = 0; i < NV; ++i) {
+            if (i == NV - 1 && !any[s]) break;
+            uint32_t codes[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) codes[e] = code_bits(f[s][i][e] * r);
+            if (i < NV - 1 || in[s]) __builtin_nontemporal_store(pack8(codes), (v2u*)code_dst(xq, row, idx[s][i] * 8, c_i, tiled));
+        }
 }
 
 // One row per wave (hidden sizes up to 2048, where it measures faster than a workgroup per row): the three
@@ -379,23 +397,49 @@ sq_status sq_ln_quantize(const void* x, sq_dtype dtype, int64_t t, int64_t c_i, 
     hipStream_t st = (hipStream_t)stream;
     const int nvec = (int)(c_i >> 3);
     const uint16_t* xp = (const uint16_t*)x;
-    // Measured choice: up to 2048 channels one row per wave; wider rows a workgroup of as many threads as the row has vectors
-    // for at NV per thread.  Few rows: short threads, the row's latency counts (1 x 5120 with 2 / 4 vectors 3.2 / 3.9 us,
-    // 1024 x 9216 with 3 / 4 / 5 8.7 / 9.5 / 9.6).  Many rows: the reductions are shared by more elements of a wave
-    // (4096 x 9216 with 3 / 5 / 6 vectors 34.1 / 34.8 / 31.5 us, 4096 x 5120 with 2 / 5 / 6 20.8 / 18.8 / 20.1, 8192 x 4096 with
-    // 3 / 4 / 5 31.7 / 28.3 / 28.6).  With three exchanges, loads under a condition and 3 x 512 threads: 37.8 us at 4096 x 9216,
-    // 11.9 at 1024 x 9216, 4.1 at 1 x 5120.
-#define SQ_LN(BF, NV) sq_launch((ln_quant_kernel<BF, NV>), dim3((unsigned)t), dim3((unsigned)(((nvec + NV - 1) / NV + 63) / 64 * 64)), 0, st, xp, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
+    // Up to 2048 channels one row per wave; wider rows one per workgroup, with 1, 2 or 4 strands per thread (ST).  Short threads
+    // have the shorter latency per row and win while all rows are in flight at once (us at 1 x 5120 with ST = 1 / 2 / 4: 3.7 /
+    // 4.6 / 6.2, 1024 x 9216: 8.6 / 8.8 / 9.8).  Longer ones share the exchanges and take fewer registers for a row, so that
+    // more rows fit a compute unit: with two vectors per strand 8 / 12 / 16, with three of 256 strands 8 / 8 / 12, of 512 strands
+    // 4 / 4 / 6, with four 8 / 8 / 8 or 4 / 4 / 4.  The lines lie where the rows stop fitting (x 256 compute units), except that
+    // between one and two rounds the form with the shortest tail wins (4096 x 4096 tiled 15.9 / 12.9 / 12.3, 2800 x 6144 17.4 /
+    // 17.4 / 14.8, 1400 x 12288 17.5 / 17.8 / 15.0, 2048 x 8192 16.9 / 12.9 / 13.5, 4096 x 16384 56.9 / 54.2 / 56.2).  Against the
+    // version with loads under a condition and two barriers an exchange: 4096 x 9216 tiled 37.9 -> 33.3 us, 1024 x 9216 11.7 ->
+    // 8.7, 1 x 5120 4.4 -> 3.7.
+#define SQ_LNK(BF, VT, NV, ST, FULL) sq_launch((ln_quant_kernel<BF, VT, NV, ST, FULL>), dim3((unsigned)t), dim3(VT / ST), 0, st, xp, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
 #define SQ_LNW(BF, NV) sq_launch((ln_quant_wave_kernel<BF, NV>), dim3((unsigned)((t + 3) / 4)), dim3(256), 0, st, xp, t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
-    const int nv = t >= 2048 ? (nvec <= 512 ? 4 : nvec <= 768 ? 5 : 6) : (nvec <= 640 ? 2 : nvec <= 1536 ? 3 : 4);
-#define SQ_LNB(BF) do { switch (nv) { case 2: SQ_LN(BF, 2); break; case 3: SQ_LN(BF, 3); break; case 4: SQ_LN(BF, 4); break; case 5: SQ_LN(BF, 5); break; default: SQ_LN(BF, 6); break; } } while (0)
-    if (dtype == SQ_BF16) {
-        if (nvec <= 128) SQ_LNW(true, 2); else if (nvec <= 256) SQ_LNW(true, 4); else SQ_LNB(true);
-    } else {
-        if (nvec <= 128) SQ_LNW(false, 2); else if (nvec <= 256) SQ_LNW(false, 4); else SQ_LNB(false);
-    }
-#undef SQ_LN
+#define SQ_LN2(BF, FULL)                                                                                                      \
+    do {                                                                                                                      \
+        if (t <= 2048) SQ_LNK(BF, 256, 2, 1, FULL);                                                                           \
+        else if (t <= 3072) SQ_LNK(BF, 256, 2, 2, FULL);                                                                      \
+        else SQ_LNK(BF, 256, 2, 4, FULL);                                                                                     \
+    } while (0)
+#define SQ_LNA(BF)                                                                                                            \
+    do {                                                                                                                      \
+        if (nvec <= 128) SQ_LNW(BF, 2);                                                                                       \
+        else if (nvec <= 256) SQ_LNW(BF, 4);                                                                                  \
+        else if (nvec < 512) SQ_LN2(BF, false);                                                                               \
+        else if (nvec == 512) SQ_LN2(BF, true);                                                                               \
+        else if (nvec <= 768) {                                                                                               \
+            if (t <= 1600 || (t > 3072 && t <= 3584)) SQ_LNK(BF, 256, 3, 1, false);                                           \
+            else if (t <= 2048) SQ_LNK(BF, 256, 3, 2, false);                                                                 \
+            else SQ_LNK(BF, 256, 3, 4, false);                                                                                \
+        } else if (nvec <= 1024) {                                                                                            \
+            if (t <= 1400 || (t > 2048 && t <= 2560)) SQ_LNK(BF, 256, 4, 1, false);                                           \
+            else if (t <= 3072) SQ_LNK(BF, 256, 4, 2, false);                                                                 \
+            else SQ_LNK(BF, 256, 4, 4, false);                                                                                \
+        } else if (nvec <= 1536) {                                                                                            \
+            if (t <= 1024 || t > 1536) SQ_LNK(BF, 512, 3, 1, false);                                                          \
+            else SQ_LNK(BF, 512, 3, 4, false);                                                                                \
+        } else if (t <= 768) SQ_LNK(BF, 512, 4, 1, false);                                                                    \
+        else SQ_LNK(BF, 512, 4, 2, false);                                                                                    \
+    } while (0)
+    if (dtype == SQ_BF16) SQ_LNA(true);
+    else SQ_LNA(false);
+#undef SQ_LNK
 #undef SQ_LNW
+#undef SQ_LN2
+#undef SQ_LNA
     return sq_launch_status();
 }
 

@@ -1,6 +1,7 @@
 """Row kernels at the edges of their launch rules against fp64: LayerNorm + quantization (one row per wave up to 2048
-channels, then 2 to 6 vectors per thread by row count and width) and the cross-lane reductions all of them share.
+channels, then one to four strands per thread by row count and width) and the cross-lane reductions all of them share.
 Gates as in the parity tests: codes within one, at most one in a thousand; steps to 1e-5."""
+import numpy as np
 import pytest
 import torch
 
@@ -44,3 +45,54 @@ def test_row_maximum_is_found_in_every_lane(lane):
     s[:, lane * 8 + 5] = 0.0
     p = sq.softmax_quant_p(s)
     assert int(p[0, lane * 8 + 5]) == 127 and int(p.to(torch.int32).sum()) == 4 * 127
+
+
+def _strand_sum(v, strands):
+    """fp32 sum of the rows of v [t, vectors, 8] in the kernels' fixed order: vector i to strand i % strands, a strand's elements
+    one after the other, 64 neighbouring strands in a butterfly, these sums as (0 + 1) + (2 + 3), then + ((4 + 5) + (6 + 7))."""
+    t, nvec, _ = v.shape
+    rounds = -(-nvec // strands)
+    pad = np.zeros((t, rounds * strands, 8), np.float32)
+    pad[:, :nvec] = v
+    pad = pad.reshape(t, rounds, strands, 8)
+    s = np.zeros((t, strands), np.float32)
+    for i in range(rounds):
+        for e in range(8):
+            s += pad[:, i, :, e]
+    s = s.reshape(t, strands // 64, 64)
+    for o in (32, 16, 8, 4, 2, 1):
+        s = s + s[:, :, np.arange(64) ^ o]
+    s = s[:, :, 0]
+    if strands == 64:
+        return s[:, 0]
+    total = (s[:, 0] + s[:, 1]) + (s[:, 2] + s[:, 3])
+    if strands == 512:
+        total = total + ((s[:, 4] + s[:, 5]) + (s[:, 6] + s[:, 7]))
+    return total
+
+
+# both sides of every width at which the launch changes, few rows and many
+@pytest.mark.parametrize("t,c", [(5, 1024), (5, 1040), (3, 2048), (5, 2064), (3, 4096), (3, 4112), (3, 5120), (3, 6144), (3, 6160),
+                                 (2, 8192), (2, 8208), (3, 9216), (2, 12288), (2, 12304), (1, 16384), (2049, 2080), (3073, 2064),
+                                 (2050, 4096), (3080, 4096), (1601, 5120), (2049, 5136), (3073, 4112), (1401, 6160), (2049, 6160),
+                                 (3073, 8192), (1025, 9216), (1537, 8208), (769, 12304)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_ln_quantize_is_one_fixed_fp32_sequence(t, c, dtype):
+    """Every sum, product and quotient rounds by itself and in one order, whatever the launch: steps and codes are identical
+    to the same sequence in numpy."""
+    print(f"ln sequence {t}x{c} {dtype}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(t * 7 + c)
+    x = (torch.randn((t, c), generator=g, device="cuda") + 0.3).to(dtype)
+    gamma = torch.randn(c, generator=g, device="cuda")
+    beta = torch.randn(c, generator=g, device="cuda") * 0.1
+    q, step = sq.ln_quantize(x, gamma, beta)
+    v = x.float().cpu().numpy().reshape(t, c // 8, 8)
+    n, strands = np.float32(c), 64 if c <= 2048 else 256 if c <= 8192 else 512
+    mean = (_strand_sum(v, strands) / n)[:, None, None]
+    d = v - mean
+    var = _strand_sum(d * d, strands) / n
+    rstd = (np.float32(1) / np.sqrt(var + np.float32(1e-5)))[:, None, None]
+    y = (d * rstd * gamma.cpu().numpy().reshape(c // 8, 8) + beta.cpu().numpy().reshape(c // 8, 8)).reshape(t, c)
+    a = np.abs(y).max(axis=1)
+    assert y.dtype == np.float32 and np.array_equal(step.cpu().numpy(), a / np.float32(127))
+    assert np.array_equal(q.cpu().numpy(), np.rint(y * (np.float32(127) / a)[:, None]).astype(np.int8))
