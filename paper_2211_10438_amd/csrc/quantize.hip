@@ -465,12 +465,13 @@ __global__ __launch_bounds__(256) void quant_per_tensor_single_kernel(const uint
 constexpr int kChannelRows = 32;
 template <bool BF16>
 __global__ __launch_bounds__(256) void act_absmax_per_channel_kernel(const uint16_t* __restrict__ x, int c_i, int64_t t, int64_t rows_per_wg,
-                                                                    uint32_t* out_bits)
+                                                                    uint32_t* out_bits, int first)
 {
     __shared__ float red[4][64];
     const int nvec = c_i >> 3;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int idx = blockIdx.x * 8 + (threadIdx.x & 7);
+    const int col = first + (int)blockIdx.x;  // 64-channel column
+    const int idx = col * 8 + (threadIdx.x & 7);
     const int64_t r0 = (int64_t)blockIdx.y * rows_per_wg, r1 = r0 + rows_per_wg < t ? r0 + rows_per_wg : t;
     float m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (idx < nvec) {
@@ -499,7 +500,7 @@ __global__ __launch_bounds__(256) void act_absmax_per_channel_kernel(const uint1
         for (int e = 0; e < 8; ++e) red[wave][lane * 8 + e] = m[e];
     }
     __syncthreads();
-    const int c = blockIdx.x * 64 + threadIdx.x;
+    const int64_t c = (int64_t)col * 64 + threadIdx.x;
     if (threadIdx.x < 64 && c < c_i) {
         const float v = __builtin_fmaxf(__builtin_fmaxf(red[0][threadIdx.x], red[1][threadIdx.x]),
                                         __builtin_fmaxf(red[2][threadIdx.x], red[3][threadIdx.x]));
@@ -678,9 +679,12 @@ sq_status sq_act_absmax_per_channel(const void* x, sq_dtype dtype, int64_t t, in
     const int64_t per = (t + ranges - 1) / ranges;
     ranges = (t + per - 1) / per;
     if (ranges > 1) sq_launch(fill_u32_kernel, dim3((unsigned)((c_i + 255) / 256)), dim3(256), 0, st, (uint32_t*)out, 0u, (int)c_i);
-    const dim3 grid((unsigned)cols, (unsigned)ranges);
-    if (dtype == SQ_BF16) sq_launch(act_absmax_per_channel_kernel<true>, grid, dim3(256), 0, st, (const uint16_t*)x, (int)c_i, t, per, (uint32_t*)out);
-    else sq_launch(act_absmax_per_channel_kernel<false>, grid, dim3(256), 0, st, (const uint16_t*)x, (int)c_i, t, per, (uint32_t*)out);
+    constexpr int64_t most = 1 << 23;  // columns per launch: a grid stays below 2^32 threads
+    for (int64_t first = 0; first < cols; first += most) {
+        const dim3 grid((unsigned)(cols - first < most ? cols - first : most), (unsigned)ranges);
+        if (dtype == SQ_BF16) sq_launch(act_absmax_per_channel_kernel<true>, grid, dim3(256), 0, st, (const uint16_t*)x, (int)c_i, t, per, (uint32_t*)out, (int)first);
+        else sq_launch(act_absmax_per_channel_kernel<false>, grid, dim3(256), 0, st, (const uint16_t*)x, (int)c_i, t, per, (uint32_t*)out, (int)first);
+    }
     return sq_launch_status();
 }
 

@@ -101,3 +101,14 @@ def test_weight_preparation_edges(c_i, c_o, per_channel, with_s, dtype):
             wq = flat[torch.from_numpy(tiled_index(c_o, c_i)).cuda()]
         assert torch.equal(wq, codes)
     assert torch.equal(sq.weight_absmax_per_in_channel(w), w.float().abs().amax(1))
+
+
+def test_channel_maxima_of_a_row_longer_than_one_grid():
+    """2^30 channels and a few: a workgroup per 64 channels would be 2^24 workgroups of 256 threads, more than a launch takes."""
+    print("channel maxima of one very long row", flush=True)
+    c_i = (1 << 30) + 48
+    x = torch.zeros((1, c_i), dtype=torch.float16, device="cuda")
+    x[0, ::4099] = -3.0
+    x[0, -1] = 5.0
+    out = sq.act_absmax_per_channel(x)
+    assert float(out[-1]) == 5.0 and torch.equal(out.half(), x[0].abs())
