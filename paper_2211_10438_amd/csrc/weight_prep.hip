@@ -14,26 +14,28 @@ template <bool BF16> SQ_DEVICE void unpack8w(const v4u raw, float (&f)[8])
     }
 }
 
-// Maxima over rows of W: one row (input channel j) per wave, four 16-byte loads per lane in flight.  ROWS: row_out[j] =
+// Maxima over rows of W: one row (input channel j) per WPR waves, four 16-byte loads per lane in flight.  ROWS: row_out[j] =
 // max_n |W_jn|.  Otherwise the maximum over the tensor, each row scaled by s_j: a wave keeps it over all its rows and
 // adds it to tensor_bits with one atomic (the integer order of the bit patterns of non-negative floats is the float order);
 // one atomic per row on that single cell, some 12 ns each, was the longest part of a narrow weight's preparation.
-template <bool BF16, bool ROWS>
+template <bool BF16, bool ROWS, int WPR>
 __global__ __launch_bounds__(256) void weight_row_absmax_kernel(const uint16_t* __restrict__ w, int c_i, int c_o,
                                                                const float* __restrict__ s, float* row_out,
                                                                uint32_t* tensor_bits)
 {
-    const int lane = threadIdx.x & 63;
+    constexpr int RPW = 4 / WPR, NT = WPR * 64;  // rows per workgroup, threads per row
+    __shared__ float red[4];
+    const int lane = threadIdx.x & 63, tid = threadIdx.x & (NT - 1);
     const int nvec = c_o >> 3;
     float all = 0.0f;
-    for (int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); j < c_i; j += (int64_t)gridDim.x * 4) {
+    for (int64_t j = (int64_t)blockIdx.x * RPW + threadIdx.x / NT; j < c_i; j += (int64_t)gridDim.x * RPW) {
         const v4u* wr = (const v4u*)(w + j * c_o);
         const float sj = s ? s[j] : 1.0f;
         float m = 0.0f;
-        for (int i0 = lane; i0 < nvec; i0 += 256) {
+        for (int i0 = tid; i0 < nvec; i0 += 4 * NT) {
             v4u raw[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) raw[i] = wr[i0 + i * 64 < nvec ? i0 + i * 64 : i0];  // past the end: the first one again
+            for (int i = 0; i < 4; ++i) raw[i] = wr[i0 + i * NT < nvec ? i0 + i * NT : i0];  // past the end: the first one again
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float f[8];
@@ -44,13 +46,18 @@ __global__ __launch_bounds__(256) void weight_row_absmax_kernel(const uint16_t* 
         }
         if constexpr (ROWS) {
             m = wave_max(m);
-            if (lane == 0) row_out[j] = m;
+            if constexpr (WPR == 4) {
+                __syncthreads();  // (the loop's trips are the same for the whole workgroup)
+                if (lane == 0) red[threadIdx.x >> 6] = m;
+                __syncthreads();
+                m = __builtin_fmaxf(__builtin_fmaxf(red[0], red[1]), __builtin_fmaxf(red[2], red[3]));
+            }
+            if (tid == 0) row_out[j] = m;
         } else {
             all = __builtin_fmaxf(all, m);
         }
     }
     if constexpr (!ROWS) {
-        __shared__ float red[4];
         all = wave_max(all);
         if (lane == 0) red[threadIdx.x >> 6] = all;
         __syncthreads();
@@ -189,6 +196,26 @@ __global__ __launch_bounds__(256) void weight_quant_transpose_kernel(const uint1
     }
 }
 
+// One wave per row, except where that leaves SIMDs without a wave and the rows are long enough for four (us, one wave / four
+// waves per row): statistic of 64 x 20480 5.3 / 3.4, 256 x 12288 4.2 / 3.2, 768 x 20480 8.1 / 7.3, 1024 x 50272 23.1 / 18.1,
+// but 768 x 4096 3.0 / 3.3, 1536 x 12288 7.7 / 8.0.  With the tensor's maximum every workgroup ends in an atomic on one cell, and
+// the line lies lower (whole preparation): 256 x 20480 18.2 / 15.8, 64 x 50272 24.8 / 14.9, but 256 x 8192 12.3 / 13.4, 768 x
+// 20480 24.4 / 28.9.
+template <bool ROWS>
+void launch_row_absmax(const uint16_t* w, sq_dtype dtype, int c_i, int c_o, const float* s, float* row_out, uint32_t* tensor_bits, hipStream_t st)
+{
+    const bool wide = ROWS ? c_i <= 1024 && c_o > 4096 : c_i <= 256 && c_o > 16384;
+    const int64_t need = wide ? c_i : ((int64_t)c_i + 3) / 4, cap = ROWS ? 65535 : 512;  // (the kernel strides over the rest)
+    const dim3 grid((unsigned)(need < cap ? need : cap));
+#define SQ_ROW(BF, WPR) sq_launch((weight_row_absmax_kernel<BF, ROWS, WPR>), grid, dim3(256), 0, st, w, c_i, c_o, s, row_out, tensor_bits)
+    if (dtype == SQ_BF16) {
+        if (wide) SQ_ROW(true, 4); else SQ_ROW(true, 1);
+    } else {
+        if (wide) SQ_ROW(false, 4); else SQ_ROW(false, 1);
+    }
+#undef SQ_ROW
+}
+
 }  // namespace
 
 extern "C" {
@@ -200,11 +227,7 @@ sq_status sq_weight_absmax_per_in_channel(const void* w, sq_dtype dtype, int64_t
     if (c_i <= 0 || c_o <= 0 || c_i >= ((int64_t)1 << 31) || c_o >= ((int64_t)1 << 31)) return SQ_ERR_SHAPE;
     if (dtype != SQ_F16 && dtype != SQ_BF16) return SQ_ERR_UNSUPPORTED;
     if ((c_o & 7) || !sq_aligned16(w)) return SQ_ERR_ALIGN;
-    const unsigned grid = (unsigned)((c_i + 3) / 4);
-    if (dtype == SQ_BF16)
-        sq_launch((weight_row_absmax_kernel<true, true>), dim3(grid), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)w, (int)c_i, (int)c_o, (const float*)nullptr, out, (uint32_t*)nullptr);
-    else
-        sq_launch((weight_row_absmax_kernel<false, true>), dim3(grid), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)w, (int)c_i, (int)c_o, (const float*)nullptr, out, (uint32_t*)nullptr);
+    launch_row_absmax<true>((const uint16_t*)w, dtype, (int)c_i, (int)c_o, nullptr, out, nullptr, (hipStream_t)stream);
     return sq_launch_status();
 }
 
@@ -226,7 +249,6 @@ sq_status sq_prepare_weight(const void* w, sq_dtype dtype, const float* s, int64
     uint32_t* amax = (uint32_t*)workspace;
     const int64_t ncell = pc ? c_o : 1;
     sq_launch(zero_u32_kernel, dim3((unsigned)((ncell + 255) / 256 < 1024 ? (ncell + 255) / 256 : 1024)), dim3(256), 0, st, amax, ncell);
-    const unsigned grid1 = (unsigned)(c_i < 2048 ? (c_i + 3) / 4 : 512);
     // about four workgroups per compute unit, slabs of at least 64 rows (each slab costs an atomic per column)
     const int64_t colb = (c_o / 8 + 63) / 64;
     int64_t slabs = (1024 + colb - 1) / colb;
@@ -236,11 +258,11 @@ sq_status sq_prepare_weight(const void* w, sq_dtype dtype, const float* s, int64
     const dim3 grid2((unsigned)((c_o + 127) / 128), (unsigned)((c_i + 255) / 256));
     if (dtype == SQ_BF16) {
         if (pc) sq_launch(weight_col_absmax_kernel<true>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, rows, amax);
-        else sq_launch((weight_row_absmax_kernel<true, false>), dim3(grid1), dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, (float*)nullptr, amax);
+        else launch_row_absmax<false>((const uint16_t*)w, dtype, (int)c_i, (int)c_o, s, nullptr, amax, st);
         sq_launch(weight_quant_transpose_kernel<true>, grid2, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax, w_scale, wq, tiled, pc);
     } else {
         if (pc) sq_launch(weight_col_absmax_kernel<false>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, rows, amax);
-        else sq_launch((weight_row_absmax_kernel<false, false>), dim3(grid1), dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, (float*)nullptr, amax);
+        else launch_row_absmax<false>((const uint16_t*)w, dtype, (int)c_i, (int)c_o, s, nullptr, amax, st);
         sq_launch(weight_quant_transpose_kernel<false>, grid2, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax, w_scale, wq, tiled, pc);
     }
     return sq_launch_status();

@@ -112,3 +112,29 @@ def test_channel_maxima_of_a_row_longer_than_one_grid():
     x[0, -1] = 5.0
     out = sq.act_absmax_per_channel(x)
     assert float(out[-1]) == 5.0 and torch.equal(out.half(), x[0].abs())
+
+
+def test_weight_maxima_of_more_rows_than_one_grid():
+    """2^26 rows and a few: one per wave would be 2^24 workgroups of 256 threads, more than a launch takes."""
+    print("weight maxima of very many rows", flush=True)
+    c_i = (1 << 26) + 5
+    w = torch.zeros((c_i, 8), dtype=torch.float16, device="cuda")
+    w[::4099, 3] = -3.0
+    w[-1, 7] = 5.0
+    out = sq.weight_absmax_per_in_channel(w)
+    assert float(out[-1]) == 5.0 and torch.equal(out.half(), w.abs().amax(1))
+
+
+# one wave per row, four waves per row (few long rows; another line with the tensor's maximum), rows on both sides of each
+@pytest.mark.parametrize("c_i,c_o", [(16, 4096), (16, 4104), (1024, 4104), (1040, 4104), (48, 8200), (256, 16384), (256, 16392), (272, 16392)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_weight_row_maxima_edges(c_i, c_o, dtype):
+    print(f"weight row maxima {c_i}x{c_o} {dtype}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(c_i + c_o)
+    w = (torch.randn((c_i, c_o), generator=g, device="cuda") * 0.02).to(dtype)
+    w[c_i - 1, c_o - 1] = -0.5
+    w[0, 0] = 0.4
+    s = torch.rand(c_i, generator=g, device="cuda") + 0.5
+    assert torch.equal(sq.weight_absmax_per_in_channel(w), w.float().abs().amax(1))
+    _, step = sq.prepare_weight(w, s)
+    assert torch.equal(step, _div((w.float() * s[:, None]).abs().max(), 127.0))
