@@ -117,7 +117,7 @@ def _stream():
     return _raw_stream(_raw_device())
 
 
-@functools.lru_cache(maxsize=4096)
+@functools.lru_cache(maxsize=4096, typed=True)  # typed: 16.0 is refused also where 16 is known
 def workspace_bytes(op: int, t: int, c_i: int, c_o: int) -> int:
     return int(lib().sq_workspace_bytes(op, t, c_i, c_o))
 

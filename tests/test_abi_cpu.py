@@ -171,3 +171,12 @@ def test_fused_attention_argument_errors_before_any_launch():
     assert L.sq_w8a8_attention_causal(*args(s_k=100)) == 3
     assert L.sq_w8a8_attention_causal(*args(d=96)) == 4
     assert L.sq_w8a8_attention_causal(*args(s_k=48)) == 2  # 64 queries, 48 keys: the first queries would see no key
+
+
+def test_workspace_bytes_takes_whole_numbers_only_whatever_was_asked_before():
+    sizes = (16, 12288, 1536)
+    assert sq.workspace_bytes(sq.OP_W8A8_LINEAR, *sizes) > 0
+    for i in range(3):
+        wrong = [float(v) if i == j else v for j, v in enumerate(sizes)]
+        with pytest.raises(ctypes.ArgumentError):
+            sq.workspace_bytes(sq.OP_W8A8_LINEAR, *wrong)
