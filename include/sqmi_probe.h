@@ -1,6 +1,7 @@
 /*
  * sqmi -- measurement aids of the library, NOT part of the method's boundary (that is sqmi.h).
- * bench.py uses them to report kernels against what the hardware sustains.
+ * bench.py uses them to report kernels against what the hardware sustains, the tests to reach a kernel whatever the
+ * library's choice of kernel for a shape is.
  */
 #ifndef SQMI_PROBE_H
 #define SQMI_PROBE_H
@@ -17,6 +18,17 @@ extern "C" {
  * workgroups * 49152 bytes: the bit patterns matter, the sustained clock depends on them); sink: device int32
  * [workgroups * 512], overwritten.  bench.py times it to report the GEMM against what the matrix pipes sustain. */
 sq_status sq_probe_mfma_i8(const int8_t* data, size_t data_bytes, int workgroups, int iters, int32_t* sink, void* stream);
+
+/* The form of the fused attention kernel that sq_w8a8_attention (causal != 0: sq_w8a8_attention_causal) takes for these
+ * sizes: 1 = row blocks of 128 queries, 2 = few queries (blocks of 16); 0 for sizes it refuses.  No GPU work. */
+int sq_probe_attention_form(int64_t b, int64_t s_q, int64_t s_k, int64_t d, int causal);
+
+/* sq_w8a8_attention / _causal in the form named (1 or 2, else SQ_ERR_UNSUPPORTED; 2 also where that form cannot hold the
+ * scores, s_k > 8192).  Other arguments, checks and results are theirs. */
+sq_status sq_probe_attention(int form, int causal, const int8_t* q, const int8_t* k, const int8_t* v, float alpha1,
+                             float alpha2, void* o, sq_dtype out, int64_t b, int64_t s_q, int64_t s_k, int64_t d,
+                             int64_t stride_q, int64_t stride_k, int64_t stride_v, int64_t stride_o, int8_t* p_codes,
+                             void* stream);
 
 #ifdef __cplusplus
 }

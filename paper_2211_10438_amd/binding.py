@@ -26,6 +26,7 @@ EXPORTS = (
     "sq_prepare_weight", "sq_quantize_act", "sq_w8a8_linear", "sq_w8a8_linear_q8", "sq_i8_gemm_i32", "sq_w8a8_bmm",
     "sq_softmax_quant_p", "sq_ln_quantize", "sq_workspace_bytes", "sq_tiled_bytes", "sq_probe_mfma_i8",
     "sq_w8a8_linear_noalloc", "sq_static_scratch_bytes", "sq_w8a8_attention", "sq_w8a8_attention_causal",
+    "sq_probe_attention", "sq_probe_attention_form",
 )
 
 
@@ -63,6 +64,8 @@ def lib() -> ctypes.CDLL:
         L.sq_w8a8_attention.argtypes = [vp, vp, vp, f32, f32, vp, i32, i64, i64, i64, i64, i64, i64, i64, i64, vp, vp]
         L.sq_w8a8_attention_causal.argtypes = L.sq_w8a8_attention.argtypes
         L.sq_probe_mfma_i8.argtypes = [vp, ctypes.c_size_t, i32, i32, vp, vp]
+        L.sq_probe_attention.argtypes = [i32, i32, *L.sq_w8a8_attention.argtypes]
+        L.sq_probe_attention_form.argtypes = [i64, i64, i64, i64, i32]
         L.sq_softmax_quant_p.argtypes = [vp, i32, i64, i64, vp, vp]
         L.sq_ln_quantize.argtypes = [vp, i32, i64, i64, vp, vp, f32, vp, vp, i32, vp]
         L.sq_workspace_bytes.restype = ctypes.c_size_t
@@ -325,6 +328,18 @@ def w8a8_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, alpha1: fl
     _check(fn(_dev(q, torch.int8, "q"), _dev(k, torch.int8, "k"), _dev(v, torch.int8, "v"), alpha1, alpha2,
               _dev(o, out_dtype, "o"), _dt(o), b, s_q, s_k, d, s_q * d, s_k * d, s_k * d, s_q * d,
               _opt(p_codes, torch.int8, "p_codes"), _stream()), "sq_w8a8_attention_causal" if causal else "sq_w8a8_attention")
+    return o
+
+
+def probe_attention(form: int, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, alpha1: float, alpha2: float, out_dtype,
+                    p_codes: torch.Tensor | None = None, causal: bool = False) -> torch.Tensor:
+    """w8a8_attention in the form named (1 row blocks of 128 queries, 2 few queries), whatever the library would choose."""
+    b, s_q, d = q.shape
+    s_k = k.shape[1]
+    o = torch.empty((b, s_q, d), dtype=out_dtype, device=q.device)
+    _check(lib().sq_probe_attention(form, int(causal), _dev(q, torch.int8, "q"), _dev(k, torch.int8, "k"), _dev(v, torch.int8, "v"),
+                                    alpha1, alpha2, _dev(o), _dt(o), b, s_q, s_k, d, s_q * d, s_k * d, s_k * d, s_q * d,
+                                    _opt(p_codes, torch.int8, "p_codes"), _stream()), "sq_probe_attention")
     return o
 
 

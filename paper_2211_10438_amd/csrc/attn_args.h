@@ -41,6 +41,7 @@ template <bool BF16> SQ_DEVICE int prob_codes4(uint32_t ph01, uint32_t ph23)
     }
 }
 
-// Few queries over many keys (attn_few.hip).
+// Few queries over many keys (attn_few.hip): whether its registers and grid take a call at all, and whether it is the faster form.
+bool sq_attn_few_possible(int64_t batch, int64_t s_q, int64_t s_k);
 bool sq_attn_few_eligible(int64_t batch, int64_t s_q, int64_t s_k, int64_t d, bool causal);
 void sq_attn_few_launch(AttnArgs a, int64_t batch, int64_t d, bool bf16, bool causal, hipStream_t st);

@@ -309,6 +309,11 @@ constexpr int kFewKeys = 8 * 8 * 128;  // what the registers of eight waves hold
 
 }  // namespace
 
+bool sq_attn_few_possible(int64_t batch, int64_t s_q, int64_t s_k)
+{
+    return s_k <= kFewKeys && (double)batch * (double)((s_q + 15) / 16) < (1 << 22);  // (a grid stays below 2^32 threads)
+}
+
 // Which of the two forms: rounds of workgroups times the time of one, in microseconds, for both.  This form's 16-row blocks
 // fill the chip early and finish early, but each reads K and V once more, out of L2; the row-block form computes 128 rows per
 // workgroup whatever s_q is.  Fitted to ninety shapes between 12 x 16 x 64 and 700 x 1900 x 1900 queries and keys; choosing by
@@ -318,7 +323,7 @@ constexpr int kFewKeys = 8 * 8 * 128;  // what the registers of eight waves hold
 bool sq_attn_few_eligible(int64_t batch, int64_t s_q, int64_t s_k, int64_t d, bool causal)
 {
     const double few_wg = (double)batch * ((s_q + 15) / 16), row_wg = (double)batch * ((s_q + 127) / 128);
-    if (s_k > kFewKeys || few_wg >= (1 << 22)) return false;  // (registers; a grid stays below 2^32 threads)
+    if (!sq_attn_few_possible(batch, s_q, s_k)) return false;
     const double keys = causal ? (double)s_k - 0.5 * (double)(s_q - 1) : (double)s_k;  // a query sees on average
     const double few_rounds = few_wg / (d == 64 ? 768.0 : 640.0), row_rounds = row_wg / 384.0;
     const double few_us = (few_rounds > 1.0 ? few_rounds : 1.0) * (d == 64 ? 6.0 + 0.006 * keys : 7.0 + 0.014 * keys);

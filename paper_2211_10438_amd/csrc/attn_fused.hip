@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "attn_args.h"
+#include "sqmi_probe.h"
 
 namespace {
 
@@ -405,7 +406,8 @@ static int attn_chunk(int64_t b, int64_t s_k, int64_t d)
     return (int)((heads + n - 1) / n);
 }
 
-static sq_status attention(const int8_t* q, const int8_t* k, const int8_t* v, float alpha1, float alpha2, void* o,
+// form: 0 by sq_attn_few_eligible, 1 row blocks, 2 few queries
+static sq_status attention(int form, const int8_t* q, const int8_t* k, const int8_t* v, float alpha1, float alpha2, void* o,
                            sq_dtype out, int64_t b, int64_t s_q, int64_t s_k, int64_t d, int64_t stride_q,
                            int64_t stride_k, int64_t stride_v, int64_t stride_o, int8_t* p_codes, void* stream, bool causal)
 {
@@ -430,7 +432,9 @@ static sq_status attention(const int8_t* q, const int8_t* k, const int8_t* v, fl
     a.stride_q = stride_q; a.stride_k = stride_k; a.stride_v = stride_v; a.stride_o = stride_o;
     a.alpha1 = alpha1; a.alpha2 = alpha2;
     hipStream_t st = (hipStream_t)stream;
-    if (sq_attn_few_eligible(b, s_q, s_k, d, causal)) {
+    if (form == 0) form = sq_attn_few_eligible(b, s_q, s_k, d, causal) ? 2 : 1;
+    if (form == 2) {
+        if (!sq_attn_few_possible(b, s_q, s_k)) return SQ_ERR_UNSUPPORTED;
         sq_attn_few_launch(a, b, d, out == SQ_BF16, causal, st);
         return sq_launch_status();
     }
@@ -463,12 +467,27 @@ extern "C" sq_status sq_w8a8_attention(const int8_t* q, const int8_t* k, const i
                                        sq_dtype out, int64_t b, int64_t s_q, int64_t s_k, int64_t d, int64_t stride_q,
                                        int64_t stride_k, int64_t stride_v, int64_t stride_o, int8_t* p_codes, void* stream)
 {
-    return attention(q, k, v, alpha1, alpha2, o, out, b, s_q, s_k, d, stride_q, stride_k, stride_v, stride_o, p_codes, stream, false);
+    return attention(0, q, k, v, alpha1, alpha2, o, out, b, s_q, s_k, d, stride_q, stride_k, stride_v, stride_o, p_codes, stream, false);
 }
 
 extern "C" sq_status sq_w8a8_attention_causal(const int8_t* q, const int8_t* k, const int8_t* v, float alpha1, float alpha2, void* o,
                                               sq_dtype out, int64_t b, int64_t s_q, int64_t s_k, int64_t d, int64_t stride_q,
                                               int64_t stride_k, int64_t stride_v, int64_t stride_o, int8_t* p_codes, void* stream)
 {
-    return attention(q, k, v, alpha1, alpha2, o, out, b, s_q, s_k, d, stride_q, stride_k, stride_v, stride_o, p_codes, stream, true);
+    return attention(0, q, k, v, alpha1, alpha2, o, out, b, s_q, s_k, d, stride_q, stride_k, stride_v, stride_o, p_codes, stream, true);
+}
+
+extern "C" int sq_probe_attention_form(int64_t b, int64_t s_q, int64_t s_k, int64_t d, int causal)
+{
+    if (b <= 0 || s_q <= 0 || s_k <= 0 || (d != 64 && d != 128)) return 0;
+    return sq_attn_few_eligible(b, s_q, s_k, d, causal != 0) ? 2 : 1;
+}
+
+extern "C" sq_status sq_probe_attention(int form, int causal, const int8_t* q, const int8_t* k, const int8_t* v, float alpha1,
+                                        float alpha2, void* o, sq_dtype out, int64_t b, int64_t s_q, int64_t s_k, int64_t d,
+                                        int64_t stride_q, int64_t stride_k, int64_t stride_v, int64_t stride_o, int8_t* p_codes,
+                                        void* stream)
+{
+    if (form != 1 && form != 2) return SQ_ERR_UNSUPPORTED;
+    return attention(form, q, k, v, alpha1, alpha2, o, out, b, s_q, s_k, d, stride_q, stride_k, stride_v, stride_o, p_codes, stream, causal != 0);
 }
