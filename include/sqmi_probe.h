@@ -23,6 +23,10 @@ sq_status sq_probe_mfma_i8(const int8_t* data, size_t data_bytes, int workgroups
  * sizes: 1 = row blocks of 128 queries, 2 = few queries (blocks of 16); 0 for sizes it refuses.  No GPU work. */
 int sq_probe_attention_form(int64_t b, int64_t s_q, int64_t s_k, int64_t d, int causal);
 
+/* The row block (of 128 queries) that workgroup `block` of the row-block form works on under the causal mask, its head in
+ * *head; below 0 past the launch's last workgroup.  Workgroups go round-robin to the 8 XCDs.  No GPU work. */
+int sq_probe_attention_place(int64_t block, int64_t b, int64_t s_q, int64_t s_k, int64_t d, int64_t* head);
+
 /* sq_w8a8_attention / _causal in the form named (1 or 2, else SQ_ERR_UNSUPPORTED; 2 also where that form cannot hold the
  * scores, s_k > 8192).  Other arguments, checks and results are theirs. */
 sq_status sq_probe_attention(int form, int causal, const int8_t* q, const int8_t* k, const int8_t* v, float alpha1,

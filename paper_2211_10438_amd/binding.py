@@ -26,7 +26,7 @@ EXPORTS = (
     "sq_prepare_weight", "sq_quantize_act", "sq_w8a8_linear", "sq_w8a8_linear_q8", "sq_i8_gemm_i32", "sq_w8a8_bmm",
     "sq_softmax_quant_p", "sq_ln_quantize", "sq_workspace_bytes", "sq_tiled_bytes", "sq_probe_mfma_i8",
     "sq_w8a8_linear_noalloc", "sq_static_scratch_bytes", "sq_w8a8_attention", "sq_w8a8_attention_causal",
-    "sq_probe_attention", "sq_probe_attention_form",
+    "sq_probe_attention", "sq_probe_attention_form", "sq_probe_attention_place",
 )
 
 
@@ -66,6 +66,7 @@ def lib() -> ctypes.CDLL:
         L.sq_probe_mfma_i8.argtypes = [vp, ctypes.c_size_t, i32, i32, vp, vp]
         L.sq_probe_attention.argtypes = [i32, i32, *L.sq_w8a8_attention.argtypes]
         L.sq_probe_attention_form.argtypes = [i64, i64, i64, i64, i32]
+        L.sq_probe_attention_place.argtypes = [i64, i64, i64, i64, i64, ctypes.POINTER(i64)]
         L.sq_softmax_quant_p.argtypes = [vp, i32, i64, i64, vp, vp]
         L.sq_ln_quantize.argtypes = [vp, i32, i64, i64, vp, vp, f32, vp, vp, i32, vp]
         L.sq_workspace_bytes.restype = ctypes.c_size_t

@@ -17,6 +17,55 @@ struct AttnArgs {
 
 constexpr float kLog2e = 1.44269504088896340736f;
 
+struct AttnPlace {
+    int64_t batch;
+    int tile;  // row block
+};
+// Causal row-block form: what workgroup `block` works on.  Block t of a head sees t + 1 of the key tiles (the last queries every
+// key), and consecutive workgroup ids go round-robin to the 8 XCDs, there to the next of 32 compute units.
+//  * Longest first: the workgroups that start last decide when the launch ends.
+//  * Whole heads go to the XCDs as far as they divide (XCD x: the heads x, x + 8, ..., `chunk` of them at a time, so that their K
+//    and V stay in its L2).  The one to seven heads left over are dealt block by block, or XCDs would idle (1 x 32768^2 x 128 with
+//    its head on one XCD 2037 us, dealt 867): eight ranks of them, then the same eight ranks of the whole heads, and so on.
+//    With several chunks they come first.
+//  * Where all workgroups are resident at once (three per compute unit) nothing balances them later: every second round over
+//    the compute units runs backwards, so that a long block shares its unit with a short one.
+__host__ __device__ __forceinline__ AttnPlace attn_causal_place(uint32_t block, uint32_t batch, uint32_t tiles, uint32_t chunk)
+{
+    const uint32_t xcd = block & 7, whole = batch >> 3, rest = batch & 7;
+    uint32_t j = block >> 3;
+    const uint32_t n = (batch * tiles + 7 - xcd) >> 3;  // workgroups of this XCD
+    if (n <= 96 && (j & 32)) {
+        const uint32_t lo = j & ~31u, hi = lo + 32 < n ? lo + 32 : n;
+        j = lo + (hi - 1 - j);
+    }
+    const bool merge = rest && chunk >= whole;
+    uint32_t rank0 = 0, ranks = tiles;  // the ranks to deal the left over heads' blocks of
+    if (merge) {
+        const uint32_t q = j / batch, full = tiles >> 3, p = q < full ? q : full;
+        j -= p * batch;
+        rank0 = 8 * p;
+        ranks = q < full ? 8 : tiles - rank0;
+    }
+    if (rest) {
+        const uint32_t mine = (rest * ranks + 7 - xcd) >> 3;
+        if (j < mine) {
+            const uint32_t f = j * 8 + xcd, r = f / rest;
+            return {(int64_t)whole * 8 + (f - r * rest), (int)(tiles - 1 - rank0 - r)};
+        }
+        j -= mine;
+    }
+    uint32_t c = 0, heads = whole;
+    if (!merge) {
+        c = j / (chunk * tiles);
+        j -= c * (chunk * tiles);
+        const uint32_t left = whole - c * chunk;
+        heads = left < chunk ? left : chunk;
+    }
+    const uint32_t r = j / heads;
+    return {(int64_t)(c * chunk + (j - r * heads)) * 8 + xcd, (int)(tiles - 1 - rank0 - r)};
+}
+
 // The 4 probability codes of two pairs of 16-bit probabilities (columns 0,1 in ph01, 2,3 in ph23), one byte each:
 // round(127 p16), exactly rounded.
 template <bool BF16> SQ_DEVICE int prob_codes4(uint32_t ph01, uint32_t ph23)

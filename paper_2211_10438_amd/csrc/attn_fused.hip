@@ -69,32 +69,19 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r32 = lane & 31, h = lane >> 5;
 
-    // Which row block.  Consecutive workgroup ids go round-robin to the 8 XCDs.  Without the mask each XCD gets a contiguous
-    // range of the logical order, so that the row blocks of one head (they share its K and V) run on one L2.  In the causal
-    // form block t sees t + 1 of the key tiles, and the workgroups that start last decide when the launch ends: XCD x works
-    // on the batch entries x, x + 8, ..., p.chunk of them at a time, and within a chunk the longest row blocks start first.
-    // (One block from the top and one from the bottom of the range per workgroup, as before, made 1152 equal pieces for 512
-    // places at 288 heads x 1024^2: three rounds for 2.25 rounds of work.)
-    // (32-bit: the grid has fewer than 2^31 workgroups, and a 64-bit division is a hundred scalar instructions)
-    int64_t batch;
-    int mt;
-    {
+    // Which row block.  Without the mask each XCD gets a contiguous range of the logical order, so that the row blocks of one head
+    // (they share its K and V) run on one L2.  (32-bit: the grid has fewer than 2^31 workgroups, and a 64-bit division is a
+    // hundred scalar instructions)
+    AttnPlace at;
+    if (p.causal) {
+        at = attn_causal_place(blockIdx.x, (uint32_t)p.batch, (uint32_t)p.tiles_m, (uint32_t)p.chunk);
+    } else {
         const uint32_t xcd = blockIdx.x & 7, j = blockIdx.x >> 3, tiles = (uint32_t)p.tiles_m;
-        if (p.causal) {
-            const uint32_t heads = ((uint32_t)p.batch - xcd + 7) >> 3, chunk = (uint32_t)p.chunk;
-            const uint32_t c = j / (chunk * tiles), in = j - c * (chunk * tiles);
-            if (c * chunk >= heads) return;
-            const uint32_t left = heads - c * chunk, hc = left < chunk ? left : chunk;
-            const uint32_t rank = in / hc;
-            if (rank >= tiles) return;  // (the last chunk of an XCD may be short of heads)
-            batch = (int64_t)(c * chunk + (in - rank * hc)) * 8 + xcd;
-            mt = (int)(tiles - 1 - rank);
-        } else {
-            const uint32_t per = gridDim.x >> 3, r = gridDim.x & 7, pid = xcd * per + (xcd < r ? xcd : r) + j, head = pid / tiles;
-            batch = head;
-            mt = (int)(pid - head * tiles);
-        }
+        const uint32_t per = gridDim.x >> 3, r = gridDim.x & 7, pid = xcd * per + (xcd < r ? xcd : r) + j, head = pid / tiles;
+        at = {head, (int)(pid - head * tiles)};
     }
+    const int64_t batch = at.batch;
+    const int mt = at.tile;
     // The four row groups of 32 rotate over the waves from workgroup to workgroup: on the diagonal tile the last group sees
     // four times the keys of the first, and wave w of every workgroup sits on the same SIMD.
     const int rg = (wave + (blockIdx.x >> 3)) & 3;
@@ -393,13 +380,14 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
 
 }  // namespace
 
-// Causal form: batch entries (heads) an XCD works on at a time.  Longest-first pays the more the fewer row blocks there are,
-// and the chunks should be equal: all heads at once up to 16 MB of K and V per XCD (288 x 1024^2 x 128: 107 us against 112 in
-// chunks of 8; 96 x 2048^2 121 against 135).  Beyond that their K and V should stay in the 4 MB L2 (768 x 2048^2: 969 us in
-// chunks of 4 MB, 1071 all at once).
+// Causal form: how many of its whole heads (every eighth) an XCD works on at a time.  Longest-first pays the more the fewer row
+// blocks there are, and the chunks should be equal: all heads at once up to 16 MB of K and V per XCD (288 x 1024^2 x 128: 107 us
+// against 112 in chunks of 8; 96 x 2048^2 121 against 135).  Beyond that their K and V should stay in the 4 MB L2 (768 x
+// 2048^2: 969 us in chunks of 4 MB, 1071 all at once).
 static int attn_chunk(int64_t b, int64_t s_k, int64_t d)
 {
-    const int64_t heads = (b + 7) / 8, bytes = 2 * s_k * d;
+    const int64_t heads = b / 8, bytes = 2 * s_k * d;
+    if (heads == 0) return 1;
     if (heads * bytes <= (16 << 20)) return (int)heads;
     int64_t n = (heads * bytes + (4 << 20) - 1) / (4 << 20);
     if (n > heads) n = heads;
@@ -445,7 +433,7 @@ static sq_status attention(int form, const int8_t* q, const int8_t* k, const int
     // The kernel's scores carry a factor 2^-26 (see kBias).  A factor beyond 2^101 makes every difference of two scores
     // infinite for the softmax, like 2^101 itself.
     a.alpha1 = (alpha1 < 0x1p+101f ? alpha1 : 0x1p+101f) * 0x1p+26f;
-    const dim3 grid((unsigned)((causal ? (b + 7) / 8 * 8 : b) * tiles_m)), block(256);
+    const dim3 grid((unsigned)(b * tiles_m)), block(256);
     const bool masked = causal || (s_k & 127) != 0;
 #define SQ_ATTN(BF, HD)                                                                  \
     do {                                                                                 \
@@ -481,6 +469,15 @@ extern "C" int sq_probe_attention_form(int64_t b, int64_t s_q, int64_t s_k, int6
 {
     if (b <= 0 || s_q <= 0 || s_k <= 0 || (d != 64 && d != 128)) return 0;
     return sq_attn_few_eligible(b, s_q, s_k, d, causal != 0) ? 2 : 1;
+}
+
+extern "C" int sq_probe_attention_place(int64_t block, int64_t b, int64_t s_q, int64_t s_k, int64_t d, int64_t* head)
+{
+    const int64_t tiles = (s_q + 127) / 128;
+    if (b <= 0 || s_q <= 0 || s_k <= 0 || d <= 0 || block < 0 || !head || b * tiles >= ((int64_t)1 << 31) || block >= b * tiles) return -1;
+    const AttnPlace at = attn_causal_place((uint32_t)block, (uint32_t)b, (uint32_t)tiles, (uint32_t)attn_chunk(b, s_k, d));
+    *head = at.batch;
+    return at.tile;
 }
 
 extern "C" sq_status sq_probe_attention(int form, int causal, const int8_t* q, const int8_t* k, const int8_t* v, float alpha1,
