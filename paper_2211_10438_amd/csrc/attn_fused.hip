@@ -38,7 +38,7 @@ constexpr int kIntMin = -2147483647 - 1;
 constexpr int kBias = 0x3e22f983;
 constexpr float kBiasF = __builtin_bit_cast(float, kBias);
 
-// Two instantiations, so that the common case carries no mask tests (with both in one kernel the register allocation
+// MASKED: two instantiations, so that the common case carries no mask tests (with both in one kernel the register allocation
 // spilled):
 //   MASKED = false  every query sees every key, and the key count is a multiple of 128;
 //   MASKED = true   query i sees the keys j <= min(i + p.coff, s_k - 1): the decoder's mask (coff = s_k - s_q: the last query
@@ -48,7 +48,8 @@ constexpr float kBiasF = __builtin_bit_cast(float, kBias);
 //                   its rows see in full without a mask, those they see in part with an element-wise one, the others not at
 //                   all (a whole-tile masked body cost 1.7 plain ones on every diagonal tile, of which a 32-row group sees
 //                   between one and four blocks).
-template <bool BF16, int HD, bool MASKED, bool CODES>
+//   BIAS            see kBias below.
+template <bool BF16, int HD, bool MASKED, bool CODES, bool BIAS>
 __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
 {
     constexpr int TK1 = 128, TK = HD == 64 ? 128 : 64;  // keys per tile of pass 1 (K only) and pass 2 (K and V)
@@ -179,13 +180,13 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
             return v4i{lo.x, lo.y, hi.x, hi.y};
         };
 
-        // The sums start at the bit pattern of kBias instead of at zero: read as a float, kBias + sum is the number
+        // BIAS: the sums start at the bit pattern of kBias instead of at zero: read as a float, kBias + sum is the number
         // kBiasF + sum * 2^-26 exactly (|sum| <= 128^3 < 2292099, the distance of the pattern from the next power of two
         // below it), so one subtraction of kBiasF, exact too, replaces the conversion to float (a subtraction issues in half
-        // the time of a conversion here).  The factor 2^26 is in alpha1; kBias = 1 / (2 pi) is a constant MFMA takes inline.
+        // the time of a conversion here).  The factor 2^26 is in alpha1.
         v16i bias;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) bias[v] = kBias;
+        for (int v = 0; v < 16; ++v) bias[v] = BIAS ? kBias : 0;
         // S tile = Q K^T for the 128 keys of a stage: acc[jn] is the transposed 32x32 block of key block jn
         // (blocks from nvis on are left out)
         auto scores = [&](const char* kt, auto& acc, int nvis) {
@@ -205,9 +206,10 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
         };
         // scores of two accumulators as the 16-bit tensor elements they stand for, widened again: round16(fl32(acc * alpha1)),
         // one narrowing instruction for the pair
-        const float alpha1 = p.alpha1;  // times 2^26
+        const float alpha1 = p.alpha1;  // BIAS: times 2^26
         auto s16f2 = [&](int a0, int a1, float& s0, float& s1) {
-            const uint32_t h = store16x2_bits<BF16>((__builtin_bit_cast(float, a0) - kBiasF) * alpha1, (__builtin_bit_cast(float, a1) - kBiasF) * alpha1);
+            auto sum = [](int a) { return BIAS ? __builtin_bit_cast(float, a) - kBiasF : (float)a; };
+            const uint32_t h = store16x2_bits<BF16>(sum(a0) * alpha1, sum(a1) * alpha1);
             s0 = load16_bits<BF16>(h);
             s1 = load16_bits<BF16>(h >> 16);
         };
@@ -225,15 +227,20 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
         auto pass1_tile = [&](const char* kt, auto PART_, int lim, int nfull, int nvis) {
             constexpr bool PART = decltype(PART_)::value;
             v16i acc[4];
-            scores(kt, acc, nvis);
+            scores(kt, acc, 4);  // (hidden blocks too: with the loads of the operands under a condition each MFMA waits for its own)
             int imax = kIntMin;
 #pragma unroll
             for (int jn = 0; jn < 4; ++jn) {
                 if (PART && jn >= nvis) break;
+                if (PART && jn >= nfull) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {  // register 4 g + e
-                    const int a = !PART || 32 * jn + 8 * (r >> 2) + (r & 3) <= lim ? acc[jn][r] : kIntMin;
-                    imax = a > imax ? a : imax;
+                    for (int r = 0; r < 16; ++r) {  // register 4 g + e
+                        const int a = 32 * jn + 8 * (r >> 2) + (r & 3) <= lim ? acc[jn][r] : kIntMin;
+                        imax = a > imax ? a : imax;
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) imax = acc[jn][r] > imax ? acc[jn][r] : imax;
                 }
             }
             const int other = __shfl_xor(imax, 32, 64);
@@ -430,17 +437,23 @@ static sq_status attention(int form, const int8_t* q, const int8_t* k, const int
     a.causal = causal ? 1 : 0;
     a.coff = causal ? (int)(s_k - s_q) : (int)s_k;
     a.chunk = attn_chunk(b, s_k, d);
-    // The kernel's scores carry a factor 2^-26 (see kBias).  A factor beyond 2^101 makes every difference of two scores
-    // infinite for the softmax, like 2^101 itself.
-    a.alpha1 = (alpha1 < 0x1p+101f ? alpha1 : 0x1p+101f) * 0x1p+26f;
     const dim3 grid((unsigned)(b * tiles_m)), block(256);
     const bool masked = causal || (s_k & 127) != 0;
-#define SQ_ATTN(BF, HD)                                                                  \
-    do {                                                                                 \
-        if (p_codes && masked) sq_launch((attn_i8_kernel<BF, HD, true, true>), grid, block, 0, st, a); \
-        else if (p_codes) sq_launch((attn_i8_kernel<BF, HD, false, true>), grid, block, 0, st, a);     \
-        else if (masked) sq_launch((attn_i8_kernel<BF, HD, true, false>), grid, block, 0, st, a);      \
-        else sq_launch((attn_i8_kernel<BF, HD, false, false>), grid, block, 0, st, a);                 \
+    // BIAS where vector issue bounds the kernel: with masks, and more than two workgroups for a compute unit.  A workgroup that
+    // has its unit to itself waits for the longer start of each sum instead (us, without / with: 768 x 2048^2 x 128 causal 954 /
+    // 931, 100 x 1900^2 x 128 causal 129 / 126, 96 x 777 x 1040 x 64 61.5 / 60.8; but 64 x 512^2 x 128 16.5 / 16.8, 288 x 1024^2 x
+    // 64 125 / 129, 2 x 16384^2 x 128 causal 421 / 428).
+    const bool bias = masked && !p_codes && b * tiles_m > 512;
+    // The kernel's scores carry a factor 2^-26 then.  A factor beyond 2^101 makes every difference of two scores infinite for
+    // the softmax, like 2^101 itself.
+    if (bias) a.alpha1 = (alpha1 < 0x1p+101f ? alpha1 : 0x1p+101f) * 0x1p+26f;
+#define SQ_ATTN(BF, HD)                                                                                       \
+    do {                                                                                                      \
+        if (p_codes && masked) sq_launch((attn_i8_kernel<BF, HD, true, true, false>), grid, block, 0, st, a); \
+        else if (p_codes) sq_launch((attn_i8_kernel<BF, HD, false, true, false>), grid, block, 0, st, a);     \
+        else if (bias) sq_launch((attn_i8_kernel<BF, HD, true, false, true>), grid, block, 0, st, a);         \
+        else if (masked) sq_launch((attn_i8_kernel<BF, HD, true, false, false>), grid, block, 0, st, a);      \
+        else sq_launch((attn_i8_kernel<BF, HD, false, false, false>), grid, block, 0, st, a);                 \
     } while (0)
     if (d == 128) {
         if (out == SQ_BF16) SQ_ATTN(true, 128); else SQ_ATTN(false, 128);
