@@ -26,44 +26,43 @@ struct AttnPlace {
 //  * Longest first: the workgroups that start last decide when the launch ends.
 //  * Whole heads go to the XCDs as far as they divide (XCD x: the heads x, x + 8, ..., `chunk` of them at a time, so that their K
 //    and V stay in its L2).  The one to seven heads left over are dealt block by block, or XCDs would idle (1 x 32768^2 x 128 with
-//    its head on one XCD 2037 us, dealt 867): eight ranks of them, then the same eight ranks of the whole heads, and so on.
-//    With several chunks they come first.
-//  * Where all workgroups are resident at once (three per compute unit) nothing balances them later: every second round over
-//    the compute units runs backwards, so that a long block shares its unit with a short one.
+//    its head on one XCD 2050 us, dealt 868): sorted in by length, eight ranks at a time; with several chunks they come first.
+//  * The first three workgroups of a compute unit start together.  The second round over the units runs backwards, so that a long
+//    block shares its unit with a short one (12 x 8192^2 x 128 334 us without, 251 with).
 __host__ __device__ __forceinline__ AttnPlace attn_causal_place(uint32_t block, uint32_t batch, uint32_t tiles, uint32_t chunk)
 {
     const uint32_t xcd = block & 7, whole = batch >> 3, rest = batch & 7;
     uint32_t j = block >> 3;
-    const uint32_t n = (batch * tiles + 7 - xcd) >> 3;  // workgroups of this XCD
-    if (n <= 96 && (j & 32)) {
-        const uint32_t lo = j & ~31u, hi = lo + 32 < n ? lo + 32 : n;
-        j = lo + (hi - 1 - j);
+    if ((j >> 5) == 1) {
+        const uint32_t n = (batch * tiles + 7 - xcd) >> 3, hi = n < 64 ? n : 64;  // n: workgroups of this XCD
+        j = 32 + (hi - 1 - j);
     }
-    const bool merge = rest && chunk >= whole;
-    uint32_t rank0 = 0, ranks = tiles;  // the ranks to deal the left over heads' blocks of
-    if (merge) {
-        const uint32_t q = j / batch, full = tiles >> 3, p = q < full ? q : full;
+    auto left_over = [&](uint32_t f, uint32_t r) { return AttnPlace{(int64_t)whole * 8 + (f - r * rest), (int)(tiles - 1 - r)}; };
+    if (rest && chunk >= whole) {
+        // eight ranks at a time (fewer at the end): of each left over head one block per XCD.  Number i of them on this XCD comes
+        // in front of the whole heads' blocks of its rank.
+        const uint32_t q = j / batch, full = tiles >> 3, p = q < full ? q : full, rank0 = 8 * p, ranks = q < full ? 8 : tiles - rank0;
         j -= p * batch;
-        rank0 = 8 * p;
-        ranks = q < full ? 8 : tiles - rank0;
+        const uint32_t mine = (rest * ranks + 7 - xcd) >> 3, inv = 65536 / rest + 1;  // f / rest = (f * inv) >> 16 for f < 64
+        uint32_t before = 0;
+        for (uint32_t i = 0; i < mine; ++i) {
+            const uint32_t f = i * 8 + xcd, r = (f * inv) >> 16, at = i + whole * r;
+            if (at == j) return left_over(rank0 * rest + f, rank0 + r);
+            if (at < j) before = i + 1;
+        }
+        j -= before;
+        const uint32_t r = j / whole;
+        return {(int64_t)(j - r * whole) * 8 + xcd, (int)(tiles - 1 - rank0 - r)};
     }
     if (rest) {
-        const uint32_t mine = (rest * ranks + 7 - xcd) >> 3;
-        if (j < mine) {
-            const uint32_t f = j * 8 + xcd, r = f / rest;
-            return {(int64_t)whole * 8 + (f - r * rest), (int)(tiles - 1 - rank0 - r)};
-        }
+        const uint32_t mine = (rest * tiles + 7 - xcd) >> 3;
+        if (j < mine) return left_over(j * 8 + xcd, (j * 8 + xcd) / rest);
         j -= mine;
     }
-    uint32_t c = 0, heads = whole;
-    if (!merge) {
-        c = j / (chunk * tiles);
-        j -= c * (chunk * tiles);
-        const uint32_t left = whole - c * chunk;
-        heads = left < chunk ? left : chunk;
-    }
-    const uint32_t r = j / heads;
-    return {(int64_t)(c * chunk + (j - r * heads)) * 8 + xcd, (int)(tiles - 1 - rank0 - r)};
+    const uint32_t c = j / (chunk * tiles);
+    j -= c * (chunk * tiles);
+    const uint32_t left = whole - c * chunk, heads = left < chunk ? left : chunk, r = j / heads;
+    return {(int64_t)(c * chunk + (j - r * heads)) * 8 + xcd, (int)(tiles - 1 - r)};
 }
 
 // The 4 probability codes of two pairs of 16-bit probabilities (columns 0,1 in ph01, 2,3 in ph23), one byte each:
