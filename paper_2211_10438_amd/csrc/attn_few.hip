@@ -307,6 +307,11 @@ template <bool BF16, int HD, int NW> void launch_g(const AttnArgs& a, unsigned g
 
 constexpr int kFewKeys = 8 * 8 * 128;  // what the registers of eight waves hold
 
+// Eight waves per workgroup where there is at most one workgroup per compute unit, or where four waves' registers do not hold
+// the scores (8 groups of 128 keys each); else four, two workgroups per compute unit, so that one loads while the other is at
+// its meeting or its epilogue.
+int few_waves(double workgroups, int64_t s_k) { return workgroups <= 256.0 || s_k > 4 * 8 * 128 ? 8 : 4; }
+
 }  // namespace
 
 bool sq_attn_few_possible(int64_t batch, int64_t s_q, int64_t s_k)
@@ -314,31 +319,39 @@ bool sq_attn_few_possible(int64_t batch, int64_t s_q, int64_t s_k)
     return s_k <= kFewKeys && (double)batch * (double)((s_q + 15) / 16) < (1 << 22);  // (a grid stays below 2^32 threads)
 }
 
-// Which of the two forms: rounds of workgroups times the time of one, in microseconds, for both.  This form's 16-row blocks
-// fill the chip early and finish early, but each reads K and V once more, out of L2; the row-block form computes 128 rows per
-// workgroup whatever s_q is.  Fitted to ninety shapes between 12 x 16 x 64 and 700 x 1900 x 1900 queries and keys; choosing by
-// it costs 1 % against the better of the two (us, this form / row blocks): 768 x 1 x 2048 x 128 66 / 139, 288 x 32 x 1024 x 128
-// 26 / 46, 33 x 200 x 1040 x 64 14 / 25, 24 x 69 x 336 x 128 8.6 / 15, but 240 x 176^2 x 128 29 / 13, 126 x 1088^2 x 128
-// 238 / 116.
+// Which of the two forms, by a model of the time of both in microseconds: a launch takes what its longest workgroup takes, or, with
+// more workgroups, what the whole work takes spread over the 256 compute units.  This form's 16-row blocks fill the chip early
+// and finish early, but each reads K and V once more, out of L2; the row-block form computes 128 rows per workgroup whatever s_q
+// is, and one, two and three workgroups on a compute unit take 1, 1.5 and 2.5 times as long.  Fitted to 790 shapes of 1 to 900
+// heads, 1 to 2048 queries and 16 to 12000 keys, both forms and the earlier row-block version timed in turn; the choice costs 0.3 %
+// against the better form, and 30 shapes take the worse one by more than 3 %, up to 22 % (450 x 21 x 640 x 128).  The line, us, this
+// form / row blocks: 768 x 1 x 2048 x 128 66 / 139, 13 x 320^2 x 64 7.7 / 10.4, 64 x 208 x 1040 x 64 22.3 / 25.0, but 123 x 208 x
+// 1040 x 64 34 / 26, 51 x 208^2 x 128 13.9 / 10.5, 42 x 320^2 x 128 18.9 / 12.9.
 bool sq_attn_few_eligible(int64_t batch, int64_t s_q, int64_t s_k, int64_t d, bool causal)
 {
-    const double few_wg = (double)batch * ((s_q + 15) / 16), row_wg = (double)batch * ((s_q + 127) / 128);
     if (!sq_attn_few_possible(batch, s_q, s_k)) return false;
     const double keys = causal ? (double)s_k - 0.5 * (double)(s_q - 1) : (double)s_k;  // a query sees on average
-    const double few_rounds = few_wg / (d == 64 ? 768.0 : 640.0), row_rounds = row_wg / 384.0;
-    const double few_us = (few_rounds > 1.0 ? few_rounds : 1.0) * (d == 64 ? 6.0 + 0.006 * keys : 7.0 + 0.014 * keys);
-    const double row_us = (row_rounds > 1.0 ? row_rounds : 1.0) * (d == 64 ? 5.0 + 0.024 * keys : 5.5 + 0.032 * keys);
-    return few_us < row_us;
+    auto larger = [](double a, double b) { return a > b ? a : b; };
+
+    const double row_per_cu = (double)batch * (double)((s_q + 127) / 128) / 256.0;
+    const double crowd = row_per_cu <= 1.0 ? 1.0 : row_per_cu <= 2.0 ? 1.5 : row_per_cu <= 3.0 ? 2.5 : 2.5 / 3.0 * row_per_cu;
+    const double row_us = d == 64 ? larger(4.1 + 0.021 * (double)s_k, 4.1 + 0.021 * keys * crowd)
+                                  : larger(5.0 + 0.0265 * (double)s_k, 5.0 + 0.0265 * keys * crowd);
+
+    const double few_wg = (double)batch * (double)((s_q + 15) / 16), few_per_cu = few_wg / 256.0;
+    const int64_t groups = (s_k + 127) / 128, waves = few_waves(few_wg, s_k), per_wave = (groups + waves - 1) / waves;
+    const double few_keys = causal ? (double)s_k - 0.4 * (double)(s_q - 1) : (double)s_k;  // (its long blocks do not start first)
+    const bool many_keys = s_k > 4 * 8 * 128;  // one workgroup of eight waves on a compute unit at a time
+    const double few_us = d == 64 ? larger(4.5 + 0.9 * (double)per_wave + 0.38 * (double)groups, 5.4 + (0.87 + (many_keys ? 0.004 : 0.003) * few_keys) * few_per_cu)
+                                  : larger(5.6 + 0.9 * (double)groups, 5.4 + (2.1 + (many_keys ? 0.009 : 0.006) * few_keys) * few_per_cu);
+    return few_us < 0.96 * row_us;
 }
 
 void sq_attn_few_launch(AttnArgs a, int64_t batch, int64_t d, bool bf16, bool causal, hipStream_t st)
 {
     a.tiles_m = (a.s_q + 15) / 16;
     const unsigned grid = (unsigned)(batch * a.tiles_m);
-    // Eight waves per workgroup where there is at most one workgroup per compute unit, or where four waves' registers do
-    // not hold the scores (8 groups of 128 keys each); else four, two workgroups per compute unit, so that one loads
-    // while the other is at its meeting or its epilogue.
-    const bool eight = grid <= 256 || a.s_k > 4 * 8 * 128;
+    const bool eight = few_waves((double)grid, a.s_k) == 8;
 #define SQ_FEW(BF, HD) do { if (eight) launch_g<BF, HD, 8>(a, grid, causal, st); else launch_g<BF, HD, 4>(a, grid, causal, st); } while (0)
     if (d == 128) {
         if (bf16) SQ_FEW(true, 128); else SQ_FEW(false, 128);
