@@ -34,6 +34,9 @@ sq_status sq_probe_attention(int form, int causal, const int8_t* q, const int8_t
                              int64_t stride_q, int64_t stride_k, int64_t stride_v, int64_t stride_o, int8_t* p_codes,
                              void* stream);
 
+/* 1 where a linear layer of this size runs the kernel for few tokens and few output channels, else 0.  No GPU work. */
+int sq_probe_narrow_gemm(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout);
+
 #ifdef __cplusplus
 }
 #endif

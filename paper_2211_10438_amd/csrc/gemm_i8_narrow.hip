@@ -1,4 +1,4 @@
-// INT8 GEMM for few tokens and few output channels (T <= 128, C_o below 16 per compute unit), gfx950.
+// INT8 GEMM for few tokens and few output channels (T <= 128 with C_o below 16 per compute unit, T <= 16 up to 1.6 times that), gfx950.
 //
 // Such a layer is a few megabytes of weights at most and is bound by latency: the time from the first load to the last store,
 // not by bandwidth.  (The tile kernels cut C_o into 256-column tiles, 12 workgroups for 3072 columns, each walking its K
@@ -11,6 +11,7 @@
 //  * the waves' int32 sums meet in LDS and the dequantizing epilogue of Eq. 2 is applied once: one kernel, no workspace.
 // The weights are the first MFMA operand, so that a lane holds four neighbouring output channels of one token.
 #include "gemm_args.h"
+#include "sqmi_probe.h"
 
 namespace {
 
@@ -137,27 +138,42 @@ __global__ __launch_bounds__(kNarrowWaves * 64, 2) void gemm_i8_narrow_kernel(co
 
 }  // namespace
 
-// Where it pays, in microseconds: this kernel against the tile kernels with their K split and reduction, both fitted to C_i 768 to
-// 49152, C_o 768 to 4088, 1 to 128 tokens.  Tiled operands (this / tiles): 16 x 768 -> 3072 4.3 / 6.6, 16 x 5120 -> 3072
-// 7.3 / 11.9, 64 x 5120 -> 768 7.3 / 12.2, 128 x 3072 -> 3072 11.4 / 18.7, 16 x 12288 -> 4088 12.7 / 25; but every workgroup
-// reads all tokens, and from some product of tokens and C_i on that decides: 128 x 12288 -> 768 27 / 22, 16 x 49152 -> 768 31 / 20.
-// Row-major operands come as sixteen 64-byte pieces per load and cost about twice as much: short C_i (16 x 768 -> 3072
-// 6.3 / 6.6, 100 x 784 -> 768 7.5 / 13) or a few tokens (1 x 12288 -> 3072 15 / 21) only.
+// Where it pays, in microseconds: this kernel against the tile and streaming kernels with their K split and reduction, 2100 shapes of
+// C_i 64 to 49152, C_o 64 to 6544, 1 to 128 tokens.
+//  * Tiled operands (this / others): 16 x 768 -> 3072 4.3 / 6.6, 16 x 5120 -> 3072 7.3 / 11.9, 64 x 5120 -> 768 7.3 / 12.2, 128 x
+//    3072 -> 3072 11.4 / 18.7, 16 x 12288 -> 4088 12.7 / 25; but every workgroup reads all tokens, and from some product of tokens
+//    and C_i on that decides: 128 x 12288 -> 768 27 / 22, 16 x 49152 -> 768 31 / 20.  That is the fit.  Near one 16-channel unit per
+//    compute unit the streaming kernel's split is ahead of it with many tokens and long C_i: 64 x 20480 -> 4088 31.5 / 27.6.
+//  * Row-major operands come as sixteen 64-byte pieces per load, and what they cost depends on the row stride: with rows of a
+//    multiple of 128 bytes the pieces fall on few channels of the memory.  C_i = 784: 0.5 to 0.8 of the others' time up to 128 tokens and
+//    4095 channels (100 x 784 -> 4088 8.1 / 13.7).  C_i = 768 or 896: 32 tokens 7.1 / 6.8, 64 tokens 8.0 / 8.3 and 8.9 / 8.9, 128
+//    tokens 10.7 / 12.9 and up to 1.2 times the others' time at 4088 channels.
+//  * Between one and 1.6 units per compute unit (tiled, up to 16 tokens) the streaming kernel, one workgroup per compute unit,
+//    deals two units to some and leaves the others idle: 20480 -> 5120 31 / 41, 5120 -> 5120 11.4 / 13.1, 16 x 1024 -> 5120 4.8 /
+//    5.9 (at 9216 -> 9216, 2.25 units, 24 / 22).  One or two tokens with C_i of 512 to 2048 are the exception, 1 x 1024 -> 5120 6.6 /
+//    5.9.
 bool sq_narrow_gemm_eligible(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled)
 {
     if (batch != 1 || M < 1 || M > 128) return false;
     if (N >= 16 * 256) {
-        // The streaming kernel's: whole 16-channel units per workgroup, one workgroup per compute unit.  Between one and about
-        // 1.6 units per compute unit it deals two to some and leaves the others idle, and with up to 16 tokens this kernel
-        // is ahead: 20480 -> 5120 31 / 41 us, 5120 -> 5120 12.1 / 13.2-14 (at 9216 -> 9216, 2.25 units, 24 / 22).
         const int64_t units = (N + 15) / 16;
-        return tiled && M <= 16 && units > 256 && units < 410;
+        return tiled && M <= 16 && units > 256 && units < 410 && !(M <= 2 && K >= 512 && K <= 2048 && units > 264);
     }
-    if (!tiled && M > 4) return K <= 1024 && N <= 3072;
+    if (!tiled && M > 4) {
+        if (K > 1024) return false;
+        if (K % 128 != 0) return true;
+        return N <= 3072 && !(M > 24 && M <= 32 && K > 640) && !(M > 40 && M <= 64 && K > 768);
+    }
+    if (tiled && M > 32 && N > 3584 && K > 14336) return false;
     const double per_k = !tiled ? 0.80e-3 : M <= 16 ? 0.62e-3 : M <= 32 ? 0.85e-3 : M <= 64 ? 1.27e-3 : 2.0e-3;
     const double this_us = (tiled ? 3.6 : 5.0) + per_k * (double)K;
-    const double tiles_us = 8.0 + (double)N * (double)K / 3.6e6 + 0.05 * (double)M;
-    return this_us < 0.9 * tiles_us;
+    const double others_us = 8.0 + (double)N * (double)K / 3.6e6 + 0.05 * (double)M;
+    return this_us < 0.9 * others_us;
+}
+
+extern "C" int sq_probe_narrow_gemm(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout)
+{
+    return t > 0 && c_i > 0 && c_o > 0 && sq_narrow_gemm_eligible(t, c_o, c_i, 1, layout == SQ_TILED) ? 1 : 0;
 }
 
 void sq_narrow_gemm_launch(const GemmArgs& a, bool to_i32, bool bf16, bool tiled, hipStream_t st)
