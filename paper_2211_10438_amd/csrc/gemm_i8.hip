@@ -848,7 +848,10 @@ sq_status run_gemm(GemmArgs a, int64_t batch, bool to_i32, bool bf16, void* work
     const int64_t total = (int64_t)a.M * a.N;
     auto reduce = [&](void* final_out) {  // a.acc_out = partials [a.splits][M][N]
         a.C = final_out;
-        const bool vec = (a.N & 3) == 0;
+        // Four columns per thread from two waves per SIMD of one column each on; below that the longer threads only add latency (us,
+        // four / one: 48 x 1024 -> 1024 in two splits 9.2 / 8.6, 64 x 4096 -> 1024 10.4 / 10.2, 130 x 4096 -> 2104 16.5 / 16.8, 512 x
+        // 4096 -> 5120 31.1 / 37.2).
+        const bool vec = (a.N & 3) == 0 && total >= 131072;
         const int64_t items = vec ? total / 4 : total;
         const unsigned blocks = (unsigned)(items < 256 * 16384 ? (items + 255) / 256 : 16384);
         if (vec && bf16) sq_launch((splitk_reduce_kernel<true, 4>), dim3(blocks), dim3(256), 0, st, a, to_i32 ? 1 : 0);

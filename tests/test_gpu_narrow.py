@@ -64,8 +64,9 @@ def test_narrow_linear(t, c_i, c_o, dtype, kind):
             assert torch.equal(y.view(torch.int16), v16.view(torch.int16))
 
 
-# K splits of the tile kernels and their reduction, four columns at a time and (C_o % 4 != 0) one by one
-@pytest.mark.parametrize("t,c_i,c_o", [(256, 16384, 256), (200, 20480, 258), (48, 12288, 333), (128, 20480, 772)])
+# K splits of the tile kernels and their reduction, one column per thread and (C_o % 4 == 0, from 2^17 outputs on) four
+@pytest.mark.parametrize("t,c_i,c_o", [(256, 16384, 256), (200, 20480, 258), (48, 12288, 333), (128, 20480, 772), (511, 12288, 256),
+                                         (512, 12288, 256)])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 def test_split_reduction(t, c_i, c_o, dtype):
     print(f"split reduction {t}x{c_i}->{c_o} {dtype}", flush=True)
