@@ -13,12 +13,25 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("t,c_i,c_o,mode", [(16, 1024, 4096, sq.PER_TOKEN_DYNAMIC),    # weight streaming
-                                            (16, 4096, 1024, sq.PER_TOKEN_DYNAMIC),    # split-K tiles + reduction
+                                            (16, 4096, 1024, sq.PER_TOKEN_DYNAMIC),    # few tokens, few channels: one kernel
                                             (128, 4096, 4096, sq.PER_TENSOR_DYNAMIC),  # streaming with a K split, O2 quantizer
                                             (300, 512, 768, sq.PER_TOKEN_DYNAMIC),     # prefill tiles
                                             (2048, 12288, 12288, sq.PER_TOKEN_DYNAMIC)])  # the 256x384 tile (uses scratch memory)
 def test_graph_replay_matches_eager(t, c_i, c_o, mode):
     print(f"[case] graph replay t={t} c_i={c_i} c_o={c_o} mode={mode}", flush=True)
+    _replay(t, c_i, c_o, mode, 64)
+
+
+# split-K tiles and their reduction, one column per thread and four; the per-tensor quantizer with its whole workspace (two
+# launches under capture, one outside), tensors that fit its one launch and that do not
+@pytest.mark.parametrize("t,c_i,c_o", [(130, 4096, 112), (140, 12288, 1024), (1000, 9216, 768)])
+def test_graph_replay_split_reduction_and_per_tensor_quantizer(t, c_i, c_o):
+    print(f"[case] graph replay split reduction t={t} c_i={c_i} c_o={c_o}", flush=True)
+    assert sq.workspace_bytes(sq.OP_W8A8_LINEAR, t, c_i, c_o) > 0 and not sq.lib().sq_probe_narrow_gemm(t, c_i, c_o, sq.TILED)
+    _replay(t, c_i, c_o, sq.PER_TENSOR_DYNAMIC, sq.workspace_bytes(sq.OP_QUANTIZE_ACT, t, c_i, 0))
+
+
+def _replay(t, c_i, c_o, mode, quantizer_workspace):
     w = synth.weights(c_i, c_o, 4242)
     wq, ws = sq.prepare_weight(to_dev_16(w, F16), None, layout=sq.TILED)
     xs_host = [synth.normal_fp16((t, c_i), 5000 + i) for i in range(3)]
@@ -26,7 +39,7 @@ def test_graph_replay_matches_eager(t, c_i, c_o, mode):
     xq = sq.empty_codes(t, c_i, sq.TILED)
     scale = torch.empty(t if mode == sq.PER_TOKEN_DYNAMIC else 1, dtype=torch.float32, device="cuda")
     y = torch.empty((t, c_o), dtype=torch.float16, device="cuda")
-    qws = torch.empty(64, dtype=torch.uint8, device="cuda")
+    qws = torch.empty(quantizer_workspace, dtype=torch.uint8, device="cuda")
     gws = torch.empty(max(sq.workspace_bytes(sq.OP_W8A8_LINEAR, t, c_i, c_o), 16), dtype=torch.uint8, device="cuda")
 
     def step():

@@ -20,13 +20,13 @@ def _codes(x, inv_s, r):
     return (v * r).round().clamp(-127, 127).to(torch.int8)
 
 
-# rows of 2, 3, 511 and 769 vectors (the row of a vector comes from a division), one vector short of and at the switch to
-# two vectors per thread (2^21), a single row, and a tensor of many short rows
-@pytest.mark.parametrize("t,c_i", [(1, 16), (3, 48), (70001, 48), (4104, 4088 // 8 * 8), (2727, 6152), (2728, 6160), (513, 4096), (2049, 8192)])
+# rows of 2 and 6 vectors and of two more and two less than 512 and 1024 (the row of a vector comes from a division); 2^21 vectors,
+# where two per thread begin, and one row less; a single row, and a tensor of many short rows
+@pytest.mark.parametrize("t,c_i", [(1, 16), (3, 48), (70001, 48), (37, 4080), (37, 4112), (513, 8176), (513, 8208), (4095, 4096), (4096, 4096),
+                                   (513, 4096), (2049, 8192)])
 @pytest.mark.parametrize("with_s", [False, True])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 def test_per_tensor_edges(t, c_i, with_s, dtype):
-    c_i = c_i // 16 * 16
     print(f"per-tensor {t}x{c_i} s={with_s} {dtype}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(t + c_i)
     full = torch.randn((t, c_i + 8), generator=g, device="cuda").to(dtype)
