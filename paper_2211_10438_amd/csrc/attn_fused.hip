@@ -21,12 +21,12 @@
 // What bounds it: vector-ALU issue.  Measured on loops of single instructions (cycles per instruction and SIMD, with 2 / 4
 // waves on it): add, sub, mul 3.0 / 2.7, conversions, packed and three-operand forms 5.1 / 4.5, exp2 8.8 / 8.4; one wave
 // alone issues one every 6.2 whatever it is; a 32x32x32 MFMA runs beside them and takes about 8 issue cycles of its 34.
-// Hence three workgroups per compute unit instead of two -- tiles of 64 keys, one accumulator
-// pair live at a time, a single copy of the P V products --, no conversion of the sums (kBias), and nothing done for keys and rows
-// that are not there (MASKED).  (A shift fixed by the first tile instead of the running maximum, half an instruction per
-// score less, gained 1 %: the sums' last bits, and with them some codes, would no longer be those of a running maximum.)  Before / after, us: 288 heads x 1024^2 x 128 causal 130 /
-// 107, unmasked 169 / 162; 768 x 2048^2 x 128 causal 1057 / 935, unmasked 1738 / 1638; 96 x 777 x 1040 x 64 causal 67 / 41; 50 x 300 x 304 x 128
-// causal 26 / 16.
+// Hence three workgroups per compute unit instead of two -- tiles of 64 keys, one accumulator pair live at a time, a single copy
+// of the P V products --, no conversion of the sums where that pays (BIAS), and little done for keys and rows that are not
+// there (MASKED).  (A shift fixed by the first tile instead of the running maximum, half an instruction per score less,
+// gained 1 %: the sums' last bits, and with them some codes, would no longer be those of a running maximum.)  With two
+// workgroups per unit / now, us, timed in turn: 288 heads x 1024^2 x 128 causal 139 / 104, unmasked 184 / 171; 768 x 2048^2 x 128
+// causal 1066 / 930, unmasked 1768 / 1636; 288 x 1024^2 x 64 unmasked 132 / 126; 96 x 777 x 1040 x 64 64.5 / 61.
 #include <type_traits>
 
 #include "attn_args.h"
@@ -45,9 +45,9 @@ constexpr float kBiasF = __builtin_bit_cast(float, kBias);
 //                   sees every key), or any key count without a mask (coff >= s_k).  A workgroup stops after the last tile any
 //                   of its rows sees; a wave runs the plain tile body on the tiles all its 32 rows see in full, and nothing on
 //                   the tiles past its rows.  On the one or two tiles in between it takes the 32-key blocks one by one: those
-//                   its rows see in full without a mask, those they see in part with an element-wise one, the others not at
-//                   all (a whole-tile masked body cost 1.7 plain ones on every diagonal tile, of which a 32-row group sees
-//                   between one and four blocks).
+//                   its rows see in full without a mask, those they see in part with an element-wise one, of the others no
+//                   more than the products (a whole-tile masked body cost 1.7 plain ones on every diagonal tile, of which a
+//                   32-row group sees between one and four blocks).
 //   BIAS            see kBias below.
 template <bool BF16, int HD, bool MASKED, bool CODES, bool BIAS>
 __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)

@@ -2,7 +2,7 @@
 // and LayerNorm in FP16) fused with the quantization that feeds the next INT8 kernel, gfx950:
 //   * softmax over attention scores + quantization of P with the fixed step 1/127,
 //   * LayerNorm with the smoothing factors folded into gamma/beta + per-token dynamic quantization.
-// One row per 256-thread workgroup, the row held in registers: one HBM pass, 2 B in + 1 B out.
+// One row per wave or workgroup, held in registers: one HBM pass, 2 B in + 1 B out.
 #include "common.h"
 
 namespace {
@@ -29,28 +29,22 @@ SQ_DEVICE float fast_exp_shifted(float z, float nm) { return __builtin_amdgcn_ex
 // once, to nearest-even, like the separate multiply and add of code_bits.
 SQ_DEVICE uint32_t prob_code_bits(float p16) { return __builtin_bit_cast(uint32_t, __builtin_fmaf(p16, 127.0f, 12582912.0f)); }
 
-template <int NT = 256> SQ_DEVICE float block_max_r(float v, float* red)
+// Over the 256 threads of a workgroup.
+SQ_DEVICE float block_max_r(float v, float* red)
 {
     v = wave_max(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    float m = __builtin_fmaxf(__builtin_fmaxf(red[0], red[1]), __builtin_fmaxf(red[2], red[3]));
-#pragma unroll
-    for (int w = 4; w < NT / 64; w += 4)
-        m = __builtin_fmaxf(m, __builtin_fmaxf(__builtin_fmaxf(red[w], red[w + 1]), __builtin_fmaxf(red[w + 2], red[w + 3])));
-    return m;
+    return __builtin_fmaxf(__builtin_fmaxf(red[0], red[1]), __builtin_fmaxf(red[2], red[3]));
 }
-template <int NT = 256> SQ_DEVICE float block_sum_r(float v, float* red)
+SQ_DEVICE float block_sum_r(float v, float* red)
 {
     v = wave_sum(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    float t = (red[0] + red[1]) + (red[2] + red[3]);
-#pragma unroll
-    for (int w = 4; w < NT / 64; w += 4) t += (red[w] + red[w + 1]) + (red[w + 2] + red[w + 3]);
-    return t;
+    return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 SQ_DEVICE v2u pack8(const uint32_t (&q)[8])  // code_bits words -> 8 bytes
