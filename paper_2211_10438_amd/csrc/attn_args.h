@@ -10,7 +10,7 @@ struct AttnArgs {
     int8_t* P;        // optional [b][s_q, s_k]: the probability codes, for inspection; or NULL
     int s_q, s_k, tiles_m;  // tiles_m: workgroups (row blocks) per batch entry
     int batch, chunk;       // batch entries, and how many of them an XCD works on at a time
-    int causal, coff;       // query i sees the keys j <= min(i + coff, s_k - 1)
+    int coff;               // causal: query i sees the keys j <= i + coff
     int64_t stride_q, stride_k, stride_v, stride_o;  // batch strides in elements
     float alpha1, alpha2;
 };

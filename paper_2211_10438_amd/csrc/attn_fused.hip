@@ -23,7 +23,7 @@
 // alone issues one every 6.2 whatever it is; a 32x32x32 MFMA runs beside them and takes about 8 issue cycles of its 34.
 // Hence three workgroups per compute unit instead of two -- tiles of 64 keys, one accumulator pair live at a time, a single copy
 // of the P V products --, no conversion of the sums where that pays (BIAS), and little done for keys and rows that are not
-// there (MASKED).  (A shift fixed by the first tile instead of the running maximum, half an instruction per score less,
+// there (MASK).  (A shift fixed by the first tile instead of the running maximum, half an instruction per score less,
 // gained 1 %: the sums' last bits, and with them some codes, would no longer be those of a running maximum.)  With two
 // workgroups per unit / now, us, timed in turn: 288 heads x 1024^2 x 128 causal 139 / 104, unmasked 184 / 171; 768 x 2048^2 x 128
 // causal 1066 / 930, unmasked 1768 / 1636; 288 x 1024^2 x 64 unmasked 132 / 126; 96 x 777 x 1040 x 64 64.5 / 61.
@@ -38,20 +38,23 @@ constexpr int kIntMin = -2147483647 - 1;
 constexpr int kBias = 0x3e22f983;
 constexpr float kBiasF = __builtin_bit_cast(float, kBias);
 
-// MASKED: two instantiations, so that the common case carries no mask tests (with both in one kernel the register allocation
+// MASK: one instantiation each, so that the common case carries no mask tests (with them in one kernel the register allocation
 // spilled):
-//   MASKED = false  every query sees every key, and the key count is a multiple of 128;
-//   MASKED = true   query i sees the keys j <= min(i + p.coff, s_k - 1): the decoder's mask (coff = s_k - s_q: the last query
-//                   sees every key), or any key count without a mask (coff >= s_k).  A workgroup stops after the last tile any
-//                   of its rows sees; a wave runs the plain tile body on the tiles all its 32 rows see in full, and nothing on
-//                   the tiles past its rows.  On the one or two tiles in between it takes the 32-key blocks one by one: those
-//                   its rows see in full without a mask, those they see in part with an element-wise one, of the others no
-//                   more than the products (a whole-tile masked body cost 1.7 plain ones on every diagonal tile, of which a
-//                   32-row group sees between one and four blocks).
-//   BIAS            see kBias below.
-template <bool BF16, int HD, bool MASKED, bool CODES, bool BIAS>
+//   kAll     every query sees every key, and the key count is a multiple of 128;
+//   kTail    the same with any key count: on the last, partial tile the 16-key groups that are there (s_k % 16 == 0), all of them
+//            in full;
+//   kCausal  query i sees the keys j <= i + p.coff (coff = s_k - s_q: the last query sees every key).  A workgroup stops after the
+//            last tile any of its rows sees; a wave runs the plain tile body on the tiles all its 32 rows see in full, and
+//            nothing on the tiles past its rows.  On the one or two tiles in between it takes the 32-key blocks one by one:
+//            those its rows see in full without a mask, those they see in part with an element-wise one, of the others no
+//            more than the products (a whole-tile masked body cost 1.7 plain ones on every diagonal tile, of which a 32-row group
+//            sees between one and four blocks).
+// BIAS: see kBias below.
+constexpr int kAll = 0, kTail = 1, kCausal = 2;
+template <bool BF16, int HD, int MASK, bool CODES, bool BIAS>
 __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
 {
+    constexpr bool CAUSAL = MASK == kCausal, TAIL = MASK == kTail;
     constexpr int TK1 = 128, TK = HD == 64 ? 128 : 64;  // keys per tile of pass 1 (K only) and pass 2 (K and V)
     constexpr int KB = TK / 32;           // 32-key blocks per tile of pass 2
     constexpr int TILE = TK * HD;         // bytes of a K or V tile of pass 2
@@ -74,7 +77,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
     // (they share its K and V) run on one L2.  (32-bit: the grid has fewer than 2^31 workgroups, and a 64-bit division is a
     // hundred scalar instructions)
     AttnPlace at;
-    if (p.causal) {
+    if constexpr (CAUSAL) {
         at = attn_causal_place(blockIdx.x, (uint32_t)p.batch, (uint32_t)p.tiles_m, (uint32_t)p.chunk);
     } else {
         const uint32_t xcd = blockIdx.x & 7, j = blockIdx.x >> 3, tiles = (uint32_t)p.tiles_m;
@@ -93,7 +96,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
         // Keys the first and the last row of this wave see, and the last valid row of the workgroup (no row: none).  A tile that
         // ends at vmin or before is seen in full, one that starts at vmax or later not at all.
         int vmin = p.s_k, vmax = p.s_k, seen = p.s_k;
-        if constexpr (MASKED) {
+        if constexpr (CAUSAL) {
             const int last_row = m0 + 127 < p.s_q ? m0 + 127 : p.s_q - 1;
             auto sees = [&](int row) { return (int64_t)row + p.coff + 1 < p.s_k ? row + p.coff + 1 : p.s_k; };
             seen = sees(last_row);
@@ -105,7 +108,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
         const int nt1 = (seen + TK1 - 1) / TK1, nt = (seen + TK - 1) / TK;  // tiles of the two passes
         // key index of accumulator register 4 g + e of key block ks in tile j: TK j + 32 ks + 8 g + 4 h + e; it is visible
         // to this lane's row when 32 ks + 8 g + e <= rowlim - TK j
-        const int rowlim = (MASKED && (int64_t)w0 + r32 + p.coff < p.s_k - 1 ? w0 + r32 + p.coff : p.s_k - 1) - 4 * h;
+        const int rowlim = ((int64_t)w0 + r32 + p.coff < p.s_k - 1 ? w0 + r32 + p.coff : p.s_k - 1) - 4 * h;  // (kCausal)
 
         // ---- LDS images.  K tile: row n at n * HD, its 16-byte chunks XOR-permuted (position = chunk ^ swzK(n)) so
         // that the operand reads (32 rows, one chunk) spread over the banks.  V tile: row k at k * HD, position =
@@ -128,7 +131,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
             uint32_t o[LOADS];  // this lane's byte of the tile; rows past the last key (the last, partial tile) stay on it
 #pragma unroll
             for (int i = 0; i < LOADS; ++i) o[i] = (uint32_t)((lrow0 + i * 4 * RPB) * HD);
-            if (MASKED && k0 + LOADS * 4 * RPB > p.s_k) {
+            if (MASK != kAll && k0 + LOADS * 4 * RPB > p.s_k) {
                 const uint32_t last = (uint32_t)((p.s_k - 1 - k0) * HD);  // >= 0: the tile has a key
 #pragma unroll
                 for (int i = 0; i < LOADS; ++i) o[i] = o[i] < last ? o[i] : last;
@@ -223,42 +226,46 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
         float m_run = -__builtin_inff(), l_run = 0.0f;
         using Plain = std::false_type;
         using Masked = std::true_type;
-        // PART: a tile this wave's rows see in part: blocks jn < nfull in full, jn < nvis in part (keys up to lim)
+        // PART: a tile this wave's rows see in part: in units of 16 (kTail) or 32 (kCausal) keys, those below nfull in full, those
+        // below nvis in part (keys up to lim), the others not at all; with kTail nfull = nvis
+        constexpr int UNIT = TAIL ? 8 : 16;  // registers of a unit
         auto pass1_tile = [&](const char* kt, auto PART_, int lim, int nfull, int nvis) {
             constexpr bool PART = decltype(PART_)::value;
             v16i acc[4];
             scores(kt, acc, 4);  // (hidden blocks too: with the loads of the operands under a condition each MFMA waits for its own)
             int imax = kIntMin;
 #pragma unroll
-            for (int jn = 0; jn < 4; ++jn) {
-                if (PART && jn >= nvis) break;
-                if (PART && jn >= nfull) {
+            for (int u = 0; u < 64 / UNIT; ++u) {
+                if (PART && u >= nvis) break;
+                const int jn = u * UNIT / 16, r0 = u * UNIT % 16;
+                if (PART && CAUSAL && u >= nfull) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {  // register 4 g + e
+                    for (int r = r0; r < r0 + UNIT; ++r) {  // register 4 g + e
                         const int a = 32 * jn + 8 * (r >> 2) + (r & 3) <= lim ? acc[jn][r] : kIntMin;
                         imax = a > imax ? a : imax;
                     }
                 } else {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) imax = acc[jn][r] > imax ? acc[jn][r] : imax;
+                    for (int r = r0; r < r0 + UNIT; ++r) imax = acc[jn][r] > imax ? acc[jn][r] : imax;
                 }
             }
             const int other = __shfl_xor(imax, 32, 64);
             imax = other > imax ? other : imax;
             float s0, s1;
             s16f2(imax, imax, s0, s1);
-            const float m_new = PART && imax == kIntMin ? m_run : __builtin_fmaxf(m_run, s0);  // (a row may see nothing of a later tile)
+            const float m_new = PART && CAUSAL && imax == kIntMin ? m_run : __builtin_fmaxf(m_run, s0);  // (a row may see nothing of a later tile)
             l_run *= __builtin_amdgcn_exp2f((m_run - m_new) * kLog2e);
             m_run = m_new;
             const float nm = -m_new * kLog2e;
             float part = 0.0f;
 #pragma unroll
-            for (int jn = 0; jn < 4; ++jn) {
-                if (PART && jn >= nvis) break;
+            for (int u = 0; u < 64 / UNIT; ++u) {
+                if (PART && u >= nvis) break;
+                const int jn = u * UNIT / 16, r0 = u * UNIT % 16;
                 auto add = [&](auto EM_) {
                     constexpr bool EM = decltype(EM_)::value;
 #pragma unroll
-                    for (int r = 0; r < 16; r += 2) {
+                    for (int r = r0; r < r0 + UNIT; r += 2) {
                         s16f2(acc[jn][r], acc[jn][r + 1], s0, s1);
                         const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s0, kLog2e, nm));
                         const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s1, kLog2e, nm));
@@ -268,8 +275,12 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
                         part += (!EM || idx + 1 <= lim) ? e1 : 0.0f;
                     }
                 };
-                if (PART && jn >= nfull) add(Masked{});
-                else add(Plain{});
+                if constexpr (PART && CAUSAL) {
+                    if (u >= nfull) add(Masked{});
+                    else add(Plain{});
+                } else {
+                    add(Plain{});
+                }
             }
             l_run += part;
         };
@@ -285,8 +296,9 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
             else issue(0, (j + 1) & 1);
             const char* kt1 = smem + (2 * (j & 1)) * SLOT;
             const int k0 = j * TK1;
-            if (k0 + TK1 <= vmin) pass1_tile(kt1, Plain{}, 0, 4, 4);
-            else if (MASKED && k0 < vmax) pass1_tile(kt1, Masked{}, rowlim - k0, n_full(k0), n_vis(k0, 4));
+            if (k0 + TK1 <= vmin) pass1_tile(kt1, Plain{}, 0, 8, 8);
+            else if (CAUSAL && k0 < vmax) pass1_tile(kt1, Masked{}, rowlim - k0, n_full(k0), n_vis(k0, 4));
+            else if (TAIL && k0 < vmax) pass1_tile(kt1, Masked{}, 0, (vmax - k0) >> 4, (vmax - k0) >> 4);
         }
         // p = e^(s - m) / l = 2^(s log2(e) - (m log2(e) + log2(l))): the division is folded into the exponent
         const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
@@ -311,10 +323,14 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
             scores(kt, acc, nvis);
 #pragma unroll
             for (int ks = 0; ks < KB; ++ks) {
-                if (MASKED && ks >= nvis) break;
+                if (MASK != kAll && ks >= nvis) break;
                 v4i fp;  // the 16 codes of this lane: word g holds columns 8g + 4h + 0..3
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
+                    if (TAIL && g == 2 && partial && 32 * ks + 16 >= lim) {  // (lim: keys of the tile) the block's second group is not there
+                        fp[2] = fp[3] = 0;
+                        break;
+                    }
                     uint32_t ph[2];  // the probabilities of columns e = 0,1 and 2,3 as 16-bit pairs (the softmax output is a 16-bit tensor)
 #pragma unroll
                     for (int e = 0; e < 4; e += 2) {
@@ -325,7 +341,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
                     }
                     fp[g] = prob_codes4<BF16>(ph[0], ph[1]);
                 }
-                if (MASKED && partial) {
+                if (CAUSAL && partial) {
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
                         const int n = lim - (32 * ks + 8 * g) + 1;  // visible keys of the four (or more)
@@ -336,7 +352,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
                 if (CODES && Prow) {
 #pragma unroll
                     for (int g = 0; g < 4; ++g)
-                        if (!MASKED || j * TK + ks * 32 + 8 * g + 4 * h < p.s_k) *(int*)(Prow + j * TK + ks * 32 + 8 * g) = fp[g];
+                        if (MASK == kAll || j * TK + ks * 32 + 8 * g + 4 * h < p.s_k) *(int*)(Prow + j * TK + ks * 32 + 8 * g) = fp[g];
                 }
 #pragma unroll
                 for (int jn = 0; jn < NB; ++jn)
@@ -350,9 +366,9 @@ __global__ __launch_bounds__(256, 3) void attn_i8_kernel(const AttnArgs p)
             if (j + 1 < nt) issue(j + 1, stage ^ 1);
             const char* kt2 = smem + (2 * stage) * SLOT;
             const int k0 = j * TK;
-            if (k0 < vmax) pass2_tile(kt2, j, k0 + TK > vmin, rowlim - k0, MASKED ? n_vis(k0, KB) : KB);
+            if (k0 < vmax) pass2_tile(kt2, j, k0 + TK > vmin, TAIL ? vmax - k0 : rowlim - k0, MASK != kAll ? n_vis(k0, KB) : KB);
         }
-        if constexpr (MASKED && CODES) {
+        if constexpr (CAUSAL && CODES) {
             // the codes of the blocks this wave skipped are 0
             if (Prow)
                 for (int c = (vmax + 31) / 32 * 32; c + 4 * h < p.s_k; c += 8) *(int*)(Prow + c) = 0;  // (Prow already points at column 4 h)
@@ -434,26 +450,31 @@ static sq_status attention(int form, const int8_t* q, const int8_t* k, const int
         return sq_launch_status();
     }
     a.batch = (int)b;
-    a.causal = causal ? 1 : 0;
-    a.coff = causal ? (int)(s_k - s_q) : (int)s_k;
+    a.coff = (int)(s_k - s_q);  // (kCausal)
     a.chunk = attn_chunk(b, s_k, d);
     const dim3 grid((unsigned)(b * tiles_m)), block(256);
-    const bool masked = causal || (s_k & 127) != 0;
     // BIAS where vector issue bounds the kernel: with masks, and more than two workgroups for a compute unit.  A workgroup that
     // has its unit to itself waits for the longer start of each sum instead (us, without / with: 768 x 2048^2 x 128 causal 954 /
     // 931, 100 x 1900^2 x 128 causal 129 / 126, 96 x 777 x 1040 x 64 61.5 / 60.8; but 64 x 512^2 x 128 16.5 / 16.8, 288 x 1024^2 x
     // 64 125 / 129, 2 x 16384^2 x 128 causal 421 / 428).
-    const bool bias = masked && !p_codes && b * tiles_m > 512;
+    const int mask = causal ? kCausal : (s_k & 127) != 0 ? kTail : kAll;
+    const bool bias = mask != kAll && !p_codes && b * tiles_m > 512;
     // The kernel's scores carry a factor 2^-26 then.  A factor beyond 2^101 makes every difference of two scores infinite for
     // the softmax, like 2^101 itself.
     if (bias) a.alpha1 = (alpha1 < 0x1p+101f ? alpha1 : 0x1p+101f) * 0x1p+26f;
-#define SQ_ATTN(BF, HD)                                                                                       \
-    do {                                                                                                      \
-        if (p_codes && masked) sq_launch((attn_i8_kernel<BF, HD, true, true, false>), grid, block, 0, st, a); \
-        else if (p_codes) sq_launch((attn_i8_kernel<BF, HD, false, true, false>), grid, block, 0, st, a);     \
-        else if (bias) sq_launch((attn_i8_kernel<BF, HD, true, false, true>), grid, block, 0, st, a);         \
-        else if (masked) sq_launch((attn_i8_kernel<BF, HD, true, false, false>), grid, block, 0, st, a);      \
-        else sq_launch((attn_i8_kernel<BF, HD, false, false, false>), grid, block, 0, st, a);                 \
+#define SQ_ATTN_K(BF, HD, MASK, CODES, BIAS) sq_launch((attn_i8_kernel<BF, HD, MASK, CODES, BIAS>), grid, block, 0, st, a)
+#define SQ_ATTN_M(BF, HD, MASK)                                  \
+    do {                                                         \
+        if (p_codes) SQ_ATTN_K(BF, HD, MASK, true, false);       \
+        else if (bias) SQ_ATTN_K(BF, HD, MASK, false, true);     \
+        else SQ_ATTN_K(BF, HD, MASK, false, false);              \
+    } while (0)
+#define SQ_ATTN(BF, HD)                                          \
+    do {                                                         \
+        if (mask == kCausal) SQ_ATTN_M(BF, HD, kCausal);         \
+        else if (mask == kTail) SQ_ATTN_M(BF, HD, kTail);        \
+        else if (p_codes) SQ_ATTN_K(BF, HD, kAll, true, false);  \
+        else SQ_ATTN_K(BF, HD, kAll, false, false);              \
     } while (0)
     if (d == 128) {
         if (out == SQ_BF16) SQ_ATTN(true, 128); else SQ_ATTN(false, 128);
@@ -461,6 +482,8 @@ static sq_status attention(int form, const int8_t* q, const int8_t* k, const int
         if (out == SQ_BF16) SQ_ATTN(true, 64); else SQ_ATTN(false, 64);
     }
 #undef SQ_ATTN
+#undef SQ_ATTN_M
+#undef SQ_ATTN_K
     return sq_launch_status();
 }
 
