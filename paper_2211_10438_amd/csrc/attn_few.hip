@@ -322,29 +322,33 @@ bool sq_attn_few_possible(int64_t batch, int64_t s_q, int64_t s_k)
 // Which of the two forms, by a model of the time of both in microseconds: a launch takes what its longest workgroup takes, or, with
 // more workgroups, what the whole work takes spread over the 256 compute units.  This form's 16-row blocks fill the chip early
 // and finish early, but each reads K and V once more, out of L2; the row-block form computes 128 rows per workgroup whatever s_q
-// is, and one, two and three workgroups on a compute unit take 1, 1.5 and 2.5 times as long.  Fitted to 790 shapes of 1 to 900
-// heads, 1 to 2048 queries and 16 to 12000 keys, both forms and the earlier row-block version timed in turn; the choice costs 0.3 %
-// against the better form, and 30 shapes take the worse one by more than 3 %, up to 22 % (450 x 21 x 640 x 128).  The line, us, this
-// form / row blocks: 768 x 1 x 2048 x 128 66 / 139, 13 x 320^2 x 64 7.7 / 10.4, 64 x 208 x 1040 x 64 22.3 / 25.0, but 123 x 208 x
-// 1040 x 64 34 / 26, 51 x 208^2 x 128 13.9 / 10.5, 42 x 320^2 x 128 18.9 / 12.9.
+// is, and one, two and three workgroups on a compute unit take 1, 1.5 and 2.3 times as long.  Fitted to 1190 shapes of 1 to 900
+// heads, 1 to 2048 queries and 16 to 12000 keys, both forms and the earlier row-block version timed in turn.  The choice costs
+// 0.3 % against the better form on the mean; 41 shapes take the worse one by more than 3 %, three by more than 16 % (528 x 4 x 96 x
+// 128, 450 x 21 x 640 x 128 and 39 x 179 x 320 x 128: 1.19 to 1.34); none is slower than the earlier version by more than 4 %.  The
+// line, us, this form / row blocks: 768 x 1 x 2048 x 128 66 / 139, 13 x 320^2 x 64 7.7 / 10.4, 64 x 208 x 1040 x 64 22.3 / 24.6, but 123 x
+// 208 x 1040 x 64 34 / 26, 51 x 208^2 x 128 13.9 / 10.1, 42 x 320^2 x 128 18.9 / 12.8.
 bool sq_attn_few_eligible(int64_t batch, int64_t s_q, int64_t s_k, int64_t d, bool causal)
 {
     if (!sq_attn_few_possible(batch, s_q, s_k)) return false;
-    const double keys = causal ? (double)s_k - 0.5 * (double)(s_q - 1) : (double)s_k;  // a query sees on average
+    const double rows = (double)(s_q - 1), all = (double)s_k;
     auto larger = [](double a, double b) { return a > b ? a : b; };
 
     const double row_per_cu = (double)batch * (double)((s_q + 127) / 128) / 256.0;
-    const double crowd = row_per_cu <= 1.0 ? 1.0 : row_per_cu <= 2.0 ? 1.5 : row_per_cu <= 3.0 ? 2.5 : 2.5 / 3.0 * row_per_cu;
-    const double row_us = d == 64 ? larger(4.1 + 0.021 * (double)s_k, 4.1 + 0.021 * keys * crowd)
-                                  : larger(5.0 + 0.0265 * (double)s_k, 5.0 + 0.0265 * keys * crowd);
+    const double row_keys = causal ? all - 0.5 * rows : all;  // a query sees on average
+    auto row_form = [&](double start, double diagonal, double tile_ends, double per_key, double two, double three) {
+        const double crowd = row_per_cu <= 1.0 ? 1.0 : row_per_cu <= 2.0 ? two : row_per_cu <= 3.0 ? three : three / 3.0 * row_per_cu;
+        return start + (causal ? diagonal : 0.0) + per_key * larger(all + tile_ends, (row_keys + tile_ends) * crowd);
+    };
+    const double row_us = d == 64 ? row_form(2.4, 0.9, 44.0, 0.021, 1.5, 2.4) : row_form(2.0, 1.0, 78.0, 0.0265, 1.4, 2.25);
 
     const double few_wg = (double)batch * (double)((s_q + 15) / 16), few_per_cu = few_wg / 256.0;
     const int64_t groups = (s_k + 127) / 128, waves = few_waves(few_wg, s_k), per_wave = (groups + waves - 1) / waves;
-    const double few_keys = causal ? (double)s_k - 0.4 * (double)(s_q - 1) : (double)s_k;  // (its long blocks do not start first)
+    const double few_keys = causal ? all - 0.4 * rows : all;  // (its long blocks do not start first)
     const bool many_keys = s_k > 4 * 8 * 128;  // one workgroup of eight waves on a compute unit at a time
     const double few_us = d == 64 ? larger(4.5 + 0.9 * (double)per_wave + 0.38 * (double)groups, 5.4 + (0.87 + (many_keys ? 0.004 : 0.003) * few_keys) * few_per_cu)
                                   : larger(5.6 + 0.9 * (double)groups, 5.4 + (2.1 + (many_keys ? 0.009 : 0.006) * few_keys) * few_per_cu);
-    return few_us < 0.96 * row_us;
+    return few_us < 0.95 * row_us;
 }
 
 void sq_attn_few_launch(AttnArgs a, int64_t batch, int64_t d, bool bf16, bool causal, hipStream_t st)

@@ -43,6 +43,9 @@ def test_causal_order_is_complete_and_spread_over_the_xcds(b, s, d):
     (200, 100, 512, 64, 0, 1),    # 17.4 / 12.4
     (89, 144, 256, 128, 0, 1),    # 17.2 / 9.9
     (82, 320, 320, 64, 0, 1),     # 18.3 / 10.8
+    (1, 12, 96, 64, 0, 1),        # 5.5 / 4.8
+    (153, 27, 160, 64, 0, 1),     # 7.7 / 6.7
+    (6, 100, 128, 128, 1, 2),     # 6.7 / 8.7: the row blocks' diagonal
     (4, 8192, 8192, 128, 1, 1),   # 363 / 219
     (5, 5008, 5008, 128, 1, 1),   # 196 / 134
     (12, 2048, 2048, 128, 1, 1),  # 66 / 58
