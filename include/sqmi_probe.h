@@ -34,8 +34,19 @@ sq_status sq_probe_attention(int form, int causal, const int8_t* q, const int8_t
                              int64_t stride_q, int64_t stride_k, int64_t stride_v, int64_t stride_o, int8_t* p_codes,
                              void* stream);
 
-/* 1 where a linear layer of this size runs the kernel for few tokens and few output channels, else 0.  No GPU work. */
+/* 1 where a linear layer of this size counts as one of few tokens and few output channels (direct kernel, never a workspace), else 0.
+ * No GPU work. */
 int sq_probe_narrow_gemm(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout);
+
+/* sq_w8a8_linear by the direct kernel (operands from memory into MFMA registers, K dealt to the waves of a workgroup) with tiles of
+ * 16 mb tokens x 16 nb channels and nw waves, whatever the library would choose; SQ_ERR_UNSUPPORTED where that combination is not
+ * built.  Other arguments, checks and results are those of sq_w8a8_linear. */
+sq_status sq_probe_linear_blocks(int mb, int nb, int nw, const int8_t* xq, const float* x_scale, int x_scale_per_token, const int8_t* wq,
+                                 const float* w_scale, int w_scale_per_channel, const float* bias, const void* residual, int relu,
+                                 void* y, sq_dtype out, int64_t t, int64_t c_i, int64_t c_o, sq_layout layout, void* stream);
+
+/* 100 mb + 10 nb + nw where a linear layer of this size runs the direct kernel, 0 where it runs another.  No GPU work. */
+int sq_probe_linear_form(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout);
 
 #ifdef __cplusplus
 }

@@ -71,17 +71,40 @@ SQ_DEVICE uint32_t dequant_pair(int acc0, int acc1, float c0, float c1, float bi
     return dequant_pair_f<BF16>((float)acc0, (float)acc1, c0, c1, bias0, bias1, has_bias, relu, res_pair, has_res);
 }
 
-// Weight-streaming GEMM for few-token shapes (gemm_i8_stream.hip).  sq_stream_gemm_splits returns 0
-// when the shape is left to the tile kernels, else the number of K splits of its plan: 1 = the kernel
-// writes the final output itself; > 1 = it writes int32 partial sums to a.acc_out[splits][M][N] (which
-// the caller points at a workspace) and the split-K reduction kernel finishes the job.
-int sq_stream_gemm_splits(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled);
-void sq_stream_gemm_launch(const GemmArgs& a, bool to_i32, bool bf16, bool tiled, hipStream_t st);
+// Weight-streaming GEMM for few-token shapes (gemm_i8_stream.hip).  No plan: the shape is left to the tile kernels.  Without a K split
+// (gk = 1) the kernel writes the final output itself; with one it writes int32 partial sums to a.acc_out[gk][M][N] (which the
+// caller points at a workspace) and the split-K reduction kernel finishes the job.
+struct StreamArgs {
+    int gn;          // slabs (workgroups along C_o)
+    int gk;          // K splits (workgroups along K); > 1: int32 partials go to acc_out[gk][M][N]
+    int units;       // 16-column units of N
+    int na;          // 16-row blocks of A
+    int ksub;        // 64-byte K steps per stage
+    int iters;       // stages per workgroup: K / 64 / gk / ksub
+    int nt_w;        // weight loads carry the non-temporal hint
+    int regs;        // the register-direct kernel (tiled operands) runs this plan
+    int tiled, to_i32, bf16;
+    double us;       // modelled time of the plan
+};
+bool sq_stream_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, StreamArgs* out);
+void sq_stream_gemm_launch(const GemmArgs& a, StreamArgs q, bool to_i32, bool bf16, bool tiled, hipStream_t st);
 
 // Strip kernel for attention scores (bmm_strip.hip): B = [N, K] with K <= 128, alpha-only epilogue.
 bool sq_strip_bmm_eligible(int64_t M, int64_t N, int64_t K, int64_t batch);
 void sq_strip_bmm_launch(const GemmArgs& a, int batch, bool bf16, hipStream_t st);
 
-// Few tokens, few output channels (gemm_i8_narrow.hip): one kernel, no workspace.
-bool sq_narrow_gemm_eligible(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled);
-void sq_narrow_gemm_launch(const GemmArgs& a, bool to_i32, bool bf16, bool tiled, hipStream_t st);
+// Few output tiles for the chip (gemm_direct.h): 16 mb tokens x 16 nb channels per workgroup of nw waves, one kernel, no workspace.
+// False: no such instantiation.
+struct DirectArgs {
+    int tiles_m, tiles_n;
+    int n_outer;  // the tiles are walked token tiles first (1: those of one channel tile side by side) or channel tiles first (0)
+    int to_i32, bf16;
+};
+struct DirectPlan {
+    int mb, nb, nw;  // 0: none
+    double us;       // modelled time
+};
+DirectPlan sq_direct_gemm_plan(int64_t M, int64_t N, int64_t K, bool tiled);
+bool sq_direct_gemm_launch(const GemmArgs& a, int mb, int nb, int nw, bool to_i32, bool bf16, bool tiled, hipStream_t st);
+bool sq_direct_gemm_launch_tiled(const GemmArgs& a, const DirectArgs& q, int mb, int nb, int nw, hipStream_t st);
+bool sq_direct_gemm_launch_rows(const GemmArgs& a, const DirectArgs& q, int mb, int nb, int nw, hipStream_t st);

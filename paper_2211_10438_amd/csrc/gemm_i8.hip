@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "gemm_args.h"
+#include "sqmi_probe.h"
 
 namespace {
 
@@ -802,6 +803,49 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool allow_split,
     return pl;
 }
 
+// Time of a tile plan against the direct kernel, microseconds, calibrated on 290 shapes (5 to 12 % rms): rounds of tiles, K steps in
+// them, the K split's second kernel and its partial sums, the output, the weights.  [row-major, tiled]
+double tile_us(const Plan& pl, double M, double N, double K, bool tiled)
+{
+    const double rounds = (double)(((int64_t)pl.tiles_m * pl.tiles_n * pl.splits + kNumCU - 1) / kNumCU);
+    const double steps = rounds * pl.iters_per_split, out = M * N * 1e-6, w = N * K * 1e-6;
+    const double split = pl.splits > 1 ? 1.0 : 0.0, part = pl.splits > 1 ? pl.splits * out : 0.0;
+    switch (pl.bm) {
+        case 256:
+            return tiled ? 2.3 + 2.65 * rounds + steps * (0.50 * pl.bn / 256.0 + 0.087) + 3.3 * split + 1.59 * part + 0.84 * out
+                         : 3.96 * rounds + steps * (0.79 * pl.bn / 256.0 + 0.035) + 4.8 * split + 1.64 * part + 0.84 * out;
+        case 128:
+            if (K <= 256.0) return 6.0 + 1.2 * (double)pl.tiles_m * pl.tiles_n / kNumCU;
+            return tiled ? 2.2 * rounds + 0.423 * steps + 8.2 * split + 1.33 * part : 8.8 * rounds + 0.381 * steps + 2.3 * split + 2.01 * part;
+        case 64:
+            return tiled ? 9.4 + 0.287 * steps + 1.16 * part : 1.7 + 3.6 * rounds + 0.563 * steps + 1.3 * split + 1.98 * part + 0.045 * w;
+        default:
+            return tiled ? 8.0 * rounds + 0.292 * steps + 2.04 * part + 0.074 * w
+                         : 1.3 + 3.8 * rounds + 0.295 * steps + 3.5 * split + 2.23 * part + 0.141 * w;
+    }
+}
+
+// Sizes of few tokens and few channels, by the shape alone: they have never asked for a workspace (sq_workspace_bytes keeps to
+// that line), and the direct kernel is ahead in all of them, or level.
+bool few_channels(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled)
+{
+    if (batch != 1 || M < 1 || M > 128) return false;
+    if (N >= 16 * 256) {
+        const int64_t units = (N + 15) / 16;
+        return tiled && M <= 16 && units > 256 && units < 410 && !(M <= 2 && K >= 512 && K <= 2048 && units > 264);
+    }
+    if (!tiled && M > 4) {
+        if (K > 1024) return false;
+        if (K % 128 != 0) return true;
+        return N <= 3072 && !(M > 24 && M <= 32 && K > 640) && !(M > 40 && M <= 64 && K > 768);
+    }
+    if (tiled && M > 32 && N > 3584 && K > 14336) return false;
+    const double per_k = !tiled ? 0.80e-3 : M <= 16 ? 0.62e-3 : M <= 32 ? 0.85e-3 : M <= 64 ? 1.27e-3 : 2.0e-3;
+    const double this_us = (tiled ? 3.6 : 5.0) + per_k * (double)K;
+    const double others_us = 8.0 + (double)N * (double)K / 3.6e6 + 0.05 * (double)M;
+    return this_us < 0.9 * others_us;
+}
+
 template <int EPI, bool BF16>
 void launch_cfg(const Plan& pl, const GemmArgs& a, int batch, hipStream_t st, bool tiled)
 {
@@ -840,6 +884,40 @@ void launch_cfg(const Plan& pl, const GemmArgs& a, int batch, hipStream_t st, bo
 #undef SQ_LAUNCH_MF
 }
 
+// Which kernel a call runs.  Apart from the shapes of few tokens and few channels (direct kernel, no further plan) there is always a
+// streaming or a tile plan; the direct kernel takes the call where it is modelled to be ahead of it.
+struct Path {
+    bool stream, tiles;
+    DirectPlan direct;
+};
+Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool b_transposed, bool allow_split, StreamArgs* sp, Plan* pl)
+{
+    Path p{};
+    const bool single = !b_transposed && batch == 1;
+    const DirectPlan dp = single ? sq_direct_gemm_plan(M, N, K, tiled) : DirectPlan{};
+    if (dp.mb && few_channels(M, N, K, batch, tiled)) {
+        p.direct = dp;
+        return p;
+    }
+    double us;
+    if (!b_transposed && sq_stream_gemm_plan(M, N, K, batch, tiled, sp) && (sp->gk == 1 || allow_split)) {  // (else the tile kernels)
+        p.stream = true;
+        us = sp->us;
+    } else {
+        p.tiles = true;
+        *pl = make_plan(M, N, K, batch, allow_split, b_transposed);
+        us = single ? tile_us(*pl, (double)M, (double)N, (double)K, tiled) : 0.0;
+    }
+    // The margins keep the models' errors from costing where the kernels are close: at 0.84 (row-major 256-row tiles 0.76) against the
+    // register-direct stream and the 256-row tiles (which those errors would make 1.1 to 1.4 times slower in six of 230 shapes at 0.97) and
+    // 0.90 against the others, 5 of 590 shapes lose more than 2 %, and the mean over all is 0.78 of the time without the direct kernel.  A long K range on few
+    // workgroups is one long chain per wave: the K split keeps it (11 x 15680 -> 248 13.3 / 10.9 us).
+    const double margin = p.tiles && pl->bm == 256 ? (tiled ? 0.84 : 0.76) : p.stream && sp->regs ? 0.84 : 0.90;
+    const bool chain = K > 12288 && dp.mb && ((M + 16 * dp.mb - 1) / (16 * dp.mb)) * ((N + 16 * dp.nb - 1) / (16 * dp.nb)) < 24;
+    if (dp.mb && !chain && dp.us < margin * us) p.direct = dp;
+    return p;
+}
+
 // allow_split = false: the caller has no workspace to offer (sq_w8a8_bmm), so only plans that finish in one kernel
 // are considered.
 sq_status run_gemm(GemmArgs a, int64_t batch, bool to_i32, bool bf16, void* workspace, size_t ws_bytes, hipStream_t st,
@@ -859,39 +937,31 @@ sq_status run_gemm(GemmArgs a, int64_t batch, bool to_i32, bool bf16, void* work
         else if (bf16) sq_launch((splitk_reduce_kernel<true, 1>), dim3(blocks), dim3(256), 0, st, a, to_i32 ? 1 : 0);
         else sq_launch((splitk_reduce_kernel<false, 1>), dim3(blocks), dim3(256), 0, st, a, to_i32 ? 1 : 0);
     };
-    if (!b_transposed && sq_narrow_gemm_eligible(a.M, a.N, a.K, batch, tiled)) {
-        sq_narrow_gemm_launch(a, to_i32, bf16, tiled, st);
+    StreamArgs sp{};
+    Plan pl{};
+    const Path path = choose(a.M, a.N, a.K, batch, tiled, b_transposed, allow_split, &sp, &pl);
+    // (a shape whose streaming or tile plan splits K is asked for its workspace also where the direct kernel, which has no use for it,
+    // takes the call)
+    const int splits = path.stream ? sp.gk : path.tiles ? pl.splits : 1;
+    if (splits > 1 && (!workspace || ws_bytes < (size_t)splits * total * sizeof(int32_t))) return SQ_ERR_WORKSPACE;
+    if (path.direct.mb) {
+        sq_direct_gemm_launch(a, path.direct.mb, path.direct.nb, path.direct.nw, to_i32, bf16, tiled, st);
         return sq_launch_status();
     }
-    int ss = b_transposed ? 0 : sq_stream_gemm_splits(a.M, a.N, a.K, batch, tiled);
-    if (ss > 1 && !allow_split) ss = 0;  // the streaming plan wants a K split: leave the shape to the tile kernels
-    if (ss) {
-        // few tokens, wide C_o: stream W once through one workgroup per CU
-        if (ss > 1) {
-            const size_t need = (size_t)ss * total * sizeof(int32_t);
-            if (!workspace || ws_bytes < need) return SQ_ERR_WORKSPACE;
-            void* final_out = to_i32 ? (void*)a.acc_out : a.C;
-            a.acc_out = (int32_t*)workspace;
-            a.splits = ss;
-            sq_stream_gemm_launch(a, true, false, tiled, st);
-            reduce(final_out);
-        } else {
-            sq_stream_gemm_launch(a, to_i32, bf16, tiled, st);
-        }
-        return sq_launch_status();
+    if (!path.stream) {
+        a.tiles_m = pl.tiles_m;
+        a.tiles_n = pl.tiles_n;
+        a.iters_per_split = pl.iters_per_split;
     }
-    Plan pl = make_plan(a.M, a.N, a.K, batch, allow_split, b_transposed);
-    a.tiles_m = pl.tiles_m;
-    a.tiles_n = pl.tiles_n;
-    a.splits = pl.splits;
-    a.iters_per_split = pl.iters_per_split;
-    if (pl.splits > 1) {
-        const size_t need = (size_t)pl.splits * a.M * a.N * sizeof(int32_t);
-        if (!workspace || ws_bytes < need) return SQ_ERR_WORKSPACE;
+    a.splits = splits;
+    if (splits > 1) {
         void* final_out = to_i32 ? (void*)a.acc_out : a.C;
         a.acc_out = (int32_t*)workspace;
-        launch_cfg<EPI_I32, false>(pl, a, 1, st, tiled);
+        if (path.stream) sq_stream_gemm_launch(a, sp, true, false, tiled, st);
+        else launch_cfg<EPI_I32, false>(pl, a, 1, st, tiled);
         reduce(final_out);
+    } else if (path.stream) {
+        sq_stream_gemm_launch(a, sp, to_i32, bf16, tiled, st);
     } else if (to_i32) {
         launch_cfg<EPI_I32, false>(pl, a, (int)batch, st, tiled);
     } else if (bf16) {
@@ -916,9 +986,10 @@ extern "C" {
 size_t sq_gemm_workspace_bytes(int64_t t, int64_t c_i, int64_t c_o)
 {
     if (!dims_ok(t, c_i, c_o)) return 0;
-    if (sq_narrow_gemm_eligible(t, c_o, c_i, 1, false) && sq_narrow_gemm_eligible(t, c_o, c_i, 1, true)) return 0;
+    if (few_channels(t, c_o, c_i, 1, false) && few_channels(t, c_o, c_i, 1, true)) return 0;
     // the layout is not known here: enough for the plan of either
-    const int ss_rows = sq_stream_gemm_splits(t, c_o, c_i, 1, false), ss_tiled = sq_stream_gemm_splits(t, c_o, c_i, 1, true);
+    StreamArgs rows{}, tiles{};
+    const int ss_rows = sq_stream_gemm_plan(t, c_o, c_i, 1, false, &rows) ? rows.gk : 0, ss_tiled = sq_stream_gemm_plan(t, c_o, c_i, 1, true, &tiles) ? tiles.gk : 0;
     if (const int ss = ss_rows > ss_tiled ? ss_rows : ss_tiled) return ss > 1 ? (size_t)ss * t * c_o * sizeof(int32_t) : 0;
     Plan pl = make_plan(t, c_o, c_i, 1, true);
     return pl.splits > 1 ? (size_t)pl.splits * t * c_o * sizeof(int32_t) : 0;
@@ -945,6 +1016,42 @@ sq_status sq_w8a8_linear(const int8_t* xq, const float* x_scale, int x_scale_per
     a.w_per_channel = w_scale_per_channel ? 1 : 0;
     a.bias = bias; a.residual = residual; a.relu = relu ? 1 : 0;
     return run_gemm(a, 1, false, out == SQ_BF16, workspace, ws_bytes, (hipStream_t)stream, false, layout == SQ_TILED);
+}
+
+int sq_probe_narrow_gemm(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout)
+{
+    return t > 0 && c_i > 0 && c_o > 0 && few_channels(t, c_o, c_i, 1, layout == SQ_TILED) ? 1 : 0;
+}
+
+int sq_probe_linear_form(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout)
+{
+    if (!dims_ok(t, c_i, c_o)) return 0;
+    StreamArgs sp{};
+    Plan pl{};
+    const DirectPlan d = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, &sp, &pl).direct;
+    return 100 * d.mb + 10 * d.nb + d.nw;
+}
+
+// Measurement and test aid: sq_w8a8_linear by the direct kernel with tiles of 16 mb tokens x 16 nb channels.
+sq_status sq_probe_linear_blocks(int mb, int nb, int nw, const int8_t* xq, const float* x_scale, int x_scale_per_token, const int8_t* wq,
+                                 const float* w_scale, int w_scale_per_channel, const float* bias, const void* residual, int relu,
+                                 void* y, sq_dtype out, int64_t t, int64_t c_i, int64_t c_o, sq_layout layout, void* stream)
+{
+    if (!xq || !x_scale || !wq || !w_scale || !y) return SQ_ERR_NULL;
+    if (!dims_ok(t, c_i, c_o)) return SQ_ERR_SHAPE;
+    if (out != SQ_F16 && out != SQ_BF16) return SQ_ERR_UNSUPPORTED;
+    if (layout != SQ_ROW_MAJOR && layout != SQ_TILED) return SQ_ERR_UNSUPPORTED;
+    if (layout == SQ_TILED && (c_i & 63)) return SQ_ERR_ALIGN;
+    if ((c_i & 15) || !sq_aligned16(xq) || !sq_aligned16(wq) || !sq_aligned16(y) || (residual && !sq_aligned16(residual))) return SQ_ERR_ALIGN;
+    GemmArgs a{};
+    a.A = xq; a.B = wq;
+    a.M = (int)t; a.N = (int)c_o; a.K = (int)c_i;
+    a.lda = c_i; a.ldb = c_i;
+    a.C = y; a.x_scale = x_scale; a.per_token = x_scale_per_token ? 1 : 0; a.w_scale = w_scale;
+    a.w_per_channel = w_scale_per_channel ? 1 : 0;
+    a.bias = bias; a.residual = residual; a.relu = relu ? 1 : 0;
+    if (!sq_direct_gemm_launch(a, mb, nb, nw, false, out == SQ_BF16, layout == SQ_TILED, (hipStream_t)stream)) return SQ_ERR_UNSUPPORTED;
+    return sq_launch_status();
 }
 
 sq_status sq_w8a8_linear_q8(const int8_t* xq, const float* x_scale, int x_scale_per_token, const int8_t* wq,
