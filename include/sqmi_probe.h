@@ -48,6 +48,9 @@ sq_status sq_probe_linear_blocks(int mb, int nb, int nw, const int8_t* xq, const
 /* 100 mb + 10 nb + nw where a linear layer of this size runs the direct kernel, 0 where it runs another.  No GPU work. */
 int sq_probe_linear_form(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout);
 
+/* 1000000 s + 1000 m + n where it runs m x n tiles staged through LDS with s K splits, else 0.  No GPU work. */
+int sq_probe_linear_tile(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout);
+
 #ifdef __cplusplus
 }
 #endif

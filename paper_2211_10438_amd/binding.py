@@ -27,7 +27,7 @@ EXPORTS = (
     "sq_softmax_quant_p", "sq_ln_quantize", "sq_workspace_bytes", "sq_tiled_bytes", "sq_probe_mfma_i8",
     "sq_w8a8_linear_noalloc", "sq_static_scratch_bytes", "sq_w8a8_attention", "sq_w8a8_attention_causal",
     "sq_probe_attention", "sq_probe_attention_form", "sq_probe_attention_place",
-    "sq_probe_narrow_gemm", "sq_probe_linear_form", "sq_probe_linear_blocks",
+    "sq_probe_narrow_gemm", "sq_probe_linear_form", "sq_probe_linear_tile", "sq_probe_linear_blocks",
 )
 
 
@@ -68,7 +68,7 @@ def lib() -> ctypes.CDLL:
         L.sq_probe_attention.argtypes = [i32, i32, *L.sq_w8a8_attention.argtypes]
         L.sq_probe_attention_form.argtypes = [i64, i64, i64, i64, i32]
         L.sq_probe_attention_place.argtypes = [i64, i64, i64, i64, i64, ctypes.POINTER(i64)]
-        L.sq_probe_narrow_gemm.argtypes = L.sq_probe_linear_form.argtypes = [i64, i64, i64, i32]
+        L.sq_probe_narrow_gemm.argtypes = L.sq_probe_linear_form.argtypes = L.sq_probe_linear_tile.argtypes = [i64, i64, i64, i32]
         L.sq_probe_linear_blocks.argtypes = [i32, i32, i32, *L.sq_w8a8_linear.argtypes[:15], vp]
         L.sq_softmax_quant_p.argtypes = [vp, i32, i64, i64, vp, vp]
         L.sq_ln_quantize.argtypes = [vp, i32, i64, i64, vp, vp, f32, vp, vp, i32, vp]

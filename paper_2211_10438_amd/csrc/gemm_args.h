@@ -40,6 +40,12 @@ template <bool BF16> SQ_DEVICE int requant_code(uint32_t bits16, float r)
 
 template <int N> SQ_DEVICE void wait_vmcnt_imm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
+// 16 bytes per lane from a buffer into LDS (lane l to dst + 16 l); what lies outside the buffer arrives as zeros and costs no traffic.
+template <bool NT> SQ_DEVICE void buffer_to_lds(__amdgpu_buffer_rsrc_t r, char* dst, uint32_t lane_offset, int offset)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, LPTR(dst), 16, (int)lane_offset, offset, 0, NT ? 2 : 0);
+}
+
 // Outer-dimension scaling of Eq. 2 on one accumulator: (float)acc * c, then the optional terms in the
 // order bias, ReLU, residual, then one rounding to the 16-bit output type.
 template <bool BF16>

@@ -35,11 +35,6 @@ constexpr int ring_depth(int mb, int nb)
     return d < 2 ? 0 : d > 4 ? 4 : d;
 }
 
-template <bool NT> SQ_DEVICE void buffer_to_lds(__amdgpu_buffer_rsrc_t r, char* dst, uint32_t lane_offset, int offset)
-{
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, LPTR(dst), 16, (int)lane_offset, offset, 0, NT ? 2 : 0);
-}
-
 template <int MB, int NB, int NW, bool TILED, bool NT>
 __global__ __launch_bounds__(NW * 64, 2) void gemm_i8_direct_kernel(const GemmArgs p, const DirectArgs q)
 {

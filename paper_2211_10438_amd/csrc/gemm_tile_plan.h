@@ -1,0 +1,23 @@
+// Plan of the LDS-staged tile kernels, shared by the host side and the translation units that hold their instantiations.
+#pragma once
+#include "gemm_args.h"
+
+struct TilePlan {
+    int cfg;     // 0: 256x256 (prefill)  1: 128x256  2: 64x256  3: 32x256  5: 256x128 B^T  6: 256x192
+                 // 7: 128x128, three workgroups per CU (short K: the output stream dominates)
+                 // 8: 128x128, K <= 128 fetched in one go, four workgroups per CU
+                 // 9: 256x384 (a round of tiles saved on wide outputs)
+                 // 10, 11, 12: 256x256, 256x384 and 256x192 with the 16x16x64 MFMA
+    int bm, bn;
+    int splits, iters_per_split;
+    int tiles_m, tiles_n;
+};
+
+// The tiles of a plan: EPI_DEQUANT into a.C (or a.q8_out), or int32 sums into a.acc_out.
+void sq_tile_gemm_launch_rows(const TilePlan& pl, const GemmArgs& a, bool to_i32, bool bf16, int batch, hipStream_t st);
+void sq_tile_gemm_launch_tiled(const TilePlan& pl, const GemmArgs& a, bool to_i32, bool bf16, int batch, hipStream_t st);
+static inline void tile_gemm_launch(const TilePlan& pl, const GemmArgs& a, bool to_i32, bool bf16, int batch, hipStream_t st, bool tiled)
+{
+    if (tiled) sq_tile_gemm_launch_tiled(pl, a, to_i32, bf16, batch, st);
+    else sq_tile_gemm_launch_rows(pl, a, to_i32, bf16, batch, st);
+}

@@ -1,0 +1,30 @@
+"""The tiles that take K in pairs of steps (256 x 160, 256 x 128, 192 x 224, 192 x 160), in both layouts: ragged tokens and channels, odd
+numbers of steps, a last step of one to three chunks, K splits.  Against the exact integer product and the fixed fp32 epilogue: outputs identical."""
+import pytest
+import torch
+
+from paper_2211_10438_amd import binding as sq
+from tests.test_gpu_narrow import test_narrow_linear as check_linear
+
+pytestmark = pytest.mark.gpu
+R, T = sq.ROW_MAJOR, sq.TILED
+
+
+@pytest.mark.parametrize("t,c_i,c_o,layout,tile", [
+    (515, 272, 10898, R, 1192160), (523, 320, 11048, T, 1192160), (772, 848, 10287, R, 1192224), (783, 1344, 10265, T, 1192224),
+    (161, 304, 8330, R, 1256128), (146, 320, 8347, T, 1256128), (585, 432, 10958, R, 1256160), (769, 832, 8308, T, 1256160),
+    (132, 2768, 11141, R, 3192160), (130, 2768, 8311, R, 3256128)])
+def test_pair_tiles(t, c_i, c_o, layout, tile):
+    assert sq.lib().sq_probe_linear_tile(t, c_i, c_o, layout) == tile
+    for n, dtype in enumerate((torch.float16, torch.bfloat16)):
+        for kind in (("plain", "all", "i32") if n == 0 else ("all",)):
+            print(f"pair tile {t}x{c_i}->{c_o} {dtype} {kind}", flush=True)
+            check_linear(t, c_i, c_o, dtype, kind)
+
+
+@pytest.mark.parametrize("t,c_i,c_o", [(520, 320, 11048), (770, 1344, 10320), (150, 384, 8352), (769, 832, 8320)])
+def test_pair_tiles_int8_out(t, c_i, c_o):
+    assert sq.lib().sq_probe_linear_tile(t, c_i, c_o, T) % 1000 in (128, 160, 224)
+    for dtype in (torch.float16, torch.bfloat16):
+        print(f"pair tile int8 {t}x{c_i}->{c_o} {dtype}", flush=True)
+        check_linear(t, c_i, c_o, dtype, "per_channel_q8")
