@@ -1,4 +1,5 @@
-"""Thin Python binding of the sqmi C ABI (``include/sqmi.h``): argument marshalling only.
+"""Thin Python binding of the sqmi C ABI (``include/sqmi.h``): argument marshalling only.  The common form of the calls on the path of a
+running model is marshalled in native code (``csrc/host_calls.cpp``), everything else here.
 
 Every function takes torch tensors that already live on the GPU (torch is used for device memory and
 streams, nothing else), passes their pointers and the current HIP stream to ``libsqmi.so`` and
@@ -9,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import importlib.util
 import os
 
 import torch
@@ -36,11 +38,29 @@ class SqmiError(RuntimeError):
 
 
 _lib = None
+_fast = None  # csrc/host_calls.cpp on this library, once it is loaded
+
+
+def _native_calls(L):
+    """The native form of the common calls, built beside the library; without it every call takes the code below."""
+    path = os.path.join(_HERE, "_host_calls.so")
+    if not os.path.exists(path):
+        return None
+    spec = importlib.util.spec_from_file_location("_host_calls", path)
+    try:
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+    except ImportError:  # (built against another torch)
+        return None
+    mod.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in (
+        "sq_quantize_act", "sq_w8a8_linear", "sq_w8a8_linear_q8", "sq_w8a8_bmm", "sq_softmax_quant_p", "sq_ln_quantize", "sq_w8a8_attention",
+        "sq_w8a8_attention_causal", "sq_workspace_bytes")))
+    return mod
 
 
 def lib() -> ctypes.CDLL:
     """Load libsqmi.so (built by ``paper_2211_10438_amd.build``); fail loudly if it is not there."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise SqmiError(f"{LIB_PATH} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
@@ -78,6 +98,7 @@ def lib() -> ctypes.CDLL:
         L.sq_tiled_bytes.argtypes = [i64, i64]
         for name in EXPORTS:
             getattr(L, name)
+        _fast = _native_calls(L)
         _lib = L
     return _lib
 
@@ -196,6 +217,10 @@ def quantize_act(x: torch.Tensor, mode: int, inv_s: torch.Tensor | None = None, 
     """x [t, ldx] -> (xq int8 [t, c_i], scale fp32 [t] or [1]).  ``c_i`` < ldx quantizes a column prefix; a
     column slice of a wider matrix (unit column stride, row stride >= its width) is taken in place: its row
     stride becomes ldx."""
+    if _fast is not None and out is None and workspace is None and c_i is None:
+        r = _fast.quantize_act(x, mode, inv_s, static_scale, layout)
+        if r is not None:
+            return r
     if x.dim() != 2 or not x.is_cuda:
         raise SqmiError("x must be a 2-D GPU tensor")
     if x.is_contiguous():
@@ -234,6 +259,10 @@ def w8a8_linear(xq: torch.Tensor, x_scale: torch.Tensor, wq: torch.Tensor, w_sca
                 layout: int = ROW_MAJOR, w_per_channel: bool | None = None) -> torch.Tensor:
     """w_scale: fp32 [1] (per tensor) or [c_o] (per output channel; inferred from its length unless
     ``w_per_channel`` says otherwise)."""
+    if _fast is not None and out is None and workspace is None and w_per_channel is None:
+        r = _fast.w8a8_linear(xq, x_scale, wq, w_scale, bias, residual, relu, layout, out_dtype)
+        if r is not None:
+            return r
     t, c_i = xq.shape
     c_o = wq.shape[0]
     if w_per_channel is None:
@@ -280,6 +309,10 @@ def w8a8_linear_q8(xq: torch.Tensor, x_scale: torch.Tensor, wq: torch.Tensor, w_
                    layout: int = ROW_MAJOR, out_layout: int = ROW_MAJOR, w_per_channel: bool | None = None) -> torch.Tensor:
     """W8A8 linear whose epilogue also applies the static quantizer of the next int8 kernel: returns int8 codes
     [t, c_o] (in ``out_layout``) of the value rounded to ``mid_dtype``, with the calibrated step ``y_step`` [1]."""
+    if _fast is not None and out is None and workspace is None and w_per_channel is None:
+        r = _fast.w8a8_linear_q8(xq, x_scale, wq, w_scale, bias, residual, relu, layout, mid_dtype, y_step, out_layout)
+        if r is not None:
+            return r
     t, c_i = xq.shape
     c_o = wq.shape[0]
     if w_per_channel is None:
@@ -308,6 +341,10 @@ def i8_gemm_i32(xq: torch.Tensor, wq: torch.Tensor, workspace=None, layout: int 
 
 def w8a8_bmm(a: torch.Tensor, bm: torch.Tensor, trans_b: bool, alpha: float, out_dtype, out=None) -> torch.Tensor:
     """a [b, m, k]; bm [b, n, k] if trans_b else [b, k, n] -> c [b, m, n]."""
+    if _fast is not None and out is None:
+        r = _fast.w8a8_bmm(a, bm, trans_b, alpha, out_dtype)
+        if r is not None:
+            return r
     b, m, k = a.shape
     n = bm.shape[1] if trans_b else bm.shape[2]
     c = torch.empty((b, m, n), dtype=out_dtype, device=a.device) if out is None else out
@@ -321,6 +358,10 @@ def w8a8_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, alpha1: fl
     """Fused INT8 attention: q [b, s_q, d], k and v [b, s_k, d] int8 -> o [b, s_q, d].  ``p_codes`` (int8
     [b, s_q, s_k]) optionally receives the probability codes the kernel formed.  ``causal`` selects
     sq_w8a8_attention_causal (query i sees the keys j <= i + (s_k - s_q))."""
+    if _fast is not None and out is None and p_codes is None:
+        r = _fast.w8a8_attention(q, k, v, alpha1, alpha2, out_dtype, causal)
+        if r is not None:
+            return r
     b, s_q, d = q.shape
     s_k = k.shape[1]
     if tuple(k.shape) != (b, s_k, d) or tuple(v.shape) != (b, s_k, d):
@@ -348,6 +389,10 @@ def probe_attention(form: int, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor
 
 
 def softmax_quant_p(s: torch.Tensor, out=None) -> torch.Tensor:
+    if _fast is not None and out is None:
+        r = _fast.softmax_quant_p(s)
+        if r is not None:
+            return r
     cols = s.shape[-1]
     rows = s.numel() // cols
     pq = torch.empty(s.shape, dtype=torch.int8, device=s.device) if out is None else out
@@ -366,6 +411,10 @@ def probe_mfma_i8(data: torch.Tensor, workgroups: int, iters: int) -> float:
 
 def ln_quantize(x: torch.Tensor, gamma_f: torch.Tensor, beta_f: torch.Tensor, eps: float = 1e-5, out=None,
                 layout: int = ROW_MAJOR):
+    if _fast is not None and out is None:
+        r = _fast.ln_quantize(x, gamma_f, beta_f, eps, layout)
+        if r is not None:
+            return r
     t, c_i = x.shape
     if out is None:
         xq = empty_codes(t, c_i, layout, x.device)

@@ -1,4 +1,4 @@
-"""Build libsqmi.so (HIP, gfx950 only) in-tree next to the sources."""
+"""Build libsqmi.so (HIP, gfx950 only) and the binding's native calls in-tree next to the sources."""
 from __future__ import annotations
 
 import os
@@ -16,6 +16,22 @@ SOURCES = ["api.hip", "quantize.hip", "weight_prep.hip", "rowops.hip", "gemm_i8.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function",
          "-I", INCLUDE, "-I", CSRC]
+
+
+def build_host_calls() -> str:
+    """The native form of the binding's common calls (host code only, against the installed torch).  Always recompiles."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    out = os.path.join(HERE, "_host_calls.so")
+    inc = [INCLUDE, os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"],
+           os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")]
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(a for i in inc for a in ("-I", i)),
+                    os.path.join(CSRC, "host_calls.cpp"), "-o", out, "-L", os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+                    f"-Wl,-rpath,{os.path.join(root, 'lib')}"], check=True)
+    return out
 
 
 def build(verbose: bool = False, jobs: int = 8) -> str:
@@ -43,6 +59,7 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
     if failed:
         raise RuntimeError("hipcc failed")
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
+    build_host_calls()
     return LIB
 
 
