@@ -231,7 +231,10 @@ __global__ __launch_bounds__(NWAVE * 64, 1) void gemm_i8_stream_kernel(const Gem
 // block is fetched by exactly one wave and every activation fragment is read from LDS by three.  Waves 6 and 7 do
 // nothing but copy the activation blocks into a 4-stage LDS ring (global_load_lds, a stage = 4 K steps of all token
 // blocks), three stages ahead; one barrier per stage.  Used from 33 tokens on; below, where the activation bytes hardly
-// matter, the kernel above is faster (all eight waves' loads feed one ring).
+// matter, the kernel above is faster (all eight waves' loads feed one ring).  Each group's loop is instantiated for its own number of
+// units, and the kernel for four, six, seven or eight token blocks: with every group at the largest number, re-reading its last unit, and
+// four or eight blocks, 100 x 9216 -> 27648 (slabs of seven units, seven blocks) took 65.2 us, now 59.3; 64 tokens 53.7 / 50.0, 128 tokens 68.5 /
+// 63.7; slabs of nine units gain 0 to 2 %.
 // Tried on top of this, no gain: the 32x32x32 MFMA on operands loaded half a block per instruction (twice the cache
 // lines per load: a third slower) or formed from whole blocks of two units with v_permlane16_swap (same time: the
 // MFMAs are not what the waves wait for); four compute waves, one per SIMD (3-8 % slower); K slices instead of units
@@ -257,7 +260,7 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int gs = blockIdx.x % q.gn, gki = blockIdx.x / q.gn;
     const int u0 = (int)((int64_t)gs * q.units / q.gn), u1 = (int)((int64_t)(gs + 1) * q.units / q.gn);
-    const int nu = u1 - u0;     // 1 <= nu <= CNT; units past the slab re-read its last one and their sums are dropped
+    const int nu = u1 - u0;     // CNT or CNT - 1, at least 1
     const int n = q.iters;      // 64-byte K steps of this workgroup: at least 2 D (the host sees to it)
     const int nst = (n + S - 1) / S;  // stages
     const int64_t k0 = (int64_t)gki * n * 1024;
@@ -309,54 +312,63 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
         }
         wait_vmcnt_imm<0>();
     } else {
-        // ---- compute waves: own step t is K step 2 t + kp, in stage t / 2
-        const int8_t* pw[CNTW];
+        // ---- compute waves: own step t is K step 2 t + kp, in stage t / 2.  The loop is instantiated for the most units of a group and
+        // for one less (a slab of seven units: 3, 2, 2), so that no wave fetches and multiplies a unit that is not there.
+        auto run = [&](auto C_) {
+            constexpr int C = decltype(C_)::value;
+            const int8_t* pw[C];
 #pragma unroll
-        for (int j = 0; j < CNTW; ++j) {
-            const int u = ug + j * 3;
-            pw[j] = p.B + (int64_t)(u0 + (u < nu ? u : nu - 1)) * 16 * p.ldb + k0;
-        }
-        v4i fb[D][CNTW];
-        auto load_w = [&](int d, int j, int s) {
-            const uint32_t off = frag_off + (uint32_t)s * 1024u;
-            if (NT) fb[d][j] = __builtin_nontemporal_load((const v4i*)(pw[j] + off));
-            else fb[d][j] = *(const v4i*)(pw[j] + off);
-        };
-        // Every step issues its refills, past the end of the range the last step again (L2 hits whose data nobody
-        // uses): the number of loads issued after any given one is then the same on every path, and the waits the
-        // compiler places leave exactly the younger loads in flight.  (With a refill under a condition it has to
-        // assume the refill did not happen, and waits for everything.)
+            for (int j = 0; j < C; ++j) pw[j] = p.B + (int64_t)(u0 + ug + j * 3) * 16 * p.ldb + k0;
+            v4i fb[D][C];
+            auto load_w = [&](int d, int j, int s) {
+                const uint32_t off = frag_off + (uint32_t)s * 1024u;
+                if (NT) fb[d][j] = __builtin_nontemporal_load((const v4i*)(pw[j] + off));
+                else fb[d][j] = *(const v4i*)(pw[j] + off);
+            };
+            // Every step issues its refills, past the end of the range the last step again (L2 hits whose data nobody
+            // uses): the number of loads issued after any given one is then the same on every path, and the waits the
+            // compiler places leave exactly the younger loads in flight.  (With a refill under a condition it has to
+            // assume the refill did not happen, and waits for everything.)
 #pragma unroll
-        for (int d = 0; d < D; ++d)
+            for (int d = 0; d < D; ++d)
 #pragma unroll
-            for (int j = 0; j < CNTW; ++j) load_w(d, j, 2 * d + kp);
-        int slot = 0;
-        for (int t0 = 0; t0 < 2 * nst; t0 += D) {
+                for (int j = 0; j < C; ++j) load_w(d, j, 2 * d + kp);
+            int slot = 0;
+            for (int t0 = 0; t0 < 2 * nst; t0 += D) {
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                if (d % 2 == 0) {
-                    if (t0 + d >= 2 * nst) break;  // the later stages of the last round may not exist
-                    __builtin_amdgcn_s_barrier();
-                }
-                const int g = 2 * (t0 + d) + kp;
-                const bool live = g < n;
-                const int gw = g + 2 * D;
-                const int sw = gw < n ? gw : n - 1;
-                const char* sa = smem + slot * STAGE + (2 * (d % 2) + kp) * MB * 1024 + frag_off;
-                v4i fa[MB];
-#pragma unroll
-                for (int i = 0; i < MB; ++i) fa[i] = *(const v4i*)(sa + i * 1024);
-#pragma unroll
-                for (int j = 0; j < CNTW; ++j) {
-                    if (live) {
-#pragma unroll
-                        for (int i = 0; i < MB; ++i)
-                            acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[d][j], acc[i][j], 0, 0, 0);
+                for (int d = 0; d < D; ++d) {
+                    if (d % 2 == 0) {
+                        if (t0 + d >= 2 * nst) break;  // the later stages of the last round may not exist
+                        __builtin_amdgcn_s_barrier();
                     }
-                    load_w(d, j, sw);
+                    const int g = 2 * (t0 + d) + kp;
+                    const bool live = g < n;
+                    const int gw = g + 2 * D;
+                    const int sw = gw < n ? gw : n - 1;
+                    const char* sa = smem + slot * STAGE + (2 * (d % 2) + kp) * MB * 1024 + frag_off;
+                    v4i fa[MB];
+#pragma unroll
+                    for (int i = 0; i < MB; ++i) fa[i] = *(const v4i*)(sa + i * 1024);
+#pragma unroll
+                    for (int j = 0; j < C; ++j) {
+                        if (live) {
+#pragma unroll
+                            for (int i = 0; i < MB; ++i)
+                                acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[d][j], acc[i][j], 0, 0, 0);
+                        }
+                        load_w(d, j, sw);
+                    }
+                    if (d % 2 == 1) slot = slot + 1 == NS ? 0 : slot + 1;
                 }
-                if (d % 2 == 1) slot = slot + 1 == NS ? 0 : slot + 1;
             }
+        };
+        const int own = nu > ug ? (nu - ug + 2) / 3 : 0;  // units ug, ug + 3, ...: CNTW or one less (slabs differ by one unit at most)
+        if (own == CNTW) {
+            run(std::integral_constant<int, CNTW>{});
+        } else if constexpr (CNTW > 1) {
+            run(std::integral_constant<int, CNTW - 1>{});
+        } else {
+            for (int t = 0; t < nst; ++t) __builtin_amdgcn_s_barrier();
         }
     }
 
@@ -374,7 +386,7 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
 #pragma unroll
                 for (int j = 0; j < CNTW; ++j) {
                     const int u = ug + j * 3;
-                    if (u >= nu) continue;  // a re-read unit
+                    if (u >= nu) continue;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         int* dst = &red[(i * 16 + row_l + v) * PITCH + u * 16 + col_l];
@@ -554,8 +566,10 @@ void sq_stream_gemm_launch(const GemmArgs& a, StreamArgs q, bool to_i32, bool bf
 #define SQ_R12(MB) SQ_R(MB, 1) SQ_R(MB, 2) SQ_R(MB, 3) SQ_R(MB, 4) SQ_R(MB, 5) SQ_R(MB, 6) SQ_R(MB, 7) SQ_R(MB, 8) \
                    SQ_R(MB, 9) SQ_R(MB, 10) SQ_R(MB, 11) SQ_R(MB, 12)
         static_assert(kRegsMaxUnits == 12, "launch table");
-        switch (q.na) {
-            case 4: switch (cnt) { SQ_R12(4) default: break; } break;
+        switch ((a.M + 15) / 16) {  // token blocks that are there
+            case 3: case 4: switch (cnt) { SQ_R12(4) default: break; } break;
+            case 5: case 6: switch (cnt) { SQ_R12(6) default: break; } break;
+            case 7: switch (cnt) { SQ_R12(7) default: break; } break;
             default: switch (cnt) { SQ_R12(8) default: break; } break;
         }
 #undef SQ_R12

@@ -1,0 +1,26 @@
+"""The weight-streaming kernel for 33 to 128 tokens (tiled): three to eight token blocks, slabs whose units do not divide among the three
+unit groups, with a shorter last slab, odd numbers of stages, K splits.  Against the exact integer product: outputs identical."""
+import pytest
+import torch
+
+from paper_2211_10438_amd import binding as sq
+from tests.test_gpu_narrow import _tile
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("t,c_i,c_o", [(40, 1024, 16441), (48, 1088, 24908), (70, 1024, 20562), (96, 1152, 10944), (100, 1024, 24765), (112, 1216, 16471),
+                                       (113, 1024, 8332), (128, 1024, 28728), (100, 1024, 45144), (120, 2880, 10936), (96, 2688, 16528), (128, 1024, 40976)])
+def test_units_and_blocks(t, c_i, c_o):
+    assert sq.lib().sq_probe_linear_form(t, c_i, c_o, sq.TILED) == 0 and sq.lib().sq_probe_linear_tile(t, c_i, c_o, sq.TILED) == 0
+    print(f"stream {t}x{c_i}->{c_o}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(t + c_i + c_o)
+    x, w = (torch.randint(-127, 128, s, generator=g, device="cuda", dtype=torch.int32).to(torch.int8) for s in ((t, c_i), (c_o, c_i)))
+    xs, ws = torch.rand(t, generator=g, device="cuda") * 0.01 + 0.001, torch.rand(c_o, generator=g, device="cuda") * 0.001 + 1e-4
+    bias = torch.randn(c_o, generator=g, device="cuda")
+    acc = (x.double() @ w.double().t()).to(torch.int32)
+    xq, wq = _tile(x), _tile(w)
+    assert torch.equal(sq.i8_gemm_i32(xq, wq, layout=sq.TILED), acc)
+    for dtype in (torch.float16, torch.bfloat16):
+        y = sq.w8a8_linear(xq, xs, wq, ws, dtype, bias=bias, layout=sq.TILED)
+        assert torch.equal(y.view(torch.int16), (acc.float() * (xs[:, None] * ws) + bias).to(dtype).view(torch.int16))
