@@ -15,13 +15,14 @@ template <bool BF16> SQ_DEVICE void unpack8w(const v4u raw, float (&f)[8])
 }
 
 // Maxima over rows of W: one row (input channel j) per WPR waves, four 16-byte loads per lane in flight.  ROWS: row_out[j] =
-// max_n |W_jn|.  Otherwise the maximum over the tensor, each row scaled by s_j: a wave keeps it over all its rows and
-// adds it to tensor_bits with one atomic (the integer order of the bit patterns of non-negative floats is the float order);
-// one atomic per row on that single cell, some 12 ns each, was the longest part of a narrow weight's preparation.
-template <bool BF16, bool ROWS, int WPR>
+// max_n |W_jn|.  Otherwise the maximum over the tensor, each row scaled by s_j: a workgroup keeps it over all its rows and leaves it in
+// tensor_max[blockIdx.x], or (ATOMIC: a workspace too small for that) adds it to the cleared tensor_max[0] with one atomic: the integer
+// order of the bit patterns of non-negative floats is the float order.  (Atomics on one cell take some 12 ns each, one
+// after the other, and want it cleared: preparation per tensor of 4096 x 4096 25.1 us, now 20.7; 768 x 3072 14.0, now 11.4.)
+template <bool BF16, bool ROWS, int WPR, bool ATOMIC>
 __global__ __launch_bounds__(256) void weight_row_absmax_kernel(const uint16_t* __restrict__ w, int c_i, int c_o,
                                                                const float* __restrict__ s, float* row_out,
-                                                               uint32_t* tensor_bits)
+                                                               uint32_t* tensor_max)
 {
     constexpr int RPW = 4 / WPR, NT = WPR * 64;  // rows per workgroup, threads per row
     __shared__ float red[4];
@@ -61,8 +62,11 @@ __global__ __launch_bounds__(256) void weight_row_absmax_kernel(const uint16_t* 
         all = wave_max(all);
         if (lane == 0) red[threadIdx.x >> 6] = all;
         __syncthreads();
-        if (threadIdx.x == 0)
-            atomicMax(tensor_bits, __builtin_bit_cast(uint32_t, __builtin_fmaxf(__builtin_fmaxf(red[0], red[1]), __builtin_fmaxf(red[2], red[3]))));
+        if (threadIdx.x == 0) {
+            const uint32_t bits = __builtin_bit_cast(uint32_t, __builtin_fmaxf(__builtin_fmaxf(red[0], red[1]), __builtin_fmaxf(red[2], red[3])));
+            if constexpr (ATOMIC) atomicMax(tensor_max, bits);
+            else tensor_max[blockIdx.x] = bits;
+        }
     }
 }
 
@@ -71,12 +75,16 @@ __global__ void zero_u32_kernel(uint32_t* p, int64_t n)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
 
-// Per-output-channel maxima: col_bits[n] = max_j |W_jn * s_j| as the bit pattern of a non-negative float.  A workgroup owns
-// 512 columns (a wave's row of 1 KB) over a slab of rows, one row in four per wave with four loads in flight; the waves meet
-// in LDS, the slabs by atomic max.
+typedef float f4w __attribute__((ext_vector_type(4), aligned(4)));  // (a workspace need not be aligned to more than its words)
+
+// Per-output-channel maxima of a slab of rows: out[slab][n] = max_j |W_jn * s_j|.  A workgroup owns 512 columns (a wave's row of 1 KB)
+// over a slab, one row in four per wave with eight loads in flight; the waves meet in LDS.  The slabs' maxima go to memory by plain
+// stores and meet in the kernel below.  (One atomic per slab and column leaves the XCD's L2 for the memory side: preparation per channel of
+// 4096 x 4096 32.2 us, now 27.3; 5120 x 20480 103.9,
+// now 94.0; 12288 x 64 41.8, now 22.7.  Eight loads in flight instead of four are 3 to 5 % of the large ones.)
 template <bool BF16>
 __global__ __launch_bounds__(256) void weight_col_absmax_kernel(const uint16_t* __restrict__ w, int c_i, int c_o,
-                                                               const float* __restrict__ s, int rows_per_wg, uint32_t* col_bits)
+                                                               const float* __restrict__ s, int rows_per_wg, float* out)
 {
     __shared__ float red[3][512];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -84,17 +92,17 @@ __global__ __launch_bounds__(256) void weight_col_absmax_kernel(const uint16_t* 
     const int j0 = blockIdx.y * rows_per_wg, j1 = c_i - j0 < rows_per_wg ? c_i : j0 + rows_per_wg;
     float m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (n < c_o) {  // c_o % 8 == 0
-        for (int j = j0 + wave; j < j1; j += 16) {
-            v4u raw[4];
-            float sj[4];
+        for (int j = j0 + wave; j < j1; j += 32) {
+            v4u raw[8];
+            float sj[8];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < 8; ++i) {
                 const int jj = j + i * 4 < j1 ? j + i * 4 : j;  // past the end: the first row again
                 raw[i] = *(const v4u*)(w + (int64_t)jj * c_o + n);
                 sj[i] = s ? s[jj] : 1.0f;
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < 8; ++i) {
                 float f[8];
                 unpack8w<BF16>(raw[i], f);
 #pragma unroll
@@ -109,11 +117,26 @@ __global__ __launch_bounds__(256) void weight_col_absmax_kernel(const uint16_t* 
     __syncthreads();
     if (wave == 0 && n < c_o) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float v = __builtin_fmaxf(__builtin_fmaxf(m[e], red[0][e * 64 + lane]), __builtin_fmaxf(red[1][e * 64 + lane], red[2][e * 64 + lane]));
-            atomicMax(col_bits + n + e, __builtin_bit_cast(uint32_t, v));
-        }
+        for (int e = 0; e < 8; ++e)
+            m[e] = __builtin_fmaxf(__builtin_fmaxf(m[e], red[0][e * 64 + lane]), __builtin_fmaxf(red[1][e * 64 + lane], red[2][e * 64 + lane]));
+        float* dst = out + (int64_t)blockIdx.y * c_o + n;
+        *(f4w*)dst = f4w{m[0], m[1], m[2], m[3]};
+        *(f4w*)(dst + 4) = f4w{m[4], m[5], m[6], m[7]};
     }
+}
+
+// col_max[n] = the largest of part[slab][n], four columns per thread.
+__global__ __launch_bounds__(64) void weight_col_reduce_kernel(const float* part, int c_o, int slabs, float* col_max)
+{
+    const int n = (blockIdx.x * 64 + threadIdx.x) * 4;
+    if (n >= c_o) return;
+    float4 m = *(const float4*)(part + n);
+#pragma unroll 8
+    for (int s = 1; s < slabs; ++s) {
+        const float4 v = *(const float4*)(part + (int64_t)s * c_o + n);
+        m = float4{__builtin_fmaxf(m.x, v.x), __builtin_fmaxf(m.y, v.y), __builtin_fmaxf(m.z, v.z), __builtin_fmaxf(m.w, v.w)};
+    }
+    *(f4w*)(col_max + n) = f4w{m.x, m.y, m.z, m.w};
 }
 
 // Quantize and transpose.  A wave owns 64 input x 128 output channels: lane (ng, jc) loads rows 16 jc .. 16 jc + 15 of its 8
@@ -125,7 +148,7 @@ __global__ __launch_bounds__(256) void weight_col_absmax_kernel(const uint16_t* 
 template <bool BF16>
 __global__ __launch_bounds__(256) void weight_quant_transpose_kernel(const uint16_t* __restrict__ w, int c_i, int c_o,
                                                                     const float* __restrict__ s,
-                                                                    const uint32_t* amax_bits, float* w_scale,
+                                                                    const uint32_t* amax_bits, int parts, float* w_scale,
                                                                     int8_t* __restrict__ wq, bool tiled, bool per_channel)
 {
     __shared__ __attribute__((aligned(1024))) char image[4][8192];
@@ -144,7 +167,9 @@ __global__ __launch_bounds__(256) void weight_quant_transpose_kernel(const uint1
             if (j0 == 0 && jc == 0 && n < c_o) w_scale[n + e] = a / 127.0f;
         }
     } else {
-        const float a = __builtin_bit_cast(float, *amax_bits);
+        float a = 0.0f;  // the largest of the parts
+        for (int i = lane; i < parts; i += 64) a = __builtin_fmaxf(a, __builtin_bit_cast(float, amax_bits[i]));
+        a = wave_max(a);
         const float r0 = a > 0.0f ? 127.0f / a : 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) r[e] = r0;
@@ -201,19 +226,27 @@ __global__ __launch_bounds__(256) void weight_quant_transpose_kernel(const uint1
 // but 768 x 4096 3.0 / 3.3, 1536 x 12288 7.7 / 8.0.  With the tensor's maximum every workgroup ends in an atomic on one cell, and
 // the line lies lower (whole preparation): 256 x 20480 18.2 / 15.8, 64 x 50272 24.8 / 14.9, but 256 x 8192 12.3 / 13.4, 768 x
 // 20480 24.4 / 28.9.
+// `room`: cells of tensor_max.  Returns the parts the tensor's maximum is left in (1 where they met by atomics, or for ROWS).
 template <bool ROWS>
-void launch_row_absmax(const uint16_t* w, sq_dtype dtype, int c_i, int c_o, const float* s, float* row_out, uint32_t* tensor_bits, hipStream_t st)
+int launch_row_absmax(const uint16_t* w, sq_dtype dtype, int c_i, int c_o, const float* s, float* row_out, uint32_t* tensor_max, size_t room, hipStream_t st)
 {
     const bool wide = ROWS ? c_i <= 1024 && c_o > 4096 : c_i <= 256 && c_o > 16384;
     const int64_t need = wide ? c_i : ((int64_t)c_i + 3) / 4, cap = ROWS ? 65535 : 512;  // (the kernel strides over the rest)
     const dim3 grid((unsigned)(need < cap ? need : cap));
-#define SQ_ROW(BF, WPR) sq_launch((weight_row_absmax_kernel<BF, ROWS, WPR>), grid, dim3(256), 0, st, w, c_i, c_o, s, row_out, tensor_bits)
+    const bool atomic = !ROWS && room < grid.x;
+    if (atomic) sq_launch(zero_u32_kernel, dim3(1), dim3(256), 0, st, tensor_max, (int64_t)1);
+#define SQ_ROW(BF, WPR)                                                                                                                    \
+    do {                                                                                                                                   \
+        if (atomic) sq_launch((weight_row_absmax_kernel<BF, ROWS, WPR, !ROWS>), grid, dim3(256), 0, st, w, c_i, c_o, s, row_out, tensor_max); \
+        else sq_launch((weight_row_absmax_kernel<BF, ROWS, WPR, false>), grid, dim3(256), 0, st, w, c_i, c_o, s, row_out, tensor_max);       \
+    } while (0)
     if (dtype == SQ_BF16) {
         if (wide) SQ_ROW(true, 4); else SQ_ROW(true, 1);
     } else {
         if (wide) SQ_ROW(false, 4); else SQ_ROW(false, 1);
     }
 #undef SQ_ROW
+    return ROWS || atomic ? 1 : (int)grid.x;
 }
 
 }  // namespace
@@ -227,7 +260,7 @@ sq_status sq_weight_absmax_per_in_channel(const void* w, sq_dtype dtype, int64_t
     if (c_i <= 0 || c_o <= 0 || c_i >= ((int64_t)1 << 31) || c_o >= ((int64_t)1 << 31)) return SQ_ERR_SHAPE;
     if (dtype != SQ_F16 && dtype != SQ_BF16) return SQ_ERR_UNSUPPORTED;
     if ((c_o & 7) || !sq_aligned16(w)) return SQ_ERR_ALIGN;
-    launch_row_absmax<true>((const uint16_t*)w, dtype, (int)c_i, (int)c_o, nullptr, out, nullptr, (hipStream_t)stream);
+    launch_row_absmax<true>((const uint16_t*)w, dtype, (int)c_i, (int)c_o, nullptr, out, nullptr, 0, (hipStream_t)stream);
     return sq_launch_status();
 }
 
@@ -247,24 +280,26 @@ sq_status sq_prepare_weight(const void* w, sq_dtype dtype, const float* s, int64
     if (((int64_t)((c_i + 63) / 64)) > 65535) return SQ_ERR_SHAPE;
     hipStream_t st = (hipStream_t)stream;
     uint32_t* amax = (uint32_t*)workspace;
-    const int64_t ncell = pc ? c_o : 1;
-    sq_launch(zero_u32_kernel, dim3((unsigned)((ncell + 255) / 256 < 1024 ? (ncell + 255) / 256 : 1024)), dim3(256), 0, st, amax, ncell);
-    // about four workgroups per compute unit, slabs of at least 64 rows (each slab costs an atomic per column)
-    const int64_t colb = (c_o / 8 + 63) / 64;
-    int64_t slabs = (1024 + colb - 1) / colb;
-    if (slabs > (c_i + 63) / 64) slabs = (c_i + 63) / 64;
-    const int rows = (int)((c_i + slabs - 1) / slabs);
-    const dim3 gridc((unsigned)colb, (unsigned)((c_i + rows - 1) / rows));
     const dim3 grid2((unsigned)((c_o + 127) / 128), (unsigned)((c_i + 255) / 256));
-    if (dtype == SQ_BF16) {
-        if (pc) sq_launch(weight_col_absmax_kernel<true>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, rows, amax);
-        else launch_row_absmax<false>((const uint16_t*)w, dtype, (int)c_i, (int)c_o, s, nullptr, amax, st);
-        sq_launch(weight_quant_transpose_kernel<true>, grid2, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax, w_scale, wq, tiled, pc);
+    int parts = 1;
+    if (pc) {
+        // about four workgroups per compute unit, slabs of at least 64 rows.  The slabs' maxima wait in the code buffer, which is
+        // written last and has room: 4 bytes per column and slab of 64 rows or more against one per weight.
+        const int64_t colb = (c_o / 8 + 63) / 64;
+        int64_t slabs = (1024 + colb - 1) / colb;
+        if (slabs > (c_i + 63) / 64) slabs = (c_i + 63) / 64;
+        const int rows = (int)((c_i + slabs - 1) / slabs);
+        slabs = (c_i + rows - 1) / rows;
+        float* part = slabs > 1 ? (float*)wq : (float*)amax;
+        const dim3 gridc((unsigned)colb, (unsigned)slabs);
+        if (dtype == SQ_BF16) sq_launch(weight_col_absmax_kernel<true>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, rows, part);
+        else sq_launch(weight_col_absmax_kernel<false>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, rows, part);
+        if (slabs > 1) sq_launch(weight_col_reduce_kernel, dim3((unsigned)((c_o / 4 + 63) / 64)), dim3(64), 0, st, part, (int)c_o, (int)slabs, (float*)amax);
     } else {
-        if (pc) sq_launch(weight_col_absmax_kernel<false>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, rows, amax);
-        else launch_row_absmax<false>((const uint16_t*)w, dtype, (int)c_i, (int)c_o, s, nullptr, amax, st);
-        sq_launch(weight_quant_transpose_kernel<false>, grid2, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax, w_scale, wq, tiled, pc);
+        parts = launch_row_absmax<false>((const uint16_t*)w, dtype, (int)c_i, (int)c_o, s, nullptr, amax, ws_bytes / sizeof(uint32_t), st);
     }
+    if (dtype == SQ_BF16) sq_launch(weight_quant_transpose_kernel<true>, grid2, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax, parts, w_scale, wq, tiled, pc);
+    else sq_launch(weight_quant_transpose_kernel<false>, grid2, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax, parts, w_scale, wq, tiled, pc);
     return sq_launch_status();
 }
 
