@@ -77,7 +77,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_i8_direct_kernel(const GemmAr
     const uint16_t* R = (const uint16_t*)p.residual;
     auto token = [&](int r, int k) { return r * IR * 16 + k * TPP + tk; };  // of the tile; the thread's k-th in round r
     auto has_output = [&](int r, int k) {
-        return k * TPP + tk < IR * 16 && token(r, k) < MB * 16 && m0 + token(r, k) < p.M && ncol > 0;
+        return k * TPP + tk < IR * 16 && token(r, k) < MB * 16 && token(r, k) < p.M - m0 && ncol > 0;
     };
     auto fetch_tokens = [&](int r) {
 #pragma unroll
