@@ -4,7 +4,8 @@ import pytest
 import torch
 
 from paper_2211_10438_amd import binding as sq
-from tests.test_gpu_narrow import test_narrow_linear as check_linear
+from tests._util import tiled_index
+from tests.test_gpu_narrow import _tile, test_narrow_linear as check_linear
 
 pytestmark = pytest.mark.gpu
 R, T = sq.ROW_MAJOR, sq.TILED
@@ -28,3 +29,17 @@ def test_pair_tiles_int8_out(t, c_i, c_o):
     for dtype in (torch.float16, torch.bfloat16):
         print(f"pair tile int8 {t}x{c_i}->{c_o} {dtype}", flush=True)
         check_linear(t, c_i, c_o, dtype, "per_channel_q8")
+
+
+@pytest.mark.parametrize("t,c_i,c_o", [(515, 320, 11072), (769, 832, 8320), (770, 1344, 10304), (150, 384, 8384)])
+def test_pair_tiles_int8_out_tiled(t, c_i, c_o):
+    assert sq.lib().sq_probe_linear_tile(t, c_i, c_o, T) % 1000 in (128, 160, 224)
+    g = torch.Generator(device="cuda").manual_seed(t)
+    x, w = (torch.randint(-127, 128, s, generator=g, device="cuda", dtype=torch.int32).to(torch.int8) for s in ((t, c_i), (c_o, c_i)))
+    xs, ws, step = torch.rand(t, generator=g, device="cuda") * 0.01 + 0.001, torch.full((1,), 3e-4, device="cuda"), torch.full((1,), 0.05, device="cuda")
+    xq, wq = _tile(x), _tile(w)
+    rows, tiled = (sq.w8a8_linear_q8(xq, xs, wq, ws, step, torch.float16, relu=True, layout=T, out_layout=o) for o in (R, T))
+    whole = t // 16 * 16  # (the padding rows of the last block are undefined)
+    assert torch.equal(_tile(rows[:whole].contiguous()).reshape(-1), tiled.reshape(-1)[: whole * c_o])
+    flat = (tiled._base if tiled._base is not None else tiled).reshape(-1)
+    assert torch.equal(flat[torch.from_numpy(tiled_index(t, c_o)).cuda()], rows)
