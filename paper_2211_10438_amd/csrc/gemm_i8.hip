@@ -230,27 +230,40 @@ TilePlan choose_tile(int64_t M, int64_t N, int64_t K, bool tiled, const TilePlan
     return best;
 }
 
-// Time of the tiles of up to 128 tokens (with their K split and its second kernel) and of short K against the direct kernel,
-// calibrated on 150 shapes (5 to 12 % rms).
-double tile_us(const TilePlan& pl, double M, double N, double K, bool tiled)
+// Time of a tile plan against the direct kernel, fitted to 3500 shapes (16-bit output, weights in the last-level cache and in memory;
+// 4 to 11 % rms).  chosen_us: what choose_tile took the plan for; its model orders tiles of a layer, and leaves out a launch's constant
+// part and rows of the output that are not whole 16-byte pieces (odd: they leave element by element).  Without those two 463 x 640 -> 2501
+// row-major was taken for 9 us and took 19.
+double tile_us(const TilePlan& pl, double M, double N, double K, bool tiled, double chosen_us)
 {
-    const double rounds = (double)(((int64_t)pl.tiles_m * pl.tiles_n * pl.splits + kNumCU - 1) / kNumCU);
-    const double steps = rounds * pl.iters_per_split, out = M * N * 1e-6, w = N * K * 1e-6;
-    const double split = pl.splits > 1 ? 1.0 : 0.0, part = pl.splits > 1 ? pl.splits * out : 0.0;
+    const double tiles = (double)((int64_t)pl.tiles_m * pl.tiles_n), out = M * N * 1e-6, w = N * K * 1e-6;
+    const double odd = (int64_t)N % 8 ? 1.0 : 0.0, split = pl.splits > 1 ? 1.0 : 0.0, part = pl.splits > 1 ? pl.splits * out : 0.0;
+    if (pl.cfg == 8) {
+        const double work = tiles / kNumCU * pl.iters_per_split;
+        return tiled ? 8.4 + 0.63 * work + 0.155 * out + (1.4 + 1.17 * out) * odd : 8.3 + 0.19 * work + 0.42 * out + (1.6 + 1.12 * out) * odd;
+    }
+    if (pl.cfg == 7) {
+        const double work = tiles / kNumCU * pl.iters_per_split;
+        return tiled ? 9.0 + 0.42 * work + (1.4 + 1.10 * out) * odd : 8.9 + 0.56 * out + (1.1 + 0.90 * out) * odd;
+    }
+    if (pl.bm > 128) return tiled ? 3.3 + 0.90 * chosen_us + (4.0 + 1.2 * out) * odd : 4.0 + 0.875 * chosen_us + (4.2 + 1.5 * out) * odd;
+    const double rounds = (double)(((int64_t)tiles * pl.splits + kNumCU - 1) / kNumCU), steps = rounds * pl.iters_per_split;
     switch (pl.bm) {
         case 128:
-            if (K <= 256.0) return 6.0 + 1.2 * (double)pl.tiles_m * pl.tiles_n / kNumCU;
-            return tiled ? 2.2 * rounds + 0.423 * steps + 8.2 * split + 1.33 * part : 8.8 * rounds + 0.381 * steps + 2.3 * split + 2.01 * part;
+            return tiled ? 6.0 + 6.9 * rounds + 0.230 * steps + 0.44 * part + 0.266 * w + 2.0 * odd
+                         : 11.1 + 1.9 * rounds + 0.300 * steps + 1.97 * part + 0.162 * w + 2.5 * odd;
         case 64:
-            return tiled ? 9.4 + 0.287 * steps + 1.16 * part : 1.7 + 3.6 * rounds + 0.563 * steps + 1.3 * split + 1.98 * part + 0.045 * w;
+            return tiled ? 8.0 + 0.6 * rounds + 0.242 * steps + 0.9 * split + 1.71 * part + 0.121 * w + 1.4 * odd
+                         : 8.1 + 0.5 * rounds + 0.337 * steps + 0.4 * split + 1.69 * part + 0.224 * w + 1.3 * odd;
         default:
-            return tiled ? 8.0 * rounds + 0.292 * steps + 2.04 * part + 0.074 * w
-                         : 1.3 + 3.8 * rounds + 0.295 * steps + 3.5 * split + 2.23 * part + 0.141 * w;
+            return tiled ? 6.0 + 0.1 * rounds + 0.223 * steps + 1.9 * split + 2.32 * part + 0.168 * w + 0.2 * odd
+                         : 5.6 + 0.6 * rounds + 0.276 * steps + 1.9 * split + 2.90 * part + 0.215 * w + 0.1 * odd;
     }
 }
 
-// Sizes of few tokens and few channels, by the shape alone: they have never asked for a workspace (sq_workspace_bytes keeps to
-// that line), and the direct kernel is ahead in all of them, or level.
+// Sizes of few tokens and few channels, by the shape alone: calls of these sizes ask for no workspace, so they cannot run a K split.  The
+// line was drawn where an earlier kernel for them was ahead of the others, and stands because the size of a workspace is part of
+// the interface.  The direct kernel takes them all: over 766 such shapes it needs 0.48 of the other path's time, and at most 1.015.
 bool few_channels(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled)
 {
     if (batch != 1 || M < 1 || M > 128) return false;
@@ -277,7 +290,8 @@ struct Path {
     int need;  // K splits the workspace is sized for, fixed by the shape
     DirectPlan direct;
 };
-Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool b_transposed, bool allow_split, StreamArgs* sp, TilePlan* pl)
+// scaled: the epilogue applies scales (a linear layer).
+Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool b_transposed, bool allow_split, bool scaled, StreamArgs* sp, TilePlan* pl)
 {
     Path p{};
     const bool single = !b_transposed && batch == 1;
@@ -286,7 +300,7 @@ Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool b_t
         p.direct = dp;
         return p;
     }
-    double us;
+    double us = 0.0;
     if (!b_transposed && sq_stream_gemm_plan(M, N, K, batch, tiled, sp) && (sp->gk == 1 || allow_split)) {  // (else the tile kernels)
         p.stream = true;
         p.need = sp->gk;
@@ -296,11 +310,17 @@ Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool b_t
         *pl = make_plan(M, N, K, batch, allow_split, b_transposed);
         p.need = pl->splits;
         if (single && pl->bm == 256) *pl = choose_tile(M, N, K, tiled, *pl, &us);
-        else us = single ? tile_us(*pl, (double)M, (double)N, (double)K, tiled) : 0.0;
+        if (single) us = tile_us(*pl, (double)M, (double)N, (double)K, tiled, us);
     }
-    // The margins keep the models' errors from costing where the kernels are close: at 0.97 those would make six of 230 shapes 1.1 to
-    // 1.4 times slower than the register-direct stream or the 256-row tiles.
-    const double margin = p.tiles ? (M > 128 ? 0.92 : 0.90) : sp->regs ? 0.84 : 0.90;
+    // Int32 sums and alpha alone: no scales and biases to wait for at the end of a small tile (128 x 128: 8 -> 5 us of fixed time; the direct
+    // kernel 3.7 -> 3.2).
+    if (!scaled && p.tiles && pl->bm <= 128 && pl->splits == 1) us -= pl->bm == 32 ? 1.0 : pl->bm == 128 && K > 256 ? 4.5 : 2.2;
+    // The margins keep the models' errors from costing where the kernels are close.  Over 4500 shapes the direct kernel is then more than
+    // 3 % behind the other in 10 with the weights in the last-level cache and in 49 with them in memory; at 0.95 it would be 26 and 81.  How
+    // long rows of a row-major weight take hangs on more than the model knows (15 x 36336 -> 1360 modelled 25 us, took 38; the tiles 25): of
+    // 413 such shapes 1 and 4 are behind, at 0.90 15 and 26.  Few workgroups with long chains are alike (58 x 31152 -> 62: 29 and 39 us, the
+    // tiles 15 and 16).
+    const double margin = K > 20480 && !tiled && M <= 128 ? 0.80 : p.tiles ? 0.90 : sp->regs ? 0.88 : 0.92;
     const bool chain = K > 12288 && dp.mb && ((M + 16 * dp.mb - 1) / (16 * dp.mb)) * ((N + 16 * dp.nb - 1) / (16 * dp.nb)) < 24;
     if (dp.mb && !chain && dp.us < margin * us) p.direct = dp;
     return p;
@@ -327,7 +347,7 @@ sq_status run_gemm(GemmArgs a, int64_t batch, bool to_i32, bool bf16, void* work
     };
     StreamArgs sp{};
     TilePlan pl{};
-    const Path path = choose(a.M, a.N, a.K, batch, tiled, b_transposed, allow_split, &sp, &pl);
+    const Path path = choose(a.M, a.N, a.K, batch, tiled, b_transposed, allow_split, a.x_scale != nullptr, &sp, &pl);
     // (a shape whose workspace is sized for a K split is asked for it also where a kernel that has no use for it takes the call)
     if (path.need > 1 && (!workspace || ws_bytes < (size_t)path.need * total * sizeof(int32_t))) return SQ_ERR_WORKSPACE;
     const int splits = path.stream ? sp.gk : path.tiles ? pl.splits : 1;
@@ -411,7 +431,7 @@ int sq_probe_linear_form(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout)
     if (!dims_ok(t, c_i, c_o)) return 0;
     StreamArgs sp{};
     TilePlan pl{};
-    const DirectPlan d = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, &sp, &pl).direct;
+    const DirectPlan d = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, true, &sp, &pl).direct;
     return 100 * d.mb + 10 * d.nb + d.nw;
 }
 
@@ -420,7 +440,7 @@ int sq_probe_linear_tile(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout)
     if (!dims_ok(t, c_i, c_o)) return 0;
     StreamArgs sp{};
     TilePlan pl{};
-    const Path p = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, &sp, &pl);
+    const Path p = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, true, &sp, &pl);
     return p.tiles && !p.direct.mb ? pl.splits * 1000000 + pl.bm * 1000 + pl.bn : 0;
 }
 

@@ -5,10 +5,12 @@
 namespace {
 
 // A time model of each instantiation, microseconds: fixed + per_round x rounds (workgroups over the slots of the chip) + per_wg x
-// workgroups of the fullest compute unit + cu x megabytes those pull from their L2 + hbm x megabytes of weights.  Fitted to 590 shapes
-// (1 to 2048 tokens, C_i 32 to 65536, C_o 16 to 49152, both layouts, graph replays with rotating weights; about 10 % rms): choosing by it
-// costs 2 % against the best instantiation of each shape.  The 10 (tiled) and 12 to 21 (row-major) microseconds per megabyte are 100 and
-// 80 to 47 GB/s per compute unit.
+// workgroups of the fullest compute unit + cu x megabytes those pull from their L2 + hbm x megabytes of weights.  Fitted to 4500 shapes
+// (1 to 4096 tokens, C_i 16 to 50000, C_o 16 to 40000, both layouts), each the geometric mean of a replay with the weights in
+// the last-level cache and one with them in memory (5 to 11 % rms): choosing by it costs 0.5 % against the best instantiation of each shape
+// (row-major 1 %).  One shape in six has K <= 256: without them the fixed work of a workgroup, its sums and stores, went
+// into the other terms, and 1000 x 64 -> 14900 row-major was modelled at 8 us and took 55.  The 11 (tiled) and 11 to 22 (row-major)
+// microseconds per megabyte are 90 and 90 to 45 GB/s per compute unit.
 struct Cost {
     float fixed, per_round, per_wg, cu, hbm;
 };
@@ -17,21 +19,21 @@ struct Form {
     Cost cost[2];    // row-major, tiled
 };
 constexpr Form kForms[] = {
-    {1, 1, 2, {{3.64f, 0.25f, 0.16f, 14.9f, 0.123f}, {3.19f, 0.57f, 0.09f, 11.0f, 0.095f}}},
-    {1, 1, 4, {{3.09f, 0.58f, 0.57f, 12.0f, 0.107f}, {3.46f, 0.00f, 0.45f, 10.8f, 0.093f}}},
-    {1, 2, 2, {{3.79f, 0.24f, 0.03f, 14.8f, 0.146f}, {3.36f, 0.15f, 0.22f, 10.3f, 0.107f}}},
-    {1, 2, 4, {{3.16f, 0.94f, 0.19f, 13.6f, 0.136f}, {3.18f, 0.38f, 0.52f, 10.3f, 0.099f}}},
-    {1, 4, 2, {{4.30f, 0.00f, 0.00f, 16.1f, 0.161f}, {3.58f, 0.34f, 0.37f, 10.5f, 0.110f}}},
-    {1, 4, 4, {{3.62f, 0.68f, 0.00f, 14.9f, 0.148f}, {3.06f, 0.92f, 0.72f, 10.1f, 0.105f}}},
-    {2, 2, 2, {{3.82f, 0.39f, 0.00f, 14.7f, 0.136f}, {2.92f, 0.83f, 0.34f, 10.0f, 0.094f}}},
-    {2, 2, 4, {{2.75f, 0.72f, 0.53f, 11.6f, 0.134f}, {2.75f, 0.67f, 0.79f, 10.0f, 0.089f}}},
-    {2, 4, 4, {{4.75f, 0.12f, 0.63f, 21.5f, 0.093f}, {3.06f, 1.02f, 0.88f, 9.8f, 0.103f}}},
-    {3, 2, 4, {{3.53f, 0.35f, 0.77f, 13.1f, 0.081f}, {2.78f, 1.19f, 1.07f, 9.7f, 0.072f}}},
-    {3, 4, 4, {{4.73f, 0.68f, 0.32f, 21.4f, 0.069f}, {3.20f, 1.13f, 0.79f, 9.6f, 0.087f}}},
-    {4, 4, 4, {{4.95f, 1.26f, 0.46f, 22.0f, 0.085f}, {3.04f, 2.00f, 0.74f, 9.5f, 0.096f}}},
-    {5, 4, 4, {{5.25f, 1.07f, 0.00f, 21.2f, 0.069f}, {2.72f, 2.78f, 0.39f, 9.6f, 0.083f}}},
-    {6, 4, 4, {{5.57f, 1.54f, 0.00f, 21.2f, 0.073f}, {2.87f, 3.59f, 0.26f, 9.9f, 0.067f}}},
-    {7, 4, 4, {{6.19f, 1.93f, 0.00f, 21.9f, 0.060f}, {2.78f, 4.28f, 0.29f, 9.6f, 0.081f}}},
+    {1, 1, 2, {{2.49f, 1.15f, 0.31f, 16.9f, 0.066f}, {3.33f, 0.00f, 0.35f, 14.3f, 0.056f}}},
+    {1, 1, 4, {{2.84f, 0.36f, 0.93f, 11.4f, 0.097f}, {3.25f, 0.00f, 0.65f, 13.1f, 0.077f}}},
+    {1, 2, 2, {{2.69f, 0.96f, 0.35f, 15.3f, 0.106f}, {3.22f, 0.12f, 0.50f, 12.3f, 0.080f}}},
+    {1, 2, 4, {{2.76f, 0.61f, 0.85f, 12.7f, 0.117f}, {3.30f, 0.00f, 0.91f, 12.2f, 0.081f}}},
+    {1, 4, 2, {{2.71f, 1.13f, 0.47f, 14.8f, 0.123f}, {3.02f, 0.55f, 0.88f, 11.5f, 0.090f}}},
+    {1, 4, 4, {{2.56f, 0.86f, 0.93f, 12.0f, 0.141f}, {2.89f, 0.45f, 1.49f, 11.3f, 0.095f}}},
+    {2, 2, 2, {{2.71f, 1.54f, 0.28f, 14.6f, 0.111f}, {3.45f, 0.51f, 0.62f, 11.4f, 0.077f}}},
+    {2, 2, 4, {{2.73f, 0.85f, 0.75f, 12.8f, 0.119f}, {3.39f, 0.00f, 1.22f, 11.4f, 0.091f}}},
+    {2, 4, 4, {{2.56f, 2.53f, 0.51f, 21.2f, 0.094f}, {2.95f, 1.20f, 1.23f, 11.3f, 0.091f}}},
+    {3, 2, 4, {{3.06f, 1.10f, 0.87f, 12.8f, 0.097f}, {3.18f, 0.85f, 1.45f, 10.9f, 0.079f}}},
+    {3, 4, 4, {{2.56f, 2.95f, 0.46f, 21.3f, 0.068f}, {2.83f, 1.81f, 0.98f, 11.0f, 0.088f}}},
+    {4, 4, 4, {{2.95f, 3.09f, 1.13f, 21.7f, 0.099f}, {2.89f, 2.22f, 1.22f, 11.0f, 0.081f}}},
+    {5, 4, 4, {{2.45f, 4.00f, 0.36f, 20.1f, 0.082f}, {2.49f, 3.15f, 0.74f, 11.1f, 0.075f}}},
+    {6, 4, 4, {{2.72f, 4.34f, 0.56f, 20.6f, 0.063f}, {2.85f, 3.36f, 1.01f, 11.2f, 0.054f}}},
+    {7, 4, 4, {{2.85f, 4.89f, 0.63f, 20.9f, 0.086f}, {2.99f, 3.73f, 1.23f, 10.7f, 0.079f}}},
 };
 
 // Waves per SIMD that the instantiations' registers (tiled) or rings (row-major) allow.

@@ -535,22 +535,26 @@ bool make_stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled
 
 }  // namespace
 
-// The plan's own model orders plans of one kernel; against the other kernels it is calibrated on 130 shapes (about 8 % rms): fixed
-// time, its factor, weights per megabyte, K steps (thin slabs of one or two steps per stage pay for each), the reduction launch.
-static double calibrated_us(const StreamArgs& q, double mb, bool tiled)
+// The plan's own model orders plans of one kernel; against the other kernels it is calibrated on 970 shapes (1 to 128 tokens, weights in
+// the last-level cache and in memory; 3 to 10 % rms): fixed time, its factor, weights per megabyte, K steps (thin slabs of one or two
+// steps per stage pay for each), partial sums, and four microseconds per million outputs (odd: their rows are not whole 16-byte
+// pieces).  Without the outputs 32 x 1088 -> 31936 tiled was taken for 13 us; it takes 20, the direct kernel 12.
+static double calibrated_us(const StreamArgs& q, double M, double N, double K, bool tiled)
 {
-    const double us = q.us, nks = (double)q.iters * q.ksub;
-    if (q.regs) return 6.1 + 0.67 * us + 0.048 * mb + (q.gk > 1 ? 2.1 : 0.0);
-    if (q.ksub == 1) return tiled ? 5.6 + 0.05 * us + 0.118 * mb + 0.175 * nks + (q.gk > 1 ? 16.5 : 0.0)
-                                  : 5.4 + 0.66 * us + 0.036 * mb + 0.142 * nks + (q.gk > 1 ? 5.4 : 0.0);
-    if (q.ksub == 2) return tiled ? 5.9 + 0.71 * us + 0.005 * mb + 0.052 * nks : 5.5 + 0.30 * us + 0.135 * mb + 0.023 * nks + (q.gk > 1 ? 8.8 : 0.0);
-    return tiled ? 6.2 + 0.38 * us + 0.074 * mb + 0.013 * nks : 5.2 + 0.52 * us + 0.084 * mb;
+    const double us = q.us, nks = (double)q.iters * q.ksub, mb = N * K * 1e-6, out = M * N * 1e-6;
+    const double split = q.gk > 1 ? 1.0 : 0.0, part = q.gk > 1 ? q.gk * out : 0.0, odd = (int64_t)N % 8 ? 1.0 : 0.0;
+    if (q.regs) return 5.0 + 0.27 * us + 0.085 * mb + 0.030 * nks + 2.2 * split + 2.3 * part + (4.1 + 0.2 * odd) * out;
+    if (q.ksub == 1) return tiled ? 5.2 + 0.09 * us + 0.094 * mb + 0.195 * nks + 4.0 * split + 1.9 * part + 4.0 * out
+                                  : 5.2 + 0.12 * us + 0.114 * mb + 0.187 * nks + 1.9 * split + 2.4 * part + (3.9 + 1.4 * odd) * out;
+    if (q.ksub == 2) return tiled ? 5.2 + 0.24 * us + 0.069 * mb + 0.105 * nks + 5.2 * part + (3.9 + 0.7 * odd) * out
+                                  : 5.4 + 0.15 * us + 0.120 * mb + 0.088 * nks + 3.5 * part + 0.33 * odd + 3.8 * out;
+    return tiled ? 5.2 + 0.13 * us + 0.073 * mb + 0.068 * nks + (5.3 + 6.0 * odd) * out : 5.3 + 0.25 * us + 0.125 * mb + 0.033 * nks + 4.2 * out;
 }
 
 bool sq_stream_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, StreamArgs* out)
 {
     if (!make_stream_plan(M, N, K, batch, tiled, out)) return false;
-    out->us = calibrated_us(*out, (double)N * (double)K * 1e-6, tiled);
+    out->us = calibrated_us(*out, (double)M, (double)N, (double)K, tiled);
     return true;
 }
 
