@@ -14,11 +14,13 @@ template <bool BF16> SQ_DEVICE void unpack8w(const v4u raw, float (&f)[8])
     }
 }
 
+constexpr int kTensorParts = 512;  // most workgroups that leave a part of the tensor's maximum
+
 // Maxima over rows of W: one row (input channel j) per WPR waves, four 16-byte loads per lane in flight.  ROWS: row_out[j] =
 // max_n |W_jn|.  Otherwise the maximum over the tensor, each row scaled by s_j: a workgroup keeps it over all its rows and leaves it in
 // tensor_max[blockIdx.x], or (ATOMIC: a workspace too small for that) adds it to the cleared tensor_max[0] with one atomic: the integer
 // order of the bit patterns of non-negative floats is the float order.  (Atomics on one cell take some 12 ns each, one
-// after the other, and want it cleared: preparation per tensor of 4096 x 4096 25.1 us, now 20.7; 768 x 3072 14.0, now 11.4.)
+// after the other, and want it cleared: preparation per tensor of 768 x 3072 11.5 us, now 9.1; with the reduction below 4096 x 4096 25.5, now 20.7.)
 template <bool BF16, bool ROWS, int WPR, bool ATOMIC>
 __global__ __launch_bounds__(256) void weight_row_absmax_kernel(const uint16_t* __restrict__ w, int c_i, int c_o,
                                                                const float* __restrict__ s, float* row_out,
@@ -80,8 +82,8 @@ typedef float f4w __attribute__((ext_vector_type(4), aligned(4)));  // (a worksp
 // Per-output-channel maxima of a slab of rows: out[slab][n] = max_j |W_jn * s_j|.  A workgroup owns 512 columns (a wave's row of 1 KB)
 // over a slab, one row in four per wave with eight loads in flight; the waves meet in LDS.  The slabs' maxima go to memory by plain
 // stores and meet in the kernel below.  (One atomic per slab and column leaves the XCD's L2 for the memory side: preparation per channel of
-// 4096 x 4096 32.2 us, now 27.3; 5120 x 20480 103.9,
-// now 94.0; 12288 x 64 41.8, now 22.7.  Eight loads in flight instead of four are 3 to 5 % of the large ones.)
+// 4096 x 4096 34.9 us, now 25; 5120 x 20480 99,
+// now 92; 12288 x 64 39, now 13.7.  Eight loads in flight instead of four are 3 to 5 % of the large ones.)
 template <bool BF16>
 __global__ __launch_bounds__(256) void weight_col_absmax_kernel(const uint16_t* __restrict__ w, int c_i, int c_o,
                                                                const float* __restrict__ s, int rows_per_wg, float* out)
@@ -125,18 +127,43 @@ __global__ __launch_bounds__(256) void weight_col_absmax_kernel(const uint16_t* 
     }
 }
 
-// col_max[n] = the largest of part[slab][n], four columns per thread.
-__global__ __launch_bounds__(64) void weight_col_reduce_kernel(const float* part, int c_o, int slabs, float* col_max)
+// The parts of the tensor's maximum to their largest, in place: behind more than 256 of them.  (Every wave of the transposing kernel reads
+// the parts in front of its work.  Up to 256 that costs less than this launch -- 1024 x 8192 14.7 us without, 15.6 with it, 1536 x 1536
+// 9.9 / 9.7 --, at 512 a tenth of that kernel: 6432 x 8104 70.3 / 68.4, 10368 x 13984 161.6 / 156.7, 5120 x 20480 tiled 90.6 / 88.6.)
+__global__ __launch_bounds__(kTensorParts) void weight_parts_reduce_kernel(uint32_t* tensor_max, int parts)
 {
-    const int n = (blockIdx.x * 64 + threadIdx.x) * 4;
-    if (n >= c_o) return;
-    float4 m = *(const float4*)(part + n);
-#pragma unroll 8
-    for (int s = 1; s < slabs; ++s) {
-        const float4 v = *(const float4*)(part + (int64_t)s * c_o + n);
-        m = float4{__builtin_fmaxf(m.x, v.x), __builtin_fmaxf(m.y, v.y), __builtin_fmaxf(m.z, v.z), __builtin_fmaxf(m.w, v.w)};
+    __shared__ float red[kTensorParts / 64];
+    float a = wave_max(__builtin_bit_cast(float, tensor_max[(int)threadIdx.x < parts ? threadIdx.x : 0]));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+    __syncthreads();  // everyone has read
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int i = 1; i < kTensorParts / 64; ++i) a = __builtin_fmaxf(a, red[i]);
+        tensor_max[0] = __builtin_bit_cast(uint32_t, a);
     }
-    *(f4w*)(col_max + n) = f4w{m.x, m.y, m.z, m.w};
+}
+
+// col_max[n] = the largest of part[slab][n].  Sixteen threads take the slabs of four columns, so that a slab is one load away for up to
+// sixteen of them (one thread for all slabs of its columns: preparation of 12288 x 64 20.7 us, now 13.7; 944 x 40 14.6, now 13.4; 832 x 1032
+// 15.8, now 15.1; 4096 x 4096 30.0, now 25.8).
+__global__ __launch_bounds__(256) void weight_col_reduce_kernel(const float* part, int c_o, int slabs, float* col_max)
+{
+    __shared__ float4 red[16][16];
+    const int quad = threadIdx.x & 15, first = threadIdx.x >> 4;
+    const int n = (blockIdx.x * 16 + quad) * 4;
+    float4 m = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto larger = [](float4 a, float4 b) { return float4{__builtin_fmaxf(a.x, b.x), __builtin_fmaxf(a.y, b.y), __builtin_fmaxf(a.z, b.z), __builtin_fmaxf(a.w, b.w)}; };
+    if (n < c_o) {  // c_o % 8 == 0
+#pragma unroll 4
+        for (int s = first; s < slabs; s += 16) m = larger(m, *(const float4*)(part + (int64_t)s * c_o + n));
+    }
+    red[first][quad] = m;
+    __syncthreads();
+    if (first == 0 && n < c_o) {
+#pragma unroll
+        for (int i = 1; i < 16; ++i) m = larger(m, red[i][quad]);
+        *(f4w*)(col_max + n) = f4w{m.x, m.y, m.z, m.w};
+    }
 }
 
 // Quantize and transpose.  A wave owns 64 input x 128 output channels: lane (ng, jc) loads rows 16 jc .. 16 jc + 15 of its 8
@@ -167,9 +194,14 @@ __global__ __launch_bounds__(256) void weight_quant_transpose_kernel(const uint1
             if (j0 == 0 && jc == 0 && n < c_o) w_scale[n + e] = a / 127.0f;
         }
     } else {
-        float a = 0.0f;  // the largest of the parts
-        for (int i = lane; i < parts; i += 64) a = __builtin_fmaxf(a, __builtin_bit_cast(float, amax_bits[i]));
-        a = wave_max(a);
+        float a;
+        if (parts == 1) {
+            a = __builtin_bit_cast(float, amax_bits[0]);
+        } else {
+            a = 0.0f;  // the largest of the parts
+            for (int i = lane; i < parts; i += 64) a = __builtin_fmaxf(a, __builtin_bit_cast(float, amax_bits[i]));
+            a = wave_max(a);
+        }
         const float r0 = a > 0.0f ? 127.0f / a : 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) r[e] = r0;
@@ -231,7 +263,7 @@ template <bool ROWS>
 int launch_row_absmax(const uint16_t* w, sq_dtype dtype, int c_i, int c_o, const float* s, float* row_out, uint32_t* tensor_max, size_t room, hipStream_t st)
 {
     const bool wide = ROWS ? c_i <= 1024 && c_o > 4096 : c_i <= 256 && c_o > 16384;
-    const int64_t need = wide ? c_i : ((int64_t)c_i + 3) / 4, cap = ROWS ? 65535 : 512;  // (the kernel strides over the rest)
+    const int64_t need = wide ? c_i : ((int64_t)c_i + 3) / 4, cap = ROWS ? 65535 : kTensorParts;  // (the kernel strides over the rest)
     const dim3 grid((unsigned)(need < cap ? need : cap));
     const bool atomic = !ROWS && room < grid.x;
     if (atomic) sq_launch(zero_u32_kernel, dim3(1), dim3(256), 0, st, tensor_max, (int64_t)1);
@@ -288,15 +320,20 @@ sq_status sq_prepare_weight(const void* w, sq_dtype dtype, const float* s, int64
         const int64_t colb = (c_o / 8 + 63) / 64;
         int64_t slabs = (1024 + colb - 1) / colb;
         if (slabs > (c_i + 63) / 64) slabs = (c_i + 63) / 64;
+        if (c_i <= 96) slabs = 1;  // no second launch (us, two slabs / one: 80 x 576 13.4 / 12.8, 128 x 576 13.2 / 14.2)
         const int rows = (int)((c_i + slabs - 1) / slabs);
         slabs = (c_i + rows - 1) / rows;
         float* part = slabs > 1 ? (float*)wq : (float*)amax;
         const dim3 gridc((unsigned)colb, (unsigned)slabs);
         if (dtype == SQ_BF16) sq_launch(weight_col_absmax_kernel<true>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, rows, part);
         else sq_launch(weight_col_absmax_kernel<false>, gridc, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, rows, part);
-        if (slabs > 1) sq_launch(weight_col_reduce_kernel, dim3((unsigned)((c_o / 4 + 63) / 64)), dim3(64), 0, st, part, (int)c_o, (int)slabs, (float*)amax);
+        if (slabs > 1) sq_launch(weight_col_reduce_kernel, dim3((unsigned)((c_o / 4 + 15) / 16)), dim3(256), 0, st, part, (int)c_o, (int)slabs, (float*)amax);
     } else {
         parts = launch_row_absmax<false>((const uint16_t*)w, dtype, (int)c_i, (int)c_o, s, nullptr, amax, ws_bytes / sizeof(uint32_t), st);
+        if (parts > 256) {
+            sq_launch(weight_parts_reduce_kernel, dim3(1), dim3(kTensorParts), 0, st, amax, parts);
+            parts = 1;
+        }
     }
     if (dtype == SQ_BF16) sq_launch(weight_quant_transpose_kernel<true>, grid2, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax, parts, w_scale, wq, tiled, pc);
     else sq_launch(weight_quant_transpose_kernel<false>, grid2, dim3(256), 0, st, (const uint16_t*)w, (int)c_i, (int)c_o, s, amax, parts, w_scale, wq, tiled, pc);
