@@ -118,14 +118,14 @@ size_t linear_workspace(int64_t t, int64_t c_i, int64_t c_o)
     return e.bytes;
 }
 
-template <class F> sq_status unlocked(F&& call)
-{
-    sq_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = call();
-    Py_END_ALLOW_THREADS
-    return st;
-}
+// The interpreter's lock is given up while outputs are allocated and kernels launched, as torch.empty and a ctypes call do: a first-time
+// allocation can wait for the device, and other Python threads go on meanwhile.
+struct Unlocked {
+    PyThreadState* state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked&) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
 PyObject* pair(const at::Tensor& a, PyObject* b) { return b ? Py_BuildValue("(NN)", THPVariable_Wrap(a), b) : nullptr; }
 
 #define GENERAL Py_RETURN_NONE
@@ -145,20 +145,22 @@ PyObject* quantize_act(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (t <= 0 || c_i <= 0 || (layout == SQ_TILED && c_i % 64)) GENERAL;
     step = nullptr;
     if (mode == SQ_PER_TENSOR_STATIC && !(step = plain(a[3], at::kFloat))) GENERAL;
-    at::Tensor xq = empty_codes(t, c_i, layout, *x), scale, ws;
-    if (mode != SQ_PER_TENSOR_STATIC) scale = empty({mode == SQ_PER_TOKEN_DYNAMIC ? t : 1}, *x, at::kFloat);
-    size_t bytes = 0;
-    if (mode == SQ_PER_TENSOR_DYNAMIC) {
-        bytes = api.workspace_bytes(SQ_OP_QUANTIZE_ACT, t, c_i, 0);
-        ws = empty({(int64_t)bytes}, *x, at::kByte);
+    at::Tensor xq, scale, ws;
+    sq_status status;
+    {
+        Unlocked u;
+        xq = empty_codes(t, c_i, layout, *x);
+        if (mode != SQ_PER_TENSOR_STATIC) scale = empty({mode == SQ_PER_TOKEN_DYNAMIC ? t : 1}, *x, at::kFloat);
+        size_t bytes = 0;
+        if (mode == SQ_PER_TENSOR_DYNAMIC) {
+            bytes = api.workspace_bytes(SQ_OP_QUANTIZE_ACT, t, c_i, 0);
+            ws = empty({(int64_t)bytes}, *x, at::kByte);
+        }
+        float* sp = (float*)(step ? step->const_data_ptr() : scale.const_data_ptr());
+        status = api.quantize_act(x->const_data_ptr(), dt, t, c_i, c_i, (const float*)ptr(inv_s), (sq_act_mode)mode, sp, (int8_t*)xq.data_ptr(), layout,
+                                  bytes ? ws.data_ptr() : nullptr, bytes, stream());
     }
-    float* sp = (float*)(step ? step->const_data_ptr() : scale.const_data_ptr());
-    void* st = stream();
-    if (unlocked([&] {
-            return api.quantize_act(x->const_data_ptr(), dt, t, c_i, c_i, (const float*)ptr(inv_s), (sq_act_mode)mode, sp, (int8_t*)xq.data_ptr(), layout,
-                                    bytes ? ws.data_ptr() : nullptr, bytes, st);
-        }) != SQ_OK)
-        GENERAL;
+    if (status != SQ_OK) GENERAL;
     if (step) {
         Py_INCREF(a[3]);
         return pair(xq, a[3]);
@@ -196,16 +198,18 @@ PyObject* w8a8_linear(PyObject*, PyObject* const* a, Py_ssize_t n)
     at::ScalarType type;
     sq_dtype dt;
     if (n != 9 || modes() || !half_dtype(a[8], &type, &dt) || !linear_args(a, type, &l)) GENERAL;
-    at::Tensor y = empty({l.t, l.c_o}, *l.xq, type), ws;
-    const size_t bytes = linear_workspace(l.t, l.c_i, l.c_o);
-    if (bytes) ws = empty({(int64_t)bytes}, *l.xq, at::kByte);
-    void* st = stream();
-    if (unlocked([&] {
-            return api.w8a8_linear((const int8_t*)ptr(l.xq), (const float*)ptr(l.xs), l.xs->numel() == l.t, (const int8_t*)ptr(l.wq), (const float*)ptr(l.ws),
-                                   l.per_channel, (const float*)ptr(l.bias), ptr(l.res), l.relu, y.data_ptr(), dt, l.t, l.c_i, l.c_o, l.layout,
-                                   bytes ? ws.data_ptr() : nullptr, bytes, st);
-        }) != SQ_OK)
-        GENERAL;
+    at::Tensor y, ws;
+    sq_status status;
+    {
+        Unlocked u;
+        y = empty({l.t, l.c_o}, *l.xq, type);
+        const size_t bytes = linear_workspace(l.t, l.c_i, l.c_o);
+        if (bytes) ws = empty({(int64_t)bytes}, *l.xq, at::kByte);
+        status = api.w8a8_linear((const int8_t*)ptr(l.xq), (const float*)ptr(l.xs), l.xs->numel() == l.t, (const int8_t*)ptr(l.wq), (const float*)ptr(l.ws),
+                                 l.per_channel, (const float*)ptr(l.bias), ptr(l.res), l.relu, y.data_ptr(), dt, l.t, l.c_i, l.c_o, l.layout,
+                                 bytes ? ws.data_ptr() : nullptr, bytes, stream());
+    }
+    if (status != SQ_OK) GENERAL;
     return THPVariable_Wrap(y);
     END_HANDLE_TH_ERRORS
 }
@@ -222,16 +226,18 @@ PyObject* w8a8_linear_q8(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (n != 11 || modes() || !half_dtype(a[8], &type, &dt) || !linear_args(a, type, &l) || !(step = plain(a[9], at::kFloat)) ||
         !layout_of(a[10], &out_layout) || (out_layout == SQ_TILED && l.c_o % 64))
         GENERAL;
-    at::Tensor y = empty_codes(l.t, l.c_o, out_layout, *l.xq), ws;
-    const size_t bytes = linear_workspace(l.t, l.c_i, l.c_o);
-    if (bytes) ws = empty({(int64_t)bytes}, *l.xq, at::kByte);
-    void* st = stream();
-    if (unlocked([&] {
-            return api.w8a8_linear_q8((const int8_t*)ptr(l.xq), (const float*)ptr(l.xs), l.xs->numel() == l.t, (const int8_t*)ptr(l.wq),
-                                      (const float*)ptr(l.ws), l.per_channel, (const float*)ptr(l.bias), ptr(l.res), l.relu, dt, (const float*)ptr(step),
-                                      (int8_t*)y.data_ptr(), out_layout, l.t, l.c_i, l.c_o, l.layout, bytes ? ws.data_ptr() : nullptr, bytes, st);
-        }) != SQ_OK)
-        GENERAL;
+    at::Tensor y, ws;
+    sq_status status;
+    {
+        Unlocked u;
+        y = empty_codes(l.t, l.c_o, out_layout, *l.xq);
+        const size_t bytes = linear_workspace(l.t, l.c_i, l.c_o);
+        if (bytes) ws = empty({(int64_t)bytes}, *l.xq, at::kByte);
+        status = api.w8a8_linear_q8((const int8_t*)ptr(l.xq), (const float*)ptr(l.xs), l.xs->numel() == l.t, (const int8_t*)ptr(l.wq),
+                                    (const float*)ptr(l.ws), l.per_channel, (const float*)ptr(l.bias), ptr(l.res), l.relu, dt, (const float*)ptr(step),
+                                    (int8_t*)y.data_ptr(), out_layout, l.t, l.c_i, l.c_o, l.layout, bytes ? ws.data_ptr() : nullptr, bytes, stream());
+    }
+    if (status != SQ_OK) GENERAL;
     return THPVariable_Wrap(y);
     END_HANDLE_TH_ERRORS
 }
@@ -250,12 +256,14 @@ PyObject* w8a8_bmm(PyObject*, PyObject* const* a, Py_ssize_t nargs)
         GENERAL;
     const int64_t b = x->size(0), m = x->size(1), k = x->size(2), n = y->size(trans ? 1 : 2);
     if (b <= 0 || m <= 0 || n <= 0 || k <= 0) GENERAL;
-    at::Tensor c = empty({b, m, n}, *x, type);
-    void* st = stream();
-    if (unlocked([&] {
-            return api.w8a8_bmm((const int8_t*)ptr(x), (const int8_t*)ptr(y), trans, alpha, c.data_ptr(), dt, b, m, n, k, m * k, n * k, m * n, st);
-        }) != SQ_OK)
-        GENERAL;
+    at::Tensor c;
+    sq_status status;
+    {
+        Unlocked u;
+        c = empty({b, m, n}, *x, type);
+        status = api.w8a8_bmm((const int8_t*)ptr(x), (const int8_t*)ptr(y), trans, alpha, c.data_ptr(), dt, b, m, n, k, m * k, n * k, m * n, stream());
+    }
+    if (status != SQ_OK) GENERAL;
     return THPVariable_Wrap(c);
     END_HANDLE_TH_ERRORS
 }
@@ -268,9 +276,14 @@ PyObject* softmax_quant_p(PyObject*, PyObject* const* a, Py_ssize_t n)
     sq_dtype dt;
     if (n != 1 || modes() || !(s = plain(a[0])) || s->dim() < 1 || s->numel() <= 0 || !half_type(s->scalar_type(), &dt)) GENERAL;
     const int64_t cols = s->size(-1), rows = s->numel() / cols;
-    at::Tensor p = empty(s->sizes(), *s, at::kChar);
-    void* st = stream();
-    if (unlocked([&] { return api.softmax_quant_p(ptr(s), dt, rows, cols, (int8_t*)p.data_ptr(), st); }) != SQ_OK) GENERAL;
+    at::Tensor p;
+    sq_status status;
+    {
+        Unlocked u;
+        p = empty(s->sizes(), *s, at::kChar);
+        status = api.softmax_quant_p(ptr(s), dt, rows, cols, (int8_t*)p.data_ptr(), stream());
+    }
+    if (status != SQ_OK) GENERAL;
     return THPVariable_Wrap(p);
     END_HANDLE_TH_ERRORS
 }
@@ -288,12 +301,15 @@ PyObject* ln_quantize(PyObject*, PyObject* const* a, Py_ssize_t n)
         GENERAL;
     const int64_t t = x->size(0), c = x->size(1);
     if (t <= 0 || c <= 0 || (layout == SQ_TILED && c % 64)) GENERAL;
-    at::Tensor xq = empty_codes(t, c, layout, *x), scale = empty({t}, *x, at::kFloat);
-    void* st = stream();
-    if (unlocked([&] {
-            return api.ln_quantize(ptr(x), dt, t, c, (const float*)ptr(g), (const float*)ptr(b), eps, (float*)scale.data_ptr(), (int8_t*)xq.data_ptr(), layout, st);
-        }) != SQ_OK)
-        GENERAL;
+    at::Tensor xq, scale;
+    sq_status status;
+    {
+        Unlocked u;
+        xq = empty_codes(t, c, layout, *x);
+        scale = empty({t}, *x, at::kFloat);
+        status = api.ln_quantize(ptr(x), dt, t, c, (const float*)ptr(g), (const float*)ptr(b), eps, (float*)scale.data_ptr(), (int8_t*)xq.data_ptr(), layout, stream());
+    }
+    if (status != SQ_OK) GENERAL;
     return pair(xq, THPVariable_Wrap(scale));
     END_HANDLE_TH_ERRORS
 }
@@ -312,13 +328,15 @@ PyObject* w8a8_attention(PyObject*, PyObject* const* a, Py_ssize_t n)
         GENERAL;
     const int64_t b = q->size(0), s_q = q->size(1), d = q->size(2), s_k = k->size(1);
     if (b <= 0 || s_q <= 0 || s_k <= 0 || d <= 0 || k->size(0) != b || k->size(2) != d) GENERAL;
-    at::Tensor o = empty({b, s_q, d}, *q, type);
-    void* st = stream();
-    if (unlocked([&] {
-            return (causal ? api.attention_causal : api.attention)((const int8_t*)ptr(q), (const int8_t*)ptr(k), (const int8_t*)ptr(v), a1, a2, o.data_ptr(),
-                                                                   dt, b, s_q, s_k, d, s_q * d, s_k * d, s_k * d, s_q * d, nullptr, st);
-        }) != SQ_OK)
-        GENERAL;
+    at::Tensor o;
+    sq_status status;
+    {
+        Unlocked u;
+        o = empty({b, s_q, d}, *q, type);
+        status = (causal ? api.attention_causal : api.attention)((const int8_t*)ptr(q), (const int8_t*)ptr(k), (const int8_t*)ptr(v), a1, a2, o.data_ptr(),
+                                                                 dt, b, s_q, s_k, d, s_q * d, s_k * d, s_k * d, s_q * d, nullptr, stream());
+    }
+    if (status != SQ_OK) GENERAL;
     return THPVariable_Wrap(o);
     END_HANDLE_TH_ERRORS
 }
