@@ -51,6 +51,12 @@ int sq_probe_linear_form(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout);
 /* 1000000 s + 1000 m + n where it runs m x n tiles staged through LDS with s K splits, else 0.  No GPU work. */
 int sq_probe_linear_tile(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout);
 
+/* The plan of a linear layer of this size: out[0] the kernel (0 direct, 1 weight streaming, 2 tiles staged through LDS), out[1] its variant
+ * (direct: 100 mb + 10 nb + nw; streaming: 1 the register-direct kernel, 0 the LDS ring; tiles: their number in the library), out[2] the K
+ * splits, out[3] the 64-byte K steps of a split, out[4] and out[5] streaming: slabs and 16-channel units, tiles: token and channel tiles,
+ * direct: 0.  No GPU work. */
+sq_status sq_probe_linear_plan(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout, int64_t out[6]);
+
 #ifdef __cplusplus
 }
 #endif

@@ -30,6 +30,7 @@ EXPORTS = (
     "sq_w8a8_linear_noalloc", "sq_static_scratch_bytes", "sq_w8a8_attention", "sq_w8a8_attention_causal",
     "sq_probe_attention", "sq_probe_attention_form", "sq_probe_attention_place",
     "sq_probe_narrow_gemm", "sq_probe_linear_form", "sq_probe_linear_tile", "sq_probe_linear_blocks",
+    "sq_probe_linear_plan",
 )
 
 
@@ -89,6 +90,7 @@ def lib() -> ctypes.CDLL:
         L.sq_probe_attention_form.argtypes = [i64, i64, i64, i64, i32]
         L.sq_probe_attention_place.argtypes = [i64, i64, i64, i64, i64, ctypes.POINTER(i64)]
         L.sq_probe_narrow_gemm.argtypes = L.sq_probe_linear_form.argtypes = L.sq_probe_linear_tile.argtypes = [i64, i64, i64, i32]
+        L.sq_probe_linear_plan.argtypes = [i64, i64, i64, i32, ctypes.POINTER(i64)]
         L.sq_probe_linear_blocks.argtypes = [i32, i32, i32, *L.sq_w8a8_linear.argtypes[:15], vp]
         L.sq_softmax_quant_p.argtypes = [vp, i32, i64, i64, vp, vp]
         L.sq_ln_quantize.argtypes = [vp, i32, i64, i64, vp, vp, f32, vp, vp, i32, vp]
@@ -407,6 +409,13 @@ def probe_mfma_i8(data: torch.Tensor, workgroups: int, iters: int) -> float:
     _check(lib().sq_probe_mfma_i8(_dev(data, torch.int8, "data"), data.numel(), workgroups, iters, sink.data_ptr(), _stream()),
            "sq_probe_mfma_i8")
     return float(workgroups) * 8 * iters * 8 * 65536
+
+
+def probe_linear_plan(t: int, c_i: int, c_o: int, layout: int = ROW_MAJOR) -> tuple:
+    """Test aid: the six numbers of sq_probe_linear_plan (kernel, variant, K splits, K steps of a split, slabs or tiles)."""
+    out = (ctypes.c_int64 * 6)()
+    _check(lib().sq_probe_linear_plan(t, c_i, c_o, layout, out), "sq_probe_linear_plan")
+    return tuple(out)
 
 
 def ln_quantize(x: torch.Tensor, gamma_f: torch.Tensor, beta_f: torch.Tensor, eps: float = 1e-5, out=None,

@@ -444,6 +444,22 @@ int sq_probe_linear_tile(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout)
     return p.tiles && !p.direct.mb ? pl.splits * 1000000 + pl.bm * 1000 + pl.bn : 0;
 }
 
+sq_status sq_probe_linear_plan(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout, int64_t out[6])
+{
+    if (!out) return SQ_ERR_NULL;
+    if (!dims_ok(t, c_i, c_o)) return SQ_ERR_SHAPE;
+    StreamArgs sp{};
+    TilePlan pl{};
+    const Path p = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, true, &sp, &pl);
+    const int64_t steps = (c_i + 63) / 64;
+    const int64_t direct[6] = {0, 100 * p.direct.mb + 10 * p.direct.nb + p.direct.nw, 1, steps, 0, 0};
+    const int64_t stream[6] = {1, sp.regs, sp.gk, (int64_t)sp.iters * sp.ksub, sp.gn, sp.units};
+    const int64_t tiles[6] = {2, pl.cfg, pl.splits, pl.iters_per_split, pl.tiles_m, pl.tiles_n};
+    const int64_t* plan = p.direct.mb ? direct : p.stream ? stream : tiles;
+    for (int i = 0; i < 6; ++i) out[i] = plan[i];
+    return SQ_OK;
+}
+
 // Measurement and test aid: sq_w8a8_linear by the direct kernel with tiles of 16 mb tokens x 16 nb channels.
 sq_status sq_probe_linear_blocks(int mb, int nb, int nw, const int8_t* xq, const float* x_scale, int x_scale_per_token, const int8_t* wq,
                                  const float* w_scale, int w_scale_per_channel, const float* bias, const void* residual, int relu,

@@ -18,19 +18,26 @@ def _progress(msg):
 
 CASES = [
     # t, c_i, c_o, mid dtype, bias, relu, residual, in layout, out layout, per-channel W
-    (300, 1024, 1000, BF16, True, True, False, sq.ROW_MAJOR, sq.ROW_MAJOR, False),   # prefill tiles, ragged
+    (300, 1024, 1000, BF16, True, True, False, sq.ROW_MAJOR, sq.ROW_MAJOR, False),   # direct kernel, ragged
     (2048, 256, 1536, F16, False, True, False, sq.TILED, sq.TILED, False),           # FC1 + ReLU -> codes for FC2
     (513, 320, 2048, F16, True, False, True, sq.ROW_MAJOR, sq.TILED, True),          # K tail, residual, per-channel W
-    (16, 4096, 1024, BF16, True, False, False, sq.TILED, sq.ROW_MAJOR, False),       # split-K + reduction kernel
-    (5, 1024, 4096, F16, True, True, True, sq.ROW_MAJOR, sq.TILED, False),           # weight streaming
-    (128, 4096, 4096, BF16, True, False, False, sq.TILED, sq.TILED, True),           # streaming with a K split
-    (70, 1088, 8192, F16, False, False, False, sq.TILED, sq.ROW_MAJOR, False),       # streaming, 8-wave shape
+    (16, 4096, 1024, BF16, True, False, False, sq.TILED, sq.ROW_MAJOR, False),       # direct kernel, few channels
+    (5, 1024, 4096, F16, True, True, True, sq.ROW_MAJOR, sq.TILED, False),           # direct kernel, five tokens
+    (128, 4096, 4096, BF16, True, False, False, sq.TILED, sq.TILED, True),           # direct kernel, 128 tokens
+    (70, 1088, 8192, F16, False, False, False, sq.TILED, sq.ROW_MAJOR, False),       # direct kernel, 70 tokens
+    (124, 20480, 1088, F16, True, True, False, sq.TILED, sq.TILED, True),            # split-K tiles + reduction kernel
+    (79, 20928, 1696, BF16, True, False, True, sq.ROW_MAJOR, sq.ROW_MAJOR, False),   # the same, row-major
+    (5, 768, 16512, F16, True, True, True, sq.ROW_MAJOR, sq.TILED, False),           # weight streaming
+    (64, 8320, 4160, BF16, True, False, False, sq.TILED, sq.TILED, True),            # streaming with a K split
+    (64, 1216, 8640, F16, False, False, False, sq.TILED, sq.ROW_MAJOR, False),       # streaming straight into registers
 ]
+PLANNED = {(2048, 256): 2, (124, 20480): 2, (79, 20928): 2, (5, 768): 1, (64, 8320): 1, (64, 1216): 1}  # the others: direct kernel
 
 
 @pytest.mark.parametrize("t,c_i,c_o,mid,use_bias,relu,use_res,lay_in,lay_out,w_pc", CASES)
 def test_linear_q8_matches_linear_then_static_quantize(t, c_i, c_o, mid, use_bias, relu, use_res, lay_in, lay_out, w_pc):
     _progress(f"linear_q8 t={t} c_i={c_i} c_o={c_o} mid={mid} in={lay_in} out={lay_out} w_pc={w_pc}")
+    assert sq.probe_linear_plan(t, c_i, c_o, lay_in)[0] == PLANNED.get((t, c_i), 0)
     seed = 11000 + t + c_i + c_o
     case = synth.linear_case(t, c_i, c_o, 0.01, 40.0, seed, calib_tokens=64)
     ax = oracle.act_absmax_per_channel(case["x_calib"], F16)

@@ -12,22 +12,26 @@ from tests._util import F16, dev, to_dev_16
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("t,c_i,c_o,mode", [(16, 1024, 4096, sq.PER_TOKEN_DYNAMIC),    # weight streaming
-                                            (16, 4096, 1024, sq.PER_TOKEN_DYNAMIC),    # few tokens, few channels: one kernel
-                                            (128, 4096, 4096, sq.PER_TENSOR_DYNAMIC),  # streaming with a K split, O2 quantizer
-                                            (300, 512, 768, sq.PER_TOKEN_DYNAMIC),     # prefill tiles
+@pytest.mark.parametrize("t,c_i,c_o,mode", [(16, 1024, 4096, sq.PER_TOKEN_DYNAMIC),    # few tokens
+                                            (16, 4096, 1024, sq.PER_TOKEN_DYNAMIC),    # few tokens, few channels
+                                            (128, 4096, 4096, sq.PER_TENSOR_DYNAMIC),  # direct kernel, O2 quantizer
+                                            (64, 7488, 4288, sq.PER_TENSOR_DYNAMIC),   # streaming with a K split
+                                            (300, 512, 768, sq.PER_TOKEN_DYNAMIC),     # few tiles' worth of outputs
                                             (2048, 12288, 12288, sq.PER_TOKEN_DYNAMIC)])  # the 256x384 tile (uses scratch memory)
 def test_graph_replay_matches_eager(t, c_i, c_o, mode):
     print(f"[case] graph replay t={t} c_i={c_i} c_o={c_o} mode={mode}", flush=True)
+    assert sq.probe_linear_plan(t, c_i, c_o, sq.TILED)[0] == {7488: 1, 12288: 2}.get(c_i, 0)
     _replay(t, c_i, c_o, mode, 64)
 
 
-# split-K tiles and their reduction, one column per thread and four; the per-tensor quantizer with its whole workspace (two
+# split-K tiles and their reduction, one column per thread and four (the last two; the others run the direct kernel); the per-tensor quantizer with its whole workspace (two
 # launches under capture, one outside), tensors that fit its one launch and that do not
-@pytest.mark.parametrize("t,c_i,c_o", [(130, 4096, 112), (140, 12288, 1024), (1000, 9216, 768)])
+@pytest.mark.parametrize("t,c_i,c_o", [(130, 4096, 112), (140, 12288, 1024), (1000, 9216, 768), (114, 22720, 544), (152, 12736, 2208)])
 def test_graph_replay_split_reduction_and_per_tensor_quantizer(t, c_i, c_o):
     print(f"[case] graph replay split reduction t={t} c_i={c_i} c_o={c_o}", flush=True)
     assert sq.workspace_bytes(sq.OP_W8A8_LINEAR, t, c_i, c_o) > 0 and not sq.lib().sq_probe_narrow_gemm(t, c_i, c_o, sq.TILED)
+    kernel, _, splits = sq.probe_linear_plan(t, c_i, c_o, sq.TILED)[:3]
+    assert (kernel, splits > 1) == ((2, True) if c_o in (544, 2208) else (0, False))
     _replay(t, c_i, c_o, sq.PER_TENSOR_DYNAMIC, sq.workspace_bytes(sq.OP_QUANTIZE_ACT, t, c_i, 0))
 
 

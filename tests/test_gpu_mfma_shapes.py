@@ -1,8 +1,7 @@
 """The compute-bound GEMM tiles exist in two MFMA shapes: 16x16x64 (taken when the K range is an even number of whole
-64-byte steps and is not split) and 32x32x32 (everything else).  These shapes are chosen so that the planner's cost
-model picks the 256x256, the 256x384 and the 256x192 tile in each of the two forms (300 tokens = one full and one ragged row block;
-32760 / 49144 output channels = one round of 256 tiles with a ragged last column tile; 4096 resp. 4160 input
-channels = 64 resp. 65 K steps), in both operand layouts.  Sampled rows against the oracle: int32 accumulators exact,
+64-byte steps and is not split) and 32x32x32 (everything else).  Wide layers of 300 tokens (one full and one ragged row block), with
+4096 resp. 4160 input channels (64 resp. 65 K steps) and a ragged last column tile, in both operand layouts, on the tile that the
+planner gives them (every tile in each of its forms is reached by name in test_gpu_planned_paths.py).  Sampled rows against the oracle: int32 accumulators exact,
 16-bit outputs with bias, ReLU and residual identical."""
 import numpy as np
 import pytest
@@ -23,12 +22,12 @@ ROWS = np.array([0, 15, 16, 63, 64, 127, 128, 255, 256, 271, 299], dtype=np.int6
     (4096, 32760, False, F16),   # 256x256, 16x16x64
     (4160, 32760, True, BF16),   # 256x256, 32x32x32 (65 K steps)
     (4096, 49144, True, BF16),   # 256x384, 16x16x64
-    (4160, 49144, False, F16),   # 256x384, 32x32x32
+    (4160, 49144, False, F16),   # 192x224, 65 K steps
     (4112, 32760, False, BF16),  # 256x256, 32x32x32 with a K tail (row-major only)
-    (384, 49144, True, F16),     # 256x384, 16x16x64 on the shortest K range that form takes (6 steps: 3 in flight before the loop)
-    (640, 49144, False, BF16),   # 256x384, 16x16x64, 10 steps
-    (12288, 24568, True, BF16),  # 256x192, 16x16x64 (taken from 192 K steps on: an odd number of parts per step, 5-stage ring)
-    (12352, 24568, False, F16),  # 256x192, 32x32x32 (193 K steps)
+    (384, 49144, True, F16),     # 256x192, 16x16x64 on a short K range (6 steps: 4 in flight before the loop)
+    (640, 49144, False, BF16),   # 192x224, 10 steps
+    (12288, 24568, True, BF16),  # 192x224, 192 steps
+    (12352, 24568, False, F16),  # 192x224, 193 steps
 ])
 def test_tile_forms_vs_oracle(c_i, c_o, tiled, odt):
     print(f"[case] tile forms t={T} c_i={c_i} c_o={c_o} tiled={tiled} out={odt}", flush=True)
@@ -70,9 +69,8 @@ def test_batched_product_on_the_16x16x64_tile():
         assert_identical_16(ulp_distance(bits_from_dev(got[i:i + 1]), ref), f"batch entry {i}")
 
 
-# Seeded shapes that the planner's cost model sends to the 256- and 384-wide tiles, about half of them in each MFMA form
-# (the general random sweep of test_gpu_random_shapes.py stays below one round of tiles and so on the 256x192 tile):
-# (t, c_i, c_o, tiled)
+# Seeded shapes of wide layers, most of them on the 256- and 384-wide tiles, some on the tiles of pairs of K steps (the general
+# random sweep of test_gpu_random_shapes.py stays below one round of tiles): (t, c_i, c_o, tiled)
 WIDE_TILE_SHAPES = [
     (768, 1904, 30064, False), (700, 2144, 24112, False), (255, 2416, 57112, False), (500, 1344, 41992, False),
     (384, 384, 25456, True), (700, 576, 53440, True), (130, 2080, 62664, False), (129, 1600, 53552, False),

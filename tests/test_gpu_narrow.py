@@ -1,5 +1,5 @@
-"""The kernel for few tokens and few output channels: 16-channel workgroups, 16-token blocks (1, 2, 4, 8 of them), 64-byte K
-steps dealt in pairs to eight waves, a last step of one to three 16-byte chunks.  Against the exact integer product and the
+"""Layers of few tokens and few output channels, which the direct kernel takes: ragged tokens and channels, 64-byte K steps dealt in pairs
+to the waves, a last step of one to three 16-byte chunks; and K splits of the tile kernels.  Against the exact integer product and the
 fixed fp32 epilogue in torch: outputs identical."""
 import pytest
 import torch
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 # K tail (row-major only)
 CASES = [(1, 16, 1), (2, 64, 8), (15, 128, 24), (16, 768, 3072), (17, 192, 100), (24, 1024, 772), (32, 1024, 772), (33, 1088, 16), (64, 960, 2048),
          (65, 80, 333), (100, 784, 768), (128, 1008, 1030), (128, 3072, 512), (1, 5120, 4095), (4, 12288, 2304), (3, 2064, 3000),
-         # wider than one 16-channel unit per compute unit, up to 16 tokens: this kernel, then (17 tokens) the streaming one
+         # wider than one 16-channel unit per compute unit: up to 16 tokens without a workspace, then (17 tokens) by the planner's models
          (4, 2048, 5120), (16, 1088, 4112), (9, 512, 6544), (17, 1024, 5120)]
 
 
@@ -31,7 +31,7 @@ def _tile(codes):
 @pytest.mark.parametrize("kind", ["plain", "all", "per_channel_q8", "i32"])
 def test_narrow_linear(t, c_i, c_o, dtype, kind):
     print(f"narrow {t}x{c_i}->{c_o} {dtype} {kind}", flush=True)
-    if (t, c_i, c_o) in CASES[:-1]:  # the last one is the other kernel's
+    if (t, c_i, c_o) in CASES[:-1]:
         assert any(sq.lib().sq_probe_narrow_gemm(t, c_i, c_o, layout) for layout in [sq.ROW_MAJOR] + ([sq.TILED] if c_i % 64 == 0 else []))
     g = torch.Generator(device="cuda").manual_seed(t + c_i + c_o)
     x, w = (torch.randint(-127, 128, s, generator=g, device="cuda", dtype=torch.int32).to(torch.int8) for s in ((t, c_i), (c_o, c_i)))
@@ -65,10 +65,12 @@ def test_narrow_linear(t, c_i, c_o, dtype, kind):
 
 
 # K splits of the tile kernels and their reduction, one column per thread and (C_o % 4 == 0, from 2^17 outputs on) four
-@pytest.mark.parametrize("t,c_i,c_o", [(256, 16384, 256), (200, 20480, 258), (48, 12288, 333), (128, 20480, 772), (511, 12288, 256),
-                                         (512, 12288, 256)])
+@pytest.mark.parametrize("t,c_i,c_o", [(79, 20928, 1656), (79, 20928, 1696), (4, 15808, 8), (150, 12160, 2497), (212, 13312, 1641), (141, 18240, 1648),
+                                         (135, 9344, 5528)])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 def test_split_reduction(t, c_i, c_o, dtype):
     print(f"split reduction {t}x{c_i}->{c_o} {dtype}", flush=True)
+    plans = [sq.probe_linear_plan(t, c_i, c_o, layout) for layout in (sq.ROW_MAJOR, sq.TILED)]
+    assert any(p[0] == 2 and p[2] > 1 for p in plans), plans
     for kind in ("plain", "all", "i32") + (("per_channel_q8",) if c_o % 8 == 0 else ()):
         test_narrow_linear(t, c_i, c_o, dtype, kind)

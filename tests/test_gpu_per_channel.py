@@ -1,5 +1,5 @@
 """GPU parity of per-output-channel weight steps (the weight granularity of Table 7; Eq. 2's diag(Delta_W) as a
-vector): weight preparation (codes and steps bit-exact) and the linear layer on every GEMM path (prefill tiles,
+vector): weight preparation (codes and steps bit-exact) and the linear layer on every GEMM path (direct kernel, tiles,
 few-token tiles with split-K, weight streaming with and without a K split), both operand layouts."""
 import numpy as np
 import pytest
@@ -36,19 +36,25 @@ def test_prepare_weight_per_channel(c_i, c_o, with_s, layout):
 
 PC_LINEAR = [
     # t, c_i, c_o, out dtype, per_token, bias, relu, residual, layout
-    (300, 1024, 1000, BF16, True, True, True, True, sq.ROW_MAJOR),    # prefill tiles, ragged
+    (300, 1024, 1000, BF16, True, True, True, True, sq.ROW_MAJOR),    # direct kernel, ragged
     (2048, 256, 1536, F16, True, False, False, False, sq.TILED),      # prefill tiles
     (513, 320, 2056, F16, False, True, False, True, sq.ROW_MAJOR),    # K tail, per-tensor activation step
-    (16, 4096, 1024, BF16, True, True, False, False, sq.TILED),       # few tokens, narrow C_o: split-K + reduction
-    (5, 1024, 4096, F16, True, True, True, True, sq.ROW_MAJOR),       # weight streaming
-    (128, 4096, 4096, BF16, True, False, False, True, sq.TILED),      # weight streaming with a K split
-    (70, 1088, 8192, F16, True, True, False, False, sq.TILED),        # weight streaming, 8-wave shape
+    (16, 4096, 1024, BF16, True, True, False, False, sq.TILED),       # direct kernel, few channels
+    (5, 1024, 4096, F16, True, True, True, True, sq.ROW_MAJOR),       # direct kernel, five tokens
+    (128, 4096, 4096, BF16, True, False, False, True, sq.TILED),      # direct kernel, 128 tokens
+    (70, 1088, 8192, F16, True, True, False, False, sq.TILED),        # direct kernel, 70 tokens
+    (124, 20480, 1088, F16, True, True, True, True, sq.TILED),        # split-K tiles + reduction
+    (5, 768, 16512, F16, True, True, True, True, sq.ROW_MAJOR),       # weight streaming
+    (64, 8320, 4160, BF16, True, False, False, True, sq.TILED),       # weight streaming with a K split
+    (64, 1216, 8640, F16, True, True, False, False, sq.TILED),        # streaming straight into registers
 ]
+PLANNED = {(2048, 256): 2, (124, 20480): 2, (5, 768): 1, (64, 8320): 1, (64, 1216): 1}  # the others: direct kernel
 
 
 @pytest.mark.parametrize("t,c_i,c_o,odt,per_token,use_bias,relu,use_res,layout", PC_LINEAR)
 def test_linear_per_channel_weight_scale(t, c_i, c_o, odt, per_token, use_bias, relu, use_res, layout):
     _progress(f"per-channel w8a8_linear t={t} c_i={c_i} c_o={c_o} out={odt} layout={layout}")
+    assert sq.probe_linear_plan(t, c_i, c_o, layout)[0] == PLANNED.get((t, c_i), 0)
     seed = 9000 + t + c_i + c_o
     case = synth.linear_case(t, c_i, c_o, 0.01, 40.0, seed, calib_tokens=64)
     # spread the column magnitudes so that per-channel steps differ by orders of magnitude

@@ -1,8 +1,7 @@
-"""Seeded sweep of random small shapes through every GEMM path and both operand layouts: int32 accumulators exact,
-16-bit outputs within 1 ulp, int8 outputs (fused static quantizer) identical to the oracle's chain.  The shapes are
-drawn so that all dispatch branches are hit many times: few tokens against narrow / wide C_o (split-K tiles, weight
-streaming with and without a K split), many tokens with short and long K (one-shot tiles, 256x256 / 256x192 tiles),
-ragged edges in every dimension."""
+"""Seeded sweep of random small shapes through the linear layer in both operand layouts: int32 accumulators exact,
+16-bit outputs within 1 ulp, int8 outputs (fused static quantizer) identical to the oracle's chain.  Few and many
+tokens against narrow and wide C_o, short and long K, ragged edges in every dimension; sizes this small mostly run the direct kernel
+(the streaming and tile kernels are reached by name in test_gpu_planned_paths.py)."""
 import numpy as np
 import pytest
 

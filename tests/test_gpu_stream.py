@@ -1,5 +1,5 @@
-"""GPU parity of the few-token (decode) GEMM path: at most 128 tokens against a wide C_o, where the library
-streams W once through one workgroup per compute unit.  Shapes are chosen to cover every activation-block
+"""GPU parity of the few-token (decode) GEMM path: at most 128 tokens against a wide C_o, where the library reads
+W once, by the streaming kernels or (the smaller sizes) the direct one.  Shapes are chosen to cover every activation-block
 count (1, 2, 4, 8 blocks of 16 tokens), slabs of 1 to 16 column units, uneven slabs, a ragged last unit,
 1 / 2 / 4 K steps per pipeline stage, K ranges shorter than the pipeline, more workgroups than one round, and
 the plans that split K (64..128 tokens against a C_o that gives narrow slabs)."""

@@ -9,10 +9,11 @@ from tests.test_gpu_narrow import _tile
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("t,c_i,c_o", [(40, 1024, 16441), (48, 1088, 24908), (70, 1024, 20562), (96, 1152, 10944), (100, 1024, 24765), (112, 1216, 16471),
-                                       (113, 1024, 8332), (128, 1024, 28728), (100, 1024, 45144), (120, 2880, 10936), (96, 2688, 16528), (128, 1024, 40976)])
+@pytest.mark.parametrize("t,c_i,c_o", [(40, 1024, 16441), (48, 2368, 24908), (70, 2624, 20562), (81, 5760, 17240), (100, 3008, 24765), (112, 1280, 16471),
+                                       (113, 1728, 8332), (128, 1664, 28728), (100, 2368, 45144), (120, 2880, 10936), (96, 2688, 16528), (128, 1216, 40976),
+                                       (49, 6912, 4312), (65, 5504, 16981), (101, 7488, 8209)])
 def test_units_and_blocks(t, c_i, c_o):
-    assert sq.lib().sq_probe_linear_form(t, c_i, c_o, sq.TILED) == 0 and sq.lib().sq_probe_linear_tile(t, c_i, c_o, sq.TILED) == 0
+    assert sq.probe_linear_plan(t, c_i, c_o, sq.TILED)[:2] == (1, 1)
     print(f"stream {t}x{c_i}->{c_o}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(t + c_i + c_o)
     x, w = (torch.randint(-127, 128, s, generator=g, device="cuda", dtype=torch.int32).to(torch.int8) for s in ((t, c_i), (c_o, c_i)))

@@ -30,3 +30,9 @@ R, T = sq.ROW_MAJOR, sq.TILED
 ])
 def test_the_faster_kernel_is_taken(t, c_i, c_o, layout, direct):
     assert bool(sq.lib().sq_probe_linear_form(t, c_i, c_o, layout)) == direct
+
+
+def test_the_sizes_that_reach_a_kernel_by_name():
+    from tests.test_gpu_planned_paths import CASES
+    for t, c_i, c_o, layout, *plan in CASES:
+        assert list(sq.probe_linear_plan(t, c_i, c_o, layout)[:3]) == plan, (t, c_i, c_o, layout)
