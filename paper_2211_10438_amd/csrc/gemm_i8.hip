@@ -162,10 +162,10 @@ TilePlan make_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool allow_sp
 
 // The tiles of layers with more than 128 tokens and more than 256 input channels.  Microseconds of a K step and of a tile beside its
 // steps, row-major and tiled; times = rounds of tiles over the compute units x (steps x step + tile) + the constants below.  Fitted to 1130
-// measurements of 91 layers (129 to 4096 tokens, Gaussian codes; 8 % rms); the choice by it costs 1 % against the best tile and split
-// of each.  The tiles of pairs of steps (13 to 16) do no better per operation than the wide ones, but leave fewer compute units
-// idle (us, best of the others / of these: 1000 x 9216 -> 9216 row-major 102 / 84, 153 x 3712 -> 30080 38.9 / 31.6, 512 x 20480 -> 5120 tiled
-// 72.6 / 64.8, 2079 x 3328 -> 1352 37.8 / 26.4); the wide ones win from about three rounds on (2048 x 12288 -> 36864 649 / 786), where the
+// measurements of 91 layers (129 to 4096 tokens, Gaussian codes; 8 % rms); over 1500 other layers the choice by it costs 1.3 % against the
+// best tile and split of each.  It orders tiles; absolute times are corrected in tile_us.  The tiles of pairs of steps (13 to 16) do no better per operation than the wide ones, but leave fewer compute units
+// idle (us by graph replay, plan without / with these: 1000 x 9216 -> 9216 row-major 104 / 81, 153 x 3712 -> 30080 45.0 / 33.9, 512 x 20480 -> 5120
+// tiled 69 / 61, 2079 x 3328 -> 1352 37.9 / 27.9); the wide ones win from about three rounds on (2048 x 12288 -> 36864 649 / 786), where the
 // power cap sets the time: no tile is modelled above the rate measured there.
 struct TileCost {
     int cfg, bm, bn;
@@ -230,14 +230,17 @@ TilePlan choose_tile(int64_t M, int64_t N, int64_t K, bool tiled, const TilePlan
     return best;
 }
 
+// What a call stores: 16-bit or int8 values with scales (a linear layer), 16-bit values with alpha alone, int32 sums.
+enum class Epilogue { scales, alpha, sums };
+
 // Time of a tile plan against the direct kernel, fitted to 3500 shapes (16-bit output, weights in the last-level cache and in memory;
 // 4 to 11 % rms).  chosen_us: what choose_tile took the plan for; its model orders tiles of a layer, and leaves out a launch's constant
 // part and rows of the output that are not whole 16-byte pieces (odd: they leave element by element).  Without those two 463 x 640 -> 2501
 // row-major was taken for 9 us and took 19.
-double tile_us(const TilePlan& pl, double M, double N, double K, bool tiled, double chosen_us)
+double tile_us(const TilePlan& pl, double M, double N, double K, bool tiled, Epilogue epi, double chosen_us)
 {
     const double tiles = (double)((int64_t)pl.tiles_m * pl.tiles_n), out = M * N * 1e-6, w = N * K * 1e-6;
-    const double odd = (int64_t)N % 8 ? 1.0 : 0.0, split = pl.splits > 1 ? 1.0 : 0.0, part = pl.splits > 1 ? pl.splits * out : 0.0;
+    const double odd = (int64_t)N % (epi == Epilogue::sums ? 4 : 8) ? 1.0 : 0.0, split = pl.splits > 1 ? 1.0 : 0.0, part = pl.splits > 1 ? pl.splits * out : 0.0;
     if (pl.cfg == 8) {
         const double work = tiles / kNumCU * pl.iters_per_split;
         return tiled ? 8.4 + 0.63 * work + 0.155 * out + (1.4 + 1.17 * out) * odd : 8.3 + 0.19 * work + 0.42 * out + (1.6 + 1.12 * out) * odd;
@@ -290,8 +293,7 @@ struct Path {
     int need;  // K splits the workspace is sized for, fixed by the shape
     DirectPlan direct;
 };
-// scaled: the epilogue applies scales (a linear layer).
-Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool b_transposed, bool allow_split, bool scaled, StreamArgs* sp, TilePlan* pl)
+Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool b_transposed, bool allow_split, Epilogue epi, StreamArgs* sp, TilePlan* pl)
 {
     Path p{};
     const bool single = !b_transposed && batch == 1;
@@ -310,11 +312,11 @@ Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool b_t
         *pl = make_plan(M, N, K, batch, allow_split, b_transposed);
         p.need = pl->splits;
         if (single && pl->bm == 256) *pl = choose_tile(M, N, K, tiled, *pl, &us);
-        if (single) us = tile_us(*pl, (double)M, (double)N, (double)K, tiled, us);
+        if (single) us = tile_us(*pl, (double)M, (double)N, (double)K, tiled, epi, us);
     }
-    // Int32 sums and alpha alone: no scales and biases to wait for at the end of a small tile (128 x 128: 8 -> 5 us of fixed time; the direct
-    // kernel 3.7 -> 3.2).
-    if (!scaled && p.tiles && pl->bm <= 128 && pl->splits == 1) us -= pl->bm == 32 ? 1.0 : pl->bm == 128 && K > 256 ? 4.5 : 2.2;
+    // Int32 sums and alpha alone: no scales and biases to wait for at the end of a tile (128 x 128: 8 -> 5 us of fixed time, 256 x 128 2.2 us
+    // less; the direct kernel 3.7 -> 3.2).
+    if (epi != Epilogue::scales && p.tiles && pl->splits == 1) us -= pl->bm == 32 ? 1.0 : pl->bm == 128 && K > 256 ? 4.5 : 2.2;
     // The margins keep the models' errors from costing where the kernels are close.  Over 4500 shapes the direct kernel is then more than
     // 3 % behind the other in 10 with the weights in the last-level cache and in 49 with them in memory; at 0.95 it would be 26 and 81.  How
     // long rows of a row-major weight take hangs on more than the model knows (15 x 36336 -> 1360 modelled 25 us, took 38; the tiles 25): of
@@ -347,7 +349,7 @@ sq_status run_gemm(GemmArgs a, int64_t batch, bool to_i32, bool bf16, void* work
     };
     StreamArgs sp{};
     TilePlan pl{};
-    const Path path = choose(a.M, a.N, a.K, batch, tiled, b_transposed, allow_split, a.x_scale != nullptr, &sp, &pl);
+    const Path path = choose(a.M, a.N, a.K, batch, tiled, b_transposed, allow_split, to_i32 ? Epilogue::sums : a.x_scale ? Epilogue::scales : Epilogue::alpha, &sp, &pl);
     // (a shape whose workspace is sized for a K split is asked for it also where a kernel that has no use for it takes the call)
     if (path.need > 1 && (!workspace || ws_bytes < (size_t)path.need * total * sizeof(int32_t))) return SQ_ERR_WORKSPACE;
     const int splits = path.stream ? sp.gk : path.tiles ? pl.splits : 1;
@@ -431,7 +433,7 @@ int sq_probe_linear_form(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout)
     if (!dims_ok(t, c_i, c_o)) return 0;
     StreamArgs sp{};
     TilePlan pl{};
-    const DirectPlan d = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, true, &sp, &pl).direct;
+    const DirectPlan d = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, Epilogue::scales, &sp, &pl).direct;
     return 100 * d.mb + 10 * d.nb + d.nw;
 }
 
@@ -440,7 +442,7 @@ int sq_probe_linear_tile(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout)
     if (!dims_ok(t, c_i, c_o)) return 0;
     StreamArgs sp{};
     TilePlan pl{};
-    const Path p = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, true, &sp, &pl);
+    const Path p = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, Epilogue::scales, &sp, &pl);
     return p.tiles && !p.direct.mb ? pl.splits * 1000000 + pl.bm * 1000 + pl.bn : 0;
 }
 
@@ -450,7 +452,7 @@ sq_status sq_probe_linear_plan(int64_t t, int64_t c_i, int64_t c_o, sq_layout la
     if (!dims_ok(t, c_i, c_o)) return SQ_ERR_SHAPE;
     StreamArgs sp{};
     TilePlan pl{};
-    const Path p = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, true, &sp, &pl);
+    const Path p = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, Epilogue::scales, &sp, &pl);
     const int64_t steps = (c_i + 63) / 64;
     const int64_t direct[6] = {0, 100 * p.direct.mb + 10 * p.direct.nb + p.direct.nw, 1, steps, 0, 0};
     const int64_t stream[6] = {1, sp.regs, sp.gk, (int64_t)sp.iters * sp.ksub, sp.gn, sp.units};
