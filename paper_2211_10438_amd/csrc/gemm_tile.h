@@ -6,16 +6,18 @@
 // accumulators while they are still in registers.
 //
 // Design (CDNA4):
-//  * v_mfma_i32_32x32x32_i8, one wave owns a (MI*32) x (NI*32) block of accumulators; the prefill
-//    tiles (256x256, 256x192, 256x384) run 8 waves = 2 per SIMD, so one wave's barrier / LDS waits are
-//    covered by the other wave's MFMAs.
-//  * Operand tiles travel HBM -> LDS with global_load_lds_dwordx4 (no VGPR staging), NSTAGE deep.
+//  * Three K loops: v_mfma_i32_32x32x32_i8 with one 64-byte K step per stage (any K, K splits, batches), v_mfma_i32_16x16x64_i8
+//    the same way (MF = 16: an even number of whole steps, no split), and v_mfma_i32_16x16x64_i8 with pairs of steps per stage (PAIR).
+//  * One wave owns a (MI*MF) x (NI*MF) block of accumulators; the tiles of 192 and 256 rows run 8 waves = 2 per SIMD, so one
+//    wave's barrier / LDS waits are covered by the other wave's MFMAs.
+//  * Operand tiles travel HBM -> LDS with global_load_lds_dwordx4 (PAIR: buffer loads, whose bounds stand in for clamps; no VGPR
+//    staging), NSTAGE deep.
 //    LDS holds a tile as 16-row blocks of 1 KB, row-major (64 B per row) with the four 16-byte
 //    K-chunks of a row XOR-permuted: (a) one wave-wide load instruction fills a block from 16 rows
 //    x 64 contiguous bytes of global memory, four neighbouring lanes per row (coalesced), and (b)
 //    the ds_read_b128 operand reads of the MFMAs spread over all banks.
-//  * One s_barrier per 64-wide K step; operand fragments are double buffered in registers so the
-//    LDS reads of the next half step are in flight while the MFMAs of this half step issue.
+//  * One s_barrier per 64-wide K step (PAIR: two per pair of steps, the second of them behind the pair's loads); operand fragments are
+//    double buffered in registers, so that the LDS reads of the next part of a step are in flight while this part's MFMAs issue.
 //  * Tiles are enumerated XCD-aware: the workgroups an XCD runs concurrently cover a compact
 //    block of output tiles, so its L2 serves the shared A rows / B rows.
 //  * Optional split-K writes int32 partial tiles to a workspace, reduced (exactly, int32) by a

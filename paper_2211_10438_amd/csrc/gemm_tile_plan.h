@@ -8,6 +8,7 @@ struct TilePlan {
                  // 8: 128x128, K <= 128 fetched in one go, four workgroups per CU
                  // 9: 256x384 (a round of tiles saved on wide outputs)
                  // 10, 11, 12: 256x256, 256x384 and 256x192 with the 16x16x64 MFMA
+                 // 13, 14, 15, 16: 256x160, 256x128, 192x224 and 192x160 with the 16x16x64 MFMA, K in pairs of steps
     int bm, bn;
     int splits, iters_per_split;
     int tiles_m, tiles_n;
