@@ -40,7 +40,7 @@ int sq_probe_narrow_gemm(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout);
 
 /* sq_w8a8_linear by the direct kernel (operands from memory into MFMA registers, K dealt to the waves of a workgroup) with tiles of
  * 16 mb tokens x 16 nb channels and nw waves, whatever the library would choose; SQ_ERR_UNSUPPORTED where that combination is not
- * built.  Other arguments, checks and results are those of sq_w8a8_linear. */
+ * built or its launch would be too large.  Other arguments, checks and results are those of sq_w8a8_linear. */
 sq_status sq_probe_linear_blocks(int mb, int nb, int nw, const int8_t* xq, const float* x_scale, int x_scale_per_token, const int8_t* wq,
                                  const float* w_scale, int w_scale_per_channel, const float* bias, const void* residual, int relu,
                                  void* y, sq_dtype out, int64_t t, int64_t c_i, int64_t c_o, sq_layout layout, void* stream);

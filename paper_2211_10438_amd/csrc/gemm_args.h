@@ -100,7 +100,7 @@ bool sq_strip_bmm_eligible(int64_t M, int64_t N, int64_t K, int64_t batch);
 void sq_strip_bmm_launch(const GemmArgs& a, int batch, bool bf16, hipStream_t st);
 
 // Few output tiles for the chip (gemm_direct.h): 16 mb tokens x 16 nb channels per workgroup of nw waves, one kernel, no workspace.
-// False: no such instantiation.
+// False: no such instantiation, or more workgroups than a launch holds.
 struct DirectArgs {
     int tiles_m, tiles_n;
     int n_outer;  // the tiles are walked token tiles first (1: those of one channel tile side by side) or channel tiles first (0)

@@ -39,6 +39,16 @@ constexpr Form kForms[] = {
 // Waves per SIMD that the instantiations' registers (tiled) or rings (row-major) allow.
 int waves_per_simd(const Form& f, bool tiled) { return tiled && f.nb * f.mb == 1 ? 5 : tiled && f.nb * f.mb == 2 ? 3 : 2; }
 
+// Workgroups of a launch, 0 where it has to go to another kernel: HIP cuts a launch of 2^32 threads or more without an error, and the kernel
+// counts tokens and channels in 32 bits, those between the end of an operand and the end of its last tile included.
+int64_t workgroups(int64_t M, int64_t N, int mb, int nb, int nw)
+{
+    constexpr int64_t last = ((int64_t)1 << 31) - 128;  // (the largest tile has 112 tokens)
+    if (M > last || N > last) return 0;
+    const int64_t wgs = ((M + 16 * mb - 1) / (16 * mb)) * ((N + 16 * nb - 1) / (16 * nb));
+    return wgs * nw * 64 < ((int64_t)1 << 32) ? wgs : 0;
+}
+
 }  // namespace
 
 DirectPlan sq_direct_gemm_plan(int64_t M, int64_t N, int64_t K, bool tiled)
@@ -46,8 +56,8 @@ DirectPlan sq_direct_gemm_plan(int64_t M, int64_t N, int64_t K, bool tiled)
     constexpr int64_t cus = 256;
     DirectPlan best{};
     for (const Form& f : kForms) {
-        const int64_t tm = (M + 16 * f.mb - 1) / (16 * f.mb), wgs = tm * ((N + 16 * f.nb - 1) / (16 * f.nb));
-        if (wgs >= ((int64_t)1 << 31) || (f.mb > 1 && 16 * (f.mb - 1) >= M)) continue;  // (a row of 16-token blocks nobody needs)
+        const int64_t wgs = workgroups(M, N, f.mb, f.nb, f.nw);
+        if (!wgs || (f.mb > 1 && 16 * (f.mb - 1) >= M)) continue;  // (a row of 16-token blocks nobody needs)
         const int64_t slots = cus * waves_per_simd(f, tiled) * 4 / f.nw;
         const Cost& c = f.cost[tiled ? 1 : 0];
         const double fullest = (double)((wgs + cus - 1) / cus);
@@ -60,6 +70,7 @@ DirectPlan sq_direct_gemm_plan(int64_t M, int64_t N, int64_t K, bool tiled)
 
 bool sq_direct_gemm_launch(const GemmArgs& a, int mb, int nb, int nw, bool to_i32, bool bf16, bool tiled, hipStream_t st)
 {
+    if (!workgroups(a.M, a.N, mb, nb, nw)) return false;
     DirectArgs q{};
     q.tiles_m = (a.M + mb * 16 - 1) / (mb * 16);
     q.tiles_n = (a.N + nb * 16 - 1) / (nb * 16);

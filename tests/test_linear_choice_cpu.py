@@ -1,6 +1,7 @@
 """Which kernel a linear layer runs (no GPU work), at sizes where the direct kernel and the others are apart on either side: few K steps
 and many outputs, rows of the output off 16 bytes, few steps in the streaming kernels, long rows.  us, direct kernel / the others."""
 import pytest
+import torch
 
 from paper_2211_10438_amd import binding as sq
 
@@ -36,3 +37,24 @@ def test_the_sizes_that_reach_a_kernel_by_name():
     from tests.test_gpu_planned_paths import CASES
     for t, c_i, c_o, layout, *plan in CASES:
         assert list(sq.probe_linear_plan(t, c_i, c_o, layout)[:3]) == plan, (t, c_i, c_o, layout)
+
+
+@pytest.mark.parametrize("t,c_i,c_o,layout", [
+    (41, 64, 1802509599, T), (38, 128, 1275606840, T), (126, 64, 571716121, T),
+    (30, 64, 1791059052, R), (28, 64, 1442480151, R), (36, 16, 1764709523, R),
+    (1 << 29, 16, 1, R), (1480621215, 176, 4, R), (2**31 - 1, 16, 1, R), (2**31 - 1, 64, 3, T), (2, 16, 2**31 - 1, R),
+])
+def test_no_launch_is_cut(t, c_i, c_o, layout):
+    """A launch of 2**32 threads or more is cut without an error: its last outputs stay unwritten."""
+    form = sq.lib().sq_probe_linear_form(t, c_i, c_o, layout)
+    if form:
+        mb, nb, nw = form // 100, form // 10 % 10, form % 10
+        assert -(-t // (16 * mb)) * -(-c_o // (16 * nb)) * 64 * nw < 2**32
+        assert max(t, c_o) + 16 * mb < 2**31  # the launch counts tiles in 32 bits
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="passes addresses of nothing")
+def test_a_named_form_with_too_many_tiles_is_refused():
+    L, one = sq.lib(), 4096
+    for t, c_i, c_o in ((1 << 29, 16, 1), (2**31 - 1, 16, 1), (16, 16, 2**31 - 1)):
+        assert L.sq_probe_linear_blocks(1, 1, 4, one, one, 0, one, one, 0, None, None, 0, one, sq.F16, t, c_i, c_o, R, None) == 4  # SQ_ERR_UNSUPPORTED
