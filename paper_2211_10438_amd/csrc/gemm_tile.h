@@ -83,7 +83,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     // The epilogue stages the 16-bit tile in LDS; a tile too large for that goes in EG groups of GR rows.
     constexpr int EG = BM * (BN * 2 + 16) <= 160 * 1024 ? 1 : 2;
     constexpr int GR = BM / EG;
-    constexpr int EPI_BYTES = EPI == EPI_DEQUANT ? GR * (BN * 2 + 16) : 0;
+    constexpr int EPI_VEC = GR * (BN * 2 + 16);  // behind it the scales and biases of the tile's columns and the scales of its rows
+    constexpr int EPI_BYTES = EPI == EPI_DEQUANT ? EPI_VEC + (2 * BN + BM) * 4 : 0;
+    static_assert(BN <= NW * 64 && BM <= NW * 64, "a thread fetches one column's and one row's");
     // BT: behind the ring, three buffers hold the B tile in MFMA operand layout (see transpose_stage).
     constexpr int BOP = NSTAGE * STAGE;
     constexpr int RING_BYTES = (ONESHOT ? NSTAGE - 1 : NSTAGE) * STAGE + (BT ? 3 * B_BYTES : 0);
@@ -259,6 +261,35 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     const int fragA0 = wm * (WM / 16) * FB + lane_off;
     const int fragB0 = (BT ? 0 : RBA * FB) + wn * (WN / 16) * FB + lane_off;
 
+    // ---- what the epilogue needs beside the sums: per column scale and bias, per row scale, one of each for a thread to fetch, and the
+    // tile of the residual, 16 bytes of a row at a time.  PRE: on their way during the K loop (the tiles of pairs of steps have the registers);
+    // fetched behind it they cost 3 us a launch.  1000 x 256 -> 9216, us, before / now: 12.2 / 9.6, with a residual and a step per channel
+    // 18.3 / 11.5; 1000 x 9216 -> 9216 with both 90.6 / 86.5 (the power cap takes the rest back).
+    constexpr bool PRE = EPI == EPI_DEQUANT && PAIR;
+    constexpr int CPR = BN / 8;                             // 16-byte pieces per tile row
+    constexpr int RCH = (GR * CPR + NW * 64 - 1) / (NW * 64);  // of them per thread
+    const uint16_t* R = (const uint16_t*)p.residual;
+    const bool vec_ok = (p.N & 7) == 0;  // 16-byte chunks never straddle the row end and stay aligned
+    float col_scale = 0.0f, col_bias = 0.0f, row_scale = 0.0f;
+    constexpr int RG = PRE || RCH <= 4 ? RCH : 4;           // ... in flight at a time
+    v4u rpre[RG];
+    auto fetch_scales = [&]() {
+        const int t = (int)threadIdx.x, col = n0 + t, row = m0 + t;
+        if (t < BN && col < p.N) {
+            col_scale = !p.x_scale ? p.alpha : p.w_per_channel ? p.w_scale[col] : p.w_scale[0];
+            if (p.bias) col_bias = p.bias[col];
+        }
+        if (t < BM && row < p.M) row_scale = !p.x_scale ? 1.0f : p.per_token ? p.x_scale[row] : p.x_scale[0];
+    };
+    auto fetch_residual = [&](int g0, int k0) {
+#pragma unroll
+        for (int k = 0; k < RG; ++k) {
+            const int q = (int)threadIdx.x + (k0 + k) * NW * 64, r = q / CPR, row = m0 + g0 + r, col = n0 + (q - r * CPR) * 8;
+            if (q < GR * CPR && row < p.M && col < p.N) rpre[k] = *(const v4u*)(R + (int64_t)row * p.N + col);
+        }
+    };
+    if constexpr (PRE) fetch_scales();
+
     typedef int acc_t __attribute__((ext_vector_type(AV)));
     acc_t acc[MI][NI];
 #pragma unroll
@@ -417,6 +448,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     issue(I0c{}, std::integral_constant<int, SL>{}, 0, 0);
     issue(I0c{}, std::integral_constant<int, SL>{}, 1, 1);
     wait_vmcnt_imm<2 * (RBT / NW)>();  // pair 0 has landed
+    if (PRE && R && vec_ok) fetch_residual(0, 0);
     __builtin_amdgcn_s_barrier();
     v4i fa[2][MI], fbq[2][2];
 #pragma unroll
@@ -602,13 +634,12 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
         // residual tile is fetched the same way.  Row pitch +16 B keeps the two half-waves (4 rows
         // apart) on different banks.
         constexpr int PITCH = BN * 2 + 16;
-        constexpr int CPR = BN / 8;  // 16-byte chunks per tile row
         static_assert(GR * PITCH <= SMEM_BYTES && GR % 32 == 0, "epilogue staging must fit in the LDS allocation");
         uint16_t* C = (uint16_t*)p.C + (int64_t)batch * p.strideC;
-        const uint16_t* R = (const uint16_t*)p.residual;
-        const bool vec_ok = (p.N & 7) == 0;  // 16-byte chunks never straddle the row end and stay aligned
-        const float ws = (p.x_scale && !p.w_per_channel) ? p.w_scale[0] : 0.0f;
-        const float xs0 = (p.x_scale && !p.per_token) ? p.x_scale[0] : 0.0f;
+        float* const sv_col = (float*)(smem + EPI_VEC);
+        float* const sv_bias = sv_col + BN;
+        float* const sv_row = sv_bias + BN;
+        if constexpr (!PRE) fetch_scales();
         // Accumulators to fp32 in place, before anything else of the epilogue: the conversion does not depend on the
         // row group or on the optional terms, so the compiler moves it in front of the loop and the switch below
         // anyway, and into new registers if left to itself (the 384-wide tile then spilled thirty per lane).
@@ -628,59 +659,69 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
         for (int eg = 0; eg < EG; ++eg) {
         const int g0 = eg * GR;  // first tile row of this group
         // A zero the compiler cannot see through, added to the row and column offsets below: without it every index,
-        // bounds predicate and bias / scale address of all variants of phase1 counts as independent of the row group and
+        // bounds predicate and LDS address of all variants of phase1 counts as independent of the row group and
         // is computed in front of this loop, where some ninety such values stay live next to the accumulators.
         int opaque0;
         asm volatile("s_mov_b32 %0, 0" : "=s"(opaque0));
         __syncthreads();  // operand reads (first group) or the previous group's stores out of LDS are done
+        if (eg == 0) {
+            const int t = (int)threadIdx.x;
+            if (t < BN) {
+                sv_col[t] = col_scale;
+                sv_bias[t] = col_bias;
+            }
+            if (t < BM) sv_row[t] = row_scale;
+        }
         if (R) {
-            for (int q = threadIdx.x; q < GR * CPR; q += NW * 64) {
-                const int r = q / CPR, c8 = (q - r * CPR) * 8;
-                const int row = m0 + g0 + r, col = n0 + c8;
-                v4u val = {0, 0, 0, 0};
-                if (row < p.M && col < p.N) {
-                    const uint16_t* src = R + (int64_t)row * p.N + col;
-                    if (vec_ok) {
-                        val = *(const v4u*)src;
-                    } else {
+            if (vec_ok) {
+#pragma unroll 1
+                for (int k0 = 0; k0 < RCH; k0 += RG) {
+                    if constexpr (!PRE) fetch_residual(g0, k0);
+#pragma unroll
+                    for (int k = 0; k < RG; ++k) {
+                        const int q = (int)threadIdx.x + (k0 + k) * NW * 64, r = q / CPR;
+                        if (q < GR * CPR) *(v4u*)(smem + r * PITCH + (q - r * CPR) * 16) = rpre[k];
+                    }
+                }
+            } else {
+                for (int q = threadIdx.x; q < GR * CPR; q += NW * 64) {
+                    const int r = q / CPR, c8 = (q - r * CPR) * 8;
+                    const int row = m0 + g0 + r, col = n0 + c8;
+                    v4u val = {0, 0, 0, 0};
+                    if (row < p.M && col < p.N) {
+                        const uint16_t* src = R + (int64_t)row * p.N + col;
                         uint32_t e[8];
 #pragma unroll
                         for (int t = 0; t < 8; ++t) e[t] = (col + t < p.N) ? src[t] : 0u;
                         val = v4u{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
                     }
+                    *(v4u*)(smem + r * PITCH + c8 * 2) = val;
                 }
-                *(v4u*)(smem + r * PITCH + c8 * 2) = val;
             }
-            __syncthreads();
         }
+        __syncthreads();
         // The optional terms are compile-time flags inside the loop (one uniform switch outside) so the
-        // common cases cost convert + multiply + round per element and one 8-byte LDS write per four.
+        // common cases cost two multiplies + round per element and one 8-byte LDS write per four.  Scales and biases come from LDS, once per
+        // column block: read from memory where they are used, with a bounds check each and again for every row block, they were most
+        // of the 3.8 us (6.4 with a step per channel, now 1.3 and 1.3) that this part of the 256 x 160 tile took.
         auto phase1 = [&](auto HB, auto RL, auto HR) {
             constexpr bool has_bias = decltype(HB)::value, relu = decltype(RL)::value, has_res = decltype(HR)::value;
+            typedef float v4f __attribute__((ext_vector_type(4)));
+            float xr[MI];
 #pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                if (EG > 1 && (wm * WM + i * MF) / GR != eg) continue;  // rows of another group
-                const int lrow = wm * WM + i * MF + row_l - g0 + opaque0;
-                const int row = m0 + g0 + lrow;
-                const float xrow = p.x_scale ? (p.per_token ? p.x_scale[row < p.M ? row : p.M - 1] : xs0) : 0.0f;
-                float c;
-                if (p.x_scale) c = xrow * ws;
-                else c = p.alpha;
+            for (int i = 0; i < MI; ++i) xr[i] = sv_row[wm * WM + i * MF + row_l + opaque0];
 #pragma unroll
-                for (int j = 0; j < NI; ++j)
+            for (int j = 0; j < NI; ++j)
 #pragma unroll
-                    for (int g = 0; g < QG; ++g) {
-                        const int lcol = wn * WN + j * MF + 8 * g + col_l + opaque0;
-                        float cq[4] = {c, c, c, c};
-                        if (p.w_per_channel) {  // c = Delta_X[row] * Delta_W[col]
+                for (int g = 0; g < QG; ++g) {
+                    const int lcol = wn * WN + j * MF + 8 * g + col_l + opaque0;
+                    const v4f wv = *(const v4f*)(sv_col + lcol);
+                    v4f bv = {0.0f, 0.0f, 0.0f, 0.0f};
+                    if constexpr (has_bias) bv = *(const v4f*)(sv_bias + lcol);
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) cq[e] = xrow * ((n0 + lcol + e < p.N) ? p.w_scale[n0 + lcol + e] : 0.0f);
-                        }
-                        float bq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                        if constexpr (has_bias) {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) bq[e] = (n0 + lcol + e < p.N) ? p.bias[n0 + lcol + e] : 0.0f;
-                        }
+                    for (int i = 0; i < MI; ++i) {
+                        if (EG > 1 && (wm * WM + i * MF) / GR != eg) continue;  // rows of another group
+                        const int lrow = wm * WM + i * MF + row_l - g0 + opaque0;
                         v2u* slot = (v2u*)(smem + lrow * PITCH + lcol * 2);
                         v2u rb = {0u, 0u};
                         if constexpr (has_res) rb = *slot;
@@ -688,11 +729,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
                             const int bits = acc[i][j][4 * g + e];  // a copy: a vector element is no object to cast from
                             return __builtin_bit_cast(float, bits);
                         };
-                        const uint32_t o01 = dequant_pair_f<BF16>(fa(0), fa(1), cq[0], cq[1], bq[0], bq[1], has_bias, relu, rb[0], has_res);
-                        const uint32_t o23 = dequant_pair_f<BF16>(fa(2), fa(3), cq[2], cq[3], bq[2], bq[3], has_bias, relu, rb[1], has_res);
+                        const uint32_t o01 = dequant_pair_f<BF16>(fa(0), fa(1), xr[i] * wv[0], xr[i] * wv[1], bv[0], bv[1], has_bias, relu, rb[0], has_res);
+                        const uint32_t o23 = dequant_pair_f<BF16>(fa(2), fa(3), xr[i] * wv[2], xr[i] * wv[3], bv[2], bv[3], has_bias, relu, rb[1], has_res);
                         *slot = v2u{o01, o23};
                     }
-            }
+                }
         };
         using T_ = std::true_type;
         using F_ = std::false_type;
