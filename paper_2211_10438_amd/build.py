@@ -16,6 +16,8 @@ SOURCES = ["api.hip", "quantize.hip", "weight_prep.hip", "rowops.hip", "gemm_i8.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function",
          "-I", INCLUDE, "-I", CSRC]
+# Tiles with one wave per SIMD: MFMAs on plain vector registers, accumulation registers only for what does not fit (gemm_tile.h).
+FLAGS_OF = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form=true"] for src in ("gemm_i8_tile_rows.hip", "gemm_i8_tile_tiled.hip")}
 
 
 def build_host_calls() -> str:
@@ -43,7 +45,7 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
     for src in SOURCES:
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
         objs.append(obj)
-        cmd = ["hipcc", *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = ["hipcc", *FLAGS, *FLAGS_OF.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))

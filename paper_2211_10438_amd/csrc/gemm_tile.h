@@ -9,14 +9,14 @@
 //  * Three K loops: v_mfma_i32_32x32x32_i8 with one 64-byte K step per stage (any K, K splits, batches), v_mfma_i32_16x16x64_i8
 //    the same way (MF = 16: an even number of whole steps, no split), and v_mfma_i32_16x16x64_i8 with pairs of steps per stage (PAIR).
 //  * One wave owns a (MI*MF) x (NI*MF) block of accumulators; the tiles of 192 and 256 rows run 8 waves = 2 per SIMD, so one
-//    wave's barrier / LDS waits are covered by the other wave's MFMAs.
+//    wave's barrier / LDS waits are covered by the other wave's MFMAs (PAIR: 4 waves, which cover their own).
 //  * Operand tiles travel HBM -> LDS with global_load_lds_dwordx4 (PAIR: buffer loads, whose bounds stand in for clamps; no VGPR
 //    staging), NSTAGE deep.
 //    LDS holds a tile as 16-row blocks of 1 KB, row-major (64 B per row) with the four 16-byte
 //    K-chunks of a row XOR-permuted: (a) one wave-wide load instruction fills a block from 16 rows
 //    x 64 contiguous bytes of global memory, four neighbouring lanes per row (coalesced), and (b)
 //    the ds_read_b128 operand reads of the MFMAs spread over all banks.
-//  * One s_barrier per 64-wide K step (PAIR: two per pair of steps, the second of them behind the pair's loads); operand fragments are
+//  * One s_barrier per 64-wide K step (PAIR: one per pair of steps); operand fragments are
 //    double buffered in registers, so that the LDS reads of the next part of a step are in flight while this part's MFMAs issue.
 //  * Tiles are enumerated XCD-aware: the workgroups an XCD runs concurrently cover a compact
 //    block of output tiles, so its L2 serves the shared A rows / B rows.
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / MF, NI = WN / MF;
     constexpr int AV = MF * MF / 64;  // accumulator registers per block
     constexpr int QG = AV / 4;        // runs of four neighbouring output columns a lane holds per block
-    static_assert(MF == 32 || (MF == 16 && !BT && !ONESHOT && (PAIR ? MI >= 3 && MI <= 4 && NI >= 3 : MI == 4 && NI % 2 == 0 && NI >= 6)), "MFMA shape");
+    static_assert(MF == 32 || (MF == 16 && !BT && !ONESHOT && (PAIR ? NW == 4 && MI >= 6 && MI <= 8 && NI >= 4 : MI == 4 && NI % 2 == 0 && NI >= 6)), "MFMA shape");
     static_assert(!PAIR || (MF == 16 && NSTAGE == 3), "pairs of steps");
     constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK, STAGE = (A_BYTES + B_BYTES) * (PAIR ? 2 : 1);
     constexpr int RBA = BM / 16, RBB = BN / 16;  // 16-row blocks per operand tile
@@ -271,7 +271,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     const uint16_t* R = (const uint16_t*)p.residual;
     const bool vec_ok = (p.N & 7) == 0;  // 16-byte chunks never straddle the row end and stay aligned
     float col_scale = 0.0f, col_bias = 0.0f, row_scale = 0.0f;
-    constexpr int RG = PRE || RCH <= 4 ? RCH : 4;           // ... in flight at a time
+    constexpr bool FULL = MI * NI * AV >= 192;              // the sums leave few registers: one piece more in flight and they spill
+    constexpr int RG = PRE || RCH <= 4 ? RCH : FULL ? 2 : 4;  // ... in flight at a time
     v4u rpre[RG];
     auto fetch_scales = [&]() {
         const int t = (int)threadIdx.x, col = n0 + t, row = m0 + t;
@@ -401,17 +402,22 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     mfma_all(fa0, fb0);
     mfma_all(fa1, fb1);
     } else if constexpr (PAIR) {
-    // ---- 16x16x64 shape, pairs of steps.  As below, a wave owns 64 rows x WN columns, the A fragments of a step stay for the step while
-    // the next step's are read, and the B fragments come in parts of two (an odd NI: one part of one), double buffered.  The parts
-    // of one step:
-    constexpr int NP = (NI + 1) / 2, PB = NP - 3 > 0 ? NP - 3 : 0;
-    static_assert(NP >= 2, "parts of a K step");
-    constexpr auto part0 = [](int q) { return NI % 2 && q > NP / 2 ? 2 * q - 1 : 2 * q; };           // first fragment of part q
-    constexpr auto parts = [](int q) { return NI % 2 && q == NP / 2 ? 1 : 2; };                      // and how many
-    // The 16-row blocks of a stage, A's then B's, are dealt to the waves; wave w fetches blocks w, w + NW, ... (both halves each).  The
-    // first N0 of its slots are issued in the first step of a pair, the others in the second.
-    constexpr int RBT = RBA + RBB, SL = (RBT + NW - 1) / NW, N0 = (SL + 1) / 2, REM = RBT % NW;
-    static_assert(2 * RBT / NW <= 63, "vmcnt");
+    // ---- 16x16x64 shape, pairs of steps: four waves, one per SIMD, each a quarter of the tile.  What a step costs beside its MFMAs is the
+    // LDS (256 x 160, per CU and step: 52 KB of fragments and 26 KB of loads written, 610 cycles at 128 bytes a cycle against 640 of
+    // MFMAs; with eight waves of half the size 72 + 26 KB, 770) and, under the power cap, the energy of moving those bytes.  A wave holds
+    // the fragments of a step and reads the next step's meanwhile into a second set, so that it needs no partner on its SIMD to cover LDS
+    // latency.  One barrier per pair: all of a pair is in registers when its second step begins, so behind that barrier its stage can
+    // be filled again, and loads have two pairs' time to arrive.  us, eight waves / these (kernel alone): 1000 x 9216 -> 9216 row-major 87.6 /
+    // 82.5, tiled 79.4 / 77.2, 512 x 5120 -> 20480 58.9 / 56.3, 512 x 20480 -> 5120 in four splits 61.8 / 59.1, 1000 x 9216 -> 9216
+    // by 192 x 224 85.6 / 78.7; equal on short K (2048 x 784 -> 2048 11.7 / 12.1).  (This loop and its registers want the compiler's option
+    // for MFMAs on plain vector registers; the other form copies fragments between the two register files, 30 % slower.)
+    constexpr int RBT = RBA + RBB;             // 16-row blocks of a stage, A's then B's, two halves (steps) each
+    constexpr int SL = RBT / NW;               // wave w fetches the blocks w, w + NW, .. whole
+    constexpr bool HALF = RBT % NW != 0;       // ... and of the two left over one half
+    static_assert(RBT % NW == 0 || RBT % NW == 2, "halves dealt evenly");
+    constexpr int LP = 2 * SL + (HALF ? 1 : 0);  // loads of a wave per pair
+    constexpr int L0 = LP / 2;                 // of pair pr + NSTAGE: issued behind the barrier in pair pr, the others in the first step of pair pr + 1
+    static_assert((NSTAGE - 1) * LP <= 63, "vmcnt");
     const int steps_end = nk;  // of this split
     int8_t* const baseA = const_cast<int8_t*>(p.A) + (int64_t)m0 * p.lda;
     int8_t* const baseB = const_cast<int8_t*>(p.B) + (int64_t)n0 * p.ldb;
@@ -420,88 +426,75 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
         return (int)(b < 0x7fffffff ? b : 0x7fffffff);
     };
     const int lenA = left(p.M - m0, p.lda), lenB = left(p.N - n0, p.ldb);
-    uint32_t vo[SL];
+    auto block_of = [&](int i) { return i < SL ? i * NW + wave : SL * NW + (wave >> 1); };
+    uint32_t vo[SL + HALF];
 #pragma unroll
-    for (int i = 0; i < SL; ++i) {
-        const int b = i * NW + wave, r = (b < RBA ? b : b - RBA) * 16;
+    for (int i = 0; i < SL + HALF; ++i) {
+        const int b = block_of(i), r = (b < RBA ? b : b - RBA) * 16;
         vo[i] = TILED ? (uint32_t)(r * (int)p.lda + lane * 16) : (uint32_t)((r + (lane >> 2)) * (int)p.lda + chunk * 16);  // (lda = ldb = K)
     }
-    // slots from I0 on, CNT of them, of the stage of pair `pr`
-    auto issue = [&](auto I0_, auto CNT_, int pr, int buf) {
-        constexpr int I0 = decltype(I0_)::value, CNT = decltype(CNT_)::value;
-        static_for<CNT>([&](auto D_) {
-            constexpr int i = I0 + decltype(D_)::value;
-            if (i * NW + NW > RBT && wave >= REM) return;  // (the last slot of the waves that have one block less)
-            const bool isA = i * NW + NW <= RBA || (i * NW < RBA && i * NW + wave < RBA);
-            char* const dst = smem + buf * STAGE + (i * NW + wave) * 2048;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int st = 2 * pr + h;
-                const auto rs = __builtin_amdgcn_make_buffer_rsrc(isA ? baseA : baseB, 0, st < steps_end ? (isA ? lenA : lenB) : 0, 0x00027000);
-                uint32_t o = vo[i];
-                if constexpr (!TILED) o |= has_tail && st == steps_end - 1 && chunk >= tail_chunks ? 0x80000000u : 0u;
-                buffer_to_lds<false>(rs, dst + h * 1024, o, (kbeg + st) * KSTEP);
-            }
-        });
+    static_assert(RBA % NW == 0, "a slot is of one operand");
+    // load number L of this wave for the stage of pair `pr`: both halves of a block one right after the other
+    auto issue = [&](auto L_, int pr, int buf) {
+        constexpr int L = decltype(L_)::value, i = L / 2;
+        constexpr bool isA = i < SL && i * NW < RBA;
+        const int h = i < SL ? (L & 1) : (wave & 1), st = 2 * pr + h;
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(isA ? baseA : baseB, 0, st < steps_end ? (isA ? lenA : lenB) : 0, 0x00027000);
+        uint32_t o = vo[i];
+        if constexpr (!TILED) o |= has_tail && st == steps_end - 1 && chunk >= tail_chunks ? 0x80000000u : 0u;
+        buffer_to_lds<false>(rs, smem + buf * STAGE + block_of(i) * 2048 + h * 1024, o, (kbeg + st) * KSTEP);
     };
-    using I0c = std::integral_constant<int, 0>;
-    issue(I0c{}, std::integral_constant<int, SL>{}, 0, 0);
-    issue(I0c{}, std::integral_constant<int, SL>{}, 1, 1);
-    wait_vmcnt_imm<2 * (RBT / NW)>();  // pair 0 has landed
+    static_for<NSTAGE>([&](auto S_) {
+        constexpr int S = decltype(S_)::value;
+        static_for<(S < NSTAGE - 1 ? LP : L0)>([&](auto L_) { issue(L_, S, S); });
+    });
+    wait_vmcnt_imm<(NSTAGE - 2) * LP + L0>();  // pair 0 has landed
     if (PRE && R && vec_ok) fetch_residual(0, 0);
     __builtin_amdgcn_s_barrier();
-    v4i fa[2][MI], fbq[2][2];
-#pragma unroll
-    for (int i = 0; i < MI; ++i) fa[0][i] = *(const v4i*)(smem + fragA0 + i * FB);
-#pragma unroll
-    for (int k = 0; k < parts(0); ++k) fbq[0][k] = *(const v4i*)(smem + fragB0 + k * FB);
-    // One step: sub-step SUB of pair `pr` out of stage `buf`; `sn` is where the next step's fragments lie.
-    auto step = [&](auto SUB_, v4i(&cur)[MI], v4i(&nxt)[MI], int pr, int buf, const char* sn, int rbuf) {
-        constexpr int SUB = decltype(SUB_)::value, P0 = SUB * NP & 1;
-        const char* sb = smem + buf * STAGE + SUB * 1024 + fragB0;
-        static_for<NP>([&](auto Q_) {
-            constexpr int q = decltype(Q_)::value, F0 = part0(q), FN = parts(q);
-            if constexpr (q == PB) {
-                // second step: pair pr + 1 has landed for everyone (younger: what the first step issued).  First step: everyone is
-                // done with pair pr - 1, whose stage is filled from here on.
-                if constexpr (SUB == 1) wait_vmcnt_imm<2 * N0>();
+    v4i fa[2][MI], fb[2][NI];
+    // read number X of a step's fragments, in the order the MFMAs want them: B 0, A 0 .. MI - 1, B 1 ..
+    auto read = [&](auto X_, auto SET_, const char* sp) {
+        constexpr int X = decltype(X_)::value, SET = decltype(SET_)::value;
+        if constexpr (X == 0) fb[SET][0] = *(const v4i*)(sp + fragB0);
+        else if constexpr (X <= MI) fa[SET][X - 1] = *(const v4i*)(sp + fragA0 + (X - 1) * FB);
+        else fb[SET][X - MI] = *(const v4i*)(sp + fragB0 + (X - MI) * FB);
+    };
+    constexpr int NM = MI * NI, NR = MI + NI;
+    static_for<NR>([&](auto X_) { read(X_, std::integral_constant<int, 0>{}, smem); });
+    // Sub-step SUB of pair `pr` out of stage `buf`; `sn` is where the next step's fragments lie.  Its reads and loads are spread over the
+    // MFMAs by scheduling fences: in the second step from the barrier on, which stands behind the eighth MFMA; none behind the last twelve,
+    // which cover the latency of the last reads.
+    auto step = [&](auto SUB_, int pr, int buf, const char* sn) {
+        constexpr int SUB = decltype(SUB_)::value, BAR = 8;
+        constexpr int FIRST = SUB ? BAR : 0, SPAN = NM - 12 - FIRST, NLD = SUB ? L0 : LP - L0;
+        constexpr auto upto = [](int m, int n) { return m <= FIRST ? 0 : m >= FIRST + SPAN ? n : (m - FIRST) * n / SPAN; };
+        static_for<NM>([&](auto M_) {
+            constexpr int m = decltype(M_)::value, j = m / MI, i = m % MI;
+            if constexpr (SUB == 1 && m == BAR) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // all of this pair is in registers
+                wait_vmcnt_imm<(NSTAGE - 2) * LP>();                // pair pr + 1 has landed
                 __builtin_amdgcn_s_barrier();
             }
-            constexpr int pa = q - PB, an0 = pa <= 1 ? 0 : 2, an_cnt = pa <= 0 ? 0 : NP - PB == 2 ? MI : pa == 1 ? 2 : MI - 2;
-            acc[0][F0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fbq[(q + P0) & 1][0], cur[0], acc[0][F0], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (q >= PB) {
-                constexpr int all = SUB ? SL - N0 : N0, first = SUB ? N0 : 0;
-                constexpr int per = (all + NP - PB - 1) / (NP - PB), i0 = (q - PB) * per, n = i0 >= all ? 0 : i0 + per <= all ? per : all - i0;
-                issue(std::integral_constant<int, first + i0>{}, std::integral_constant<int, n>{}, pr + 2, rbuf);
+            acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[SUB][j], fa[SUB][i], acc[i][j], 0, 0, 0);
+            constexpr int r0 = upto(m, NR), r1 = upto(m + 1, NR), l0 = upto(m, NLD), l1 = upto(m + 1, NLD);
+            if constexpr (r1 > r0 || l1 > l0) {
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<r1 - r0>([&](auto D_) { read(std::integral_constant<int, r0 + decltype(D_)::value>{}, std::integral_constant<int, 1 - SUB>{}, sn); });
+                static_for<l1 - l0>([&](auto D_) {
+                    constexpr int L = l0 + decltype(D_)::value;
+                    if constexpr (SUB) issue(std::integral_constant<int, L>{}, pr + NSTAGE, buf);
+                    else issue(std::integral_constant<int, L0 + L>{}, pr - 1 + NSTAGE, buf == 0 ? NSTAGE - 1 : buf - 1);
+                });
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if constexpr (q < NP - 1) {
-#pragma unroll
-                for (int k = 0; k < parts(q + 1); ++k) fbq[(q + 1 + P0) & 1][k] = *(const v4i*)(sb + (part0(q + 1) + k) * FB);
-            } else {
-#pragma unroll
-                for (int k = 0; k < parts(0); ++k) fbq[(q + 1 + P0) & 1][k] = *(const v4i*)(sn + fragB0 + k * FB);
-            }
-            static_for<an_cnt>([&](auto K_) {
-                constexpr int k = an0 + decltype(K_)::value;
-                nxt[k] = *(const v4i*)(sn + fragA0 + k * FB);
-            });
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int k = 0; k < FN; ++k)
-#pragma unroll
-                for (int i = 0; i < MI; ++i)
-                    if (k + i > 0)
-                        acc[i][F0 + k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fbq[(q + P0) & 1][k], cur[i], acc[i][F0 + k], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
         });
     };
     const int npairs = (nk + 1) >> 1;
     int buf = 0;
     for (int pr = 0; pr < npairs; ++pr) {
-        const int nbuf = buf == 2 ? 0 : buf + 1, rbuf = buf == 0 ? 2 : buf - 1;
-        step(std::integral_constant<int, 0>{}, fa[0], fa[1], pr, buf, smem + buf * STAGE + 1024, rbuf);
-        step(std::integral_constant<int, 1>{}, fa[1], fa[0], pr, buf, smem + nbuf * STAGE, rbuf);
+        const int nbuf = buf + 1 == NSTAGE ? 0 : buf + 1;
+        step(std::integral_constant<int, 0>{}, pr, buf, smem + buf * STAGE + 1024);
+        step(std::integral_constant<int, 1>{}, pr, buf, smem + nbuf * STAGE);
         buf = nbuf;
     }
     } else {
@@ -704,18 +697,24 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
         // common cases cost two multiplies + round per element and one 8-byte LDS write per four.  Scales and biases come from LDS, once per
         // column block: read from memory where they are used, with a bounds check each and again for every row block, they were most
         // of the 3.8 us (6.4 with a step per channel, now 1.3 and 1.3) that this part of the 256 x 160 tile took.
-        auto phase1 = [&](auto HB, auto RL, auto HR) {
-            constexpr bool has_bias = decltype(HB)::value, relu = decltype(RL)::value, has_res = decltype(HR)::value;
+        auto phase1 = [&](auto HB, auto RL, auto HR, auto PC) {
+            constexpr bool has_bias = decltype(HB)::value, relu = decltype(RL)::value, has_res = decltype(HR)::value, per_col = decltype(PC)::value;
             typedef float v4f __attribute__((ext_vector_type(4)));
             float xr[MI];
 #pragma unroll
             for (int i = 0; i < MI; ++i) xr[i] = sv_row[wm * WM + i * MF + row_l + opaque0];
+            if constexpr (!per_col) {  // one scale for all columns
+                const float ws = sv_col[opaque0];
+#pragma unroll
+                for (int i = 0; i < MI; ++i) xr[i] = xr[i] * ws;
+            }
 #pragma unroll
             for (int j = 0; j < NI; ++j)
 #pragma unroll
                 for (int g = 0; g < QG; ++g) {
                     const int lcol = wn * WN + j * MF + 8 * g + col_l + opaque0;
-                    const v4f wv = *(const v4f*)(sv_col + lcol);
+                    v4f wv;
+                    if constexpr (per_col) wv = *(const v4f*)(sv_col + lcol);
                     v4f bv = {0.0f, 0.0f, 0.0f, 0.0f};
                     if constexpr (has_bias) bv = *(const v4f*)(sv_bias + lcol);
 #pragma unroll
@@ -729,28 +728,52 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
                             const int bits = acc[i][j][4 * g + e];  // a copy: a vector element is no object to cast from
                             return __builtin_bit_cast(float, bits);
                         };
-                        const uint32_t o01 = dequant_pair_f<BF16>(fa(0), fa(1), xr[i] * wv[0], xr[i] * wv[1], bv[0], bv[1], has_bias, relu, rb[0], has_res);
-                        const uint32_t o23 = dequant_pair_f<BF16>(fa(2), fa(3), xr[i] * wv[2], xr[i] * wv[3], bv[2], bv[3], has_bias, relu, rb[1], has_res);
+                        auto c = [&](int e) { return per_col ? xr[i] * wv[e] : xr[i]; };
+                        const uint32_t o01 = dequant_pair_f<BF16>(fa(0), fa(1), c(0), c(1), bv[0], bv[1], has_bias, relu, rb[0], has_res);
+                        const uint32_t o23 = dequant_pair_f<BF16>(fa(2), fa(3), c(2), c(3), bv[2], bv[3], has_bias, relu, rb[1], has_res);
                         *slot = v2u{o01, o23};
                     }
+                    if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);  // (or the LDS reads of all column blocks are moved up here)
                 }
         };
         using T_ = std::true_type;
         using F_ = std::false_type;
-        switch ((p.bias ? 1 : 0) | (p.relu ? 2 : 0) | (R ? 4 : 0)) {
-            case 0: phase1(F_{}, F_{}, F_{}); break;
-            case 1: phase1(T_{}, F_{}, F_{}); break;
-            case 2: phase1(F_{}, T_{}, F_{}); break;
-            case 3: phase1(T_{}, T_{}, F_{}); break;
-            case 4: phase1(F_{}, F_{}, T_{}); break;
-            case 5: phase1(T_{}, F_{}, T_{}); break;
-            case 6: phase1(F_{}, T_{}, T_{}); break;
-            default: phase1(T_{}, T_{}, T_{}); break;
-        }
+        auto with = [&](auto PC) {
+            switch ((p.bias ? 1 : 0) | (p.relu ? 2 : 0) | (R ? 4 : 0)) {
+                case 0: phase1(F_{}, F_{}, F_{}, PC); break;
+                case 1: phase1(T_{}, F_{}, F_{}, PC); break;
+                case 2: phase1(F_{}, T_{}, F_{}, PC); break;
+                case 3: phase1(T_{}, T_{}, F_{}, PC); break;
+                case 4: phase1(F_{}, F_{}, T_{}, PC); break;
+                case 5: phase1(T_{}, F_{}, T_{}, PC); break;
+                case 6: phase1(F_{}, T_{}, T_{}, PC); break;
+                default: phase1(T_{}, T_{}, T_{}, PC); break;
+            }
+        };
+        if (p.w_per_channel) with(T_{});
+        else with(F_{});
         __syncthreads();
         // int8 codes in the tiled layout leave in another order: a wave instruction covers 8 rows x 64 columns, which are
         // 512 contiguous bytes of a 1 KB block (walking along a row it would write 64-byte pieces of eight blocks)
         const bool q8_blocks = p.q8_step && p.q8_tiled && (BN % 64 == 0);
+        if (!p.q8_step && vec_ok) {
+            constexpr int SG = FULL ? 2 : RCH % 5 == 0 ? 5 : RCH % 4 == 0 ? 4 : RCH % 3 == 0 ? 3 : 4;  // pieces a thread has in flight out of LDS
+#pragma unroll 1
+            for (int k0 = 0; k0 < RCH; k0 += SG) {
+                v4u val[SG];
+#pragma unroll
+                for (int k = 0; k < SG; ++k) {
+                    const int q = (int)threadIdx.x + (k0 + k) * NW * 64, r = q / CPR;
+                    if (GR * CPR % (SG * NW * 64) == 0 || q < GR * CPR) val[k] = *(const v4u*)(smem + r * PITCH + (q - r * CPR) * 16);
+                }
+#pragma unroll
+                for (int k = 0; k < SG; ++k) {
+                    const int q = (int)threadIdx.x + (k0 + k) * NW * 64, r = q / CPR, row = m0 + g0 + r, col = n0 + (q - r * CPR) * 8;
+                    if ((GR * CPR % (SG * NW * 64) == 0 || q < GR * CPR) && row < p.M && col < p.N)
+                        __builtin_nontemporal_store(val[k], (v4u*)(C + (int64_t)row * p.N + col));
+                }
+            }
+        } else
         for (int q = threadIdx.x; q < GR * CPR; q += NW * 64) {
             int r = q / CPR, c8 = (q - r * CPR) * 8;
             if (q8_blocks) {
@@ -779,13 +802,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
                     continue;
                 }
                 uint16_t* dst = C + (int64_t)row * p.N + col;
-                if (vec_ok) {
-                    __builtin_nontemporal_store(val, (v4u*)dst);
-                } else {
 #pragma unroll
-                    for (int t = 0; t < 8; ++t)
-                        if (col + t < p.N) dst[t] = (uint16_t)(val[t >> 1] >> ((t & 1) * 16));
-                }
+                for (int t = 0; t < 8; ++t)
+                    if (col + t < p.N) dst[t] = (uint16_t)(val[t >> 1] >> ((t & 1) * 16));
             }
         }
         }  // row groups
@@ -801,7 +820,7 @@ void launch_cfg(const TilePlan& pl, const GemmArgs& a, int batch, hipStream_t st
     do {                                                                                                          \
         sq_launch((gemm_i8_kernel<BM, BN, WGM, WGN, NST, EPI, BF16, LAY, 1, false, MF>), grid, dim3(WGM * WGN * 64), 0, st, a); \
     } while (0)
-#define SQ_LAUNCH_PAIR(BM, BN, WGM, WGN) sq_launch((gemm_i8_kernel<BM, BN, WGM, WGN, 3, EPI, BF16, LAY, 1, false, 16, true>), grid, dim3(WGM * WGN * 64), 0, st, a)
+#define SQ_LAUNCH_PAIR(BM, BN) sq_launch((gemm_i8_kernel<BM, BN, 2, 2, 3, EPI, BF16, LAY, 1, false, 16, true>), grid, dim3(256), 0, st, a)
 #define SQ_LAUNCH(BM, BN, WGM, WGN, NST) SQ_LAUNCH_MF(BM, BN, WGM, WGN, NST, 32)
     switch (pl.cfg) {
         case 0: SQ_LAUNCH(256, 256, 2, 4, 4); break;
@@ -813,10 +832,10 @@ void launch_cfg(const TilePlan& pl, const GemmArgs& a, int batch, hipStream_t st
         case 10: SQ_LAUNCH_MF(256, 256, 4, 2, 4, 16); break;
         case 11: SQ_LAUNCH_MF(256, 384, 4, 2, 4, 16); break;
         case 12: SQ_LAUNCH_MF(256, 192, 4, 2, 5, 16); break;
-        case 13: SQ_LAUNCH_PAIR(256, 160, 4, 2); break;
-        case 14: SQ_LAUNCH_PAIR(256, 128, 4, 2); break;
-        case 15: SQ_LAUNCH_PAIR(192, 224, 4, 2); break;
-        case 16: SQ_LAUNCH_PAIR(192, 160, 4, 2); break;
+        case 13: SQ_LAUNCH_PAIR(256, 160); break;
+        case 14: SQ_LAUNCH_PAIR(256, 128); break;
+        case 15: SQ_LAUNCH_PAIR(192, 224); break;
+        case 16: SQ_LAUNCH_PAIR(192, 160); break;
         case 8:
             sq_launch((gemm_i8_kernel<128, 128, 2, 2, 3, EPI, BF16, LAY, 4, true>), grid, dim3(256), 0, st, a);
             break;
