@@ -46,6 +46,43 @@ template <bool NT> SQ_DEVICE void buffer_to_lds(__amdgpu_buffer_rsrc_t r, char* 
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, LPTR(dst), 16, (int)lane_offset, offset, 0, NT ? 2 : 0);
 }
 
+// Byte-transposing LDS reads (16 lanes name the 8-byte halves of eight rows' 16 bytes; lane i receives byte i of each row), and the wait for
+// them: out[2 k], out[2 k + 1] from the LDS addresses p[k] + LO and p[k] + HI.  In asm because the compiler, before the builtin, waits for
+// every global->LDS load in flight -- those of the next stages, which nobody needs yet -- as if they wrote what is read here.  (It
+// sees neither these reads nor the loads they follow: the caller's barriers order them.)
+template <int LO, int HI, int N> SQ_DEVICE void lds_read_tr(const uint32_t (&p)[N], v2i (&out)[2 * N])
+{
+    static_assert(N >= 1 && N <= 4, "columns blocks at a time");
+    if constexpr (N == 1) {
+        asm volatile("ds_read_b64_tr_b8 %0, %2 offset:%3\n\t" "ds_read_b64_tr_b8 %1, %2 offset:%4\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(out[0]), "=&v"(out[1])
+                 : "v"(p[0]), "n"(LO), "n"(HI));
+    } else if constexpr (N == 2) {
+        asm volatile("ds_read_b64_tr_b8 %0, %4 offset:%6\n\t" "ds_read_b64_tr_b8 %1, %4 offset:%7\n\t"
+                 "ds_read_b64_tr_b8 %2, %5 offset:%6\n\t" "ds_read_b64_tr_b8 %3, %5 offset:%7\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(out[0]), "=&v"(out[1]), "=&v"(out[2]), "=&v"(out[3])
+                 : "v"(p[0]), "v"(p[1]), "n"(LO), "n"(HI));
+    } else if constexpr (N == 3) {
+        asm volatile("ds_read_b64_tr_b8 %0, %6 offset:%9\n\t" "ds_read_b64_tr_b8 %1, %6 offset:%10\n\t"
+                 "ds_read_b64_tr_b8 %2, %7 offset:%9\n\t" "ds_read_b64_tr_b8 %3, %7 offset:%10\n\t"
+                 "ds_read_b64_tr_b8 %4, %8 offset:%9\n\t" "ds_read_b64_tr_b8 %5, %8 offset:%10\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(out[0]), "=&v"(out[1]), "=&v"(out[2]), "=&v"(out[3]), "=&v"(out[4]), "=&v"(out[5])
+                 : "v"(p[0]), "v"(p[1]), "v"(p[2]), "n"(LO), "n"(HI));
+    } else {
+        asm volatile("ds_read_b64_tr_b8 %0, %8 offset:%12\n\t" "ds_read_b64_tr_b8 %1, %8 offset:%13\n\t"
+                 "ds_read_b64_tr_b8 %2, %9 offset:%12\n\t" "ds_read_b64_tr_b8 %3, %9 offset:%13\n\t"
+                 "ds_read_b64_tr_b8 %4, %10 offset:%12\n\t" "ds_read_b64_tr_b8 %5, %10 offset:%13\n\t"
+                 "ds_read_b64_tr_b8 %6, %11 offset:%12\n\t" "ds_read_b64_tr_b8 %7, %11 offset:%13\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(out[0]), "=&v"(out[1]), "=&v"(out[2]), "=&v"(out[3]), "=&v"(out[4]), "=&v"(out[5]), "=&v"(out[6]), "=&v"(out[7])
+                 : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "n"(LO), "n"(HI));
+    }
+}
+SQ_DEVICE uint32_t lds_address(const char* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p; }
+
 // Outer-dimension scaling of Eq. 2 on one accumulator: (float)acc * c, then the optional terms in the
 // order bias, ReLU, residual, then one rounding to the 16-bit output type.
 template <bool BF16>
@@ -98,6 +135,9 @@ void sq_stream_gemm_launch(const GemmArgs& a, StreamArgs q, bool to_i32, bool bf
 // Strip kernel for attention scores (bmm_strip.hip): B = [N, K] with K <= 128, alpha-only epilogue.
 bool sq_strip_bmm_eligible(int64_t M, int64_t N, int64_t K, int64_t batch);
 void sq_strip_bmm_launch(const GemmArgs& a, int batch, bool bf16, hipStream_t st);
+
+// P V of attention (bmm_pv.hip): B = [K, N], N % 16 == 0, alpha-only epilogue.
+void sq_pv_bmm_launch(GemmArgs a, int batch, bool bf16, hipStream_t st);
 
 // Few output tiles for the chip (gemm_direct.h): 16 mb tokens x 16 nb channels per workgroup of nw waves, one kernel, no workspace.
 // False: no such instantiation, or more workgroups than a launch holds.

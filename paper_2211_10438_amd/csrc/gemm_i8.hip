@@ -68,17 +68,11 @@ constexpr int kNumCU = 256;
 
 // The plan that sizes the workspace (callers keep that size, so its K splits are fixed by the shape), and the plan that runs for up to
 // 128 tokens, for short K and for batches; longer layers of more tokens choose their tile below.
-TilePlan make_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool allow_split, bool b_transposed = false)
+TilePlan make_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool allow_split)
 {
     TilePlan pl{};
     pl.bn = 256;
-    if (b_transposed) {
-        pl.bm = 256;
-        pl.cfg = 5;
-        pl.bn = 128;
-        allow_split = false;
-    }
-    else if (M > 128 && K <= 128) {
+    if (M > 128 && K <= 128) {
         // The same, with the whole K range fetched in one go and four workgroups per CU.
         pl.cfg = 8;
         pl.bm = 128;
@@ -293,23 +287,23 @@ struct Path {
     int need;  // K splits the workspace is sized for, fixed by the shape
     DirectPlan direct;
 };
-Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool b_transposed, bool allow_split, Epilogue epi, StreamArgs* sp, TilePlan* pl)
+Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool allow_split, Epilogue epi, StreamArgs* sp, TilePlan* pl)
 {
     Path p{};
-    const bool single = !b_transposed && batch == 1;
+    const bool single = batch == 1;
     const DirectPlan dp = single ? sq_direct_gemm_plan(M, N, K, tiled) : DirectPlan{};
     if (dp.mb && few_channels(M, N, K, batch, tiled)) {
         p.direct = dp;
         return p;
     }
     double us = 0.0;
-    if (!b_transposed && sq_stream_gemm_plan(M, N, K, batch, tiled, sp) && (sp->gk == 1 || allow_split)) {  // (else the tile kernels)
+    if (sq_stream_gemm_plan(M, N, K, batch, tiled, sp) && (sp->gk == 1 || allow_split)) {  // (else the tile kernels)
         p.stream = true;
         p.need = sp->gk;
         us = sp->us;
     } else {
         p.tiles = true;
-        *pl = make_plan(M, N, K, batch, allow_split, b_transposed);
+        *pl = make_plan(M, N, K, batch, allow_split);
         p.need = pl->splits;
         if (single && pl->bm == 256) *pl = choose_tile(M, N, K, tiled, *pl, &us);
         if (single) us = tile_us(*pl, (double)M, (double)N, (double)K, tiled, epi, us);
@@ -331,7 +325,7 @@ Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool b_t
 // allow_split = false: the caller has no workspace to offer (sq_w8a8_bmm), so only plans that finish in one kernel
 // are considered.
 sq_status run_gemm(GemmArgs a, int64_t batch, bool to_i32, bool bf16, void* workspace, size_t ws_bytes, hipStream_t st,
-                   bool b_transposed = false, bool tiled = false, bool allow_split = true)
+                   bool tiled = false, bool allow_split = true)
 {
     const int64_t total = (int64_t)a.M * a.N;
     auto reduce = [&](void* final_out) {  // a.acc_out = partials [a.splits][M][N]
@@ -349,7 +343,7 @@ sq_status run_gemm(GemmArgs a, int64_t batch, bool to_i32, bool bf16, void* work
     };
     StreamArgs sp{};
     TilePlan pl{};
-    const Path path = choose(a.M, a.N, a.K, batch, tiled, b_transposed, allow_split, to_i32 ? Epilogue::sums : a.x_scale ? Epilogue::scales : Epilogue::alpha, &sp, &pl);
+    const Path path = choose(a.M, a.N, a.K, batch, tiled, allow_split, to_i32 ? Epilogue::sums : a.x_scale ? Epilogue::scales : Epilogue::alpha, &sp, &pl);
     // (a shape whose workspace is sized for a K split is asked for it also where a kernel that has no use for it takes the call)
     if (path.need > 1 && (!workspace || ws_bytes < (size_t)path.need * total * sizeof(int32_t))) return SQ_ERR_WORKSPACE;
     const int splits = path.stream ? sp.gk : path.tiles ? pl.splits : 1;
@@ -420,7 +414,7 @@ sq_status sq_w8a8_linear(const int8_t* xq, const float* x_scale, int x_scale_per
     a.C = y; a.x_scale = x_scale; a.per_token = x_scale_per_token ? 1 : 0; a.w_scale = w_scale;
     a.w_per_channel = w_scale_per_channel ? 1 : 0;
     a.bias = bias; a.residual = residual; a.relu = relu ? 1 : 0;
-    return run_gemm(a, 1, false, out == SQ_BF16, workspace, ws_bytes, (hipStream_t)stream, false, layout == SQ_TILED);
+    return run_gemm(a, 1, false, out == SQ_BF16, workspace, ws_bytes, (hipStream_t)stream, layout == SQ_TILED);
 }
 
 int sq_probe_narrow_gemm(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout)
@@ -433,7 +427,7 @@ int sq_probe_linear_form(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout)
     if (!dims_ok(t, c_i, c_o)) return 0;
     StreamArgs sp{};
     TilePlan pl{};
-    const DirectPlan d = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, Epilogue::scales, &sp, &pl).direct;
+    const DirectPlan d = choose(t, c_o, c_i, 1, layout == SQ_TILED, true, Epilogue::scales, &sp, &pl).direct;
     return 100 * d.mb + 10 * d.nb + d.nw;
 }
 
@@ -442,7 +436,7 @@ int sq_probe_linear_tile(int64_t t, int64_t c_i, int64_t c_o, sq_layout layout)
     if (!dims_ok(t, c_i, c_o)) return 0;
     StreamArgs sp{};
     TilePlan pl{};
-    const Path p = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, Epilogue::scales, &sp, &pl);
+    const Path p = choose(t, c_o, c_i, 1, layout == SQ_TILED, true, Epilogue::scales, &sp, &pl);
     return p.tiles && !p.direct.mb ? pl.splits * 1000000 + pl.bm * 1000 + pl.bn : 0;
 }
 
@@ -452,7 +446,7 @@ sq_status sq_probe_linear_plan(int64_t t, int64_t c_i, int64_t c_o, sq_layout la
     if (!dims_ok(t, c_i, c_o)) return SQ_ERR_SHAPE;
     StreamArgs sp{};
     TilePlan pl{};
-    const Path p = choose(t, c_o, c_i, 1, layout == SQ_TILED, false, true, Epilogue::scales, &sp, &pl);
+    const Path p = choose(t, c_o, c_i, 1, layout == SQ_TILED, true, Epilogue::scales, &sp, &pl);
     const int64_t steps = (c_i + 63) / 64;
     const int64_t direct[6] = {0, 100 * p.direct.mb + 10 * p.direct.nb + p.direct.nw, 1, steps, 0, 0};
     const int64_t stream[6] = {1, sp.regs, sp.gk, (int64_t)sp.iters * sp.ksub, sp.gn, sp.units};
@@ -508,7 +502,7 @@ sq_status sq_w8a8_linear_q8(const int8_t* xq, const float* x_scale, int x_scale_
     a.w_per_channel = w_scale_per_channel ? 1 : 0;
     a.bias = bias; a.residual = residual; a.relu = relu ? 1 : 0;
     a.q8_step = y_step; a.q8_out = yq; a.q8_tiled = yq_layout == SQ_TILED ? 1 : 0;
-    return run_gemm(a, 1, false, mid == SQ_BF16, workspace, ws_bytes, (hipStream_t)stream, false, layout == SQ_TILED);
+    return run_gemm(a, 1, false, mid == SQ_BF16, workspace, ws_bytes, (hipStream_t)stream, layout == SQ_TILED);
 }
 
 sq_status sq_i8_gemm_i32(const int8_t* xq, const int8_t* wq, int32_t* acc, int64_t t, int64_t c_i, int64_t c_o,
@@ -527,7 +521,7 @@ sq_status sq_i8_gemm_i32(const int8_t* xq, const int8_t* wq, int32_t* acc, int64
     a.lda = c_i; a.ldb = c_i;
     a.acc_out = acc;
     a.C = acc;
-    return run_gemm(a, 1, true, false, workspace, ws_bytes, (hipStream_t)stream, false, layout == SQ_TILED);
+    return run_gemm(a, 1, true, false, workspace, ws_bytes, (hipStream_t)stream, layout == SQ_TILED);
 }
 
 // ---- sq_w8a8_linear for callers that cannot allocate: the K-split scratch lives in a device array of the library.
@@ -600,7 +594,11 @@ sq_status sq_internal_bmm(const int8_t* a_, const int8_t* b_, int trans_b, float
         sq_strip_bmm_launch(a, (int)batch, out == SQ_BF16, (hipStream_t)stream);
         return sq_launch_status();
     }
-    return run_gemm(a, batch, false, out == SQ_BF16, nullptr, 0, (hipStream_t)stream, !trans_b, false, false);
+    if (!trans_b) {
+        sq_pv_bmm_launch(a, (int)batch, out == SQ_BF16, (hipStream_t)stream);
+        return sq_launch_status();
+    }
+    return run_gemm(a, batch, false, out == SQ_BF16, nullptr, 0, (hipStream_t)stream, false, false);
 }
 
 }  // extern "C"

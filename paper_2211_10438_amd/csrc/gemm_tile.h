@@ -32,19 +32,16 @@ namespace {
 enum { EPI_DEQUANT = 0, EPI_I32 = 1 };
 
 // BM x BN output tile per workgroup, WGM x WGN waves, BK = 64 bytes of K per pipeline stage.
-// BT = false: B is [N, K] (K-contiguous rows, like A).  BT = true: B is [K, N] (the V operand of
-// attention's P V product): its tiles are read through registers, transposed bytewise in registers
-// and written to the same LDS layout, so the MFMA loop is identical.
+// B is [N, K] (K-contiguous rows, like A).
 //
 // LAY selects the operand layouts in global memory:
 //   LAY_ROWS  A [M, K] and B [N, K] row-major (K contiguous);
-//   LAY_BT    A row-major, B [K, N] (transposed, see above);
 //   LAY_TILED A and B in the tiled layout of sq_layout SQ_TILED: 16-row x 64-byte blocks of 1 KB,
 //             stored block-row-major, each block an exact image of the LDS block (chunk permutation
 //             included).  One wave-wide load then copies 1 KB of contiguous global memory -- eight whole
 //             128-byte lines instead of sixteen 64-byte row segments -- which is what the L2 -> CU path
 //             serves best.
-enum { LAY_ROWS = 0, LAY_BT = 1, LAY_TILED = 2 };
+enum { LAY_ROWS = 0, LAY_TILED = 2 };
 
 //
 // ONESHOT (host guarantees K <= 64 * (NSTAGE - 1)): the whole K range is fetched up front into NSTAGE - 1
@@ -64,21 +61,19 @@ enum { LAY_ROWS = 0, LAY_BT = 1, LAY_TILED = 2 };
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool BF16, int LAY, int OCC = 1, bool ONESHOT = false, int MF = 32, bool PAIR = false>
 __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmArgs p)
 {
-    constexpr bool BT = LAY == LAY_BT, TILED = LAY == LAY_TILED;
+    constexpr bool TILED = LAY == LAY_TILED;
     constexpr int NW = WGM * WGN, BK = 64;
     constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / MF, NI = WN / MF;
     constexpr int AV = MF * MF / 64;  // accumulator registers per block
     constexpr int QG = AV / 4;        // runs of four neighbouring output columns a lane holds per block
-    static_assert(MF == 32 || (MF == 16 && !BT && !ONESHOT && (PAIR ? NW == 4 && MI >= 6 && MI <= 8 && NI >= 4 : MI == 4 && NI % 2 == 0 && NI >= 6)), "MFMA shape");
+    static_assert(MF == 32 || (MF == 16 && !ONESHOT && (PAIR ? NW == 4 && MI >= 6 && MI <= 8 && NI >= 4 : MI == 4 && NI % 2 == 0 && NI >= 6)), "MFMA shape");
     static_assert(!PAIR || (MF == 16 && NSTAGE == 3), "pairs of steps");
     constexpr int A_BYTES = BM * BK, B_BYTES = BN * BK, STAGE = (A_BYTES + B_BYTES) * (PAIR ? 2 : 1);
     constexpr int RBA = BM / 16, RBB = BN / 16;  // 16-row blocks per operand tile
-    constexpr int SA = (RBA + NW - 1) / NW, SB = (RBB + NW - 1) / NW;  // BT: SB raw 1 KB blocks of the [64, BN] B tile
-    constexpr int KR = BT ? BN / 16 : 0;  // BT: each lane transposes a KR (k) x 4 (n) byte block per stage
+    constexpr int SA = (RBA + NW - 1) / NW, SB = (RBB + NW - 1) / NW;
     constexpr int LPS = SA + SB;          // vector-memory loads per wave per stage
-    static_assert(!BT || (NW == 4 && BN == 128 && RBB % NW == 0), "transposed-B path assumes 256 lanes and 128 columns");
     static_assert(WM % MF == 0 && WN % MF == 0, "wave tile must be a multiple of the MFMA block");
-    static_assert(NSTAGE >= (BT ? 4 : 3) && (NSTAGE - 2) * LPS <= 63, "pipeline depth exceeds the 6-bit vmcnt");
+    static_assert(NSTAGE >= 3 && (NSTAGE - 2) * LPS <= 63, "pipeline depth exceeds the 6-bit vmcnt");
     static_assert(NSTAGE * STAGE <= 160 * 1024, "LDS budget");
     // The epilogue stages the 16-bit tile in LDS; a tile too large for that goes in EG groups of GR rows.
     constexpr int EG = BM * (BN * 2 + 16) <= 160 * 1024 ? 1 : 2;
@@ -86,11 +81,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     constexpr int EPI_VEC = GR * (BN * 2 + 16);  // behind it the scales and biases of the tile's columns and the scales of its rows
     constexpr int EPI_BYTES = EPI == EPI_DEQUANT ? EPI_VEC + (2 * BN + BM) * 4 : 0;
     static_assert(BN <= NW * 64 && BM <= NW * 64, "a thread fetches one column's and one row's");
-    // BT: behind the ring, three buffers hold the B tile in MFMA operand layout (see transpose_stage).
-    constexpr int BOP = NSTAGE * STAGE;
-    constexpr int RING_BYTES = (ONESHOT ? NSTAGE - 1 : NSTAGE) * STAGE + (BT ? 3 * B_BYTES : 0);
+    constexpr int RING_BYTES = (ONESHOT ? NSTAGE - 1 : NSTAGE) * STAGE;
     constexpr int SMEM_BYTES = RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES;
-    static_assert(!ONESHOT || !BT, "one-shot loading is not combined with the transposed-B path");
     static_assert(SMEM_BYTES <= 160 * 1024, "LDS budget");
     __shared__ __attribute__((aligned(1024))) char smem[SMEM_BYTES];
 
@@ -137,8 +129,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     // Tiled operands: a 16-row block row is 16*K contiguous bytes and a K step advances 1 KB.
     constexpr int KSTEP = TILED ? 1024 : BK;
     const int8_t* Ab = p.A + (int64_t)batch * p.strideA + (int64_t)m0 * p.lda + (int64_t)kbeg * KSTEP;
-    const int8_t* Bb = BT ? p.B + (int64_t)batch * p.strideB + n0
-                          : p.B + (int64_t)batch * p.strideB + (int64_t)n0 * p.ldb + (int64_t)kbeg * KSTEP;
+    const int8_t* Bb = p.B + (int64_t)batch * p.strideB + (int64_t)n0 * p.ldb + (int64_t)kbeg * KSTEP;
 
     // ---- global -> LDS load slots of this wave.  Slot i moves 16-row block (i*NW + wave), 1 KB per
     // stage.  Lane l lands at LDS byte l*16 of the block, i.e. the block is row-major (64 B per row),
@@ -147,8 +138,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     // (position = chunk ^ swz(row)) so that the MFMA operand reads below stay bank-conflict free.
     auto swz = [](int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); };
     const int chunk = (lane & 3) ^ swz(lane >> 2);
-    uint32_t offA[SA], offB[SB + 1];
-    int ldsA[SA], ldsB[SB + 1];
+    uint32_t offA[SA], offB[SB];
+    int ldsA[SA], ldsB[SB];
 #pragma unroll
     for (int i = 0; i < SA; ++i) {
         const int rb = (i * NW + wave) % RBA;  // wraps only when RBA is not a multiple of NW: a benign duplicate
@@ -163,19 +154,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
         }
         ldsA[i] = rb * 1024;
     }
-    // BT: raw block (i*NW + wave) holds 1024/BN consecutive k rows of the stage, BN/16 lanes per row.
-    int rawrow[SB + 1], rawcol = 0;
-    if constexpr (BT) {
-        rawcol = (lane % (BN / 16)) * 16;
-        if (n0 + rawcol + 16 > p.N) rawcol = p.N - 16 - n0;  // ragged N tile: re-read valid columns (N % 16 == 0)
 #pragma unroll
-        for (int i = 0; i < SB; ++i) {
-            rawrow[i] = (i * NW + wave) * (1024 / BN) + lane / (BN / 16);
-            ldsB[i] = A_BYTES + (i * NW + wave) * 1024;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < (BT ? 0 : SB); ++i) {
+    for (int i = 0; i < SB; ++i) {
         const int rb = (i * NW + wave) % RBB;
         if constexpr (TILED) {
             const int last_rb = (p.N - 1 - n0) >> 4;
@@ -200,54 +180,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
 #pragma unroll
         for (int i = 0; i < SA; ++i)
             __builtin_amdgcn_global_load_lds(GPTR(a + (offA[i] - back)), LPTR(base + ldsA[i]), 16, 0, 0);
-        if constexpr (BT) {
-            // raw [64, BN] tile of B = [K, N]; rows past K (K tail) re-read row K-1, where the A fragments are zero
 #pragma unroll
-            for (int i = 0; i < SB; ++i) {
-                int k = (kbeg + kt) * BK + rawrow[i];
-                k = k < p.K ? k : p.K - 1;
-                __builtin_amdgcn_global_load_lds(GPTR(Bb + (int64_t)k * p.ldb + rawcol), LPTR(base + ldsB[i]), 16, 0, 0);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < SB; ++i)
-                __builtin_amdgcn_global_load_lds(GPTR(b + (offB[i] - back)), LPTR(base + ldsB[i]), 16, 0, 0);
-        }
-    };
-
-    // ---- transposed-B path.  The raw [64 k, BN n] tile of a stage arrives in the ring like A does (LDS-DMA,
-    // NSTAGE deep, so no global-memory latency sits in the K loop).  One K step before a stage is consumed
-    // every lane reads a KR (k) x 4 (n) byte block of it from LDS, transposes it bytewise in registers
-    // (v_perm_b32) and writes it, n-major, into one of three operand-layout buffers behind the ring; the
-    // MFMA loop then reads B fragments from there exactly as it reads them from the ring otherwise.
-    const int bt_cg = BT ? (int)(threadIdx.x % (BN / 4)) : 0;   // column group: columns 4*cg .. 4*cg+3
-    const int bt_ks = BT ? (int)(threadIdx.x / (BN / 4)) : 0;   // k slab: rows ks*KR .. ks*KR+KR-1 of the stage
-    auto transpose_stage = [&](int ring_buf, int op_buf) {
-        if constexpr (BT) {
-            const char* raw = smem + ring_buf * STAGE + A_BYTES + (bt_ks * KR) * BN + bt_cg * 4;
-            uint32_t breg[KR + 1];
-#pragma unroll
-            for (int j = 0; j < KR; ++j) breg[j] = *(const uint32_t*)(raw + j * BN);
-            // 4x4 byte transposes: out[e][m] = bytes e of rows 4m .. 4m+3
-            uint32_t out[4][KR / 4 + 1];
-#pragma unroll
-            for (int m = 0; m < KR / 4; ++m) {
-                const uint32_t r0 = breg[4 * m], r1 = breg[4 * m + 1], r2 = breg[4 * m + 2], r3 = breg[4 * m + 3];
-                const uint32_t t0 = __builtin_amdgcn_perm(r1, r0, 0x05010400u), t1 = __builtin_amdgcn_perm(r1, r0, 0x07030602u);
-                const uint32_t u0 = __builtin_amdgcn_perm(r3, r2, 0x05010400u), u1 = __builtin_amdgcn_perm(r3, r2, 0x07030602u);
-                out[0][m] = __builtin_amdgcn_perm(u0, t0, 0x05040100u);
-                out[1][m] = __builtin_amdgcn_perm(u0, t0, 0x07060302u);
-                out[2][m] = __builtin_amdgcn_perm(u1, t1, 0x05040100u);
-                out[3][m] = __builtin_amdgcn_perm(u1, t1, 0x07060302u);
-            }
-            char* base = smem + BOP + op_buf * B_BYTES;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int n = bt_cg * 4 + e, r = n & 15;
-                const int pos = (bt_ks >> 1) ^ swz(r);  // KR = 8: a lane holds half a 16-byte chunk
-                *(v2u*)(base + (n >> 4) * 1024 + r * 64 + pos * 16 + (bt_ks & 1) * 8) = v2u{out[e][0], out[e][1]};
-            }
-        }
+        for (int i = 0; i < SB; ++i)
+            __builtin_amdgcn_global_load_lds(GPTR(b + (offB[i] - back)), LPTR(base + ldsB[i]), 16, 0, 0);
     };
 
     // ---- MFMA operand fragments.  For the 32x32x32 MFMA lane l feeds row (l & 31) with the 16
@@ -259,7 +194,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
                                   : frow * 64 + (((lane >> 4) ^ swz(frow)) * 16);
     constexpr int FB = PAIR ? 2048 : 1024;  // bytes from one 16-row block of a stage to the next
     const int fragA0 = wm * (WM / 16) * FB + lane_off;
-    const int fragB0 = (BT ? 0 : RBA * FB) + wn * (WN / 16) * FB + lane_off;
+    const int fragB0 = RBA * FB + wn * (WN / 16) * FB + lane_off;
 
     // ---- what the epilogue needs beside the sums: per column scale and bias, per row scale, one of each for a thread to fetch, and the
     // tile of the residual, 16 bytes of a row at a time.  PRE: on their way during the K loop (the tiles of pairs of steps have the registers);
@@ -303,9 +238,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     if constexpr (MF == 32) {
     v4i fa0[MI], fb0[NI], fa1[MI], fb1[NI];
 
-    auto read_frags = [&](v4i(&fa)[MI], v4i(&fb)[NI], int buf, int kk, int op_buf) {
+    auto read_frags = [&](v4i(&fa)[MI], v4i(&fb)[NI], int buf, int kk) {
         const char* sa = smem + buf * STAGE + (fragA0 ^ (kk * 32));
-        const char* sb = smem + (BT ? BOP + op_buf * B_BYTES : buf * STAGE) + (fragB0 ^ (kk * 32));
+        const char* sb = smem + buf * STAGE + (fragB0 ^ (kk * 32));
 #pragma unroll
         for (int i = 0; i < MI; ++i) fa[i] = *(const v4i*)(sa + i * 2048);
 #pragma unroll
@@ -353,43 +288,32 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     }
     if constexpr (ONESHOT) {
         wait_vmcnt_imm<0>();
-    } else if constexpr (BT) {
-        // stages 0 and 1 landed; their B tiles go to operand buffers 0 and 1
-        wait_vmcnt_imm<(NSTAGE - 3) * LPS>();
-        __builtin_amdgcn_s_barrier();
-        transpose_stage(0, 0);
-        transpose_stage(1, 1);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     } else {
         wait_vmcnt_imm<(NSTAGE - 2) * LPS>();
     }
     __builtin_amdgcn_s_barrier();
-    read_frags(fa0, fb0, 0, 0, 0);
+    read_frags(fa0, fb0, 0, 0);
 
-    int buf = 0, ob = 0;  // ring buffer and operand buffer of the current K step
+    int buf = 0;  // ring buffer of the current K step
     for (int it = 0; it < nk - 1; ++it) {
         // first half of K step `it`
-        read_frags(fa1, fb1, buf, 1, ob);
+        read_frags(fa1, fb1, buf, 1);
         mfma_all(fa0, fb0);
         interleave_hint(std::integral_constant<int, 0>{});
         // second half; meanwhile make stage it+1 visible and refill the buffer freed by step it-1
         const int nbuf = buf + 1 == NSTAGE ? 0 : buf + 1;
-        const int nob = ob == 2 ? 0 : ob + 1;
         if constexpr (!ONESHOT) {
-            // BT needs stage it+2 landed (its B tile is transposed now, for the step after next)
-            wait_vmcnt_imm<(NSTAGE - (BT ? 4 : 3)) * LPS>();
+            wait_vmcnt_imm<(NSTAGE - 3) * LPS>();
             __builtin_amdgcn_s_barrier();
-            if constexpr (BT) transpose_stage(buf + 2 >= NSTAGE ? buf + 2 - NSTAGE : buf + 2, ob == 0 ? 2 : ob - 1);
             issue_stage(it + NSTAGE - 1 < nk ? it + NSTAGE - 1 : nk - 1, buf == 0 ? NSTAGE - 1 : buf - 1);
         }
-        read_frags(fa0, fb0, nbuf, 0, nob);
+        read_frags(fa0, fb0, nbuf, 0);
         mfma_all(fa1, fb1);
-        interleave_hint(std::integral_constant<int, (BT || ONESHOT) ? 0 : SA + SB>{});
+        interleave_hint(std::integral_constant<int, ONESHOT ? 0 : SA + SB>{});
         buf = nbuf;
-        ob = nob;
     }
     // last K step
-    read_frags(fa1, fb1, buf, 1, ob);
+    read_frags(fa1, fb1, buf, 1);
     if (has_tail) {
         // chunk index of this lane inside the 64-byte step: kk*2 + (lane >> 5)
         const int c0 = lane >> 5, c1 = 2 + (lane >> 5);
@@ -841,11 +765,6 @@ void launch_cfg(const TilePlan& pl, const GemmArgs& a, int batch, hipStream_t st
             break;
         case 7:
             sq_launch((gemm_i8_kernel<128, 128, 2, 2, 3, EPI, BF16, LAY, 3>), grid, dim3(256), 0, st, a);
-            break;
-        default:
-            if constexpr (EPI == EPI_DEQUANT && !TILED) {
-                sq_launch((gemm_i8_kernel<256, 128, 4, 1, 5, EPI, BF16, LAY_BT>), grid, dim3(256), 0, st, a);
-            }
             break;
     }
 #undef SQ_LAUNCH

@@ -3,7 +3,7 @@
 #include "gemm_args.h"
 
 struct TilePlan {
-    int cfg;     // 0: 256x256 (prefill)  1: 128x256  2: 64x256  3: 32x256  5: 256x128 B^T  6: 256x192
+    int cfg;     // 0: 256x256 (prefill)  1: 128x256  2: 64x256  3: 32x256  6: 256x192
                  // 7: 128x128, three workgroups per CU (short K: the output stream dominates)
                  // 8: 128x128, K <= 128 fetched in one go, four workgroups per CU
                  // 9: 256x384 (a round of tiles saved on wide outputs)

@@ -55,3 +55,17 @@ def test_pv_signed_saturated_codes_and_untouched_neighbours():
     assert np.array_equal(bits_from_dev(out), ref)
     g = guard.cpu().numpy()
     assert (g[:4096] == 0x7BFF).all() and (g[4096 + b * m * n:] == 0x7BFF).all()
+
+
+@pytest.mark.parametrize("n", [16, 32, 48, 64, 80, 96, 112, 128, 144, 256])
+@pytest.mark.parametrize("b,m,k", [(2, 65, 16), (1, 130, 128), (2, 47, 144), (1, 1, 656), (520, 17, 256)])
+def test_pv_column_blocks(n, b, m, k):
+    """Every number of 16-column blocks a workgroup may hold (and more columns than one holds), workgroups of 64 and of 128
+    rows (the last shape), contraction lengths below, at and behind a stage of 128."""
+    print(f"[case] pv column blocks b={b} m={m} n={n} k={k}", flush=True)
+    rng = np.random.default_rng(n * 1000 + m)
+    a = rng.integers(-127, 128, (b, m, k)).astype(np.int8)
+    v = rng.integers(-127, 128, (b, k, n)).astype(np.int8)
+    alpha = float(np.float32(0.013 / 127.0))
+    c = sq.w8a8_bmm(dev(a), dev(v), False, alpha, torch_dtype(F16))
+    assert_identical_16(ulp_distance(bits_from_dev(c), oracle.w8a8_bmm(a, v, False, alpha, F16)))
