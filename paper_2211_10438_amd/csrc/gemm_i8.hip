@@ -8,7 +8,9 @@ namespace {
 
 // Split-K reduction: sums the int32 partial tiles (exact) and applies the same epilogue, four neighbouring columns per
 // thread (N % 4 == 0; any other N one column), the partials read 16 bytes at a time, several splits in flight.  One column
-// per thread and a 64-bit division per output made it 17-19 us for 512 x 5120 outputs of 4 splits (42 MB).
+// per thread and a 64-bit division per output made it 17-19 us for 512 x 5120 outputs of 4 splits (42 MB).  Short threads: what counts
+// is how often each waits for memory, so the scales, bias and residual are under way before the partials are (behind them: 512 x
+// 4096 -> 5120 in splits with a residual 33.3 us, now 28.7; 700 x 6000 -> 3000 34.6 / 30.5, the tiles' share of that about 2 us each).
 template <bool BF16, int VEC>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs p, int to_i32)
 {
@@ -27,24 +29,52 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs p, in
         const int col = (int)(it - (int64_t)row * per_row) * VEC;
         const int64_t idx = it * VEC;
         typedef int vec_t __attribute__((ext_vector_type(VEC)));
-        vec_t sum;
+        typedef float vecf_t __attribute__((ext_vector_type(VEC)));
+        typedef uint16_t vech_t __attribute__((ext_vector_type(VEC)));
+        // everything the output needs is asked for before the sums are waited for
+        float xs = xs0;
+        vecf_t ws, bias;
+        vech_t res;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) sum[e] = 0;
-#pragma unroll 4
-        for (int s = 0; s < p.splits; ++s) sum += *(const vec_t*)(p.acc_out + (int64_t)s * total + idx);
+        for (int e = 0; e < VEC; ++e) {
+            ws[e] = ws0;
+            bias[e] = 0.0f;
+            res[e] = 0;
+        }
+        if (!to_i32) {
+            if (p.per_token && p.x_scale) xs = p.x_scale[row];
+            if (p.w_per_channel && p.x_scale) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) ws[e] = p.w_scale[col + e];
+            }
+            if (p.bias) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) bias[e] = p.bias[col + e];
+            }
+            if (R) res = *(const vech_t*)(R + idx);
+        }
+        const int32_t* part = p.acc_out + idx;
+        vec_t sum = *(const vec_t*)part;
+        for (int s = 1; s < p.splits; s += 4) {
+            vec_t v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {  // (past the last split: that one again, left out below)
+                const int at = s + k < p.splits ? s + k : p.splits - 1;
+                v[k] = *(const vec_t*)(part + at * total);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (s + k < p.splits) sum += v[k];
+        }
         if (to_i32) {
             *(vec_t*)((int32_t*)p.C + idx) = sum;
             continue;
         }
-        const float xs = p.per_token && p.x_scale ? p.x_scale[row] : xs0;
         uint32_t o[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
-            float c;
-            if (p.x_scale) c = xs * (p.w_per_channel ? p.w_scale[col + e] : ws0);
-            else c = p.alpha;
-            o[e] = dequant_one<BF16>(sum[e], c, p.bias ? p.bias[col + e] : 0.0f, p.bias != nullptr, p.relu != 0,
-                                     R ? R[idx + e] : 0u, R != nullptr) & 0xffffu;
+            const float c = p.x_scale ? xs * ws[e] : p.alpha;
+            o[e] = dequant_one<BF16>(sum[e], c, bias[e], p.bias != nullptr, p.relu != 0, res[e], R != nullptr) & 0xffffu;
         }
         if (p.q8_step) {
             int8_t* dst = code_dst(p.q8_out, row, col & ~7, p.N, p.q8_tiled != 0) + (col & 7);
