@@ -55,7 +55,8 @@ def _native_calls(L):
         return None
     mod.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in (
         "sq_quantize_act", "sq_w8a8_linear", "sq_w8a8_linear_q8", "sq_w8a8_bmm", "sq_softmax_quant_p", "sq_ln_quantize", "sq_w8a8_attention",
-        "sq_w8a8_attention_causal", "sq_workspace_bytes")))
+        "sq_w8a8_attention_causal", "sq_workspace_bytes", "sq_smooth_scales", "sq_act_absmax_per_channel", "sq_weight_absmax_per_in_channel",
+        "sq_prepare_weight")))
     return mod
 
 
@@ -176,6 +177,10 @@ def empty_codes(rows: int, k: int, layout: int = ROW_MAJOR, device="cuda") -> to
 
 def smooth_scales(x_absmax: torch.Tensor, w_absmax: torch.Tensor, alpha: float):
     """Eq. 4 on HOST fp32 tensors -> (s, inv_s) host fp32 tensors."""
+    if _fast is not None:
+        r = _fast.smooth_scales(x_absmax, w_absmax, alpha)
+        if r is not None:
+            return r
     xa = x_absmax.detach().to("cpu", torch.float32).contiguous()
     wa = w_absmax.detach().to("cpu", torch.float32).contiguous()
     s = torch.empty_like(xa)
@@ -186,6 +191,10 @@ def smooth_scales(x_absmax: torch.Tensor, w_absmax: torch.Tensor, alpha: float):
 
 
 def act_absmax_per_channel(x: torch.Tensor) -> torch.Tensor:
+    if _fast is not None:
+        r = _fast.act_absmax_per_channel(x)
+        if r is not None:
+            return r
     t, c_i = x.shape
     out = torch.empty(c_i, dtype=torch.float32, device=x.device)
     _check(lib().sq_act_absmax_per_channel(_dev(x, None, "x"), _dt(x), t, c_i, out.data_ptr(), _stream()),
@@ -194,6 +203,10 @@ def act_absmax_per_channel(x: torch.Tensor) -> torch.Tensor:
 
 
 def weight_absmax_per_in_channel(w: torch.Tensor) -> torch.Tensor:
+    if _fast is not None:
+        r = _fast.weight_absmax_per_in_channel(w)
+        if r is not None:
+            return r
     c_i, c_o = w.shape
     out = torch.empty(c_i, dtype=torch.float32, device=w.device)
     _check(lib().sq_weight_absmax_per_in_channel(_dev(w, None, "w"), _dt(w), c_i, c_o, out.data_ptr(), _stream()),
@@ -205,6 +218,10 @@ def prepare_weight(w: torch.Tensor, s: torch.Tensor | None = None, workspace=Non
                    per_channel: bool = False):
     """W [c_i, c_o] (+ optional device fp32 s [c_i]) -> (wq int8 [c_o, c_i] in `layout`, w_scale fp32 [1], or
     [c_o] with per_channel: one step per output channel)."""
+    if _fast is not None and workspace is None:
+        r = _fast.prepare_weight(w, s, layout, per_channel)
+        if r is not None:
+            return r
     c_i, c_o = w.shape
     wq = empty_codes(c_o, c_i, layout, w.device)
     w_scale = torch.empty(c_o if per_channel else 1, dtype=torch.float32, device=w.device)

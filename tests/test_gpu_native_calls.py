@@ -102,6 +102,31 @@ def test_what_is_left_to_the_general_code(both):
     assert taken == [21]  # (a product by NaN is an ordinary call)
 
 
+def test_native_calls_of_layer_preparation(both):
+    """Statistics, smoothing factors and weight codes: taken natively with the general code's results, else left to it."""
+    c_i, c_o = 192, 160
+    for dt in (torch.float16, torch.bfloat16):
+        x, w = torch.randn((40, c_i), device="cuda").to(dt), torch.randn((c_i, c_o), device="cuda").to(dt)
+        xm, = both(lambda: sq.act_absmax_per_channel(x))
+        wm, = both(lambda: sq.weight_absmax_per_in_channel(w))
+        xm, wm = xm.cpu(), wm.cpu()
+        xm[3], wm[5] = 0.0, float("nan")
+        for alpha in (0.5, 0.8):
+            f, _ = both(lambda: sq.smooth_scales(xm, wm, alpha))
+        both(lambda: sq.smooth_scales(xm.view(2, -1), wm.view(2, -1), 0.5))
+        f = torch.rand(c_i) + 0.5
+        for layout in (sq.ROW_MAJOR, sq.TILED):
+            for per_channel in (False, True):
+                for s in (None, f.cuda()):
+                    both(lambda: sq.prepare_weight(w, s, layout=layout, per_channel=per_channel))
+    for g in (lambda: sq.act_absmax_per_channel(x[0]), lambda: sq.act_absmax_per_channel(x.t()), lambda: sq.weight_absmax_per_in_channel(w.float()),
+              lambda: sq.smooth_scales(xm.cuda(), wm, 0.5), lambda: sq.smooth_scales(xm.double(), wm, 0.5), lambda: sq.smooth_scales(xm[::2], wm[::2], 0.5),
+              lambda: sq.smooth_scales(xm, wm, 1), lambda: sq.smooth_scales(xm, wm, 1.5), lambda: sq.smooth_scales(xm[:0], wm[:0], 0.5),
+              lambda: sq.prepare_weight(w.float()), lambda: sq.prepare_weight(w, f), lambda: sq.prepare_weight(w.t()), lambda: sq.prepare_weight(w, per_channel=1),
+              lambda: sq.prepare_weight(w[:100].contiguous(), layout=sq.TILED), lambda: sq.prepare_weight(w, workspace=torch.empty(4096, dtype=torch.uint8, device="cuda"))):
+        both(g, native_takes=False)
+
+
 def _queue_of_work(stream):
     """A tensor written on `stream` only after some milliseconds of products: what reads it on another stream comes too early."""
     a = torch.randn((8192, 8192), device="cuda").bfloat16()
