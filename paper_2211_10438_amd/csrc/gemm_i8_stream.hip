@@ -122,6 +122,25 @@ __global__ __launch_bounds__(NWAVE * 64, 1) void gemm_i8_stream_kernel(const Gem
 #pragma unroll
         for (int j = 0; j < NUW; ++j) acc[i][j] = v4i{0, 0, 0, 0};
 
+    // What the epilogue needs beside the sums, on its way during the K loop.
+    const int col_l = lane & 15, row_l = (lane >> 4) * 4;
+    const bool raw = q.to_i32 || q.gk > 1;
+    float row_scale[MB][4], col_scale[NUW], col_bias[NUW];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = (wm * MB + i) * 16 + row_l + v;
+            row_scale[i][v] = !raw && p.x_scale ? p.x_scale[p.per_token && row < p.M ? row : 0] : 1.0f;
+        }
+#pragma unroll
+    for (int j = 0; j < NUW; ++j) {
+        const int u = j * WN + wn, col = (u0 + u) * 16 + col_l;
+        const bool there = !raw && u < nu && col < p.N;
+        col_scale[j] = !there ? 0.0f : !p.x_scale ? p.alpha : p.w_scale[p.w_per_channel ? col : 0];
+        col_bias[j] = there && p.bias ? p.bias[col] : 0.0f;
+    }
+
     // Every K step issues exactly one stage of loads (past the end of the range the last stage again,
     // into a slot nobody reads), so the number of loads in flight at each wait is a constant.
     const int iters = q.iters;
@@ -168,10 +187,7 @@ __global__ __launch_bounds__(NWAVE * 64, 1) void gemm_i8_stream_kernel(const Gem
     wait_vmcnt_imm<0>();  // the refills issued past the end of the K range have landed
 
     // ---- epilogue.  16x16 accumulator layout: lane l, register v holds row 4*(l >> 4) + v, column l & 15.
-    const int col_l = lane & 15, row_l = (lane >> 4) * 4;
-    const bool raw = q.to_i32 || q.gk > 1;
     int32_t* out32 = p.acc_out + (int64_t)gki * p.M * p.N;
-    const float ws = (!raw && p.x_scale && !p.w_per_channel) ? p.w_scale[0] : 0.0f;
     const uint16_t* R = (const uint16_t*)p.residual;
     float rq = 0.0f;
     if (!raw && p.q8_step) {
@@ -184,8 +200,7 @@ __global__ __launch_bounds__(NWAVE * 64, 1) void gemm_i8_stream_kernel(const Gem
         if (u >= nu) continue;
         const int col = (u0 + u) * 16 + col_l;
         if (col >= p.N) continue;
-        const float bias = (!raw && p.bias) ? p.bias[col] : 0.0f;
-        const float wsc = (!raw && p.x_scale && p.w_per_channel) ? p.w_scale[col] : ws;
+        const float bias = col_bias[j];
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -196,9 +211,7 @@ __global__ __launch_bounds__(NWAVE * 64, 1) void gemm_i8_stream_kernel(const Gem
                 if (raw) {
                     out32[idx] = acc[i][j][v];
                 } else {
-                    float c;
-                    if (p.x_scale) c = (p.per_token ? p.x_scale[row] : p.x_scale[0]) * wsc;
-                    else c = p.alpha;
+                    const float c = row_scale[i][v] * col_scale[j];
                     const uint32_t rb = R ? (uint32_t)R[idx] : 0u;
                     const uint32_t o = q.bf16 ? dequant_one<true>(acc[i][j][v], c, bias, p.bias != nullptr, p.relu != 0, rb, R != nullptr)
                                               : dequant_one<false>(acc[i][j][v], c, bias, p.bias != nullptr, p.relu != 0, rb, R != nullptr);
@@ -251,8 +264,8 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
     constexpr int STAGE = S * MB * 1024;      // bytes
     constexpr int LW = S * MB / 2;            // loads per loader wave and stage
     constexpr int PITCH = CNT * 16 + 4;       // ints per row of the output staging buffer
-    constexpr int RING = NS * STAGE, RED = MB * 16 * PITCH * 4;
-    __shared__ __attribute__((aligned(1024))) char smem[RING > RED ? RING : RED];
+    constexpr int RING = NS * STAGE, RED = MB * 16 * PITCH * 4, EPI = RED + (MB * 16 + 2 * CNT * 16) * 4;
+    __shared__ __attribute__((aligned(1024))) char smem[RING > EPI ? RING : EPI];
     static_assert(S == 4 && D % 2 == 0, "a stage is two own steps of a compute wave; whole stages in the unrolled body");
     static_assert(S * MB % 2 == 0 && 3 * LW <= 63, "loads of a loader wave: whole, and countable by vmcnt");
 
@@ -275,7 +288,21 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
 #pragma unroll
         for (int j = 0; j < CNTW; ++j) acc[i][j] = v4i{0, 0, 0, 0};
 
+    const bool raw = q.to_i32 || q.gk > 1;
+    float row_scale = 0.0f, col_scale[2] = {0.0f, 0.0f}, col_bias[2] = {0.0f, 0.0f};  // (loader waves: for the epilogue)
     if (wave >= 6) {
+        if (!raw) {
+            const int t = (int)threadIdx.x - 384;
+            if (t < p.M) row_scale = !p.x_scale ? 1.0f : p.per_token ? p.x_scale[t] : p.x_scale[0];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int c = t + 128 * e, col = u0 * 16 + c;
+                if (c < nu * 16 && col < p.N) {
+                    col_scale[e] = !p.x_scale ? p.alpha : p.w_per_channel ? p.w_scale[col] : p.w_scale[0];
+                    if (p.bias) col_bias[e] = p.bias[col];
+                }
+            }
+        }
         // ---- loader waves: block b of a stage = (K step b / MB of the stage, token block b % MB); wave 6 takes the
         // even blocks, wave 7 the odd ones.  Ragged M: blocks past the last one re-read it (their rows are never stored).
         const int lw = wave - 6;
@@ -354,7 +381,7 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
                         if (live) {
 #pragma unroll
                             for (int i = 0; i < MB; ++i)
-                                acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[d][j], acc[i][j], 0, 0, 0);
+                                acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[d][j], fa[i], acc[i][j], 0, 0, 0);
                         }
                         load_w(d, j, sw);
                     }
@@ -374,78 +401,109 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
 
     // ---- the accumulators meet in LDS (the ring is free now): the waves of K parity 0 store, those of parity 1 add
     // (the same lane of the same unit group owns an element in both), and the epilogue writes whole rows of the slab.
-    // 16x16 accumulator layout: lane l, register v holds row 4*(l >> 4) + v, column l & 15.
+    // 16x16 accumulator layout (weights as first operand): lane l, register v holds row l & 15, column 4*(l >> 4) + v.
     int* red = (int*)smem;
+    float* const sv_row = (float*)(smem + RED);
+    float* const sv_col = sv_row + MB * 16;
+    float* const sv_bias = sv_col + CNT * 16;
     __syncthreads();  // everyone is done with the ring
+    if (wave >= 6) {
+        const int t = (int)threadIdx.x - 384;
+        if (t < MB * 16) sv_row[t] = row_scale;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int c = t + 128 * e;
+            if (c < CNT * 16) {
+                sv_col[c] = col_scale[e];
+                sv_bias[c] = col_bias[e];
+            }
+        }
+    }
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         if (wave < 6 && kp == pass) {
-            const int col_l = lane & 15, row_l = (lane >> 4) * 4;
 #pragma unroll
             for (int i = 0; i < MB; ++i)
 #pragma unroll
                 for (int j = 0; j < CNTW; ++j) {
                     const int u = ug + j * 3;
                     if (u >= nu) continue;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        int* dst = &red[(i * 16 + row_l + v) * PITCH + u * 16 + col_l];
-                        *dst = pass ? *dst + acc[i][j][v] : acc[i][j][v];
-                    }
+                    v4i* dst = (v4i*)&red[(i * 16 + (lane & 15)) * PITCH + u * 16 + (lane >> 4) * 4];
+                    *dst = pass ? *dst + acc[i][j] : acc[i][j];
                 }
         }
         __syncthreads();
     }
 
-    // ---- epilogue: two neighbouring columns per thread
-    const bool raw = q.to_i32 || q.gk > 1;
+    // ---- epilogue: eight neighbouring columns per thread, 16 bytes of a row (rows that are not whole 16-byte pieces: element by element).
+    // Scales and biases come from LDS, where the loader waves put them: fetched here, two columns at a time, they made this part 11 of the
+    // 59 us of 100 x 9216 -> 27648.
     int32_t* out32 = p.acc_out + (int64_t)gki * p.M * p.N;
-    const float ws = (!raw && p.x_scale && !p.w_per_channel) ? p.w_scale[0] : 0.0f;
     const uint16_t* R = (const uint16_t*)p.residual;
     float rq = 0.0f;
     if (!raw && p.q8_step) {
         const float delta = p.q8_step[0];
         rq = delta > 0.0f ? 1.0f / delta : 0.0f;
     }
-    const int pairs = nu * 8;  // column pairs per row
     const int rows = p.M < MB * 16 ? p.M : MB * 16;
-    for (int idx = threadIdx.x; idx < rows * pairs; idx += 512) {
-        const int row = idx / pairs, cp = idx - row * pairs;
-        const int col = u0 * 16 + cp * 2;
-        if (col >= p.N) continue;
-        const bool two = col + 1 < p.N;
-        const int a0 = red[row * PITCH + cp * 2], a1 = red[row * PITCH + cp * 2 + 1];
-        const int64_t o = (int64_t)row * p.N + col;
-        if (raw) {
-            out32[o] = a0;
-            if (two) out32[o + 1] = a1;
-            continue;
-        }
-        const float xs = p.x_scale ? (p.per_token ? p.x_scale[row] : p.x_scale[0]) : 0.0f;
-        uint32_t ob[2];
+    auto emit = [&](auto BF_) {
+        constexpr bool BF = decltype(BF_)::value;
+        typedef float v4f __attribute__((ext_vector_type(4)));
+        const bool whole = (p.N & 7) == 0;
+        for (int idx = threadIdx.x; idx < rows * nu * 2; idx += 512) {
+            const int row = idx / (nu * 2), c8 = (idx - row * (nu * 2)) * 8, col = u0 * 16 + c8;
+            if (col >= p.N) continue;
+            const int64_t o = (int64_t)row * p.N + col;
+            const v4i lo = *(const v4i*)&red[row * PITCH + c8], hi = *(const v4i*)&red[row * PITCH + c8 + 4];
+            if (raw) {
+                if (whole) {
+                    *(v4i*)(out32 + o) = lo;
+                    *(v4i*)(out32 + o + 4) = hi;
+                } else {
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            if (e == 1 && !two) break;
-            const float c = p.x_scale ? xs * (p.w_per_channel ? p.w_scale[col + e] : ws) : p.alpha;
-            const float bias = p.bias ? p.bias[col + e] : 0.0f;
-            const uint32_t rb = R ? (uint32_t)R[o + e] : 0u;
-            const int a = e ? a1 : a0;
-            ob[e] = q.bf16 ? dequant_one<true>(a, c, bias, p.bias != nullptr, p.relu != 0, rb, R != nullptr)
-                           : dequant_one<false>(a, c, bias, p.bias != nullptr, p.relu != 0, rb, R != nullptr);
-            if (p.q8_step) {
-                const int code = q.bf16 ? requant_code<true>(ob[e], rq) : requant_code<false>(ob[e], rq);
-                code_dst(p.q8_out, row, (col + e) & ~7, p.N, p.q8_tiled != 0)[(col + e) & 7] = (int8_t)code;
+                    for (int e = 0; e < 8; ++e)
+                        if (col + e < p.N) out32[o + e] = e < 4 ? lo[e & 3] : hi[e & 3];
+                }
+                continue;
+            }
+            uint32_t res[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (R) {
+                if (whole) {
+                    const v4u r = *(const v4u*)(R + o);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) res[e] = (r[e >> 1] >> ((e & 1) * 16)) & 0xffffu;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) res[e] = col + e < p.N ? R[o + e] : 0u;
+                }
+            }
+            const float xs = sv_row[row];
+            const v4f w0 = *(const v4f*)(sv_col + c8), w1 = *(const v4f*)(sv_col + c8 + 4);
+            const v4f b0 = *(const v4f*)(sv_bias + c8), b1 = *(const v4f*)(sv_bias + c8 + 4);
+            uint32_t ob[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                ob[e] = dequant_one<BF>(e < 4 ? lo[e & 3] : hi[e & 3], xs * (e < 4 ? w0[e & 3] : w1[e & 3]), e < 4 ? b0[e & 3] : b1[e & 3], p.bias != nullptr,
+                                        p.relu != 0, res[e], R != nullptr) & 0xffffu;
+            if (p.q8_step) {  // (codes: whole pieces of eight)
+                uint32_t c[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) c[e] = (uint32_t)requant_code<BF>(ob[e], rq);
+                *(v2u*)code_dst(p.q8_out, row, col, p.N, p.q8_tiled != 0) = v2u{pack4_low_bytes(c[0], c[1], c[2], c[3]), pack4_low_bytes(c[4], c[5], c[6], c[7])};
+                continue;
+            }
+            uint16_t* dst = (uint16_t*)p.C + o;
+            if (whole) {
+                *(v4u*)dst = v4u{ob[0] | (ob[1] << 16), ob[2] | (ob[3] << 16), ob[4] | (ob[5] << 16), ob[6] | (ob[7] << 16)};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (col + e < p.N) dst[e] = (uint16_t)ob[e];
             }
         }
-        if (p.q8_step) continue;
-        uint16_t* dst = (uint16_t*)p.C + o;
-        if (two && !(p.N & 1)) {
-            *(uint32_t*)dst = (ob[0] & 0xffffu) | (ob[1] << 16);
-        } else {
-            dst[0] = (uint16_t)ob[0];
-            if (two) dst[1] = (uint16_t)ob[1];
-        }
-    }
+    };
+    if (q.bf16) emit(std::true_type{});
+    else emit(std::false_type{});
 }
 
 int num_cus()
