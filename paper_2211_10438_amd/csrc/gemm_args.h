@@ -120,16 +120,18 @@ SQ_DEVICE uint32_t dequant_pair(int acc0, int acc1, float c0, float c1, float bi
 struct StreamArgs {
     int gn;          // slabs (workgroups along C_o)
     int gk;          // K splits (workgroups along K); > 1: int32 partials go to acc_out[gk][M][N]
+    int need;        // K splits the workspace is sized for: gk or more
     int units;       // 16-column units of N
     int na;          // 16-row blocks of A
     int ksub;        // 64-byte K steps per stage
     int iters;       // stages per workgroup: K / 64 / gk / ksub
     int nt_w;        // weight loads carry the non-temporal hint
-    int regs;        // the register-direct kernel (tiled operands) runs this plan
+    int regs;        // the register-direct kernel runs this plan
     int tiled, to_i32, bf16;
     double us;       // modelled time of the plan
 };
 bool sq_stream_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, StreamArgs* out);
+bool sq_stream_rows_plan(int64_t M, int64_t N, int64_t K, StreamArgs* out);
 void sq_stream_gemm_launch(const GemmArgs& a, StreamArgs q, bool to_i32, bool bf16, bool tiled, hipStream_t st);
 
 // Strip kernel for attention scores (bmm_strip.hip): B = [N, K] with K <= 128, alpha-only epilogue.

@@ -329,7 +329,7 @@ Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool all
     double us = 0.0;
     if (sq_stream_gemm_plan(M, N, K, batch, tiled, sp) && (sp->gk == 1 || allow_split)) {  // (else the tile kernels)
         p.stream = true;
-        p.need = sp->gk;
+        p.need = sp->need;
         us = sp->us;
     } else {
         p.tiles = true;
@@ -349,6 +349,18 @@ Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool all
     const double margin = K > 20480 && !tiled && M <= 128 ? 0.80 : p.tiles ? 0.90 : sp->regs ? 0.88 : 0.92;
     const bool chain = K > 12288 && dp.mb && ((M + 16 * dp.mb - 1) / (16 * dp.mb)) * ((N + 16 * dp.nb - 1) / (16 * dp.nb)) < 24;
     if (dp.mb && !chain && dp.us < margin * us) p.direct = dp;
+    // Row-major, 33 to 128 tokens: the weights-in-registers kernel where it is modelled clearly ahead of whatever was chosen.  Over 220 timings
+    // (110 shapes, weights in memory and in the last-level cache) the calls take 0.86 of the time; at 0.90 and without the constant 0.85, but 24
+    // of them lose more than 3 % and the worst a third (33 x 1664 -> 8672, where the direct kernel is ahead); so 9, the worst 13 % (86 x 1920 ->
+    // 10672 9.8 / 11.1 us).
+    StreamArgs rows{};
+    if (single && !tiled && sq_stream_rows_plan(M, N, K, &rows) && rows.us < 0.87 * (p.direct.mb ? dp.us : us) - 1.0) {
+        rows.need = p.need;
+        *sp = rows;
+        p.stream = true;
+        p.tiles = false;
+        p.direct = DirectPlan{};
+    }
     return p;
 }
 
@@ -418,7 +430,7 @@ size_t sq_gemm_workspace_bytes(int64_t t, int64_t c_i, int64_t c_o)
     if (few_channels(t, c_o, c_i, 1, false) && few_channels(t, c_o, c_i, 1, true)) return 0;
     // the layout is not known here: enough for the plan of either
     StreamArgs rows{}, tiles{};
-    const int ss_rows = sq_stream_gemm_plan(t, c_o, c_i, 1, false, &rows) ? rows.gk : 0, ss_tiled = sq_stream_gemm_plan(t, c_o, c_i, 1, true, &tiles) ? tiles.gk : 0;
+    const int ss_rows = sq_stream_gemm_plan(t, c_o, c_i, 1, false, &rows) ? rows.need : 0, ss_tiled = sq_stream_gemm_plan(t, c_o, c_i, 1, true, &tiles) ? tiles.need : 0;
     if (const int ss = ss_rows > ss_tiled ? ss_rows : ss_tiled) return ss > 1 ? (size_t)ss * t * c_o * sizeof(int32_t) : 0;
     TilePlan pl = make_plan(t, c_o, c_i, 1, true);
     return pl.splits > 1 ? (size_t)pl.splits * t * c_o * sizeof(int32_t) : 0;

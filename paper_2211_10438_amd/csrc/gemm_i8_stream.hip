@@ -226,7 +226,7 @@ __global__ __launch_bounds__(NWAVE * 64, 1) void gemm_i8_stream_kernel(const Gem
     }
 }
 
-// ---- Variant for tiled operands: weights straight into registers, activations through two loader waves.
+// ---- Variant for 33 to 128 tokens: weights straight into registers, activations through two loader waves.
 // Two measurements with pure read loops (256 workgroups, 4 streaming waves each) shape it:
 //  * a wave's loads return in issue order, so an activation block that would be an L2 hit waits behind the HBM
 //    misses the same wave issued before it.  A QKV-sized weight stream (453 MB) takes 65 us alone; with every wave
@@ -243,7 +243,10 @@ __global__ __launch_bounds__(NWAVE * 64, 1) void gemm_i8_stream_kernel(const Gem
 // owns the units ug, ug + 3, ... of the slab on the K steps 2 t + kp, so two compute waves share a SIMD, every weight
 // block is fetched by exactly one wave and every activation fragment is read from LDS by three.  Waves 6 and 7 do
 // nothing but copy the activation blocks into a 4-stage LDS ring (global_load_lds, a stage = 4 K steps of all token
-// blocks), three stages ahead; one barrier per stage.  Used from 33 tokens on; below, where the activation bytes hardly
+// blocks), three stages ahead; one barrier per stage.  Row-major operands (ROWS): a lane fetches the 16 bytes of its row that the MFMA wants, and the
+// loader waves write the same LDS image; us, the faster of the ring kernel (its K splits included) and the direct kernel / this: 128 x 4096 ->
+// 12288 39.0 / 20.3, 100 x 9216 -> 27648 86.6 / 69.8, 121 x 4032 -> 18832 44.5 / 29.0, 62 x 1984 -> 14120 16.6 / 10.7, 33 x 5632 -> 9072
+// 19.5 / 18.2.  Used from 33 tokens on; below, where the activation bytes hardly
 // matter, the kernel above is faster (all eight waves' loads feed one ring).  Each group's loop is instantiated for its own number of
 // units, and the kernel for four, six, seven or eight token blocks: with every group at the largest number, re-reading its last unit, and
 // four or eight blocks, 100 x 9216 -> 27648 (slabs of seven units, seven blocks) took 65.2 us, now 59.3; 64 tokens 53.7 / 50.0, 128 tokens 68.5 /
@@ -255,7 +258,7 @@ __global__ __launch_bounds__(NWAVE * 64, 1) void gemm_i8_stream_kernel(const Gem
 constexpr int kRegsStageSteps = 4, kRegsStages = 4, kRegsMaxUnits = 12;
 constexpr int regs_depth(int cntw) { return cntw <= 1 ? 8 : 4; }  // own K steps of weight blocks in flight per wave
 
-template <int MB, int CNT, bool NT>
+template <int MB, int CNT, bool ROWS>
 __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmArgs p, const StreamArgs q)
 {
     constexpr int CNTW = (CNT + 2) / 3;       // units per compute wave
@@ -276,7 +279,8 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
     const int nu = u1 - u0;     // CNT or CNT - 1, at least 1
     const int n = q.iters;      // 64-byte K steps of this workgroup: at least 2 D (the host sees to it)
     const int nst = (n + S - 1) / S;  // stages
-    const int64_t k0 = (int64_t)gki * n * 1024;
+    constexpr int KS = ROWS ? 64 : 1024;  // bytes of an operand per K step of a 16-row block, or of a row
+    const int64_t k0 = (int64_t)gki * n * KS;
     // lane l feeds row (l & 15), K chunk (l >> 4) of a block; the chunks of a row are stored permuted
     const int frow = lane & 15;
     const uint32_t frag_off = (uint32_t)(frow * 64 + ((((lane >> 4) ^ ((frow >> 1) & 3) ^ ((frow >> 3) & 1))) << 4));
@@ -311,18 +315,24 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
         int step_of[LW];
 #pragma unroll
         for (int i = 0; i < LW; ++i) {
-            const int b = 2 * i + lw;
+            // (row-major: the steps of a pair one right after the other, so that the second finds its line on the way)
+            const int b = ROWS ? (2 * lw + (i & 1)) * MB + i / 2 : 2 * i + lw;
             const int blk = b % MB;
             step_of[i] = b / MB;
-            src[i] = p.A + (int64_t)(blk < last_a ? blk : last_a) * 16 * p.lda + k0 + lane * 16;
+            if constexpr (ROWS) {  // four neighbouring lanes copy the 64 bytes of a row, chunks permuted as in the tiled layout
+                const int r = lane >> 2, row = blk * 16 + r;
+                src[i] = p.A + (int64_t)(row < p.M ? row : p.M - 1) * p.lda + k0 + (((lane & 3) ^ ((r >> 1) & 3) ^ ((r >> 3) & 1)) << 4);
+            } else {
+                src[i] = p.A + (int64_t)(blk < last_a ? blk : last_a) * 16 * p.lda + k0 + lane * 16;
+            }
         }
         auto issue_stage = [&](int t, int slot) {
-            char* base = smem + slot * STAGE + lw * 1024;
+            char* base = smem + slot * STAGE;
 #pragma unroll
             for (int i = 0; i < LW; ++i) {
                 int s = t * S + step_of[i];
                 s = s < n ? s : n - 1;  // past the end of the K range: the last step again, nobody reads it
-                __builtin_amdgcn_global_load_lds(GPTR(src[i] + (int64_t)s * 1024), LPTR(base + i * 2048), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds(GPTR(src[i] + (int64_t)s * KS), LPTR(base + (ROWS ? (2 * lw + (i & 1)) * MB + i / 2 : 2 * i + lw) * 1024), 16, 0, 0);
             }
         };
         // Every iteration issues exactly one stage of loads (past the end the last stage again, into a slot nobody
@@ -346,10 +356,20 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
             const int8_t* pw[C];
 #pragma unroll
             for (int j = 0; j < C; ++j) pw[j] = p.B + (int64_t)(u0 + ug + j * 3) * 16 * p.ldb + k0;
+            // this lane's bytes of a unit's block (row-major: of its row, or of the last one where the last unit has fewer than 16)
+            uint32_t wo[ROWS ? C : 1];
+#pragma unroll
+            for (int j = 0; j < (ROWS ? C : 1); ++j) {
+                const int last = p.N - 1 - (u0 + ug + j * 3) * 16;
+                wo[j] = ROWS ? (uint32_t)((frow < last ? frow : last) * (int)p.ldb + (lane >> 4) * 16) : frag_off;
+            }
+            // Own step t of this wave is K step 2 t + kp; row-major: the pairs of steps alternate, so that both halves of a row's 128-byte line
+            // are asked for one right after the other (64-byte steps in turn fetch every line twice: 100 x 9216 -> 27648 79 us, so 70).
+            auto own_step = [&](int t) { return ROWS ? 4 * (t >> 1) + 2 * kp + (t & 1) : 2 * t + kp; };
             v4i fb[D][C];
             auto load_w = [&](int d, int j, int s) {
-                const uint32_t off = frag_off + (uint32_t)s * 1024u;
-                if (NT) fb[d][j] = __builtin_nontemporal_load((const v4i*)(pw[j] + off));
+                const uint32_t off = wo[ROWS ? j : 0] + (uint32_t)s * (uint32_t)KS;
+                if (!ROWS) fb[d][j] = __builtin_nontemporal_load((const v4i*)(pw[j] + off));
                 else fb[d][j] = *(const v4i*)(pw[j] + off);
             };
             // Every step issues its refills, past the end of the range the last step again (L2 hits whose data nobody
@@ -357,9 +377,12 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
             // compiler places leave exactly the younger loads in flight.  (With a refill under a condition it has to
             // assume the refill did not happen, and waits for everything.)
 #pragma unroll
-            for (int d = 0; d < D; ++d)
+            for (int d = 0; d < D; d += ROWS ? 2 : 1)
 #pragma unroll
-                for (int j = 0; j < C; ++j) load_w(d, j, 2 * d + kp);
+                for (int j = 0; j < C; ++j) {
+                    load_w(d, j, own_step(d));
+                    if (ROWS) load_w(d + 1, j, own_step(d + 1));
+                }
             int slot = 0;
             for (int t0 = 0; t0 < 2 * nst; t0 += D) {
 #pragma unroll
@@ -368,11 +391,10 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
                         if (t0 + d >= 2 * nst) break;  // the later stages of the last round may not exist
                         __builtin_amdgcn_s_barrier();
                     }
-                    const int g = 2 * (t0 + d) + kp;
+                    const int g = own_step(t0 + d);
                     const bool live = g < n;
-                    const int gw = g + 2 * D;
-                    const int sw = gw < n ? gw : n - 1;
-                    const char* sa = smem + slot * STAGE + (2 * (d % 2) + kp) * MB * 1024 + frag_off;
+                    auto refill = [&](int step) { return step < n ? step : n - 1; };
+                    const char* sa = smem + slot * STAGE + (ROWS ? 2 * kp + d % 2 : 2 * (d % 2) + kp) * MB * 1024 + frag_off;
                     v4i fa[MB];
 #pragma unroll
                     for (int i = 0; i < MB; ++i) fa[i] = *(const v4i*)(sa + i * 1024);
@@ -383,7 +405,11 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
                             for (int i = 0; i < MB; ++i)
                                 acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[d][j], fa[i], acc[i][j], 0, 0, 0);
                         }
-                        load_w(d, j, sw);
+                        if (!ROWS) load_w(d, j, refill(g + 2 * D));
+                        if (ROWS && d % 2 == 1) {
+                            load_w(d - 1, j, refill(g - 1 + 2 * D));
+                            load_w(d, j, refill(g + 2 * D));
+                        }
                     }
                     if (d % 2 == 1) slot = slot + 1 == NS ? 0 : slot + 1;
                 }
@@ -525,7 +551,8 @@ int num_cus()
 //             at about 26 GB/s while most loads miss to HBM; workgroups beyond one per CU run in rounds;
 //   HBM side: W once plus the int32 partials when K is split, at about 5.5 TB/s;
 //   a K split adds the reduction kernel (launch + reading the partials).
-bool make_stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, StreamArgs* out)
+// gk_most: K splits at most; direct: weights straight into registers (more than 32 tokens)
+bool make_stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool direct, int gk_most, StreamArgs* out)
 {
     if (batch != 1 || M < 1 || M > 128 || (K & 63) || K < 64) return false;
     const int64_t units = (N + 15) / 16;
@@ -535,12 +562,12 @@ bool make_stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled
     const int nk = (int)(K >> 6);
     // Tiled operands with more than 32 tokens go to the kernel with loader waves: a CU moves a little more per second
     // there (fitted to the OPT-175B layers at 64 and 128 tokens), and a wave accumulates up to 4 of at most 12 units.
-    const bool regs = tiled && na >= 4;
+    const bool regs = direct && na >= 4;
     const double cu_rate = regs ? 32e9 : 26e9, hbm_rate = regs ? 6.0e12 : 5.5e12, red_rate = 4e12, red_launch = 5e-6;
     const int s_max = regs ? kRegsMaxUnits : (na == 8 ? 24 : 16);  // widest slab the kernel shapes accumulate
     double best = 1e30, best_cu = 1e30;
     int best_gn = 0, best_gk = 0;
-    for (int gk = 1; gk <= 8; ++gk) {
+    for (int gk = 1; gk <= gk_most; ++gk) {
         if (nk % gk) continue;
         if (gk > 1 && (nk / gk < 8 || M <= 32)) continue;
         for (int s = 1; s <= s_max; ++s) {
@@ -575,7 +602,7 @@ bool make_stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled
     if (regs) {
         // a compute wave starts with its first 8 K steps of weight blocks (every other one of 16); shorter ranges go
         // to the LDS-ring kernel
-        if (nks < 16) return make_stream_plan(M, N, K, batch, false, out);
+        if (nks < 16) return make_stream_plan(M, N, K, batch, false, gk_most, out);
     }
     if (!regs)
         for (int c = 4; c > 1; c >>= 1)
@@ -611,8 +638,21 @@ static double calibrated_us(const StreamArgs& q, double M, double N, double K, b
 
 bool sq_stream_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, StreamArgs* out)
 {
-    if (!make_stream_plan(M, N, K, batch, tiled, out)) return false;
+    if (!make_stream_plan(M, N, K, batch, tiled, 8, out)) return false;
+    out->need = out->gk;
     out->us = calibrated_us(*out, (double)M, (double)N, (double)K, tiled);
+    return true;
+}
+
+// Row-major operands of 33 to 128 tokens by the kernel with the weights in registers, without a K split.  Fitted like the others to 110 shapes
+// (10 % rms).
+bool sq_stream_rows_plan(int64_t M, int64_t N, int64_t K, StreamArgs* out)
+{
+    // (barely more units than compute units: slabs of two leave half of them without one, and the ring's K split is as fast: 49 x 6080 -> 4208
+    // 16.7 / 16.0)
+    // Eight token blocks and long rows: the ring with a K split (116 x 10752 -> 9200 45.1 / 46.9, 128 x 12288 -> 36864 133 / 136).
+    if (M <= 32 || (N + 15) / 16 * 4 <= num_cus() * 5 || (M > 112 && K > 10240) || !make_stream_plan(M, N, K, 1, true, 1, out) || !out->regs) return false;
+    out->us = (M > 112 ? 1.05 : 1.0) * (4.2 + 0.292 * out->us + 0.107 * (double)N * (double)K * 1e-6 + 0.017 * out->iters + 1.76 * (double)M * (double)N * 1e-6);
     return true;
 }
 
@@ -624,7 +664,8 @@ void sq_stream_gemm_launch(const GemmArgs& a, StreamArgs q, bool to_i32, bool bf
     const dim3 grid((unsigned)(q.gn * q.gk)), block(256), block8(512);
     if (q.regs) {
         const int cnt = (q.units + q.gn - 1) / q.gn;  // widest slab
-#define SQ_R(MB, C) case C: sq_launch((gemm_i8_stream_regs_kernel<MB, C, true>), grid, block8, 0, st, a, q); break;
+#define SQ_R(MB, C) case C: if (tiled) sq_launch((gemm_i8_stream_regs_kernel<MB, C, false>), grid, block8, 0, st, a, q); \
+                            else sq_launch((gemm_i8_stream_regs_kernel<MB, C, true>), grid, block8, 0, st, a, q); break;
 #define SQ_R12(MB) SQ_R(MB, 1) SQ_R(MB, 2) SQ_R(MB, 3) SQ_R(MB, 4) SQ_R(MB, 5) SQ_R(MB, 6) SQ_R(MB, 7) SQ_R(MB, 8) \
                    SQ_R(MB, 9) SQ_R(MB, 10) SQ_R(MB, 11) SQ_R(MB, 12)
         static_assert(kRegsMaxUnits == 12, "launch table");

@@ -25,3 +25,28 @@ def test_units_and_blocks(t, c_i, c_o):
     for dtype in (torch.float16, torch.bfloat16):
         y = sq.w8a8_linear(xq, xs, wq, ws, dtype, bias=bias, layout=sq.TILED)
         assert torch.equal(y.view(torch.int16), (acc.float() * (xs[:, None] * ws) + bias).to(dtype).view(torch.int16))
+
+
+@pytest.mark.parametrize("t,c_i,c_o", [(33, 3584, 10009), (48, 2624, 20012), (70, 4032, 24563), (81, 2048, 16392), (100, 4160, 27648), (112, 2432, 12289),
+                                       (113, 3008, 30011), (128, 4096, 12288), (120, 1728, 22264), (62, 1984, 14120), (36, 2240, 40984)])
+def test_row_major_units_and_blocks(t, c_i, c_o):
+    """The same kernel on row-major operands: rows of the last unit and the last token block that are not there, steps in pairs (odd
+    numbers of steps and of pairs), every output type."""
+    assert sq.probe_linear_plan(t, c_i, c_o, sq.ROW_MAJOR)[:3] == (1, 1, 1)
+    print(f"stream rows {t}x{c_i}->{c_o}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(t + c_i + c_o)
+    x, w = (torch.randint(-127, 128, s, generator=g, device="cuda", dtype=torch.int32).to(torch.int8) for s in ((t, c_i), (c_o, c_i)))
+    xs, ws = torch.rand(t, generator=g, device="cuda") * 0.01 + 0.001, torch.rand(c_o, generator=g, device="cuda") * 0.001 + 1e-4
+    bias = torch.randn(c_o, generator=g, device="cuda")
+    acc = (x.double() @ w.double().t()).to(torch.int32)
+    assert torch.equal(sq.i8_gemm_i32(x, w), acc)
+    for dtype in (torch.float16, torch.bfloat16):
+        res = torch.randn((t, c_o), generator=g, device="cuda").to(dtype)
+        v = ((acc.float() * (xs[:, None] * ws) + bias).clamp_min(0) + res.float()).to(dtype)
+        y = sq.w8a8_linear(x, xs, w, ws, dtype, bias=bias, relu=True, residual=res)
+        assert torch.equal(y.view(torch.int16), v.view(torch.int16))
+        if c_o % 8 == 0:
+            step = torch.full((1,), 0.037, device="cuda")
+            r = (torch.ones(1) / torch.full((1,), 0.037)).cuda()
+            q = sq.w8a8_linear_q8(x, xs, w, ws, step, dtype, bias=bias, relu=True, residual=res)
+            assert torch.equal(q, (v.float() * r).round().clamp(-127, 127).to(torch.int8))
