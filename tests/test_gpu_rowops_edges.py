@@ -1,11 +1,12 @@
 """Row kernels at the edges of their launch rules against fp64: LayerNorm + quantization (one row per wave up to 2048
-channels, then one to four strands per thread by row count and width) and the cross-lane reductions all of them share.
-Gates as in the parity tests: codes within one, at most one in a thousand; steps to 1e-5."""
+channels, then one to four strands per thread by row count and width, many rows per workgroup where there are many) and the
+cross-lane reductions all of them share.  Gates as in the parity tests: codes within one, at most one in a thousand; steps to 1e-5."""
 import numpy as np
 import pytest
 import torch
 
 from paper_2211_10438_amd import binding as sq
+from tests._util import tiled_to_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -96,3 +97,21 @@ def test_ln_quantize_is_one_fixed_fp32_sequence(t, c, dtype):
     a = np.abs(y).max(axis=1)
     assert y.dtype == np.float32 and np.array_equal(step.cpu().numpy(), a / np.float32(127))
     assert np.array_equal(q.cpu().numpy(), np.rint(y * (np.float32(127) / a)[:, None]).astype(np.int8))
+
+
+@pytest.mark.parametrize("t,c,tiled", [(1537, 8208, False), (1537, 12288, True), (2047, 9216, True), (2049, 8256, True), (3585, 4112, False),
+                                       (3585, 6144, True), (4607, 5120, False), (4609, 5184, True)])
+def test_ln_quantize_many_rows_per_workgroup(t, c, tiled):
+    """Rows that share a workgroup, and the workgroups that have one row more than others: each row's codes and step are those of
+    a call with a few rows, in an order of magnitude that changes from row to row."""
+    print(f"ln many rows {t}x{c} tiled={tiled}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(t + c)
+    x = torch.randn((t, c), generator=g, device="cuda", dtype=torch.float16) * (torch.arange(t, device="cuda") % 13 + 1)[:, None].half()
+    x[t - 1] = 0
+    gamma = torch.randn(c, generator=g, device="cuda")
+    beta = torch.randn(c, generator=g, device="cuda") * 0.1
+    q, step = sq.ln_quantize(x, gamma, beta, layout=sq.TILED if tiled else sq.ROW_MAJOR)
+    codes = tiled_to_rows(q)[:t, :c] if tiled else q.cpu().numpy()
+    for r in range(0, t, 1024):
+        few, few_step = sq.ln_quantize(x[r:r + 1024].contiguous(), gamma, beta)
+        assert torch.equal(step[r:r + 1024], few_step) and np.array_equal(codes[r:r + 1024], few.cpu().numpy())
