@@ -5,17 +5,9 @@
 // handled by a 256-thread workgroup (wide rows) or by one 64-lane wave (narrow rows, reduction
 // with cross-lane shuffles only).
 // Per-tensor static (O3): pure elementwise pass, saturating.
-// Per-tensor dynamic (O2): tensors of up to 512 x 16384 elements run as ONE ordinary launch and cross HBM once.
-// Workgroup b loads its 16384 elements into registers, stores its absmax to partial[b] (plain store: nothing to
-// clear), adds 1 to an arrival count and waits until the count reaches the grid size; then every workgroup reduces
-// the partial maxima and quantizes its registers.  The grid is at most 512 workgroups (a quarter of what the
-// device keeps resident; the occupancy query sizes it), so every workgroup gets a slot while the others wait; the
-// wait is bounded all the same (spin limit; on expiry scale[0] = NaN and nothing is quantized), so every wave
-// leaves the kernel whatever happens.  The arrival count carries a per-call ticket in its upper half, so a stale
-// workspace counts as zero.  Same-address atomics cost about 30 ns each on this part and serialize, which is why
-// larger tensors (more workgroups, and the second read served by the memory-side cache anyway) and streams under HIP
-// graph capture (a replay would reuse the ticket) take two launches (partial maxima, quantize), and callers with a small
-// workspace three (clear, absmax with atomic max on the float's bit pattern, quantize); results are identical.
+// Per-tensor dynamic (O2): tensors that one workgroup holds in its registers take one launch; larger ones two (partial maxima,
+// quantize; the second read is served by the memory-side cache), callers with a small workspace three (clear, absmax with
+// atomic max on the float's bit pattern, quantize); results are identical.
 #include "common.h"
 
 namespace {
@@ -308,15 +300,11 @@ __global__ __launch_bounds__(kAbsmaxThreads) void tensor_absmax_kernel(const uin
         int col[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            const int64_t g = base + i * NT;
-            raw[i] = v4u{0, 0, 0, 0};
-            col[i] = 0;
-            if (g < g1) {
-                const int64_t row = ro.row<WIDE>(g);
-                const int idx = (int)(g - row * ro.nvec);
-                raw[i] = ((const v4u*)(x + row * ldx))[idx];
-                col[i] = idx * 8;
-            }
+            const int64_t g = base + i * NT < g1 ? base + i * NT : g1 - 1;  // past the end: the last one again
+            const int64_t row = ro.row<WIDE>(g);
+            const int idx = (int)(g - row * ro.nvec);
+            raw[i] = ((const v4u*)(x + row * ldx))[idx];
+            col[i] = idx * 8;
         }
 #pragma unroll
         for (int i = 0; i < U; ++i) {
@@ -384,74 +372,46 @@ __global__ __launch_bounds__(256) void quant_per_tensor_kernel(const uint16_t* _
     }
 }
 
-constexpr int kO2MaxGrid = 512;  // workgroups of the single-launch kernel (= partial maxima in the workspace)
+constexpr int kO2Parts = 512;  // most partial maxima of a tensor
 
-// Workspace layout: bytes [0, 8) arrival cell {ticket : count}; bytes [256, 256 + 4 * kO2MaxGrid) partial maxima.
-// spin_limit bounds the wait (0.5 to 2 us per poll); it is not reached unless a workgroup of the grid never gets to
-// run, and if it is, scale[0] becomes NaN and nothing is quantized: every wave still leaves the kernel.
+// A tensor that one workgroup holds in its registers: one launch.  A launch and a load's way from memory and back are the time (16 x 768
+// 2.6 us, 16 x 2048 3.4; as two launches 4.6 and 4.5; eight vectors per thread spill, 16 x 4096 11.9 against 4.6).  A grid that
+// meets at an arrival count between maximum and rounding is not worth its wait at any size: 3 us and more for atomics, polls and
+// the maxima's way through memory on top of one pass, where a second launch costs 2.5 (16 x 768 6.7 us, now 2.6; 64 x 4096 10.5,
+// now 5.2; 333 x 5120 16.5, now 6.5).
 template <bool BF16, int NV>
-__global__ __launch_bounds__(256) void quant_per_tensor_single_kernel(const uint16_t* __restrict__ x, int64_t ldx, int c_i, RowOf ro, int total,
-                                                                     const float* __restrict__ inv_s, float* scale,
-                                                                     unsigned char* ws, uint32_t ticket, uint32_t spin_limit,
-                                                                     int8_t* __restrict__ xq, bool tiled)
+__global__ __launch_bounds__(1024) void quant_per_tensor_small_kernel(const uint16_t* __restrict__ x, int64_t ldx, int c_i, RowOf ro, int total,
+                                                                     const float* __restrict__ inv_s, float* scale, int8_t* __restrict__ xq, bool tiled)
 {
-    __shared__ float red[4];
-    __shared__ uint32_t ok_flag;
-    unsigned long long* cell = (unsigned long long*)ws;
-    uint32_t* partial = (uint32_t*)(ws + 256);
-    const int g0 = blockIdx.x * (256 * NV) + threadIdx.x;
+    __shared__ float red[16];
     v4u raw[NV];
+    int row[NV], col[NV];
     float m = 0.0f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int g = g0 + i * 256;
-        raw[i] = v4u{0, 0, 0, 0};
-        if (g < total) {
-            const int64_t row = ro.row<false>(g);
-            const int idx = g - (int)row * (int)ro.nvec;
-            raw[i] = __builtin_nontemporal_load((const v4u*)(x + row * ldx) + idx);
-            float f[8];
-            unpack8<BF16>(raw[i], f);
-            if (inv_s) smooth8(f, inv_s, idx * 8);
-            m = __builtin_fmaxf(m, absmax8(f));
-        }
+        const int g = (int)threadIdx.x + i * 1024 < total ? (int)threadIdx.x + i * 1024 : total - 1;  // past the end: the last one again
+        row[i] = (int)ro.row<false>(g);
+        const int idx = g - row[i] * (int)ro.nvec;
+        raw[i] = __builtin_nontemporal_load((const v4u*)(x + row[i] * ldx) + idx);
+        col[i] = idx * 8;
     }
-    m = block_max_256(m, red);
-    if (threadIdx.x == 0) {
-        __hip_atomic_store(partial + blockIdx.x, __builtin_bit_cast(uint32_t, m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ticket_open(cell, ticket);
-        // release: the partial maximum above is visible device-wide before the count moves
-        __hip_atomic_fetch_add(cell, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t spins = 0;
-        bool ok = true;
-        while ((uint32_t)__hip_atomic_load(cell, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x) {
-            if (++spins > spin_limit) { ok = false; break; }
-            if (spins < 16) __builtin_amdgcn_s_sleep(16); else __builtin_amdgcn_s_sleep(64);
-        }
-        ok_flag = ok ? 1u : 0u;
-    }
-    __syncthreads();
-    if (!ok_flag) {  // the wait gave up (see above)
-        if (threadIdx.x == 0) scale[0] = __builtin_nanf("");
-        return;
-    }
-    float a = 0.0f;
-    for (int i = threadIdx.x; i < (int)gridDim.x; i += 256)
-        a = __builtin_fmaxf(a, __builtin_bit_cast(float, __hip_atomic_load(partial + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
-    __syncthreads();  // `red` is reused
-    a = block_max_256(a, red);
-    const float r = a > 0.0f ? 127.0f / a : 0.0f;
-    if (blockIdx.x == 0 && threadIdx.x == 0) scale[0] = a / 127.0f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int g = g0 + i * 256;
-        if (g < total) {
-            const int64_t row = ro.row<false>(g);
-            const int idx = g - (int)row * (int)ro.nvec;
+        float f[8];
+        unpack8<BF16>(raw[i], f);
+        if (inv_s) smooth8(f, inv_s, col[i]);
+        m = __builtin_fmaxf(m, absmax8(f));
+    }
+    const float a = block_max<1024>(m, red);
+    const float r = a > 0.0f ? 127.0f / a : 0.0f;
+    if (threadIdx.x == 0) scale[0] = a / 127.0f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        if ((int)threadIdx.x + i * 1024 < total) {
             float f[8];
             unpack8<BF16>(raw[i], f);
-            if (inv_s) smooth8(f, inv_s, idx * 8);
-            __builtin_nontemporal_store(quant8(f, r), (v2u*)code_dst(xq, row, idx * 8, c_i, tiled));
+            if (inv_s) smooth8(f, inv_s, col[i]);
+            __builtin_nontemporal_store(quant8(f, r), (v2u*)code_dst(xq, row[i], col[i], c_i, tiled));
         }
     }
 }
@@ -567,9 +527,9 @@ int launch_absmax(const uint16_t* x, int64_t ldx, int c_i, int64_t total, const 
 {
     constexpr int64_t chunk = (int64_t)kAbsmaxThreads * kAbsmaxUnroll;
     int64_t grid = (total + chunk - 1) / chunk;
-    if (grid > kO2MaxGrid) grid = kO2MaxGrid;
+    if (grid > kO2Parts) grid = kO2Parts;
     int64_t per = (total + grid - 1) / grid;
-    per = (per + kAbsmaxThreads - 1) / kAbsmaxThreads * kAbsmaxThreads;
+    per = (per + 63) / 64 * 64;  // (whole kilobytes; in steps of the workgroup 1000 x 9216 13.5 us for both launches, now 12.9)
     grid = (total + per - 1) / per;
     const RowOf ro = row_of(c_i >> 3);
     if (total >= ((int64_t)1 << 31)) sq_launch((tensor_absmax_kernel<BF16, true, ATOMIC>), dim3((unsigned)grid), dim3(kAbsmaxThreads), 0, st, x, ldx, ro, total, per, inv_s, partial);
@@ -577,31 +537,24 @@ int launch_absmax(const uint16_t* x, int64_t ldx, int c_i, int64_t total, const 
     return (int)grid;
 }
 
-constexpr int kO2NV = 8;  // 16-byte vectors a thread holds: a workgroup covers 256 x 8 x 8 = 16384 elements
-
-// Largest grid of the single-launch kernel: a quarter of the workgroups the device keeps resident (occupancy x
-// compute units), at most kO2MaxGrid.
-template <bool BF16> int single_launch_grid()
+constexpr int64_t kSmallVecs = 4096;  // 16-byte vectors of a tensor for one workgroup: four per thread
+template <bool BF16>
+void launch_small(const uint16_t* x, int64_t ldx, int c_i, int64_t total, const float* inv_s, float* scale, int8_t* xq, bool tiled, hipStream_t st)
 {
-    static int limit = -1;
-    if (limit < 0) {
-        int dev = 0, cus = 0, per_cu = 0;
-        limit = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0 &&
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, quant_per_tensor_single_kernel<BF16, kO2NV>, 256, 0) == hipSuccess &&
-            per_cu > 0)
-            limit = cus * per_cu / 4 < kO2MaxGrid ? cus * per_cu / 4 : kO2MaxGrid;
-    }
-    return limit;
+    const RowOf ro = row_of(c_i >> 3);
+#define SQ_SMALL(NV) sq_launch((quant_per_tensor_small_kernel<BF16, NV>), dim3(1), dim3(1024), 0, st, x, ldx, c_i, ro, (int)total, inv_s, scale, xq, tiled)
+    if (total <= 1024) SQ_SMALL(1);
+    else if (total <= 2048) SQ_SMALL(2);
+    else SQ_SMALL(4);
+#undef SQ_SMALL
 }
 
 }  // namespace
 
 extern "C" {
 
-// Workspace of the per-tensor dynamic mode: arrival cell + partial maxima of the single-launch kernel.
-size_t sq_quantize_workspace_bytes(void) { return 256 + kO2MaxGrid * sizeof(uint32_t); }
+// Workspace of the per-tensor dynamic mode: the partial maxima, behind 256 bytes that are not used.
+size_t sq_quantize_workspace_bytes(void) { return 256 + kO2Parts * sizeof(uint32_t); }
 
 sq_status sq_quantize_act(const void* x, sq_dtype dtype, int64_t t, int64_t c_i, int64_t ldx, const float* inv_s,
                           sq_act_mode mode, float* scale, int8_t* xq, sq_layout xq_layout, void* workspace,
@@ -628,18 +581,10 @@ sq_status sq_quantize_act(const void* x, sq_dtype dtype, int64_t t, int64_t c_i,
     }
     const int64_t vecs = t * (c_i >> 3);
     if (mode == SQ_PER_TENSOR_DYNAMIC) {
-        const int64_t nwg = (vecs + 256 * kO2NV - 1) / (256 * kO2NV);  // workgroups that hold the whole tensor in registers
-        const int limit = bf ? single_launch_grid<true>() : single_launch_grid<false>();
         const bool full_ws = ws_bytes >= sq_quantize_workspace_bytes() && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
-        // A stream that is being captured into a HIP graph records the two-launch version: a replay would reuse
-        // the ticket.
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
-        if (hipStreamIsCapturing(st, &cap) != hipSuccess) cap = hipStreamCaptureStatusActive;
-        if (cap == hipStreamCaptureStatusNone && nwg <= limit && full_ws) {
-            const uint32_t ticket = sq_next_ticket(), spin_limit = 1u << 21;
-            const RowOf ro = row_of(c_i >> 3);
-            if (bf) sq_launch((quant_per_tensor_single_kernel<true, kO2NV>), dim3((unsigned)nwg), dim3(256), 0, st, xp, ldx, (int)c_i, ro, (int)vecs, inv_s, scale, (unsigned char*)workspace, ticket, spin_limit, xq, tiled);
-            else sq_launch((quant_per_tensor_single_kernel<false, kO2NV>), dim3((unsigned)nwg), dim3(256), 0, st, xp, ldx, (int)c_i, ro, (int)vecs, inv_s, scale, (unsigned char*)workspace, ticket, spin_limit, xq, tiled);
+        if (vecs <= kSmallVecs) {
+            if (bf) launch_small<true>(xp, ldx, (int)c_i, vecs, inv_s, scale, xq, tiled, st);
+            else launch_small<false>(xp, ldx, (int)c_i, vecs, inv_s, scale, xq, tiled, st);
             return sq_launch_status();
         }
         // Two launches: partial maxima, then every workgroup of the second kernel reduces them.  A caller with less than

@@ -115,3 +115,25 @@ def test_ln_quantize_many_rows_per_workgroup(t, c, tiled):
     for r in range(0, t, 1024):
         few, few_step = sq.ln_quantize(x[r:r + 1024].contiguous(), gamma, beta)
         assert torch.equal(step[r:r + 1024], few_step) and np.array_equal(codes[r:r + 1024], few.cpu().numpy())
+
+
+@pytest.mark.parametrize("t,c,ldx,tiled", [(1, 16, 16, False), (1, 8192, 8192, False), (1, 8208, 8224, False), (16, 1024, 1088, True), (17, 1024, 1024, True),
+                                           (4, 8192, 8192, False), (15, 2192, 2200, False), (256, 8192, 8192, True), (257, 8208, 8208, False)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("smooth", [False, True])
+def test_quantize_per_tensor_dynamic_edges(t, c, ldx, tiled, dtype, smooth):
+    """One workgroup for the tensor and the first sizes beyond it, full and ragged ranges of the maxima; the maximum in the very last element."""
+    print(f"per tensor {t}x{c} ldx={ldx} tiled={tiled} {dtype} smooth={smooth}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(t + c)
+    full = torch.randn((t, ldx), generator=g, device="cuda").to(dtype)
+    full[:, c:] = 99.0  # not part of the tensor
+    full[t - 1, c - 1] = -17.0
+    inv_s = torch.rand(c, generator=g, device="cuda") * 0.5 + 0.5 if smooth else None
+    q, step = sq.quantize_act(full[:, :c], sq.PER_TENSOR_DYNAMIC, inv_s=inv_s, layout=sq.TILED if tiled else sq.ROW_MAJOR)
+    v = full[:, :c].float().cpu().numpy()
+    if smooth:
+        v = v * inv_s.cpu().numpy()
+    a = np.abs(v).max()
+    assert step.item() == a / np.float32(127)
+    codes = tiled_to_rows(q)[:t, :c] if tiled else q.cpu().numpy()
+    assert np.array_equal(codes, np.rint(v * (np.float32(127) / a)).astype(np.int8))
