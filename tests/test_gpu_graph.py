@@ -24,8 +24,8 @@ def test_graph_replay_matches_eager(t, c_i, c_o, mode):
     _replay(t, c_i, c_o, mode, 64)
 
 
-# split-K tiles and their reduction, one column per thread and four (the last two; the others run the direct kernel); the per-tensor quantizer with its whole workspace (two
-# launches under capture, one outside), tensors that fit its one launch and that do not
+# split-K tiles and their reduction, one column per thread and four (the last two; the others run the direct kernel); the per-tensor quantizer with its whole
+# workspace (two launches)
 @pytest.mark.parametrize("t,c_i,c_o", [(130, 4096, 112), (140, 12288, 1024), (1000, 9216, 768), (114, 22720, 544), (152, 12736, 2208)])
 def test_graph_replay_split_reduction_and_per_tensor_quantizer(t, c_i, c_o):
     print(f"[case] graph replay split reduction t={t} c_i={c_i} c_o={c_o}", flush=True)
