@@ -507,7 +507,10 @@ void launch_per_token(const uint16_t* x, int64_t ldx, int c_i, int64_t t, const 
 
 // Vectors per thread of the elementwise pass, static mode measured on rotating buffers (rows / tiled codes): two from 2^21
 // vectors on (2048 x 12288: 14.6 / 16.1 us against 15.5 / 15.1 with one and 16.0 / 18.1 with four; 2048 x 49152: 49 / 53
-// against 56 / 55 and 54 / 58), one below (1000 x 9216: 7.0 / 7.3 us against 7.0 / 8.1 and 8.2 / 9.2).
+// against 56 / 55 and 54 / 58), one below (1000 x 9216: 7.0 / 7.3 us against 7.0 / 8.1 and 8.2 / 9.2).  With a dynamic step every
+// workgroup reduces the partial maxima first, and fewer of them pay from 2^19 vectors on (both passes, one / two / four: 512 x 5120
+// 7.1 / 7.2 / -, 512 x 9216 9.0 / 8.6 / 9.5, 512 x 12288 10.3 / 9.6 / 10.3, 1000 x 9216 12.8 / 12.4 / 13.3; each wave reducing them for itself, without
+// a barrier, takes longer at every size).
 template <bool BF16, bool DYNAMIC>
 void launch_per_tensor(const uint16_t* x, int64_t ldx, int c_i, int64_t total, const float* inv_s, float* scale, const uint32_t* partial,
                        int n_partial, int8_t* xq, bool tiled, hipStream_t st)
@@ -518,7 +521,7 @@ void launch_per_tensor(const uint16_t* x, int64_t ldx, int c_i, int64_t total, c
         return dim3((unsigned)(n < 65536 ? n : 65536));  // (the kernel strides over the rest)
     };
     if (total >= ((int64_t)1 << 31)) sq_launch((quant_per_tensor_kernel<BF16, DYNAMIC, true, 2>), grid(2), dim3(256), 0, st, x, ldx, c_i, ro, total, inv_s, scale, partial, n_partial, xq, tiled);
-    else if (total >= (1 << 21)) sq_launch((quant_per_tensor_kernel<BF16, DYNAMIC, false, 2>), grid(2), dim3(256), 0, st, x, ldx, c_i, ro, total, inv_s, scale, partial, n_partial, xq, tiled);
+    else if (total >= (DYNAMIC ? 1 << 19 : 1 << 21)) sq_launch((quant_per_tensor_kernel<BF16, DYNAMIC, false, 2>), grid(2), dim3(256), 0, st, x, ldx, c_i, ro, total, inv_s, scale, partial, n_partial, xq, tiled);
     else sq_launch((quant_per_tensor_kernel<BF16, DYNAMIC, false, 1>), grid(1), dim3(256), 0, st, x, ldx, c_i, ro, total, inv_s, scale, partial, n_partial, xq, tiled);
 }
 

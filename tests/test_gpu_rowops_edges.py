@@ -118,7 +118,8 @@ def test_ln_quantize_many_rows_per_workgroup(t, c, tiled):
 
 
 @pytest.mark.parametrize("t,c,ldx,tiled", [(1, 16, 16, False), (1, 8192, 8192, False), (1, 8208, 8224, False), (16, 1024, 1088, True), (17, 1024, 1024, True),
-                                           (4, 8192, 8192, False), (15, 2192, 2200, False), (256, 8192, 8192, True), (257, 8208, 8208, False)])
+                                           (4, 8192, 8192, False), (15, 2192, 2200, False), (256, 8192, 8192, True), (257, 8208, 8208, False), (512, 8192, 8192, True),
+                                           (513, 8208, 8216, False)])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("smooth", [False, True])
 def test_quantize_per_tensor_dynamic_edges(t, c, ldx, tiled, dtype, smooth):
