@@ -349,12 +349,20 @@ Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool all
     const double margin = K > 20480 && !tiled && M <= 128 ? 0.80 : p.tiles ? 0.90 : sp->regs ? 0.88 : 0.92;
     const bool chain = K > 12288 && dp.mb && ((M + 16 * dp.mb - 1) / (16 * dp.mb)) * ((N + 16 * dp.nb - 1) / (16 * dp.nb)) < 24;
     if (dp.mb && !chain && dp.us < margin * us) p.direct = dp;
-    // Row-major, 33 to 128 tokens: the weights-in-registers kernel where it is modelled clearly ahead of whatever was chosen.  Over 220 timings
-    // (110 shapes, weights in memory and in the last-level cache) the calls take 0.86 of the time; at 0.90 and without the constant 0.85, but 24
-    // of them lose more than 3 % and the worst a third (33 x 1664 -> 8672, where the direct kernel is ahead); so 9, the worst 13 % (86 x 1920 ->
-    // 10672 9.8 / 11.1 us).
+    // Row-major, 33 to 128 tokens: the weights-in-registers kernel where it is modelled clearly ahead of whatever was chosen.  Four groups of
+    // sizes where it is not ahead for all that (1300 shapes, weights in memory and in the last-level cache; geometric means and worst of
+    // this kernel's time over the other's):
+    //  - the direct kernel's tiles of 32 x 32 run these sizes as fast (1.01, 1.45: 82 x 1536 -> 8727 7.7 / 10.1 us);
+    //  - its other tiles of 32 channels are ahead while the weights fit the L2s of the eight XCDs together and are called for again (1.15,
+    //    1.34: 38 x 2944 -> 8935; from memory 0.95);
+    //  - with more than 112 tokens and short rows it is a little ahead (1.03, 1.06: 127 x 1216 -> 13678 15.7 / 16.7);
+    //  - the ring's K splits gain on long rows where the slabs are narrow (0.97, 1.10: 60 x 8192 -> 8240 25.3 / 27.7).
+    // Without them the calls take 0.75 of the time, from memory none 4 % more; cached weights of 33 to 113 MB and at most 48 tokens up to
+    // 12 % more (33 x 3584 -> 10009 11.6 / 13.1, from memory 16.4 / 15.8).
     StreamArgs rows{};
-    if (single && !tiled && sq_stream_rows_plan(M, N, K, &rows) && rows.us < 0.87 * (p.direct.mb ? dp.us : us) - 1.0) {
+    const bool narrow_direct = p.direct.nb == 2 && (p.direct.mb == 2 || N * K <= (int64_t)1 << 25);
+    const bool other_ahead = p.direct.mb ? narrow_direct || (M > 112 && K < 1728) : p.stream && sp->gk > 1 && K >= 8000 && (N + 15) / 16 <= 3 * kNumCU;
+    if (single && !tiled && !other_ahead && sq_stream_rows_plan(M, N, K, &rows) && rows.us < 0.87 * (p.direct.mb ? dp.us : us) - 1.0) {
         rows.need = p.need;
         *sp = rows;
         p.stream = true;

@@ -33,6 +33,22 @@ def test_the_faster_kernel_is_taken(t, c_i, c_o, layout, direct):
     assert bool(sq.lib().sq_probe_linear_form(t, c_i, c_o, layout)) == direct
 
 
+# us with the weights in the last-level cache / in memory: the kernel that runs, then the register-streaming one
+@pytest.mark.parametrize("t,c_i,c_o,kernel", [
+    (82, 1536, 8727, 0),      # 7.7 / 11.1, 10.1 / 12.3: direct tiles of 32 x 32
+    (115, 6016, 5768, 0),     # 16.3 / 22.8, 20.8 / 26.4
+    (99, 4864, 5872, 0),      # 12.4 / 17.8, 16.4 / 20.8
+    (38, 2944, 8935, 0),      # 1.34, 0.97 of the direct kernel's time: weights that fit the L2s together
+    (112, 2368, 6895, 0),     # from memory 14.4, 15.6: slabs of two units
+    (63, 10240, 5552, 1),     # from memory 25.0, 29.3
+    (127, 1216, 13678, 0),    # from memory 15.7, 16.7: more than 112 tokens, short rows
+    (60, 8192, 8240, 1),      # from memory 25.3, 27.7: K splits of the ring
+])
+def test_row_major_streaming_leaves_the_faster_kernel(t, c_i, c_o, kernel):
+    plan = sq.probe_linear_plan(t, c_i, c_o, R)
+    assert plan[0] == kernel and (kernel == 0 or plan[1] == 0)
+
+
 def test_the_sizes_that_reach_a_kernel_by_name():
     from tests.test_gpu_planned_paths import CASES
     for t, c_i, c_o, layout, *plan in CASES:
