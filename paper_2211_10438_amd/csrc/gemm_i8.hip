@@ -349,19 +349,22 @@ Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool all
     const double margin = K > 20480 && !tiled && M <= 128 ? 0.80 : p.tiles ? 0.90 : sp->regs ? 0.88 : 0.92;
     const bool chain = K > 12288 && dp.mb && ((M + 16 * dp.mb - 1) / (16 * dp.mb)) * ((N + 16 * dp.nb - 1) / (16 * dp.nb)) < 24;
     if (dp.mb && !chain && dp.us < margin * us) p.direct = dp;
-    // Row-major, 33 to 128 tokens: the weights-in-registers kernel where it is modelled clearly ahead of whatever was chosen.  Four groups of
-    // sizes where it is not ahead for all that (1300 shapes, weights in memory and in the last-level cache; geometric means and worst of
-    // this kernel's time over the other's):
-    //  - the direct kernel's tiles of 32 x 32 run these sizes as fast (1.01, 1.45: 82 x 1536 -> 8727 7.7 / 10.1 us);
-    //  - its other tiles of 32 channels are ahead while the weights fit the L2s of the eight XCDs together and are called for again (1.15,
-    //    1.34: 38 x 2944 -> 8935; from memory 0.95);
-    //  - with more than 112 tokens and short rows it is a little ahead (1.03, 1.06: 127 x 1216 -> 13678 15.7 / 16.7);
-    //  - the ring's K splits gain on long rows where the slabs are narrow (0.97, 1.10: 60 x 8192 -> 8240 25.3 / 27.7).
-    // Without them the calls take 0.75 of the time, from memory none 4 % more; cached weights of 33 to 113 MB and at most 48 tokens up to
-    // 12 % more (33 x 3584 -> 10009 11.6 / 13.1, from memory 16.4 / 15.8).
+    // Row-major, 33 to 128 tokens: the weights-in-registers kernel where it is modelled clearly ahead of whatever was chosen.  Groups of sizes
+    // where it is not ahead for all that, by 1160 shapes (this kernel's time over the other's, weights in the last-level cache / in memory, means):
+    //  - rows of whole 128-byte lines, which the direct kernel's small tiles take best: those of 32 x 32 1.23 / 1.06, the others while the
+    //    weights fit the L2s of the eight XCDs together 1.22 / 0.95 (82 x 1536 -> 8727 7.7 / 10.1 us cached, 34 x 2432 -> 8320 7.6 / 9.5);
+    //  - rows that are not and slabs of at most two units, against the direct kernel 0.97 / 1.02 (116 x 3776 -> 6519 19.2 / 21.2 from memory);
+    //  - rows of 8000 and more against the ring's K splits, with slabs of two units 0.90 / 1.06 (63 x 10240 -> 5552 25.0 / 29.3), of three where
+    //    whole lines and the four or eight token blocks the ring always has suit that 0.92 / 1.04 (60 x 8192 -> 8240 25.3 / 27.7).
+    // The others take 0.73 / 0.85 of the time (400 layers apart from these: one is more than 3 % behind from memory, at 4 %; cached five, the
+    // worst but the one above 11 %: 43 x 2752 -> 8448 8.5 / 9.5).
     StreamArgs rows{};
-    const bool narrow_direct = p.direct.nb == 2 && (p.direct.mb == 2 || N * K <= (int64_t)1 << 25);
-    const bool other_ahead = p.direct.mb ? narrow_direct || (M > 112 && K < 1728) : p.stream && sp->gk > 1 && K >= 8000 && (N + 15) / 16 <= 3 * kNumCU;
+    const int64_t units = (N + 15) / 16, blocks = (M + 15) / 16;
+    const bool lines = K % 128 == 0;
+    const bool direct_ahead = lines ? (p.direct.mb == 2 && p.direct.nb == 2) || ((p.direct.mb == 1 || p.direct.nb == 2) && N * K <= (int64_t)1 << 25)
+                                    : units <= 2 * kNumCU;
+    const bool ring_ahead = K >= 8000 && (units <= 2 * kNumCU || (units <= 3 * kNumCU && lines && blocks % 4 == 0));
+    const bool other_ahead = p.direct.mb ? direct_ahead : p.stream && ring_ahead;
     if (single && !tiled && !other_ahead && sq_stream_rows_plan(M, N, K, &rows) && rows.us < 0.87 * (p.direct.mb ? dp.us : us) - 1.0) {
         rows.need = p.need;
         *sp = rows;

@@ -648,10 +648,10 @@ bool sq_stream_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool ti
 // (10 % rms).
 bool sq_stream_rows_plan(int64_t M, int64_t N, int64_t K, StreamArgs* out)
 {
-    // (slabs of two units: three activation blocks and more for two of weights.  77 such shapes, from memory, against the direct kernel 0.95, against
-    // the ring 1.01, worst 1.17: 63 x 10240 -> 5552 25.0 / 29.3 us)
+    // (barely more units than compute units: slabs of two leave half of them without one, and the ring's K split is as fast: 49 x 6080 -> 4208
+    // 16.7 / 16.0)
     // Eight token blocks and long rows: the ring with a K split (116 x 10752 -> 9200 45.1 / 46.9, 128 x 12288 -> 36864 133 / 136).
-    if (M <= 32 || (N + 15) / 16 <= 2 * num_cus() || (M > 112 && K > 10240) || !make_stream_plan(M, N, K, 1, true, 1, out) || !out->regs) return false;
+    if (M <= 32 || (N + 15) / 16 * 4 <= num_cus() * 5 || (M > 112 && K > 10240) || !make_stream_plan(M, N, K, 1, true, 1, out) || !out->regs) return false;
     out->us = (M > 112 ? 1.05 : 1.0) * (4.2 + 0.292 * out->us + 0.107 * (double)N * (double)K * 1e-6 + 0.017 * out->iters + 1.76 * (double)M * (double)N * 1e-6);
     return true;
 }
