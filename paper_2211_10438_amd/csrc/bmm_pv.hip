@@ -9,7 +9,7 @@
 // v_mfma_i32_16x16x64_i8 as they are, sixteen columns at a time: no columns are computed that are not there.
 // us by graph replay, operands from memory; a 256 x 128 LDS-staged tile with the transposition in registers / this: 128 heads x 1024^2 x 80
 // 48.8 / 38.4, x 128 48.8 / 42.8, 256 x 1024^2 x 112 81.8 / 68.1, 199 x 448^2 x 96 26.9 / 15.0, 12 x 64^2 x 80 7.7 / 3.1, 768 x 2048^2 x 128
-// 793 / 771.  With one column block the first takes 29 us (4.8 TB/s): the rest is LDS reads and MFMAs that do not overlap with the stream.
+// 824 / 715.  With one column block the first takes 29 us (4.8 TB/s): the rest is LDS reads and MFMAs that do not overlap with the stream.
 // A fifth wave that only loads B, or 256 bytes of a row at a time: 41-42 us; the compiler's own transpose reads: see lds_read_tr.
 #include "gemm_args.h"
 
@@ -18,9 +18,10 @@ namespace {
 constexpr int PV_KC = 128;     // keys per stage
 constexpr int PV_STAGES = 3;
 
-// NB: 16-column blocks of a workgroup; MB: 16-row blocks of a wave (four of them).
+// NB: 16-column blocks of a workgroup; MB: 16-row blocks of a wave (four of them).  Workgroups per compute unit: three or four, with MB = 4 two (208 to 256
+// registers).
 template <bool BF16, int NB, int MB>
-__global__ __launch_bounds__(256, NB <= 6 ? 4 : 3) void pv_kernel(const GemmArgs p)
+__global__ __launch_bounds__(256, MB == 4 ? 2 : NB <= 6 ? 4 : 3) void pv_kernel(const GemmArgs p)
 {
     constexpr int N = NB * 16, VST = PV_KC * N, LPS = VST / 1024;
     constexpr int PITCH = N * 2 + 16, STG = 16 * MB * PITCH;
@@ -178,10 +179,48 @@ template <int NB> void launch(const GemmArgs& a, int mb, dim3 grid, bool bf16, h
     if (mb == 1) {
         if (bf16) sq_launch((pv_kernel<true, NB, 1>), grid, dim3(256), 0, st, a);
         else sq_launch((pv_kernel<false, NB, 1>), grid, dim3(256), 0, st, a);
+    } else if (mb == 4) {
+        if constexpr (NB >= 7) {
+            if (bf16) sq_launch((pv_kernel<true, NB, 4>), grid, dim3(256), 0, st, a);
+            else sq_launch((pv_kernel<false, NB, 4>), grid, dim3(256), 0, st, a);
+        }
     } else {
         if (bf16) sq_launch((pv_kernel<true, NB, 2>), grid, dim3(256), 0, st, a);
         else sq_launch((pv_kernel<false, NB, 2>), grid, dim3(256), 0, st, a);
     }
+}
+
+// Rows of a wave (16, 32 or 64; four waves a workgroup).  Workgroups of 128 rows where two of them per compute unit keep it busy, else of 64 (B is
+// fetched twice as often then); short rows end before the second one pays.  us, 64 / 128 rows: 32 x 448 x 448 x 80 (128 workgroups of 128)
+// 4.8 / 5.5, 96 x 448 x 448 x 112 9.3 / 9.9, 128 x 448 x 448 x 112 (512) 11.7 / 10.7, 128 x 1024 x 1024 x 96 41.9 / 38.3; 600 x 128 x 128 x 80
+// 6.6 / 7.1, 1200 of them 12.0 / 11.1.  Nor where blocks of 128 leave a quarter more rows empty (462 x 135 x 5264 x 32 95 / 140).
+// Seven or eight column blocks and longer rows: what a workgroup reads of B and of the LDS per product counts, and A and B of many columns are read
+// by several.  Then 128 rows already where those of 64 need a second round (three a compute unit: 15 x 3708 x 7904 x 128 149 / 122), with several
+// column tiles from more than one of 64 a compute unit on (7 x 709 x 2448 x 1536 39.8 / 32.8), though not where they are just over one of 128 (3 x 902
+// x 3680 x 1408 30.9 / 36.0) nor on shorter rows.  256 rows (two a compute unit) where they come to one round, to two, or to so many that the last does
+// not count (532 of them, 2 x 4798 x 3376 x 1792, 128 / 256 rows: 89.5 / 100): 64 / 128 / 256 rows 8192 x 8192 x 8192 1265 / 766 / 605, 512 x 4096 x 16384
+// 94 / 62 / 49, 768 x 2048 x 2048 x 128 932 / 796 / 714, 32 x 8192 x 8192 x 128 579 / 474 / 424.  Over 680 shapes within 3 % of the best of the three, and
+// 0.57 of a 256 x 128 tile with both operands in LDS (679, 51, 806, 458 us on those four); 14 shapes lose more than 2 % to that tile, all of rows of 2600
+// and more in one or two rounds, the worst 15 % (6 x 3796 x 2944 x 240 40.7 / 46.7).
+int rows_per_wave(int64_t batch, int64_t m, int64_t k, int nb, int64_t tiles_n)
+{
+    auto padded = [&](int64_t r) { return (m + r - 1) / r * r; };
+    auto groups = [&](int64_t r) { return batch * (padded(r) / r) * tiles_n; };
+    const int64_t g64 = groups(64), g128 = groups(128), g256 = groups(256);
+    const bool several = tiles_n > 1;
+    if (nb >= 7 && k >= 512) {
+        const bool no_more = padded(256) == padded(128);
+        if (no_more && g256 >= 192 && g256 <= 256) return 64;
+        if (k >= 1024 && g256 >= (several ? 400 : 480) && g256 <= 512 && padded(256) * 8 <= padded(128) * 9) return 64;
+        if (k >= 1024 && no_more && g256 >= 768) return 64;
+    }
+    if (k >= 512 && g128 < 512 && padded(128) * 8 <= padded(64) * 9) {
+        if (nb >= 7 && g64 > 768) return 32;
+        if (nb >= 7 && several && g64 > 320 && (g128 <= 256 || (g128 > 288 && k >= 2048))) return 32;
+        if (nb < 7 && several && g128 > 384 && k >= 2048) return 32;
+    }
+    if (g128 < (k < 256 ? 1024 : 512)) return 16;
+    return padded(128) * 4 > padded(64) * 5 && (nb < 7 || (!several && k >= 1024)) ? 16 : 32;
 }
 
 }  // namespace
@@ -192,10 +231,7 @@ void sq_pv_bmm_launch(GemmArgs a, int batch, bool bf16, hipStream_t st)
     const int blocks = a.N / 16;
     a.tiles_n = (blocks + 7) / 8;
     const int nb = (blocks + a.tiles_n - 1) / a.tiles_n;
-    // Workgroups of 128 rows where two of them per compute unit keep it busy, else of 64 (B is fetched twice as often then); short rows end
-    // before the second one pays.  us, 64 / 128 rows: 32 x 448 x 448 x 80 (128 workgroups of 128) 4.8 / 5.5, 96 x 448 x 448 x 112 9.3 / 9.9,
-    // 128 x 448 x 448 x 112 (512) 11.7 / 10.7, 128 x 1024 x 1024 x 96 41.9 / 38.3; 600 x 128 x 128 x 80 6.6 / 7.1, 1200 of them 12.0 / 11.1.
-    const int mb = (int64_t)batch * ((a.M + 127) / 128) * a.tiles_n < (a.K < 256 ? 1024 : 512) ? 1 : 2;
+    const int mb = rows_per_wave(batch, a.M, a.K, nb, a.tiles_n) / 16;
     // A launch holds 2^32 threads: rows beyond that in further launches.
     const int64_t most = ((int64_t)1 << 23) / a.tiles_n * (64 * mb);
     const int64_t rows = a.M;

@@ -4,6 +4,7 @@ shapes cover ragged row blocks, contraction lengths that end in a partly filled 
 dimensions below, at and above one 128-column tile, and codes that reach the largest accumulators."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2211_10438_amd import binding as sq
@@ -69,3 +70,26 @@ def test_pv_column_blocks(n, b, m, k):
     alpha = float(np.float32(0.013 / 127.0))
     c = sq.w8a8_bmm(dev(a), dev(v), False, alpha, torch_dtype(F16))
     assert_identical_16(ulp_distance(bits_from_dev(c), oracle.w8a8_bmm(a, v, False, alpha, F16)))
+
+
+def _exact(a, v, alpha, dtype):
+    """The integer product in fp64 (exact), then the fixed fp32 epilogue, on the device."""
+    acc = torch.bmm(a.double(), v.double())
+    return (acc.float() * torch.tensor(alpha, dtype=torch.float32, device="cuda")).to(dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("b,m,n,k", [
+    *[(260, 250, 16 * nb, 272) for nb in range(1, 9)],  # 128 rows a workgroup: four live waves, the last one ragged; three stages, the last of 16 keys
+    *[(1030, 121, 16 * nb, 144) for nb in range(1, 9)],  # the same below 256 keys
+    (24, 2170, 128, 528), (9, 2040, 272, 2064), (3, 705, 1536, 656),  # ... fewer than two of them per compute unit; more columns than one holds
+    (800, 250, 128, 1040), (130, 1530, 112, 1104), (64, 2048, 128, 1024), (1, 2033, 3328, 784), (100, 510, 128, 512),  # 256 rows a workgroup
+    (300, 135, 32, 528), (450, 178, 112, 1040)])  # 64 rows: 128 would leave a quarter more empty
+def test_pv_rows_of_a_workgroup(b, m, n, k, dtype):
+    print(f"[case] pv rows b={b} m={m} n={n} k={k} {dtype}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(b + m + n + k)
+    a = torch.randint(0, 128, (b, m, k), generator=g, device="cuda", dtype=torch.int32).to(torch.int8)
+    v = torch.randint(-127, 128, (b, k, n), generator=g, device="cuda", dtype=torch.int32).to(torch.int8)
+    alpha = float(np.float32(0.013 / 127.0))
+    c = sq.w8a8_bmm(a, v, False, alpha, dtype)
+    assert torch.equal(c.view(torch.int16), _exact(a, v, alpha, dtype).view(torch.int16))
