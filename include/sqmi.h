@@ -118,7 +118,8 @@ sq_status sq_prepare_weight(const void* w, sq_dtype dtype, const float* s, int64
  * xq: device int8 [t, c_i] in layout `xq_layout`;  workspace: device, needed for
  *   SQ_PER_TENSOR_DYNAMIC only: tensors of up to 32768 elements run as one launch, larger ones with
  *   sq_workspace_bytes(SQ_OP_QUANTIZE_ACT, ...) bytes as two, with a smaller workspace (at least 4 bytes) as three, with
- *   identical results.  The workspace needs no initialisation; concurrent calls must not share it. */
+ *   identical results.  The workspace needs 4-byte alignment (SQ_ERR_ALIGN where it is used) and no initialisation; concurrent
+ *   calls must not share it. */
 sq_status sq_quantize_act(const void* x, sq_dtype dtype, int64_t t, int64_t c_i, int64_t ldx,
                           const float* inv_s, sq_act_mode mode, float* scale, int8_t* xq,
                           sq_layout xq_layout, void* workspace, size_t ws_bytes, void* stream);

@@ -568,8 +568,8 @@ void launch_small(const uint16_t* x, int64_t ldx, int c_i, int64_t total, const 
 
 extern "C" {
 
-// Workspace of the per-tensor dynamic mode: the partial maxima, behind 256 bytes that are not used.
-size_t sq_quantize_workspace_bytes(void) { return 256 + kO2Parts * sizeof(uint32_t); }
+// Workspace of the per-tensor dynamic mode: the partial maxima.
+size_t sq_quantize_workspace_bytes(void) { return kO2Parts * sizeof(uint32_t); }
 
 sq_status sq_quantize_act(const void* x, sq_dtype dtype, int64_t t, int64_t c_i, int64_t ldx, const float* inv_s,
                           sq_act_mode mode, float* scale, int8_t* xq, sq_layout xq_layout, void* workspace,
@@ -596,7 +596,6 @@ sq_status sq_quantize_act(const void* x, sq_dtype dtype, int64_t t, int64_t c_i,
     }
     const int64_t vecs = t * (c_i >> 3);
     if (mode == SQ_PER_TENSOR_DYNAMIC) {
-        const bool full_ws = ws_bytes >= sq_quantize_workspace_bytes() && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
         if (vecs <= kSmallVecs) {
             if (bf) launch_small<true>(xp, ldx, (int)c_i, vecs, inv_s, scale, xq, tiled, st);
             else launch_small<false>(xp, ldx, (int)c_i, vecs, inv_s, scale, xq, tiled, st);
@@ -604,10 +603,10 @@ sq_status sq_quantize_act(const void* x, sq_dtype dtype, int64_t t, int64_t c_i,
         }
         // Two launches: partial maxima, then every workgroup of the second kernel reduces them.  A caller with less than
         // the full workspace gets three (clear one cell, maxima by atomic, quantize); results are identical.
+        if (reinterpret_cast<uintptr_t>(workspace) & 3u) return SQ_ERR_ALIGN;  // (words and atomics on words)
         int n_partial = 1;
         uint32_t* amax = (uint32_t*)workspace;
-        if (full_ws) {
-            amax = (uint32_t*)((unsigned char*)workspace + 256);
+        if (ws_bytes >= sq_quantize_workspace_bytes()) {
             n_partial = bf ? launch_absmax<true, false>(xp, ldx, (int)c_i, vecs, inv_s, amax, st)
                            : launch_absmax<false, false>(xp, ldx, (int)c_i, vecs, inv_s, amax, st);
         } else {

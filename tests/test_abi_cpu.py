@@ -66,6 +66,8 @@ def test_argument_validation_happens_before_any_launch():
     assert L.sq_quantize_act(fake, 7, 4, 64, 64, NULL, 0, fake, fake, 0, NULL, 0, NULL) == 4   # dtype
     assert L.sq_quantize_act(fake, 0, 4, 64, 64, NULL, 9, fake, fake, 0, NULL, 0, NULL) == 4   # mode
     assert L.sq_quantize_act(fake, 0, 4, 64, 64, NULL, 1, fake, fake, 0, NULL, 0, NULL) == 5   # O2 needs workspace
+    for at in (0x1001, 0x1002):  # ... words of it, where it is used
+        assert L.sq_quantize_act(fake, 0, 64, 4096, 4096, NULL, 1, fake, fake, 0, ctypes.c_void_p(at), 4096, NULL) == 3
     # linear
     assert L.sq_w8a8_linear(NULL, fake, 1, fake, fake, 0, NULL, NULL, 0, fake, 0, 4, 64, 64, 0, NULL, 0, NULL) == 1
     assert L.sq_w8a8_linear(fake, fake, 1, fake, fake, 0, NULL, NULL, 0, fake, 0, 4, 0, 64, 0, NULL, 0, NULL) == 2

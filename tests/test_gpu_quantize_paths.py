@@ -138,3 +138,20 @@ def test_weight_row_maxima_edges(c_i, c_o, dtype):
     assert torch.equal(sq.weight_absmax_per_in_channel(w), w.float().abs().amax(1))
     _, step = sq.prepare_weight(w, s)
     assert torch.equal(step, _div((w.float() * s[:, None]).abs().max(), 127.0))
+
+
+@pytest.mark.parametrize("offset", [4, 8, 16])
+def test_workspace_of_the_stated_size_needs_word_alignment_only(offset):
+    """The stated bytes at any word boundary hold one maximum for each workgroup (two launches), and nothing beyond them is written."""
+    t, c = 129, 4096
+    print(f"per tensor workspace at offset {offset}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(offset)
+    x = torch.randn((t, c), generator=g, device="cuda", dtype=torch.float16)
+    need = sq.workspace_bytes(sq.OP_QUANTIZE_ACT, t, c, 0)
+    room = torch.full((offset + need + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    q, step = sq.quantize_act(x, sq.PER_TENSOR_DYNAMIC, workspace=room[offset:offset + need])
+    ref, ref_step = sq.quantize_act(x, sq.PER_TENSOR_DYNAMIC)
+    assert torch.equal(q, ref) and torch.equal(step, ref_step) and torch.equal(step, _div(x.abs().max(), 127.0))
+    words = (room != 0xA5).view(-1, 4).any(1)
+    assert words[offset // 4:][:need // 4].sum() > 8  # (three launches write one word)
+    assert not words[:offset // 4].any() and not words[(offset + need) // 4:].any()
