@@ -116,7 +116,7 @@ sq_status sq_prepare_weight(const void* w, sq_dtype dtype, const float* s, int64
  * scale: device fp32; written in the dynamic modes ([t] per token, [1] per tensor), read in
  *   SQ_PER_TENSOR_STATIC ([1], the calibrated Delta);
  * xq: device int8 [t, c_i] in layout `xq_layout`;  workspace: device, needed for
- *   SQ_PER_TENSOR_DYNAMIC only: tensors of up to 32768 elements run as one launch, larger ones with
+ *   SQ_PER_TENSOR_DYNAMIC only: tensors of up to 65536 elements (smoothed 32768) run as one launch, larger ones with
  *   sq_workspace_bytes(SQ_OP_QUANTIZE_ACT, ...) bytes as two, with a smaller workspace (at least 4 bytes) as three, with
  *   identical results.  The workspace needs 4-byte alignment (SQ_ERR_ALIGN where it is used) and no initialisation; concurrent
  *   calls must not share it. */

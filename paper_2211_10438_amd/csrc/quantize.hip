@@ -5,7 +5,7 @@
 // handled by a 256-thread workgroup (wide rows) or by one 64-lane wave (narrow rows, reduction
 // with cross-lane shuffles only).
 // Per-tensor static (O3): pure elementwise pass, saturating.
-// Per-tensor dynamic (O2): tensors that one workgroup holds in its registers take one launch; larger ones two (partial maxima,
+// Per-tensor dynamic (O2): tensors that one workgroup or a few can read whole take one launch; larger ones two (partial maxima,
 // quantize; the second read is served by the memory-side cache), callers with a small workspace three (clear, absmax with
 // atomic max on the float's bit pattern, quantize); results are identical.
 #include <type_traits>
@@ -387,10 +387,9 @@ __global__ __launch_bounds__(256) void quant_per_tensor_kernel(const uint16_t* _
 constexpr int kO2Parts = 512;  // most partial maxima of a tensor
 
 // A tensor that one workgroup holds in its registers: one launch.  A launch and a load's way from memory and back are the time (16 x 768
-// 2.6 us, 16 x 2048 3.4; as two launches 4.6 and 4.5; eight vectors per thread spill, 16 x 4096 11.9 against 4.6).  A grid that
-// meets at an arrival count between maximum and rounding is not worth its wait at any size: 3 us and more for atomics, polls and
-// the maxima's way through memory on top of one pass, where a second launch costs 2.5 (16 x 768 6.7 us, now 2.6; 64 x 4096 10.5,
-// now 5.2; 333 x 5120 16.5, now 6.5).
+// 2.6 us, as two launches 4.6).  A grid that meets at an arrival count between maximum and rounding is not worth its wait at any size: 3 us
+// and more for atomics, polls and the maxima's way through memory on top of one pass, where a second launch costs 2.5 (16 x 768 6.7 us,
+// now 2.6; 64 x 4096 10.5, now 5.2; 333 x 5120 16.5, now 6.5).
 template <bool BF16, int NV>
 __global__ __launch_bounds__(1024) void quant_per_tensor_small_kernel(const uint16_t* __restrict__ x, int64_t ldx, int c_i, RowOf ro, int total,
                                                                      const float* __restrict__ inv_s, float* scale, int8_t* __restrict__ xq, bool tiled)
@@ -425,6 +424,53 @@ __global__ __launch_bounds__(1024) void quant_per_tensor_small_kernel(const uint
             if (inv_s) smooth8(f, inv_s, col[i]);
             __builtin_nontemporal_store(quant8(f, r), (v2u*)code_dst(xq, row[i], col[i], c_i, tiled));
         }
+    }
+}
+
+// Somewhat larger tensors in one launch too: each of a few workgroups reads the whole tensor for its maximum (one pass through an L2 at some 40
+// GB/s per compute unit) and quantizes one vector per thread.  us, this / the one workgroup above with four vectors per thread / two
+// launches: 8 x 4096 3.1 / 3.6 / 4.3 (smoothed 3.7 / 4.6 / 4.9), 9 x 4096 3.4 / - / 4.3, 16 x 4096 4.0 / - / 4.3, 32 x 4096 6.2 / - / 4.4; smoothed, where
+// every workgroup reads the factors too, 12 x 4096 5.2 / - / 4.8.  And a launch less of the host's time: calls one after the other 16 x 4096
+// 5.9 / - / 8.7.
+template <bool BF16>
+__global__ __launch_bounds__(1024) void quant_per_tensor_shared_kernel(const uint16_t* __restrict__ x, int64_t ldx, int c_i, RowOf ro, int total,
+                                                                      const float* __restrict__ inv_s, float* scale, int8_t* __restrict__ xq, bool tiled)
+{
+    constexpr int U = 4;  // loads in flight per thread
+    __shared__ float red[16];
+    auto load = [&](int g, v4u& raw, int& row, int& col) {
+        const int at = g < total ? g : total - 1;  // past the end: the last one again
+        row = (int)ro.row<false>(at);
+        const int idx = at - row * (int)ro.nvec;
+        raw = *((const v4u*)(x + row * ldx) + idx);
+        col = idx * 8;
+    };
+    const int mine = (int)blockIdx.x * 1024 + (int)threadIdx.x;
+    v4u own;
+    int row, col;
+    load(mine, own, row, col);
+    float m = 0.0f;
+    for (int base = threadIdx.x; base < total; base += 1024 * U) {
+        v4u raw[U];
+        int c[U], any_row;
+#pragma unroll
+        for (int i = 0; i < U; ++i) load(base + i * 1024, raw[i], any_row, c[i]);
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            float f[8];
+            unpack8<BF16>(raw[i], f);
+            if (inv_s) smooth8(f, inv_s, c[i]);
+            m = __builtin_fmaxf(m, absmax8(f));
+        }
+    }
+    const float a = block_max<1024>(m, red);
+    const float r = a > 0.0f ? 127.0f / a : 0.0f;
+    if (mine == 0) scale[0] = a / 127.0f;
+    if (mine < total) {
+        float f[8];
+        unpack8<BF16>(own, f);
+        if (inv_s) smooth8(f, inv_s, col);
+        __builtin_nontemporal_store(quant8(f, r), (v2u*)code_dst(xq, row, col, c_i, tiled));
     }
 }
 
@@ -552,16 +598,16 @@ int launch_absmax(const uint16_t* x, int64_t ldx, int c_i, int64_t total, const 
     return (int)grid;
 }
 
-constexpr int64_t kSmallVecs = 4096;  // 16-byte vectors of a tensor for one workgroup: four per thread
+// Tensors of one launch, by their 16-byte vectors: up to 2048 one workgroup (two vectors per thread), then one workgroup for each 1024.
+constexpr int64_t kSmallVecs = 2048;
+int64_t one_launch_vecs(bool smoothed) { return smoothed ? 4096 : 8192; }
 template <bool BF16>
 void launch_small(const uint16_t* x, int64_t ldx, int c_i, int64_t total, const float* inv_s, float* scale, int8_t* xq, bool tiled, hipStream_t st)
 {
     const RowOf ro = row_of(c_i >> 3);
-#define SQ_SMALL(NV) sq_launch((quant_per_tensor_small_kernel<BF16, NV>), dim3(1), dim3(1024), 0, st, x, ldx, c_i, ro, (int)total, inv_s, scale, xq, tiled)
-    if (total <= 1024) SQ_SMALL(1);
-    else if (total <= 2048) SQ_SMALL(2);
-    else SQ_SMALL(4);
-#undef SQ_SMALL
+    if (total > kSmallVecs) sq_launch((quant_per_tensor_shared_kernel<BF16>), dim3((unsigned)((total + 1023) / 1024)), dim3(1024), 0, st, x, ldx, c_i, ro, (int)total, inv_s, scale, xq, tiled);
+    else if (total > 1024) sq_launch((quant_per_tensor_small_kernel<BF16, 2>), dim3(1), dim3(1024), 0, st, x, ldx, c_i, ro, (int)total, inv_s, scale, xq, tiled);
+    else sq_launch((quant_per_tensor_small_kernel<BF16, 1>), dim3(1), dim3(1024), 0, st, x, ldx, c_i, ro, (int)total, inv_s, scale, xq, tiled);
 }
 
 }  // namespace
@@ -596,7 +642,7 @@ sq_status sq_quantize_act(const void* x, sq_dtype dtype, int64_t t, int64_t c_i,
     }
     const int64_t vecs = t * (c_i >> 3);
     if (mode == SQ_PER_TENSOR_DYNAMIC) {
-        if (vecs <= kSmallVecs) {
+        if (vecs <= one_launch_vecs(inv_s != nullptr)) {
             if (bf) launch_small<true>(xp, ldx, (int)c_i, vecs, inv_s, scale, xq, tiled, st);
             else launch_small<false>(xp, ldx, (int)c_i, vecs, inv_s, scale, xq, tiled, st);
             return sq_launch_status();

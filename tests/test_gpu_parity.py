@@ -60,10 +60,11 @@ def test_quantize_per_tensor(mode, t, c_i, dtype):
         assert np.abs(q_ref).max() == 127 and (np.abs(q_ref) == 127).sum() > 1
 
 
-@pytest.mark.parametrize("t,c_i,ldx", [(7, 64, 64), (1000, 4096, 4096), (2500, 9216, 9216), (3000, 4096, 12288)])
+@pytest.mark.parametrize("t,c_i,ldx", [(7, 64, 64), (2, 8192, 8192), (5, 4096, 4160), (16, 4096, 4096), (1000, 4096, 4096), (2500, 9216, 9216), (3000, 4096, 12288)])
 def test_quantize_per_tensor_dynamic_single_launch(t, c_i, ldx):
-    """Table 2's O2 (one dynamic step for the whole tensor): a tensor that fits the registers of one workgroup runs as
-    one launch (first case), larger ones as two; a column slice of a wider matrix is among them.  Checked against the
+    """Table 2's O2 (one dynamic step for the whole tensor): a tensor that fits the registers of one workgroup (first two
+    cases) or that a few can read whole (the next two) runs as one launch, larger ones as two; column slices of wider
+    matrices are among them.  Checked against the
     oracle, and against the library's three-launch version, which a caller selects by passing a workspace too small for
     the partial maxima."""
     _progress(f"O2 single launch t={t} c_i={c_i} ldx={ldx}")

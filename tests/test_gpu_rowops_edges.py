@@ -119,11 +119,13 @@ def test_ln_quantize_many_rows_per_workgroup(t, c, tiled):
 
 @pytest.mark.parametrize("t,c,ldx,tiled", [(1, 16, 16, False), (1, 8192, 8192, False), (1, 8208, 8224, False), (16, 1024, 1088, True), (17, 1024, 1024, True),
                                            (4, 8192, 8192, False), (15, 2192, 2200, False), (256, 8192, 8192, True), (257, 8208, 8208, False), (512, 8192, 8192, True),
-                                           (513, 8208, 8216, False)])
+                                           (513, 8208, 8216, False), (2, 8192, 8192, True), (2, 8208, 8208, False), (4, 8208, 8224, False),
+                                           (8, 8192, 8192, True), (8, 8208, 8208, False)])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("smooth", [False, True])
 def test_quantize_per_tensor_dynamic_edges(t, c, ldx, tiled, dtype, smooth):
-    """One workgroup for the tensor and the first sizes beyond it, full and ragged ranges of the maxima; the maximum in the very last element."""
+    """One workgroup for the tensor, one for each 1024 vectors of it, and the first sizes beyond either (smoothed tensors earlier), full and ragged ranges of the
+    maxima; the maximum in the very last element."""
     print(f"per tensor {t}x{c} ldx={ldx} tiled={tiled} {dtype} smooth={smooth}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(t + c)
     full = torch.randn((t, ldx), generator=g, device="cuda").to(dtype)
