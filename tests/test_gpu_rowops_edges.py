@@ -76,7 +76,7 @@ def _strand_sum(v, strands):
 @pytest.mark.parametrize("t,c", [(5, 1024), (5, 1040), (3, 2048), (5, 2064), (3, 4096), (3, 4112), (3, 5120), (3, 6144), (3, 6160),
                                  (2, 8192), (2, 8208), (3, 9216), (2, 12288), (2, 12304), (1, 16384), (2049, 2080), (3073, 2064),
                                  (2050, 4096), (3080, 4096), (1601, 5120), (2049, 5136), (3073, 4112), (1401, 6160), (2049, 6160),
-                                 (3073, 8192), (1025, 9216), (1537, 8208), (769, 12304)])
+                                 (3073, 8192), (1025, 9216), (1537, 8208), (769, 12304), (3585, 4112), (3600, 5120), (4609, 6144)])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 def test_ln_quantize_is_one_fixed_fp32_sequence(t, c, dtype):
     """Every sum, product and quotient rounds by itself and in one order, whatever the launch: steps and codes are identical
@@ -101,12 +101,13 @@ def test_ln_quantize_is_one_fixed_fp32_sequence(t, c, dtype):
 
 @pytest.mark.parametrize("t,c,tiled", [(1537, 8208, False), (1537, 12288, True), (2047, 9216, True), (2049, 8256, True), (3585, 4112, False),
                                        (3585, 6144, True), (4607, 5120, False), (4609, 5184, True)])
-def test_ln_quantize_many_rows_per_workgroup(t, c, tiled):
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_ln_quantize_many_rows_per_workgroup(t, c, tiled, dtype):
     """Rows that share a workgroup, and the workgroups that have one row more than others: each row's codes and step are those of
     a call with a few rows, in an order of magnitude that changes from row to row."""
-    print(f"ln many rows {t}x{c} tiled={tiled}", flush=True)
+    print(f"ln many rows {t}x{c} tiled={tiled} {dtype}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(t + c)
-    x = torch.randn((t, c), generator=g, device="cuda", dtype=torch.float16) * (torch.arange(t, device="cuda") % 13 + 1)[:, None].half()
+    x = torch.randn((t, c), generator=g, device="cuda").to(dtype) * (torch.arange(t, device="cuda") % 13 + 1)[:, None].to(dtype)
     x[t - 1] = 0
     gamma = torch.randn(c, generator=g, device="cuda")
     beta = torch.randn(c, generator=g, device="cuda") * 0.1

@@ -50,3 +50,17 @@ def test_row_major_units_and_blocks(t, c_i, c_o):
             r = (torch.ones(1) / torch.full((1,), 0.037)).cuda()
             q = sq.w8a8_linear_q8(x, xs, w, ws, step, dtype, bias=bias, relu=True, residual=res)
             assert torch.equal(q, (v.float() * r).round().clamp(-127, 127).to(torch.int8))
+
+
+@pytest.mark.parametrize("m,k,n", [(48, 2624, 20012), (112, 2432, 12289), (100, 4160, 27648), (36, 2240, 40984)])
+def test_one_batch_product_with_alpha_alone(m, k, n):
+    """The same kernel as sq_w8a8_bmm of one batch entry reaches it: no scales, no bias, alpha in their place."""
+    assert sq.probe_linear_plan(m, k, n, sq.ROW_MAJOR)[:3] == (1, 1, 1)
+    print(f"stream rows, alpha alone {m}x{k}->{n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(m + k + n)
+    a, b = (torch.randint(-127, 128, s, generator=g, device="cuda", dtype=torch.int32).to(torch.int8) for s in ((1, m, k), (1, n, k)))
+    acc = (a[0].double() @ b[0].double().t()).float()
+    for dtype in (torch.float16, torch.bfloat16):
+        c = sq.w8a8_bmm(a, b, True, 3e-4, dtype)
+        v = (acc * torch.tensor(3e-4, dtype=torch.float32, device="cuda")).to(dtype)
+        assert torch.equal(c[0].view(torch.int16), v.view(torch.int16))
