@@ -120,7 +120,6 @@ SQ_DEVICE uint32_t dequant_pair(int acc0, int acc1, float c0, float c1, float bi
 struct StreamArgs {
     int gn;          // slabs (workgroups along C_o)
     int gk;          // K splits (workgroups along K); > 1: int32 partials go to acc_out[gk][M][N]
-    int need;        // K splits the workspace is sized for: gk or more
     int units;       // 16-column units of N
     int na;          // 16-row blocks of A
     int ksub;        // 64-byte K steps per stage

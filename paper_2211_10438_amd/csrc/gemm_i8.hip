@@ -103,7 +103,7 @@ TilePlan make_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool allow_sp
     TilePlan pl{};
     pl.bn = 256;
     if (M > 128 && K <= 128) {
-        // The same, with the whole K range fetched in one go and four workgroups per CU.
+        // One or two K steps: the whole range fetched in one go, four small workgroups per CU (see the next case).
         pl.cfg = 8;
         pl.bm = 128;
         pl.bn = 128;
@@ -186,8 +186,11 @@ TilePlan make_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool allow_sp
 
 // The tiles of layers with more than 128 tokens and more than 256 input channels.  Microseconds of a K step and of a tile beside its
 // steps, row-major and tiled; times = rounds of tiles over the compute units x (steps x step + tile) + the constants below.  Fitted to 1130
-// measurements of 91 layers (129 to 4096 tokens, Gaussian codes; 8 % rms); over 1500 other layers the choice by it costs 1.3 % against the
-// best tile and split of each.  It orders tiles; absolute times are corrected in tile_us.  The tiles of pairs of steps (13 to 16) do no better per operation than the wide ones, but leave fewer compute units
+// measurements of 91 layers (129 to 4096 tokens, Gaussian codes) when the tiles of pairs of steps had eight waves and all epilogues waited for
+// their scales; of the kernels as they are, with weights from memory, the choice costs 2.7 % against the best tile and split of each of 379
+// layers that run a tile (121 more than 3 %, 26 more than 10 %, worst 1.31: 1168 x 13184 -> 968 row-major 40.5 us in six splits of 256 x 128, 31.0
+// in five of 192 x 160).  All constants fitted anew to 450 such layers came to 2.1 to 2.7 % on 150 others: it is the form of the model that
+// does not tell them apart.  It orders tiles; absolute times are corrected in tile_us.  The tiles of pairs of steps (13 to 16) do no better per operation than the wide ones, but leave fewer compute units
 // idle (us by graph replay, plan without / with these: 1000 x 9216 -> 9216 row-major 104 / 81, 153 x 3712 -> 30080 45.0 / 33.9, 512 x 20480 -> 5120
 // tiled 69 / 61, 2079 x 3328 -> 1352 37.9 / 27.9); the wide ones win from about three rounds on (2048 x 12288 -> 36864 649 / 786), where the
 // power cap sets the time: no tile is modelled above the rate measured there.
@@ -257,7 +260,7 @@ TilePlan choose_tile(int64_t M, int64_t N, int64_t K, bool tiled, const TilePlan
 // What a call stores: 16-bit or int8 values with scales (a linear layer), 16-bit values with alpha alone, int32 sums.
 enum class Epilogue { scales, alpha, sums };
 
-// Time of a tile plan against the direct kernel, fitted to 3500 shapes (16-bit output, weights in the last-level cache and in memory;
+// Time of a tile plan against the direct kernel, fitted to 3500 shapes before the tiles' epilogues stopped waiting for scales (16-bit output, weights in the last-level cache and in memory;
 // 4 to 11 % rms).  chosen_us: what choose_tile took the plan for; its model orders tiles of a layer, and leaves out a launch's constant
 // part and rows of the output that are not whole 16-byte pieces (odd: they leave element by element).  Without those two 463 x 640 -> 2501
 // row-major was taken for 9 us and took 19.
@@ -329,7 +332,7 @@ Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool all
     double us = 0.0;
     if (sq_stream_gemm_plan(M, N, K, batch, tiled, sp) && (sp->gk == 1 || allow_split)) {  // (else the tile kernels)
         p.stream = true;
-        p.need = sp->need;
+        p.need = sp->gk;
         us = sp->us;
     } else {
         p.tiles = true;
@@ -341,8 +344,10 @@ Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool all
     // Int32 sums and alpha alone: no scales and biases to wait for at the end of a tile (128 x 128: 8 -> 5 us of fixed time, 256 x 128 2.2 us
     // less; the direct kernel 3.7 -> 3.2).
     if (epi != Epilogue::scales && p.tiles && pl->splits == 1) us -= pl->bm == 32 ? 1.0 : pl->bm == 128 && K > 256 ? 4.5 : 2.2;
-    // The margins keep the models' errors from costing where the kernels are close.  Over 4500 shapes the direct kernel is then more than
-    // 3 % behind the other in 10 with the weights in the last-level cache and in 49 with them in memory; at 0.95 it would be 26 and 81.  How
+    // The margins keep the models' errors from costing where the kernels are close.  Over 4500 shapes the direct kernel was then more than
+    // 3 % behind the other in 10 with the weights in the last-level cache and in 49 with them in memory; at 0.95 it would have been 26 and 81.  (Before the
+    // tiles' epilogues stopped waiting for scales: of 221 layers of more than 128 tokens it takes now, 12 are more than 3 % behind the tile, the worst
+    // 2011 x 512 -> 1088 row-major, 11.3 us against 8.9; it takes 0.705 of their time.)  How
     // long rows of a row-major weight take hangs on more than the model knows (15 x 36336 -> 1360 modelled 25 us, took 38; the tiles 25): of
     // 413 such shapes 1 and 4 are behind, at 0.90 15 and 26.  Few workgroups with long chains are alike (58 x 31152 -> 62: 29 and 39 us, the
     // tiles 15 and 16).
@@ -366,7 +371,6 @@ Path choose(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, bool all
     const bool ring_ahead = K >= 8000 && (units <= 2 * kNumCU || (units <= 3 * kNumCU && lines && blocks % 4 == 0));
     const bool other_ahead = p.direct.mb ? direct_ahead : p.stream && ring_ahead;
     if (single && !tiled && !other_ahead && sq_stream_rows_plan(M, N, K, &rows) && rows.us < 0.87 * (p.direct.mb ? dp.us : us) - 1.0) {
-        rows.need = p.need;
         *sp = rows;
         p.stream = true;
         p.tiles = false;
@@ -441,7 +445,7 @@ size_t sq_gemm_workspace_bytes(int64_t t, int64_t c_i, int64_t c_o)
     if (few_channels(t, c_o, c_i, 1, false) && few_channels(t, c_o, c_i, 1, true)) return 0;
     // the layout is not known here: enough for the plan of either
     StreamArgs rows{}, tiles{};
-    const int ss_rows = sq_stream_gemm_plan(t, c_o, c_i, 1, false, &rows) ? rows.need : 0, ss_tiled = sq_stream_gemm_plan(t, c_o, c_i, 1, true, &tiles) ? tiles.need : 0;
+    const int ss_rows = sq_stream_gemm_plan(t, c_o, c_i, 1, false, &rows) ? rows.gk : 0, ss_tiled = sq_stream_gemm_plan(t, c_o, c_i, 1, true, &tiles) ? tiles.gk : 0;
     if (const int ss = ss_rows > ss_tiled ? ss_rows : ss_tiled) return ss > 1 ? (size_t)ss * t * c_o * sizeof(int32_t) : 0;
     TilePlan pl = make_plan(t, c_o, c_i, 1, true);
     return pl.splits > 1 ? (size_t)pl.splits * t * c_o * sizeof(int32_t) : 0;

@@ -560,8 +560,8 @@ bool make_stream_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool direc
     if (units < cus) return false;  // narrow C_o: the tile kernels with split-K cover it
     const int na = M <= 16 ? 1 : M <= 32 ? 2 : M <= 64 ? 4 : 8;
     const int nk = (int)(K >> 6);
-    // Tiled operands with more than 32 tokens go to the kernel with loader waves: a CU moves a little more per second
-    // there (fitted to the OPT-175B layers at 64 and 128 tokens), and a wave accumulates up to 4 of at most 12 units.
+    // `direct` plans of more than 32 tokens (tiled operands always, row-major ones where the caller asks) are for the kernel with loader waves: a CU
+    // moves a little more per second there (fitted to the OPT-175B layers at 64 and 128 tokens, tiled), and a wave accumulates up to 4 of at most 12 units.
     const bool regs = direct && na >= 4;
     const double cu_rate = regs ? 32e9 : 26e9, hbm_rate = regs ? 6.0e12 : 5.5e12, red_rate = 4e12, red_launch = 5e-6;
     const int s_max = regs ? kRegsMaxUnits : (na == 8 ? 24 : 16);  // widest slab the kernel shapes accumulate
@@ -639,7 +639,6 @@ static double calibrated_us(const StreamArgs& q, double M, double N, double K, b
 bool sq_stream_gemm_plan(int64_t M, int64_t N, int64_t K, int64_t batch, bool tiled, StreamArgs* out)
 {
     if (!make_stream_plan(M, N, K, batch, tiled, 8, out)) return false;
-    out->need = out->gk;
     out->us = calibrated_us(*out, (double)M, (double)N, (double)K, tiled);
     return true;
 }
