@@ -9,7 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libsqmi.so")
-SOURCES = ["api.hip", "quantize.hip", "weight_prep.hip", "rowops.hip", "gemm_i8.hip", "gemm_i8_tile_rows.hip", "gemm_i8_tile_tiled.hip", "gemm_i8_stream.hip", "gemm_i8_direct.hip", "gemm_i8_direct_rows.hip", "gemm_i8_direct_tiled.hip", "bmm_strip.hip", "bmm_pv.hip", "attn_fused.hip", "attn_few.hip", "probe.hip"]
+TILE_SOURCES = ["gemm_i8_tile_rows.hip", "gemm_i8_tile_tiled.hip", "gemm_i8_tile_rows_codes.hip", "gemm_i8_tile_tiled_codes.hip"]
+SOURCES = ["api.hip", "quantize.hip", "weight_prep.hip", "rowops.hip", "gemm_i8.hip", *TILE_SOURCES, "gemm_i8_stream.hip", "gemm_i8_direct.hip", "gemm_i8_direct_rows.hip", "gemm_i8_direct_tiled.hip", "bmm_strip.hip", "bmm_pv.hip", "attn_fused.hip", "attn_few.hip", "probe.hip"]
 
 # -ffp-contract=off: scale arithmetic must round every product and sum separately (bit-exact codes).
 # packed-fp32 ops are disabled for the whole library.
@@ -19,7 +20,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
 # Tiles with one wave per SIMD: MFMAs on plain vector registers, accumulation registers only for what does not fit (gemm_tile.h).  The other tiles of
 # these files run with the option as without it (times with / without it, means over ten to twenty calls of each: tiles of 32, 64 and 128 rows
 # 0.99, 0.98 and 0.97, of 256 x 192 1.00, x 256 1.00 and 1.01, x 384 1.00 and 1.01, of 128 x 128 1.00).
-FLAGS_OF = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form=true"] for src in ("gemm_i8_tile_rows.hip", "gemm_i8_tile_tiled.hip")}
+FLAGS_OF = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form=true"] for src in TILE_SOURCES}
 
 
 def build_host_calls() -> str:

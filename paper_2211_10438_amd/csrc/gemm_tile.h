@@ -29,7 +29,9 @@
 
 namespace {
 
-enum { EPI_DEQUANT = 0, EPI_I32 = 1 };
+// What a tile stores.  Int8 codes have kernels of their own: as one more branch of the 16-bit kernels their store costs those 0.2 to 0.5 us a
+// launch (scalar registers, kernel arguments loaded late), e.g. 300 x 4096 -> 16384 tiled 28.4 / 28.9.
+enum { EPI_DEQUANT = 0, EPI_I32 = 1, EPI_CODES = 2 };
 
 // BM x BN output tile per workgroup, WGM x WGN waves, BK = 64 bytes of K per pipeline stage.
 // B is [N, K] (K-contiguous rows, like A).
@@ -79,7 +81,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     constexpr int EG = BM * (BN * 2 + 16) <= 160 * 1024 ? 1 : 2;
     constexpr int GR = BM / EG;
     constexpr int EPI_VEC = GR * (BN * 2 + 16);  // behind it the scales and biases of the tile's columns and the scales of its rows
-    constexpr int EPI_BYTES = EPI == EPI_DEQUANT ? EPI_VEC + (2 * BN + BM) * 4 : 0;
+    constexpr int EPI_BYTES = EPI != EPI_I32 ? EPI_VEC + (2 * BN + BM) * 4 : 0;
     static_assert(BN <= NW * 64 && BM <= NW * 64, "a thread fetches one column's and one row's");
     constexpr int RING_BYTES = (ONESHOT ? NSTAGE - 1 : NSTAGE) * STAGE;
     constexpr int SMEM_BYTES = RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES;
@@ -200,11 +202,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     // tile of the residual, 16 bytes of a row at a time.  PRE: on their way during the K loop (the tiles of pairs of steps have the registers);
     // fetched behind it they cost 3 us a launch.  1000 x 256 -> 9216, us, before / now: 12.2 / 9.6, with a residual and a step per channel
     // 18.3 / 11.5; 1000 x 9216 -> 9216 with both 90.6 / 86.5 (the power cap takes the rest back).
-    constexpr bool PRE = EPI == EPI_DEQUANT && PAIR;
+    constexpr bool PRE = EPI != EPI_I32 && PAIR;
     constexpr int CPR = BN / 8;                             // 16-byte pieces per tile row
     constexpr int RCH = (GR * CPR + NW * 64 - 1) / (NW * 64);  // of them per thread
     const uint16_t* R = (const uint16_t*)p.residual;
-    const bool vec_ok = (p.N & 7) == 0;  // 16-byte chunks never straddle the row end and stay aligned
+    const bool vec_ok = EPI == EPI_CODES || (p.N & 7) == 0;  // 16-byte chunks never straddle the row end and stay aligned
     float col_scale = 0.0f, col_bias = 0.0f, row_scale = 0.0f;
     constexpr bool FULL = MI * NI * AV >= 192;              // the sums leave few registers: one piece more in flight and they spill
     constexpr int RG = PRE || RCH <= 4 ? RCH : FULL ? 2 : 4;  // ... in flight at a time
@@ -568,7 +570,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
                 acc[i][j] = __builtin_bit_cast(acc_t, __builtin_convertvector(acc[i][j], accf_t));
             }
         float rq = 0.0f;
-        if (p.q8_step) {
+        if constexpr (EPI == EPI_CODES) {
             const float delta = p.q8_step[0];
             rq = delta > 0.0f ? 1.0f / delta : 0.0f;
         }
@@ -677,10 +679,63 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
         if (p.w_per_channel) with(T_{});
         else with(F_{});
         __syncthreads();
-        // int8 codes in the tiled layout leave in another order: a wave instruction covers 8 rows x 64 columns, which are
-        // 512 contiguous bytes of a 1 KB block (walking along a row it would write 64-byte pieces of eight blocks)
-        const bool q8_blocks = p.q8_step && p.q8_tiled && (BN % 64 == 0);
-        if (!p.q8_step && vec_ok) {
+        if constexpr (EPI == EPI_CODES) {
+            // int8 output (N % 8 == 0): a thread quantizes W neighbouring 16-bit values, 16 (one chunk of the tiled layout, 16 bytes of a row) or,
+            // where rows are not whole 16-byte pieces, 8.  Tiled codes leave in the order of the 1 KB blocks, 32 columns of 16 rows after the
+            // other where the tile is not whole blocks wide.  What counts is LDS latency: eight codes a trip, with an index division, a read
+            // and its wait each, took 300 x 4096 -> 16384 tiled 36.2 us (now 33.6; 16-bit values 32.0), 512 x 2048 -> 8192 20.1 (18.0; 17.5).
+            auto store_codes = [&](auto W_, bool tiled_codes) {
+                constexpr int W = decltype(W_)::value, CQ = BN / W, ALL = GR * CQ, QCH = (ALL + NW * 64 - 1) / (NW * 64);
+                constexpr int SG = FULL ? 1 : QCH < 4 ? QCH : QCH % 5 == 0 ? 5 : QCH % 4 == 0 ? 4 : QCH % 3 == 0 ? 3 : 4;  // pieces a thread has in flight out of LDS
+                auto place = [&](int q, int& r, int& c) {
+                    if (W == 16 && tiled_codes) {
+                        constexpr int CB = BN % 64 == 0 ? 4 : 2;  // chunks of a row that go out together
+                        static_assert(BN % 32 == 0 && GR % 16 == 0, "whole groups of chunks");
+                        const int strip = q / (16 * CQ), in = q - strip * (16 * CQ);
+                        r = strip * 16 + in / CB % 16;
+                        c = (in / (16 * CB) * CB + in % CB) * W;
+                    } else {
+                        r = q / CQ;
+                        c = (q - r * CQ) * W;
+                    }
+                };
+#pragma unroll 1
+                for (int k0 = 0; k0 < QCH; k0 += SG) {
+                    v4u val[SG][W / 8];
+#pragma unroll
+                    for (int k = 0; k < SG; ++k) {
+                        const int q = (int)threadIdx.x + (k0 + k) * NW * 64;
+                        int r, c;
+                        place(q, r, c);
+                        if (ALL % (SG * NW * 64) == 0 || q < ALL) {
+#pragma unroll
+                            for (int h = 0; h < W / 8; ++h) val[k][h] = *(const v4u*)(smem + r * PITCH + c * 2 + h * 16);
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < SG; ++k) {
+                        const int q = (int)threadIdx.x + (k0 + k) * NW * 64;
+                        int r, c;
+                        place(q, r, c);
+                        const int row = m0 + g0 + r, col = n0 + c;
+                        if ((ALL % (SG * NW * 64) == 0 || q < ALL) && row < p.M && col < p.N) {
+                            uint32_t w[W / 4];  // (clamp + add of 1.5 * 2^23: the code in the low byte, the same integer as requant_code's rint + clamp)
+#pragma unroll
+                            for (int t = 0; t < W / 4; ++t) {
+                                const uint32_t lo = val[k][t >> 1][(t & 1) * 2], hi = val[k][t >> 1][(t & 1) * 2 + 1];
+                                w[t] = pack4_low_bytes(code_bits(load16_bits<BF16>(lo) * rq), code_bits(load16_bits<BF16>(lo >> 16) * rq),
+                                                       code_bits(load16_bits<BF16>(hi) * rq), code_bits(load16_bits<BF16>(hi >> 16) * rq));
+                            }
+                            int8_t* dst = code_dst(p.q8_out, row, col, p.N, W == 16 && tiled_codes);
+                            if constexpr (W == 16) *(v4u*)dst = v4u{w[0], w[1], w[2], w[3]};
+                            else *(v2u*)dst = v2u{w[0], w[1]};
+                        }
+                    }
+                }
+            };
+            if ((p.N & 15) == 0) store_codes(std::integral_constant<int, 16>{}, p.q8_tiled != 0);
+            else store_codes(std::integral_constant<int, 8>{}, false);
+        } else if (vec_ok) {
             constexpr int SG = FULL ? 2 : RCH % 5 == 0 ? 5 : RCH % 4 == 0 ? 4 : RCH % 3 == 0 ? 3 : 4;  // pieces a thread has in flight out of LDS
 #pragma unroll 1
             for (int k0 = 0; k0 < RCH; k0 += SG) {
@@ -697,34 +752,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
                         __builtin_nontemporal_store(val[k], (v4u*)(C + (int64_t)row * p.N + col));
                 }
             }
-        } else
-        for (int q = threadIdx.x; q < GR * CPR; q += NW * 64) {
-            int r = q / CPR, c8 = (q - r * CPR) * 8;
-            if (q8_blocks) {
-                const int blk = q >> 6, cb = blk % (BN / 64);
-                r = (blk / (BN / 64)) * 8 + ((q >> 3) & 7);
-                c8 = (cb * 8 + (q & 7)) * 8;
-            }
-            const int row = m0 + g0 + r, col = n0 + c8;
-            if (row < p.M && col < p.N) {
+        } else {
+            for (int q = threadIdx.x; q < GR * CPR; q += NW * 64) {
+                const int r = q / CPR, c8 = (q - r * CPR) * 8, row = m0 + g0 + r, col = n0 + c8;
+                if (row >= p.M || col >= p.N) continue;
                 const v4u val = *(const v4u*)(smem + r * PITCH + c8 * 2);
-                if (p.q8_step) {
-                    // int8 output: quantize the eight 16-bit values of this chunk (they never straddle a
-                    // 16-byte chunk of the tiled layout) and store 8 codes
-                    // (clamp + add of 1.5 * 2^23: the code in the low byte, the same integer as requant_code's rint + clamp)
-                    uint32_t cq[8];
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) cq[t] = code_bits(load16_bits<BF16>(val[t >> 1] >> ((t & 1) * 16)) * rq);
-                    int8_t* dq = code_dst(p.q8_out, row, col, p.N, p.q8_tiled != 0);
-                    if (vec_ok) {
-                        *(v2u*)dq = v2u{pack4_low_bytes(cq[0], cq[1], cq[2], cq[3]), pack4_low_bytes(cq[4], cq[5], cq[6], cq[7])};
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < 8; ++t)
-                            if (col + t < p.N) dq[t] = (int8_t)(cq[t] & 0xffu);
-                    }
-                    continue;
-                }
                 uint16_t* dst = C + (int64_t)row * p.N + col;
 #pragma unroll
                 for (int t = 0; t < 8; ++t)
@@ -777,6 +809,11 @@ template <bool TILED> void tile_launch(const TilePlan& pl, const GemmArgs& a, bo
     if (to_i32) launch_cfg<EPI_I32, false, TILED>(pl, a, batch, st);
     else if (bf16) launch_cfg<EPI_DEQUANT, true, TILED>(pl, a, batch, st);
     else launch_cfg<EPI_DEQUANT, false, TILED>(pl, a, batch, st);
+}
+template <bool TILED> void tile_launch_codes(const TilePlan& pl, const GemmArgs& a, bool bf16, hipStream_t st)
+{
+    if (bf16) launch_cfg<EPI_CODES, true, TILED>(pl, a, 1, st);
+    else launch_cfg<EPI_CODES, false, TILED>(pl, a, 1, st);
 }
 
 }  // namespace

@@ -3,11 +3,13 @@
 quantize_act in static mode -- the fused kernel must produce exactly those codes, on every GEMM path."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2211_10438_amd import binding as sq
 from paper_2211_10438_amd import synth
-from tests._util import (BF16, F16, dev, random_bf16_bits, rows_to_tiled_dev, tiled_to_rows, to_dev_16, torch_dtype)
+from tests._util import (BF16, F16, dev, random_bf16_bits, rows_to_tiled_dev, tiled_index, tiled_to_rows, to_dev_16, torch_dtype)
+from tests.test_gpu_narrow import _tile
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +72,39 @@ def test_linear_q8_zero_step_gives_zero_codes():
     yq = sq.w8a8_linear_q8(dev(xq), dev(np.full(40, 1e-4, np.float32)), dev(wq), dev(np.ones(1, np.float32)),  # finite values
                            dev(np.zeros(1, np.float32)), torch_dtype(F16))
     assert not yq.cpu().numpy().any()
+
+
+# Every tile, unsplit, with c_o of whole 64 (both output layouts), of 16 and of 8; both MFMA forms of the wide ones (c_i a multiple of 128 or not).
+TILE_FORMS = [
+    (175, 128, 12160, sq.ROW_MAJOR, 128128), (2091, 128, 1232, sq.TILED, 128128), (162, 64, 12488, sq.TILED, 128128),
+    (114, 464, 20672, sq.ROW_MAJOR, 128256), (119, 432, 19792, sq.ROW_MAJOR, 128256), (119, 496, 18920, sq.ROW_MAJOR, 128256),
+    (315, 320, 18112, sq.TILED, 192160), (281, 336, 16848, sq.ROW_MAJOR, 192160), (315, 320, 18152, sq.TILED, 192160),
+    (522, 320, 17408, sq.TILED, 192224), (566, 320, 17760, sq.ROW_MAJOR, 192224), (519, 384, 18584, sq.TILED, 192224),
+    (197, 320, 11328, sq.TILED, 256128), (137, 288, 17328, sq.ROW_MAJOR, 256128), (135, 304, 20376, sq.ROW_MAJOR, 256128),
+    (773, 464, 8704, sq.ROW_MAJOR, 256160), (824, 320, 17104, sq.TILED, 256160), (803, 448, 8520, sq.ROW_MAJOR, 256160),
+    (541, 384, 14272, sq.ROW_MAJOR, 256192), (391, 320, 18368, sq.TILED, 256192), (775, 384, 8208, sq.TILED, 256192), (389, 272, 17944, sq.ROW_MAJOR, 256192),
+    (643, 384, 16832, sq.TILED, 256256), (612, 272, 16640, sq.ROW_MAJOR, 256256), (592, 320, 16720, sq.TILED, 256256), (795, 384, 13176, sq.TILED, 256256),
+    (1373, 768, 14592, sq.TILED, 256384), (1406, 272, 13760, sq.ROW_MAJOR, 256384), (1166, 768, 16480, sq.TILED, 256384), (1125, 288, 17240, sq.ROW_MAJOR, 256384)]
+
+
+@pytest.mark.parametrize("t,c_i,c_o,layout,tile", TILE_FORMS)
+def test_linear_q8_of_every_tile(t, c_i, c_o, layout, tile):
+    """Codes of the fused call against those of the 16-bit call's values, by the static quantizer's formula: identical."""
+    assert sq.lib().sq_probe_linear_tile(t, c_i, c_o, layout) == 1000000 + tile
+    g = torch.Generator(device="cuda").manual_seed(t + c_o)
+    rows = [torch.randint(-127, 128, s, generator=g, device="cuda", dtype=torch.int32).to(torch.int8) for s in ((t, c_i), (c_o, c_i))]
+    xq, wq = [_tile(a) for a in rows] if layout == sq.TILED else rows
+    xs, ws, bias = (torch.rand(n, generator=g, device="cuda") * 0.01 + 0.001 for n in (t, c_o, c_o))
+    for dtype in (torch.float16, torch.bfloat16):
+        res = torch.randn(t, c_o, generator=g, device="cuda").to(dtype)
+        for kw in (dict(), dict(bias=bias, residual=res, relu=True)):
+            _progress(f"tile {tile} q8 {t}x{c_i}->{c_o} layout {layout} {dtype} {list(kw)}")
+            y = sq.w8a8_linear(xq, xs, wq, ws, dtype, layout=layout, **kw)
+            step = (0.8 * y.float().abs().amax() / 127).reshape(1)
+            want = (y.float() * (1.0 / step)).round().clamp(-127, 127).to(torch.int8)
+            assert want.abs().max() == 127
+            for out_layout in (sq.ROW_MAJOR, sq.TILED)[: 2 if c_o % 64 == 0 else 1]:
+                got = sq.w8a8_linear_q8(xq, xs, wq, ws, step, dtype, layout=layout, out_layout=out_layout, **kw)
+                if out_layout == sq.TILED:  # (the padding rows of the last block are undefined)
+                    got = (got._base if got._base is not None else got).reshape(-1)[torch.from_numpy(tiled_index(t, c_o)).cuda()]
+                assert torch.equal(got, want)
