@@ -179,14 +179,17 @@ __global__ __launch_bounds__(256) void softmax_quant_wave_kernel(const uint16_t*
 // workgroup, so that their last vectors fall on other SIMDs (36.1).
 //
 // The second launch bound holds the four waves per SIMD that the rows per compute unit named at the launch rule need.
-template <bool BF16, int VT, int NV, int ST, bool FULL, bool LOOP = false>
+//
+// KEEP: the differences from the mean stay in registers for the last pass instead of being taken again from the values: fewer registers and
+// instructions where rows queue for the chip, but for a row alone the subtractions no longer come in one burst ahead of the chain
+// of squares.  us, without / with: 4 x 8192 4.48 / 4.57, 64 x 6144 4.36 / 4.43, 17 x 2048 4.57 / 4.66; 1400 x 8192 13.4 / 12.6, 5500 x 1296 10.4 / 8.7.
+template <bool BF16, int VT, int NV, int ST, bool FULL, bool KEEP, bool LOOP = false>
 __global__ __launch_bounds__(VT / ST, LOOP || (ST == 2 && NV == 4) ? 4 : 1)
 void ln_quant_kernel(const uint16_t* __restrict__ x, int t, int c_i, const float* __restrict__ gamma_f,
                                                            const float* __restrict__ beta_f, float eps, float* __restrict__ scale,
                                                            int8_t* __restrict__ xq, bool tiled)
 {
     constexpr int W = VT / 64;  // 64-strand groups
-    constexpr bool KEEP = ST < 4;  // the differences from the mean are kept (four strands: taken again from the 16-bit values, for the registers)
     __shared__ __attribute__((aligned(16))) float cells[3][W];
     int row = blockIdx.x;
     const int nvec = c_i >> 3, lane = threadIdx.x & 63;
@@ -320,7 +323,7 @@ void ln_quant_kernel(const uint16_t* __restrict__ x, int t, int c_i, const float
 
 // One row per wave (hidden sizes up to 2048, where it measures faster than a workgroup per row): the three
 // reductions are cross-lane shuffles, no barriers, and a lane keeps NV 16-byte loads in flight.
-template <bool BF16, int NV>
+template <bool BF16, int NV, bool KEEP>
 __global__ __launch_bounds__(256) void ln_quant_wave_kernel(const uint16_t* __restrict__ x, int64_t t, int c_i,
                                                            const float* __restrict__ gamma_f, const float* __restrict__ beta_f,
                                                            float eps, float* __restrict__ scale, int8_t* __restrict__ xq, bool tiled)
@@ -349,8 +352,9 @@ __global__ __launch_bounds__(256) void ln_quant_wave_kernel(const uint16_t* __re
         if (idx < nvec) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                f[i][e] -= mean;
-                sq += f[i][e] * f[i][e];
+                const float d = f[i][e] - mean;
+                sq += d * d;
+                if constexpr (KEEP) f[i][e] = d;
             }
         }
     }
@@ -367,7 +371,7 @@ __global__ __launch_bounds__(256) void ln_quant_wave_kernel(const uint16_t* __re
             const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                f[i][e] = f[i][e] * rstd * g[e] + b[e];
+                f[i][e] = (KEEP ? f[i][e] : f[i][e] - mean) * rstd * g[e] + b[e];
                 m = __builtin_fmaxf(m, __builtin_fabsf(f[i][e]));
             }
         }
@@ -439,43 +443,53 @@ sq_status sq_ln_quantize(const void* x, sq_dtype dtype, int64_t t, int64_t c_i, 
     // 17.4 / 14.8, 1400 x 12288 17.5 / 17.8 / 15.0, 2048 x 8192 16.9 / 12.9 / 13.5, 4096 x 16384 56.9 / 54.2 / 56.2).  Against the
     // version with loads under a condition and two barriers an exchange: 4096 x 9216 tiled 37.9 -> 33.3 us, 1024 x 9216 11.7 ->
     // 8.7, 1 x 5120 4.4 -> 3.7.  Rows of three vectors per strand beyond one round of the four-strand form walk (LOOP): of 512 strands
-    // 1536 x 9216 13.1 without / 14.4 with, 1700 16.1 / 15.0; of 256 strands 3000 x 5120 13.4 / 14.7, 3600 19.6 / 16.9.
-#define SQ_LNK(BF, VT, NV, ST, FULL) sq_launch((ln_quant_kernel<BF, VT, NV, ST, FULL>), dim3((unsigned)t), dim3(VT / ST), 0, st, xp, (int)t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
-#define SQ_LNL(BF, VT, PER_CU) sq_launch((ln_quant_kernel<BF, VT, 3, 1, false, true>), dim3(256 * PER_CU), dim3(VT), 0, st, xp, (int)t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
-#define SQ_LNW(BF, NV) sq_launch((ln_quant_wave_kernel<BF, NV>), dim3((unsigned)((t + 3) / 4)), dim3(256), 0, st, xp, t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
+    // 1536 x 9216 13.1 without / 14.4 with, 1700 16.1 / 15.0; of 256 strands 3000 x 5120 13.4 / 14.7, 3600 19.6 / 16.9.  Differences kept (KEEP) beyond
+    // a row per compute unit, a wave's rows beyond four per SIMD (2560 x 1296 6.35 / 6.40, 4096 7.35 / 7.20, 5500 10.4 / 8.7; 2560 x 2048 7.50 / 7.56, 5500
+    // 14.0 / 12.2).
+#define SQ_LNK(BF, VT, NV, ST, FULL, KEEP) sq_launch((ln_quant_kernel<BF, VT, NV, ST, FULL, KEEP>), dim3((unsigned)t), dim3(VT / ST), 0, st, xp, (int)t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
+#define SQ_LNL(BF, VT, PER_CU) sq_launch((ln_quant_kernel<BF, VT, 3, 1, false, true, true>), dim3(256 * PER_CU), dim3(VT), 0, st, xp, (int)t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
+#define SQ_LNW(BF, NV, KEEP) sq_launch((ln_quant_wave_kernel<BF, NV, KEEP>), dim3((unsigned)((t + 3) / 4)), dim3(256), 0, st, xp, t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
+#define SQ_LN1(BF, VT, NV, FULL)                                                                                              \
+    do {                                                                                                                      \
+        if (t <= 256) SQ_LNK(BF, VT, NV, 1, FULL, false);                                                                     \
+        else SQ_LNK(BF, VT, NV, 1, FULL, true);                                                                               \
+    } while (0)
 #define SQ_LN2(BF, FULL)                                                                                                      \
     do {                                                                                                                      \
-        if (t <= 2048) SQ_LNK(BF, 256, 2, 1, FULL);                                                                           \
-        else if (t <= 3072) SQ_LNK(BF, 256, 2, 2, FULL);                                                                      \
-        else SQ_LNK(BF, 256, 2, 4, FULL);                                                                                     \
+        if (t <= 2048) SQ_LN1(BF, 256, 2, FULL);                                                                              \
+        else if (t <= 3072) SQ_LNK(BF, 256, 2, 2, FULL, true);                                                                \
+        else SQ_LNK(BF, 256, 2, 4, FULL, false);                                                                              \
     } while (0)
 #define SQ_LNA(BF)                                                                                                            \
     do {                                                                                                                      \
-        if (nvec <= 128) SQ_LNW(BF, 2);                                                                                       \
-        else if (nvec <= 256) SQ_LNW(BF, 4);                                                                                  \
+        if (nvec <= 128 && t <= 4096) SQ_LNW(BF, 2, false);                                                                   \
+        else if (nvec <= 128) SQ_LNW(BF, 2, true);                                                                            \
+        else if (nvec <= 256 && t <= 4096) SQ_LNW(BF, 4, false);                                                              \
+        else if (nvec <= 256) SQ_LNW(BF, 4, true);                                                                            \
         else if (nvec < 512) SQ_LN2(BF, false);                                                                               \
         else if (nvec == 512) SQ_LN2(BF, true);                                                                               \
         else if (nvec <= 768) {                                                                                               \
             if (t > 3584) SQ_LNL(BF, 256, 3);                                                                                 \
-            else if (t <= 1600 || t > 3072) SQ_LNK(BF, 256, 3, 1, false);                                                     \
-            else if (t <= 2048) SQ_LNK(BF, 256, 3, 2, false);                                                                 \
-            else SQ_LNK(BF, 256, 3, 4, false);                                                                                \
+            else if (t <= 1600 || t > 3072) SQ_LN1(BF, 256, 3, false);                                                        \
+            else if (t <= 2048) SQ_LNK(BF, 256, 3, 2, false, true);                                                           \
+            else SQ_LNK(BF, 256, 3, 4, false, false);                                                                         \
         } else if (nvec <= 1024) {                                                                                            \
-            if (t <= 1400 || (t > 2048 && t <= 2560)) SQ_LNK(BF, 256, 4, 1, false);                                           \
-            else if (t <= 3072) SQ_LNK(BF, 256, 4, 2, false);                                                                 \
-            else SQ_LNK(BF, 256, 4, 4, false);                                                                                \
+            if (t <= 1400 || (t > 2048 && t <= 2560)) SQ_LN1(BF, 256, 4, false);                                              \
+            else if (t <= 3072) SQ_LNK(BF, 256, 4, 2, false, true);                                                           \
+            else SQ_LNK(BF, 256, 4, 4, false, false);                                                                         \
         } else if (nvec <= 1536) {                                                                                            \
             if (t > 1536) SQ_LNL(BF, 512, 2);                                                                                 \
-            else if (t <= 1024) SQ_LNK(BF, 512, 3, 1, false);                                                                 \
-            else SQ_LNK(BF, 512, 3, 4, false);                                                                                \
-        } else if (t <= 768) SQ_LNK(BF, 512, 4, 1, false);                                                                    \
-        else SQ_LNK(BF, 512, 4, 2, false);                                                                                    \
+            else if (t <= 1024) SQ_LN1(BF, 512, 3, false);                                                                    \
+            else SQ_LNK(BF, 512, 3, 4, false, false);                                                                         \
+        } else if (t <= 768) SQ_LNK(BF, 512, 4, 1, false, true);                                                              \
+        else SQ_LNK(BF, 512, 4, 2, false, true);                                                                              \
     } while (0)
     if (dtype == SQ_BF16) SQ_LNA(true);
     else SQ_LNA(false);
 #undef SQ_LNK
 #undef SQ_LNL
 #undef SQ_LNW
+#undef SQ_LN1
 #undef SQ_LN2
 #undef SQ_LNA
     return sq_launch_status();
