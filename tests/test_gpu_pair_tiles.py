@@ -43,3 +43,23 @@ def test_pair_tiles_int8_out_tiled(t, c_i, c_o):
     assert torch.equal(_tile(rows[:whole].contiguous()).reshape(-1), tiled.reshape(-1)[: whole * c_o])
     flat = (tiled._base if tiled._base is not None else tiled).reshape(-1)
     assert torch.equal(flat[torch.from_numpy(tiled_index(t, c_o)).cuda()], rows)
+
+
+@pytest.mark.parametrize("t,c_i,c_o,layout,tile", [(523, 320, 11048, T, 1192160), (770, 1344, 10320, T, 1192224), (204, 384, 11328, T, 1256128),
+                                                   (906, 560, 8316, R, 1256160), (145, 3600, 8372, R, 3256128)])
+def test_pair_tiles_sums_end_with_the_output(t, c_i, c_o, layout, tile):
+    """Int32 sums of whole 16-byte pieces: ragged tiles write their rows and columns and nothing else."""
+    print(f"pair tile sums {t}x{c_i}->{c_o} layout {layout}", flush=True)
+    assert sq.lib().sq_probe_linear_tile(t, c_i, c_o, layout) == tile
+    g = torch.Generator(device="cuda").manual_seed(t)
+    x, w = (torch.randint(-127, 128, s, generator=g, device="cuda", dtype=torch.int32).to(torch.int8) for s in ((t, c_i), (c_o, c_i)))
+    want = (x.double() @ w.double().t()).to(torch.int32)  # (exact: below 2^53)
+    xq, wq = (_tile(x), _tile(w)) if layout == T else (x, w)
+    flat = lambda a: (a._base if a._base is not None else a).data_ptr()
+    n, guard = t * c_o, 1 << 16
+    acc = torch.full((n + 2 * guard,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    ws = torch.empty(max(16, sq.lib().sq_workspace_bytes(3, t, c_i, c_o)), dtype=torch.uint8, device="cuda")
+    status = sq.lib().sq_i8_gemm_i32(flat(xq), flat(wq), acc.data_ptr() + 4 * guard, t, c_i, c_o, layout, ws.data_ptr(), ws.numel(),
+                                     torch.cuda.current_stream().cuda_stream)
+    assert status == 0 and torch.equal(acc[guard:guard + n].reshape(t, c_o), want)
+    assert torch.all(acc[:guard] == 0x5A5A5A5A) and torch.all(acc[guard + n:] == 0x5A5A5A5A)
