@@ -170,28 +170,19 @@ __global__ __launch_bounds__(256) void softmax_quant_wave_kernel(const uint16_t*
 // and an exchange has cells of its own and one barrier.  Only the last of a strand's vectors can lie past the end of the row: it
 // re-reads the row's last one, adds nothing to the sums, and in the maximum is that vector once more.
 //
-// LOOP (many rows): a workgroup walks through the rows, the next one's loads under way from the moment the present one is unpacked, its
-// share of gamma and beta in registers for good.  With a row per workgroup the loads were in flight for a third of a row's time, and
-// eight bytes of gamma and beta per element came out of the L2 behind them.  Two workgroups of 512 threads or three of 256 per compute
-// unit measure best, and what is left is vector issue (85 % of the time).  us, a row per workgroup / LOOP, inputs from memory: 4096 x
-// 9216 tiled 38.6 / 32.5, 2100 x 9216 20.7 / 18.4, 4096 x 12288 44.1 / 37.5, 4096 x 5120 20.1 / 17.5.  Not kept: three or four workgroups
-// of 512 (33.4, 35.0), two strands per thread or four vectors per strand (spills), another order of the waves in every second
-// workgroup, so that their last vectors fall on other SIMDs (36.1).
-//
-// The second launch bound holds the four waves per SIMD that the rows per compute unit named at the launch rule need.
-//
 // KEEP: the differences from the mean stay in registers for the last pass instead of being taken again from the values: fewer registers and
 // instructions where rows queue for the chip, but for a row alone the subtractions no longer come in one burst ahead of the chain
-// of squares.  us, without / with: 4 x 8192 4.48 / 4.57, 64 x 6144 4.36 / 4.43, 17 x 2048 4.57 / 4.66; 1400 x 8192 13.4 / 12.6, 5500 x 1296 10.4 / 8.7.
-template <bool BF16, int VT, int NV, int ST, bool FULL, bool KEEP, bool LOOP = false>
-__global__ __launch_bounds__(VT / ST, LOOP || (ST == 2 && NV == 4) ? 4 : 1)
-void ln_quant_kernel(const uint16_t* __restrict__ x, int t, int c_i, const float* __restrict__ gamma_f,
+// of squares.  us, without / with: 4 x 8192 4.97 / 5.06, 64 x 6144 4.36 / 4.43; 1400 x 8192 13.3 / 12.4, 1400 x 6144 10.4 / 10.0, 768 x 14336 10.6 / 10.3.
+// (With four strands they cost a wave per SIMD, with two of 512 more than they save: 2560 x 16384 36.5 / 38.1.)
+template <bool BF16, int VT, int NV, int ST, bool FULL, bool KEEP>
+__global__ __launch_bounds__(VT / ST, KEEP && ST == 2 && NV == 4 ? 4 : 1) void ln_quant_kernel(const uint16_t* __restrict__ x, int c_i, const float* __restrict__ gamma_f,
                                                            const float* __restrict__ beta_f, float eps, float* __restrict__ scale,
                                                            int8_t* __restrict__ xq, bool tiled)
 {
     constexpr int W = VT / 64;  // 64-strand groups
     __shared__ __attribute__((aligned(16))) float cells[3][W];
-    int row = blockIdx.x;
+    const int64_t row = blockIdx.x;
+    const v4u* xr = (const v4u*)(x + row * (int64_t)c_i);
     const int nvec = c_i >> 3, lane = threadIdx.x & 63;
     const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * ST;  // first of this wave's groups
     int idx[ST][NV];
@@ -207,29 +198,8 @@ void ln_quant_kernel(const uint16_t* __restrict__ x, int t, int c_i, const float
                 in[s] = FULL || idx[s][i] < nvec;
                 idx[s][i] = in[s] ? idx[s][i] : nvec - 1;
             }
+            raw[s][i] = __builtin_nontemporal_load(xr + idx[s][i]);
         }
-    }
-    auto load_row = [&](int r) {
-        const v4u* xr = (const v4u*)(x + r * (int64_t)c_i);
-#pragma unroll
-        for (int s = 0; s < ST; ++s)
-#pragma unroll
-            for (int i = 0; i < NV; ++i) raw[s][i] = __builtin_nontemporal_load(xr + idx[s][i]);
-    };
-    load_row(row);
-    constexpr int GN = LOOP ? NV : 1, GS = LOOP ? ST : 1;
-    float gam[GS][GN][8], bet[GS][GN][8];
-    auto load_affine = [&](int s, int i, float (&g)[8], float (&b)[8]) {
-        const float4 g0 = *(const float4*)(gamma_f + idx[s][i] * 8), g1 = *(const float4*)(gamma_f + idx[s][i] * 8 + 4);
-        const float4 b0 = *(const float4*)(beta_f + idx[s][i] * 8), b1 = *(const float4*)(beta_f + idx[s][i] * 8 + 4);
-        g[0] = g0.x; g[1] = g0.y; g[2] = g0.z; g[3] = g0.w; g[4] = g1.x; g[5] = g1.y; g[6] = g1.z; g[7] = g1.w;
-        b[0] = b0.x; b[1] = b0.y; b[2] = b0.z; b[3] = b0.w; b[4] = b1.x; b[5] = b1.y; b[6] = b1.z; b[7] = b1.w;
-    };
-    if constexpr (LOOP) {
-#pragma unroll
-        for (int s = 0; s < ST; ++s)
-#pragma unroll
-            for (int i = 0; i < NV; ++i) load_affine(s, i, gam[s][i], bet[s][i]);
     }
     auto exchange = [&](const float (&v)[ST], float* cell, auto&& op) {
         if (lane == 0) {
@@ -247,75 +217,179 @@ void ln_quant_kernel(const uint16_t* __restrict__ x, int t, int c_i, const float
     };
     auto add = [](float a, float b) { return a + b; };
     auto max = [](float a, float b) { return __builtin_fmaxf(a, b); };
-    for (;;) {
-        float f[ST][NV][8], part[ST];
+    float f[ST][NV][8], part[ST];
 #pragma unroll
-        for (int s = 0; s < ST; ++s) {
-            part[s] = 0.0f;
+    for (int s = 0; s < ST; ++s) {
+        part[s] = 0.0f;
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                if (i == NV - 1 && !any[s]) break;
-                unpack8r<BF16>(raw[s][i], f[s][i]);
-                float v = part[s];
+        for (int i = 0; i < NV; ++i) {
+            if (i == NV - 1 && !any[s]) break;
+            unpack8r<BF16>(raw[s][i], f[s][i]);
+            float v = part[s];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v += f[s][i][e];
-                part[s] = i < NV - 1 || in[s] ? v : part[s];
-            }
-            part[s] = wave_sum(part[s]);
+            for (int e = 0; e < 8; ++e) v += f[s][i][e];
+            part[s] = i < NV - 1 || in[s] ? v : part[s];
         }
-        const bool more = LOOP && row < t - (int)gridDim.x;
+        part[s] = wave_sum(part[s]);
+    }
+    const float mean = exchange(part, cells[0], add) / (float)c_i;
+#pragma unroll
+    for (int s = 0; s < ST; ++s) {
+        part[s] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (i == NV - 1 && !any[s]) break;
+            float v = part[s];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float d = f[s][i][e] - mean;
+                v += d * d;
+                if constexpr (KEEP) f[s][i][e] = d;
+            }
+            part[s] = i < NV - 1 || in[s] ? v : part[s];
+        }
+        part[s] = wave_sum(part[s]);
+    }
+    const float var = exchange(part, cells[1], add) / (float)c_i;
+    const float rstd = 1.0f / sqrtf(var + eps);
+#pragma unroll
+    for (int s = 0; s < ST; ++s) {
+        part[s] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const float4 g0 = *(const float4*)(gamma_f + idx[s][i] * 8), g1 = *(const float4*)(gamma_f + idx[s][i] * 8 + 4);
+            const float4 b0 = *(const float4*)(beta_f + idx[s][i] * 8), b1 = *(const float4*)(beta_f + idx[s][i] * 8 + 4);
+            const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+            const float b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+            if (i == NV - 1 && !any[s]) break;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                f[s][i][e] = (KEEP ? f[s][i][e] : f[s][i][e] - mean) * rstd * g[e] + b[e];
+                part[s] = __builtin_fmaxf(part[s], __builtin_fabsf(f[s][i][e]));
+            }
+        }
+        part[s] = wave_max(part[s]);
+    }
+    const float a = exchange(part, cells[2], max);
+    const float r = a > 0.0f ? 127.0f / a : 0.0f;
+    if (threadIdx.x == 0) scale[row] = a / 127.0f;
+#pragma unroll
+    for (int s = 0; s < ST; ++s)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (i == NV - 1 && !any[s]) break;
+            uint32_t codes[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) codes[e] = code_bits(f[s][i][e] * r);
+            if (i < NV - 1 || in[s]) __builtin_nontemporal_store(pack8(codes), (v2u*)code_dst(xq, row, idx[s][i] * 8, c_i, tiled));
+        }
+}
+
+// The same for many rows: a workgroup walks through them, the next one's loads under way from the moment the present one is unpacked, its
+// share of gamma and beta in registers for good.  With a row per workgroup the loads were in flight for a third of a row's time, and
+// eight bytes of gamma and beta per element came out of the L2 behind them.  Two workgroups of 512 threads or three of 256 per compute
+// unit measure best, and what is left is vector issue (85 % of the time).  us, a row per workgroup / this, inputs from memory: 4096 x
+// 9216 tiled 38.6 / 32.5, 2100 x 9216 20.7 / 18.4, 4096 x 12288 44.1 / 37.5, 4096 x 5120 20.1 / 17.5.  Not kept: three or four workgroups
+// of 512 (33.4, 35.0), two strands per thread or four vectors per strand (spills), another order of the waves in every second
+// workgroup, so that their last vectors fall on other SIMDs (36.1), one kernel for both (the compiler then schedules the loads and sums of
+// a row alone in another order, 1024 x 12288 12.7 / 13.1).  The second launch bound holds the four waves per SIMD of those workgroups.
+template <bool BF16, int VT>
+__global__ __launch_bounds__(VT, 4) void ln_quant_walk_kernel(const uint16_t* __restrict__ x, int t, int c_i, const float* __restrict__ gamma_f,
+                                                              const float* __restrict__ beta_f, float eps, float* __restrict__ scale,
+                                                              int8_t* __restrict__ xq, bool tiled)
+{
+    constexpr int W = VT / 64, NV = 3;
+    __shared__ __attribute__((aligned(16))) float cells[3][W];
+    const int nvec = c_i >> 3, lane = threadIdx.x & 63;
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int idx[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) idx[i] = group * 64 + lane + i * VT;
+    const bool any = group * 64 + (NV - 1) * VT < nvec;  // the last vector of one of the wave's lanes lies in the row, of this lane
+    const bool in = idx[NV - 1] < nvec;
+    idx[NV - 1] = in ? idx[NV - 1] : nvec - 1;
+    v4u raw[NV];
+    auto load_row = [&](int r) {
+        const v4u* xr = (const v4u*)(x + r * (int64_t)c_i);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) raw[i] = __builtin_nontemporal_load(xr + idx[i]);
+    };
+    int row = blockIdx.x;
+    load_row(row);
+    float gam[NV][8], bet[NV][8];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const float4 g0 = *(const float4*)(gamma_f + idx[i] * 8), g1 = *(const float4*)(gamma_f + idx[i] * 8 + 4);
+        const float4 b0 = *(const float4*)(beta_f + idx[i] * 8), b1 = *(const float4*)(beta_f + idx[i] * 8 + 4);
+        gam[i][0] = g0.x; gam[i][1] = g0.y; gam[i][2] = g0.z; gam[i][3] = g0.w; gam[i][4] = g1.x; gam[i][5] = g1.y; gam[i][6] = g1.z; gam[i][7] = g1.w;
+        bet[i][0] = b0.x; bet[i][1] = b0.y; bet[i][2] = b0.z; bet[i][3] = b0.w; bet[i][4] = b1.x; bet[i][5] = b1.y; bet[i][6] = b1.z; bet[i][7] = b1.w;
+    }
+    // (a cell is written again three barriers after it was read)
+    auto exchange = [&](float v, float* cell, auto&& op) {
+        if (lane == 0) cell[group] = v;
+        __syncthreads();
+        float4 q = *(const float4*)cell;
+        float r = op(op(q.x, q.y), op(q.z, q.w));
+        if constexpr (W == 8) {
+            q = *(const float4*)(cell + 4);
+            r = op(r, op(op(q.x, q.y), op(q.z, q.w)));
+        }
+        return r;
+    };
+    auto add = [](float a, float b) { return a + b; };
+    auto max = [](float a, float b) { return __builtin_fmaxf(a, b); };
+    for (;;) {
+        float f[NV][8], part = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (i == NV - 1 && !any) break;
+            unpack8r<BF16>(raw[i], f[i]);
+            float v = part;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v += f[i][e];
+            part = i < NV - 1 || in ? v : part;
+        }
+        part = wave_sum(part);
+        const bool more = row < t - (int)gridDim.x;
         if (more) load_row(row + (int)gridDim.x);
         const float mean = exchange(part, cells[0], add) / (float)c_i;
+        part = 0.0f;
 #pragma unroll
-        for (int s = 0; s < ST; ++s) {
-            part[s] = 0.0f;
+        for (int i = 0; i < NV; ++i) {
+            if (i == NV - 1 && !any) break;
+            float v = part;
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                if (i == NV - 1 && !any[s]) break;
-                float v = part[s];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float d = f[s][i][e] - mean;
-                    v += d * d;
-                    if constexpr (KEEP) f[s][i][e] = d;
-                }
-                part[s] = i < NV - 1 || in[s] ? v : part[s];
+            for (int e = 0; e < 8; ++e) {
+                f[i][e] -= mean;
+                v += f[i][e] * f[i][e];
             }
-            part[s] = wave_sum(part[s]);
+            part = i < NV - 1 || in ? v : part;
         }
+        part = wave_sum(part);
         const float var = exchange(part, cells[1], add) / (float)c_i;
         const float rstd = 1.0f / sqrtf(var + eps);
+        part = 0.0f;
 #pragma unroll
-        for (int s = 0; s < ST; ++s) {
-            part[s] = 0.0f;
+        for (int i = 0; i < NV; ++i) {
+            if (i == NV - 1 && !any) break;
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                float gl[8], bl[8];
-                if constexpr (!LOOP) load_affine(s, i, gl, bl);
-                const float(&g)[8] = LOOP ? gam[LOOP ? s : 0][LOOP ? i : 0] : gl;
-                const float(&b)[8] = LOOP ? bet[LOOP ? s : 0][LOOP ? i : 0] : bl;
-                if (i == NV - 1 && !any[s]) break;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    f[s][i][e] = (KEEP ? f[s][i][e] : f[s][i][e] - mean) * rstd * g[e] + b[e];
-                    part[s] = __builtin_fmaxf(part[s], __builtin_fabsf(f[s][i][e]));
-                }
+            for (int e = 0; e < 8; ++e) {
+                f[i][e] = f[i][e] * rstd * gam[i][e] + bet[i][e];
+                part = __builtin_fmaxf(part, __builtin_fabsf(f[i][e]));
             }
-            part[s] = wave_max(part[s]);
         }
+        part = wave_max(part);
         const float a = exchange(part, cells[2], max);
         const float r = a > 0.0f ? 127.0f / a : 0.0f;
         if (threadIdx.x == 0) scale[row] = a / 127.0f;
 #pragma unroll
-        for (int s = 0; s < ST; ++s)
+        for (int i = 0; i < NV; ++i) {
+            if (i == NV - 1 && !any) break;
+            uint32_t codes[8];
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                if (i == NV - 1 && !any[s]) break;
-                uint32_t codes[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) codes[e] = code_bits(f[s][i][e] * r);
-                if (i < NV - 1 || in[s]) __builtin_nontemporal_store(pack8(codes), (v2u*)code_dst(xq, row, idx[s][i] * 8, c_i, tiled));
-            }
+            for (int e = 0; e < 8; ++e) codes[e] = code_bits(f[i][e] * r);
+            if (i < NV - 1 || in) __builtin_nontemporal_store(pack8(codes), (v2u*)code_dst(xq, row, idx[i] * 8, c_i, tiled));
+        }
         if (!more) break;
         row += (int)gridDim.x;
     }
@@ -442,21 +516,21 @@ sq_status sq_ln_quantize(const void* x, sq_dtype dtype, int64_t t, int64_t c_i, 
     // between one and two rounds the form with the shortest tail wins (4096 x 4096 tiled 15.9 / 12.9 / 12.3, 2800 x 6144 17.4 /
     // 17.4 / 14.8, 1400 x 12288 17.5 / 17.8 / 15.0, 2048 x 8192 16.9 / 12.9 / 13.5, 4096 x 16384 56.9 / 54.2 / 56.2).  Against the
     // version with loads under a condition and two barriers an exchange: 4096 x 9216 tiled 37.9 -> 33.3 us, 1024 x 9216 11.7 ->
-    // 8.7, 1 x 5120 4.4 -> 3.7.  Rows of three vectors per strand beyond one round of the four-strand form walk (LOOP): of 512 strands
+    // 8.7, 1 x 5120 4.4 -> 3.7.  Rows of three vectors per strand beyond one round of the four-strand form walk: of 512 strands
     // 1536 x 9216 13.1 without / 14.4 with, 1700 16.1 / 15.0; of 256 strands 3000 x 5120 13.4 / 14.7, 3600 19.6 / 16.9.  Differences kept (KEEP) beyond
-    // a row per compute unit, a wave's rows beyond four per SIMD (2560 x 1296 6.35 / 6.40, 4096 7.35 / 7.20, 5500 10.4 / 8.7; 2560 x 2048 7.50 / 7.56, 5500
-    // 14.0 / 12.2).
-#define SQ_LNK(BF, VT, NV, ST, FULL, KEEP) sq_launch((ln_quant_kernel<BF, VT, NV, ST, FULL, KEEP>), dim3((unsigned)t), dim3(VT / ST), 0, st, xp, (int)t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
-#define SQ_LNL(BF, VT, PER_CU) sq_launch((ln_quant_kernel<BF, VT, 3, 1, false, true, true>), dim3(256 * PER_CU), dim3(VT), 0, st, xp, (int)t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
+    // two rows per compute unit (300 x 7680 6.01 / 6.08, 600 x 7680 7.04 / 7.02, 1400 12.8 / 12.3), a wave's rows beyond four per SIMD (2560 x 1296 6.35 / 6.40, 4096
+    // 7.35 / 7.20, 5500 10.4 / 8.7; 2560 x 2048 7.50 / 7.56, 5500 14.0 / 12.2).
+#define SQ_LNK(BF, VT, NV, ST, FULL, KEEP) sq_launch((ln_quant_kernel<BF, VT, NV, ST, FULL, KEEP>), dim3((unsigned)t), dim3(VT / ST), 0, st, xp, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
+#define SQ_LNL(BF, VT, PER_CU) sq_launch((ln_quant_walk_kernel<BF, VT>), dim3(256 * PER_CU), dim3(VT), 0, st, xp, (int)t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
 #define SQ_LNW(BF, NV, KEEP) sq_launch((ln_quant_wave_kernel<BF, NV, KEEP>), dim3((unsigned)((t + 3) / 4)), dim3(256), 0, st, xp, t, (int)c_i, gamma_f, beta_f, eps, scale, xq, tiled)
-#define SQ_LN1(BF, VT, NV, FULL)                                                                                              \
+#define SQ_LN1(BF, NV, FULL)                                                                                                  \
     do {                                                                                                                      \
-        if (t <= 256) SQ_LNK(BF, VT, NV, 1, FULL, false);                                                                     \
-        else SQ_LNK(BF, VT, NV, 1, FULL, true);                                                                               \
+        if (t <= 512) SQ_LNK(BF, 256, NV, 1, FULL, false);                                                                    \
+        else SQ_LNK(BF, 256, NV, 1, FULL, true);                                                                              \
     } while (0)
 #define SQ_LN2(BF, FULL)                                                                                                      \
     do {                                                                                                                      \
-        if (t <= 2048) SQ_LN1(BF, 256, 2, FULL);                                                                              \
+        if (t <= 2048) SQ_LN1(BF, 2, FULL);                                                                                   \
         else if (t <= 3072) SQ_LNK(BF, 256, 2, 2, FULL, true);                                                                \
         else SQ_LNK(BF, 256, 2, 4, FULL, false);                                                                              \
     } while (0)
@@ -470,19 +544,19 @@ sq_status sq_ln_quantize(const void* x, sq_dtype dtype, int64_t t, int64_t c_i, 
         else if (nvec == 512) SQ_LN2(BF, true);                                                                               \
         else if (nvec <= 768) {                                                                                               \
             if (t > 3584) SQ_LNL(BF, 256, 3);                                                                                 \
-            else if (t <= 1600 || t > 3072) SQ_LN1(BF, 256, 3, false);                                                        \
+            else if (t <= 1600 || t > 3072) SQ_LN1(BF, 3, false);                                                             \
             else if (t <= 2048) SQ_LNK(BF, 256, 3, 2, false, true);                                                           \
             else SQ_LNK(BF, 256, 3, 4, false, false);                                                                         \
         } else if (nvec <= 1024) {                                                                                            \
-            if (t <= 1400 || (t > 2048 && t <= 2560)) SQ_LN1(BF, 256, 4, false);                                              \
+            if (t <= 1400 || (t > 2048 && t <= 2560)) SQ_LN1(BF, 4, false);                                                   \
             else if (t <= 3072) SQ_LNK(BF, 256, 4, 2, false, true);                                                           \
             else SQ_LNK(BF, 256, 4, 4, false, false);                                                                         \
         } else if (nvec <= 1536) {                                                                                            \
             if (t > 1536) SQ_LNL(BF, 512, 2);                                                                                 \
-            else if (t <= 1024) SQ_LN1(BF, 512, 3, false);                                                                    \
+            else if (t <= 1024) SQ_LNK(BF, 512, 3, 1, false, false);                                                          \
             else SQ_LNK(BF, 512, 3, 4, false, false);                                                                         \
         } else if (t <= 768) SQ_LNK(BF, 512, 4, 1, false, true);                                                              \
-        else SQ_LNK(BF, 512, 4, 2, false, true);                                                                              \
+        else SQ_LNK(BF, 512, 4, 2, false, false);                                                                             \
     } while (0)
     if (dtype == SQ_BF16) SQ_LNA(true);
     else SQ_LNA(false);
