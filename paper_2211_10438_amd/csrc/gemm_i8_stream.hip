@@ -461,9 +461,9 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
         __syncthreads();
     }
 
-    // ---- epilogue: eight neighbouring columns per thread, 16 bytes of a row (rows that are not whole 16-byte pieces: element by element).
-    // Scales and biases come from LDS, where the loader waves put them: fetched here, two columns at a time, they made this part 11 of the
-    // 59 us of 100 x 9216 -> 27648.
+    // ---- epilogue: eight neighbouring columns per thread, 16 bytes of a row; where rows are not whole 16-byte pieces two, so that neighbouring lanes
+    // still fill lines (eight a thread, element by element: 107 x 6784 -> 19676 49.5 us, now 43.3).  Scales and biases come from LDS, where the
+    // loader waves put them: fetched here, two columns at a time, they made this part 11 of the 59 us of 100 x 9216 -> 27648.
     int32_t* out32 = p.acc_out + (int64_t)gki * p.M * p.N;
     const uint16_t* R = (const uint16_t*)p.residual;
     float rq = 0.0f;
@@ -472,64 +472,78 @@ __global__ __launch_bounds__(512, 1) void gemm_i8_stream_regs_kernel(const GemmA
         rq = delta > 0.0f ? 1.0f / delta : 0.0f;
     }
     const int rows = p.M < MB * 16 ? p.M : MB * 16;
-    auto emit = [&](auto BF_) {
+    // W = 8: N % 8 == 0; codes always
+    auto emit = [&](auto BF_, auto W_) {
         constexpr bool BF = decltype(BF_)::value;
-        typedef float v4f __attribute__((ext_vector_type(4)));
-        const bool whole = (p.N & 7) == 0;
-        for (int idx = threadIdx.x; idx < rows * nu * 2; idx += 512) {
-            const int row = idx / (nu * 2), c8 = (idx - row * (nu * 2)) * 8, col = u0 * 16 + c8;
+        constexpr int W = decltype(W_)::value;
+        typedef float vf __attribute__((ext_vector_type(W)));
+        typedef int vi __attribute__((ext_vector_type(W)));
+        const bool even = W == 8 || (p.N & 1) == 0;
+        for (int idx = threadIdx.x; idx < rows * nu * (16 / W); idx += 512) {
+            const int row = idx / (nu * (16 / W)), c = (idx - row * (nu * (16 / W))) * W, col = u0 * 16 + c;
             if (col >= p.N) continue;
             const int64_t o = (int64_t)row * p.N + col;
-            const v4i lo = *(const v4i*)&red[row * PITCH + c8], hi = *(const v4i*)&red[row * PITCH + c8 + 4];
+            const bool both = even || col + 1 < p.N;
+            const vi sum = *(const vi*)&red[row * PITCH + c];
             if (raw) {
-                if (whole) {
-                    *(v4i*)(out32 + o) = lo;
-                    *(v4i*)(out32 + o + 4) = hi;
+                if constexpr (W == 8) {
+                    *(v4i*)(out32 + o) = v4i{sum[0], sum[1], sum[2], sum[3]};
+                    *(v4i*)(out32 + o + 4) = v4i{sum[4], sum[5], sum[6], sum[7]};
+                } else if (even) {
+                    *(v2i*)(out32 + o) = v2i{sum[0], sum[1]};
                 } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (col + e < p.N) out32[o + e] = e < 4 ? lo[e & 3] : hi[e & 3];
+                    out32[o] = sum[0];
+                    if (both) out32[o + 1] = sum[1];
                 }
                 continue;
             }
-            uint32_t res[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            uint32_t res[W];
+#pragma unroll
+            for (int e = 0; e < W; ++e) res[e] = 0u;
             if (R) {
-                if (whole) {
+                if constexpr (W == 8) {
                     const v4u r = *(const v4u*)(R + o);
 #pragma unroll
                     for (int e = 0; e < 8; ++e) res[e] = (r[e >> 1] >> ((e & 1) * 16)) & 0xffffu;
                 } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) res[e] = col + e < p.N ? R[o + e] : 0u;
+                    res[0] = R[o];
+                    if (both) res[1] = R[o + 1];
                 }
             }
             const float xs = sv_row[row];
-            const v4f w0 = *(const v4f*)(sv_col + c8), w1 = *(const v4f*)(sv_col + c8 + 4);
-            const v4f b0 = *(const v4f*)(sv_bias + c8), b1 = *(const v4f*)(sv_bias + c8 + 4);
-            uint32_t ob[8];
+            const vf ws = *(const vf*)(sv_col + c), bias = *(const vf*)(sv_bias + c);
+            uint32_t ob[W];
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                ob[e] = dequant_one<BF>(e < 4 ? lo[e & 3] : hi[e & 3], xs * (e < 4 ? w0[e & 3] : w1[e & 3]), e < 4 ? b0[e & 3] : b1[e & 3], p.bias != nullptr,
-                                        p.relu != 0, res[e], R != nullptr) & 0xffffu;
-            if (p.q8_step) {  // (codes: whole pieces of eight)
-                uint32_t c[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) c[e] = (uint32_t)requant_code<BF>(ob[e], rq);
-                *(v2u*)code_dst(p.q8_out, row, col, p.N, p.q8_tiled != 0) = v2u{pack4_low_bytes(c[0], c[1], c[2], c[3]), pack4_low_bytes(c[4], c[5], c[6], c[7])};
-                continue;
-            }
+            for (int e = 0; e < W; ++e)
+                ob[e] = dequant_one<BF>(sum[e], xs * ws[e], bias[e], p.bias != nullptr, p.relu != 0, res[e], R != nullptr) & 0xffffu;
             uint16_t* dst = (uint16_t*)p.C + o;
-            if (whole) {
-                *(v4u*)dst = v4u{ob[0] | (ob[1] << 16), ob[2] | (ob[3] << 16), ob[4] | (ob[5] << 16), ob[6] | (ob[7] << 16)};
-            } else {
+            if constexpr (W == 8) {
+                if (p.q8_step) {
+                    uint32_t k[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (col + e < p.N) dst[e] = (uint16_t)ob[e];
+                    for (int e = 0; e < 8; ++e) k[e] = (uint32_t)requant_code<BF>(ob[e], rq);
+                    *(v2u*)code_dst(p.q8_out, row, col, p.N, p.q8_tiled != 0) = v2u{pack4_low_bytes(k[0], k[1], k[2], k[3]), pack4_low_bytes(k[4], k[5], k[6], k[7])};
+                    continue;
+                }
+                *(v4u*)dst = v4u{ob[0] | (ob[1] << 16), ob[2] | (ob[3] << 16), ob[4] | (ob[5] << 16), ob[6] | (ob[7] << 16)};
+            } else if (even) {
+                *(uint32_t*)dst = ob[0] | (ob[1] << 16);
+            } else {
+                dst[0] = (uint16_t)ob[0];
+                if (both) dst[1] = (uint16_t)ob[1];
             }
         }
     };
-    if (q.bf16) emit(std::true_type{});
-    else emit(std::false_type{});
+    using Eight = std::integral_constant<int, 8>;
+    using Two = std::integral_constant<int, 2>;
+    const bool whole = (p.N & 7) == 0;
+    if (q.bf16) {
+        if (whole) emit(std::true_type{}, Eight{});
+        else emit(std::true_type{}, Two{});
+    } else {
+        if (whole) emit(std::false_type{}, Eight{});
+        else emit(std::false_type{}, Two{});
+    }
 }
 
 int num_cus()
