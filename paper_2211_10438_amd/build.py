@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libsqmi.so")
-TILE_SOURCES = ["gemm_i8_tile_rows.hip", "gemm_i8_tile_tiled.hip", "gemm_i8_tile_rows_codes.hip", "gemm_i8_tile_tiled_codes.hip"]
+TILE_SOURCES = [f"gemm_i8_tile_{layout}{output}.hip" for layout in ("rows", "tiled") for output in ("", "_ragged", "_codes")]
 SOURCES = ["api.hip", "quantize.hip", "weight_prep.hip", "rowops.hip", "gemm_i8.hip", *TILE_SOURCES, "gemm_i8_stream.hip", "gemm_i8_direct.hip", "gemm_i8_direct_rows.hip", "gemm_i8_direct_tiled.hip", "bmm_strip.hip", "bmm_pv.hip", "attn_fused.hip", "attn_few.hip", "probe.hip"]
 
 # -ffp-contract=off: scale arithmetic must round every product and sum separately (bit-exact codes).

@@ -29,9 +29,10 @@
 
 namespace {
 
-// What a tile stores.  Int8 codes have kernels of their own: as one more branch of the 16-bit kernels their store costs those 0.2 to 0.5 us a
-// launch (scalar registers, kernel arguments loaded late), e.g. 300 x 4096 -> 16384 tiled 28.4 / 28.9.
-enum { EPI_DEQUANT = 0, EPI_I32 = 1, EPI_CODES = 2 };
+// What a tile stores: 16-bit values in whole 16-byte pieces, the same where rows are not whole pieces, int8 codes, int32 sums.  Each has kernels of its
+// own: as branches of one kernel the rarer stores cost the first some 0.2 to 0.5 us a launch (scalar registers, kernel arguments loaded late, residual
+// pieces fetched branch by branch), e.g. 300 x 4096 -> 16384 tiled 28.4 / 28.9, 991 x 864 -> 3624 row-major with a residual 14.0 / 14.7.
+enum { EPI_DEQUANT = 0, EPI_I32 = 1, EPI_CODES = 2, EPI_RAGGED = 3 };
 
 // BM x BN output tile per workgroup, WGM x WGN waves, BK = 64 bytes of K per pipeline stage.
 // B is [N, K] (K-contiguous rows, like A).
@@ -202,11 +203,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     // tile of the residual, 16 bytes of a row at a time.  PRE: on their way during the K loop (the tiles of pairs of steps have the registers);
     // fetched behind it they cost 3 us a launch.  1000 x 256 -> 9216, us, before / now: 12.2 / 9.6, with a residual and a step per channel
     // 18.3 / 11.5; 1000 x 9216 -> 9216 with both 90.6 / 86.5 (the power cap takes the rest back).
-    constexpr bool PRE = EPI != EPI_I32 && PAIR;
+    constexpr bool PRE = EPI != EPI_I32 && PAIR, PRE_RES = PRE && EPI != EPI_RAGGED;
     constexpr int CPR = BN / 8;                             // 16-byte pieces per tile row
     constexpr int RCH = (GR * CPR + NW * 64 - 1) / (NW * 64);  // of them per thread
     const uint16_t* R = (const uint16_t*)p.residual;
-    const bool vec_ok = EPI == EPI_CODES || (p.N & 7) == 0;  // 16-byte chunks never straddle the row end and stay aligned
+    constexpr bool WHOLE = EPI != EPI_RAGGED;               // N % 8 == 0: 16-byte pieces never straddle the row end and stay aligned
     float col_scale = 0.0f, col_bias = 0.0f, row_scale = 0.0f;
     constexpr bool FULL = MI * NI * AV >= 192;              // the sums leave few registers: one piece more in flight and they spill
     constexpr int RG = PRE || RCH <= 4 ? RCH : FULL ? 2 : 4;  // ... in flight at a time
@@ -375,7 +376,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
         static_for<(S < NSTAGE - 1 ? LP : L0)>([&](auto L_) { issue(L_, S, S); });
     });
     wait_vmcnt_imm<(NSTAGE - 2) * LP + L0>();  // pair 0 has landed
-    if (PRE && R && vec_ok) fetch_residual(0, 0);
+    if (PRE_RES && R) fetch_residual(0, 0);
     __builtin_amdgcn_s_barrier();
     v4i fa[2][MI], fb[2][NI];
     // read number X of a step's fragments, in the order the MFMAs want them: B 0, A 0 .. MI - 1, B 1 ..
@@ -595,6 +596,64 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
             const float delta = p.q8_step[0];
             rq = delta > 0.0f ? 1.0f / delta : 0.0f;
         }
+        // Rows that are not whole 16-byte pieces: between memory and LDS in aligned pieces of W neighbouring values (N % 4 == 0: four, else two), so that
+        // neighbouring lanes share lines, several pieces in flight; an odd N eight values a thread, one by one.  IN: the residual, of which what lies
+        // outside is some other value (loads under a condition are waited for one by one; nobody reads it).  us, eight values a thread one by one / so, with a
+        // residual: 530 x 2304 -> 17220 tiled 53.0 / 34.3, 222 x 2400 -> 21958 row-major 48.9 / 40.6.
+        auto ragged = [&](auto W_, auto IN_, int g0, int opaque0) {
+            constexpr int W = decltype(W_)::value, PW = W == 1 ? 8 : W, CW = BN / PW, ALL = GR * CW, U = W == 1 ? 2 : 8;
+            typedef uint32_t piece __attribute__((ext_vector_type(PW / 2)));
+#pragma unroll 1
+            for (int k0 = 0; k0 < (ALL + NW * 64 - 1) / (NW * 64); k0 += U) {
+                uint16_t one[U][W == 1 ? 8 : 1];
+                piece val[U];
+                auto place = [&](int k, int& r, int& c) {
+                    const int q = (int)threadIdx.x + opaque0 + (k0 + k) * NW * 64;
+                    r = q / CW;
+                    c = (q - r * CW) * PW;
+                    return ALL % (U * NW * 64) == 0 || q < ALL;
+                };
+#pragma unroll
+                for (int k = 0; k < U; ++k) {
+                    int r, c;
+                    const bool there = place(k, r, c);
+                    if constexpr (decltype(IN_)::value) {
+                        const int row = m0 + g0 + r < p.M ? m0 + g0 + r : p.M - 1, col = n0 + c;
+                        const uint16_t* src = R + (int64_t)row * p.N;
+                        if constexpr (W == 1) {
+#pragma unroll
+                            for (int t = 0; t < 8; ++t) one[k][t] = src[col + t < p.N ? col + t : p.N - 1];
+                        } else {
+                            val[k] = *(const piece*)(src + (col < p.N ? col : 0));
+                        }
+                    } else if (there) {
+                        val[k] = *(const piece*)(smem + r * PITCH + c * 2);
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < U; ++k) {
+                    int r, c;
+                    const bool there = place(k, r, c);
+                    const int row = m0 + g0 + r, col = n0 + c;
+                    if constexpr (decltype(IN_)::value) {
+                        if constexpr (W == 1) {
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) val[k][t] = (uint32_t)one[k][2 * t] | ((uint32_t)one[k][2 * t + 1] << 16);
+                        }
+                        if (there) *(piece*)(smem + r * PITCH + c * 2) = val[k];
+                    } else if (there && row < p.M && col < p.N) {
+                        uint16_t* dst = C + (int64_t)row * p.N + col;
+                        if constexpr (W == 1) {
+#pragma unroll
+                            for (int t = 0; t < 8; ++t)
+                                if (col + t < p.N) dst[t] = (uint16_t)(val[k][t >> 1] >> ((t & 1) * 16));
+                        } else {
+                            *(piece*)dst = val[k];
+                        }
+                    }
+                }
+            }
+        };
 #pragma unroll
         for (int eg = 0; eg < EG; ++eg) {
         const int g0 = eg * GR;  // first tile row of this group
@@ -613,31 +672,19 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
             if (t < BM) sv_row[t] = row_scale;
         }
         if (R) {
-            if (vec_ok) {
+            if constexpr (WHOLE) {
 #pragma unroll 1
                 for (int k0 = 0; k0 < RCH; k0 += RG) {
-                    if constexpr (!PRE) fetch_residual(g0, k0);
+                    if constexpr (!PRE_RES) fetch_residual(g0, k0);
 #pragma unroll
                     for (int k = 0; k < RG; ++k) {
                         const int q = (int)threadIdx.x + (k0 + k) * NW * 64, r = q / CPR;
                         if (q < GR * CPR) *(v4u*)(smem + r * PITCH + (q - r * CPR) * 16) = rpre[k];
                     }
                 }
-            } else {
-                for (int q = threadIdx.x; q < GR * CPR; q += NW * 64) {
-                    const int r = q / CPR, c8 = (q - r * CPR) * 8;
-                    const int row = m0 + g0 + r, col = n0 + c8;
-                    v4u val = {0, 0, 0, 0};
-                    if (row < p.M && col < p.N) {
-                        const uint16_t* src = R + (int64_t)row * p.N + col;
-                        uint32_t e[8];
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) e[t] = (col + t < p.N) ? src[t] : 0u;
-                        val = v4u{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
-                    }
-                    *(v4u*)(smem + r * PITCH + c8 * 2) = val;
-                }
-            }
+            } else if ((p.N & 3) == 0) ragged(std::integral_constant<int, 4>{}, std::true_type{}, g0, opaque0);
+            else if ((p.N & 1) == 0) ragged(std::integral_constant<int, 2>{}, std::true_type{}, g0, opaque0);
+            else ragged(std::integral_constant<int, 1>{}, std::true_type{}, g0, opaque0);
         }
         __syncthreads();
         // The optional terms are compile-time flags inside the loop (one uniform switch outside) so the
@@ -756,7 +803,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
             };
             if ((p.N & 15) == 0) store_codes(std::integral_constant<int, 16>{}, p.q8_tiled != 0);
             else store_codes(std::integral_constant<int, 8>{}, false);
-        } else if (vec_ok) {
+        } else if constexpr (WHOLE) {
             constexpr int SG = FULL ? 2 : RCH % 5 == 0 ? 5 : RCH % 4 == 0 ? 4 : RCH % 3 == 0 ? 3 : 4;  // pieces a thread has in flight out of LDS
 #pragma unroll 1
             for (int k0 = 0; k0 < RCH; k0 += SG) {
@@ -773,17 +820,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
                         __builtin_nontemporal_store(val[k], (v4u*)(C + (int64_t)row * p.N + col));
                 }
             }
-        } else {
-            for (int q = threadIdx.x; q < GR * CPR; q += NW * 64) {
-                const int r = q / CPR, c8 = (q - r * CPR) * 8, row = m0 + g0 + r, col = n0 + c8;
-                if (row >= p.M || col >= p.N) continue;
-                const v4u val = *(const v4u*)(smem + r * PITCH + c8 * 2);
-                uint16_t* dst = C + (int64_t)row * p.N + col;
-#pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    if (col + t < p.N) dst[t] = (uint16_t)(val[t >> 1] >> ((t & 1) * 16));
-            }
-        }
+        } else if ((p.N & 3) == 0) ragged(std::integral_constant<int, 4>{}, std::false_type{}, g0, opaque0);
+        else if ((p.N & 1) == 0) ragged(std::integral_constant<int, 2>{}, std::false_type{}, g0, opaque0);
+        else ragged(std::integral_constant<int, 1>{}, std::false_type{}, g0, opaque0);
         }  // row groups
     }
 }
@@ -830,6 +869,11 @@ template <bool TILED> void tile_launch(const TilePlan& pl, const GemmArgs& a, bo
     if (to_i32) launch_cfg<EPI_I32, false, TILED>(pl, a, batch, st);
     else if (bf16) launch_cfg<EPI_DEQUANT, true, TILED>(pl, a, batch, st);
     else launch_cfg<EPI_DEQUANT, false, TILED>(pl, a, batch, st);
+}
+template <bool TILED> void tile_launch_ragged(const TilePlan& pl, const GemmArgs& a, bool bf16, int batch, hipStream_t st)
+{
+    if (bf16) launch_cfg<EPI_RAGGED, true, TILED>(pl, a, batch, st);
+    else launch_cfg<EPI_RAGGED, false, TILED>(pl, a, batch, st);
 }
 template <bool TILED> void tile_launch_codes(const TilePlan& pl, const GemmArgs& a, bool bf16, hipStream_t st)
 {

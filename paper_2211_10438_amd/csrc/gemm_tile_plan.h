@@ -14,16 +14,21 @@ struct TilePlan {
     int tiles_m, tiles_n;
 };
 
-// The tiles of a plan: 16-bit values into a.C, codes into a.q8_out (a.q8_step set), or int32 sums into a.acc_out.
+// The tiles of a plan: 16-bit values into a.C (ragged: N % 8 != 0), codes into a.q8_out (a.q8_step set; N % 8 == 0), or int32 sums into a.acc_out.
 void sq_tile_gemm_launch_rows(const TilePlan& pl, const GemmArgs& a, bool to_i32, bool bf16, int batch, hipStream_t st);
 void sq_tile_gemm_launch_tiled(const TilePlan& pl, const GemmArgs& a, bool to_i32, bool bf16, int batch, hipStream_t st);
+void sq_tile_gemm_ragged_rows(const TilePlan& pl, const GemmArgs& a, bool bf16, int batch, hipStream_t st);
+void sq_tile_gemm_ragged_tiled(const TilePlan& pl, const GemmArgs& a, bool bf16, int batch, hipStream_t st);
 void sq_tile_gemm_codes_rows(const TilePlan& pl, const GemmArgs& a, bool bf16, hipStream_t st);
 void sq_tile_gemm_codes_tiled(const TilePlan& pl, const GemmArgs& a, bool bf16, hipStream_t st);
 static inline void tile_gemm_launch(const TilePlan& pl, const GemmArgs& a, bool to_i32, bool bf16, int batch, hipStream_t st, bool tiled)
 {
-    if (a.q8_step && !to_i32) {  // (one batch entry)
+    if (!to_i32 && a.q8_step) {  // (one batch entry)
         if (tiled) sq_tile_gemm_codes_tiled(pl, a, bf16, st);
         else sq_tile_gemm_codes_rows(pl, a, bf16, st);
+    } else if (!to_i32 && (a.N & 7)) {
+        if (tiled) sq_tile_gemm_ragged_tiled(pl, a, bf16, batch, st);
+        else sq_tile_gemm_ragged_rows(pl, a, bf16, batch, st);
     } else if (tiled) sq_tile_gemm_launch_tiled(pl, a, to_i32, bf16, batch, st);
     else sq_tile_gemm_launch_rows(pl, a, to_i32, bf16, batch, st);
 }
