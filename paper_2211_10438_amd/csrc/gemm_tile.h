@@ -520,6 +520,18 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_i8_kernel(const GemmA
     }
     }
     wait_vmcnt_imm<0>();  // the refills issued past the end of the K range have landed
+    if constexpr (PAIR && EPI == EPI_I32 && MI * NI * AV >= 160) {
+        // A zero the compiler cannot see through, added to the sums: with stores alone behind the loop it keeps some of them in the accumulation registers
+        // and copies fragments between the two files in every step (256 x 160 tiled 26 copies a pair: 1000 x 9216 -> 9216 82.9 us, so 80.2).
+        int zero;
+        asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int e = 0; e < AV; ++e) acc[i][j][e] += zero;
+    }
 
     // ---- epilogue.  Accumulator block (i, j) is the transposed 32x32 output block: lane l, register v
     // holds output row (l & 31), column 8*(v/4) + 4*(l >> 5) + (v & 3) of the block, i.e. registers

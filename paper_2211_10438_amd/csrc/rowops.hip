@@ -300,21 +300,26 @@ __global__ __launch_bounds__(VT, 4) void ln_quant_walk_kernel(const uint16_t* __
 {
     constexpr int W = VT / 64, NV = 3;
     __shared__ __attribute__((aligned(16))) float cells[3][W];
+    int row = blockIdx.x;
     const int nvec = c_i >> 3, lane = threadIdx.x & 63;
     const int group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int idx[NV];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) idx[i] = group * 64 + lane + i * VT;
-    const bool any = group * 64 + (NV - 1) * VT < nvec;  // the last vector of one of the wave's lanes lies in the row, of this lane
-    const bool in = idx[NV - 1] < nvec;
-    idx[NV - 1] = in ? idx[NV - 1] : nvec - 1;
+    const bool any = group * 64 + (NV - 1) * VT < nvec;  // the last vector of one of the wave's lanes lies in the row, ...
+    bool in = false;                                     // ... of this lane
     v4u raw[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        idx[i] = group * 64 + lane + i * VT;
+        if (i == NV - 1) {
+            in = idx[i] < nvec;
+            idx[i] = in ? idx[i] : nvec - 1;
+        }
+    }
     auto load_row = [&](int r) {
         const v4u* xr = (const v4u*)(x + r * (int64_t)c_i);
 #pragma unroll
         for (int i = 0; i < NV; ++i) raw[i] = __builtin_nontemporal_load(xr + idx[i]);
     };
-    int row = blockIdx.x;
     load_row(row);
     float gam[NV][8], bet[NV][8];
 #pragma unroll
@@ -360,8 +365,9 @@ __global__ __launch_bounds__(VT, 4) void ln_quant_walk_kernel(const uint16_t* __
             float v = part;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                f[i][e] -= mean;
-                v += f[i][e] * f[i][e];
+                const float d = f[i][e] - mean;
+                v += d * d;
+                f[i][e] = d;
             }
             part = i < NV - 1 || in ? v : part;
         }
